@@ -92,6 +92,16 @@ template <> struct Vec<float> {
   static __device__ __forceinline__ void store1(float* p, float v) { *p = v; }
 };
 
+// Rows that are not 16-byte aligned (an odd vocabulary makes every row start somewhere else) are split into the
+// elements before their first 128-byte boundary, whole 16-byte vectors from there on, and the elements after the last
+// vector: the vectors of a wavefront then cover whole lines like those of an aligned row.  Number of elements before
+// the boundary, at most 128 / sizeof(T) - 1.
+template <typename T>
+__device__ __forceinline__ int head_elements(const T* p, int vocab) {
+  const int h = (int)((0u - (uint32_t)reinterpret_cast<uintptr_t>(p)) & 127u) / (int)sizeof(T);
+  return h < vocab ? h : vocab;
+}
+
 // ---- wavefront reductions ----------------------------------------------------------------------
 // Lane exchange inside a row of 16 lanes goes through DPP (no LDS traffic); the two steps across
 // rows use ds_bpermute via __shfl_xor.

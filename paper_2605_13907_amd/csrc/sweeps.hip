@@ -16,14 +16,20 @@
 #include "ais_internal.h"
 #include "device_utils.h"
 
+#include <type_traits>
+
 namespace ais {
 namespace {
 
 using namespace dev;
 
 // ---- sweep 1: token log-probability --------------------------------------------------------------
-// grid.x = n_rows, block = kSweepThreads.  VEC: 16-byte vector path (row base and pitch 16-byte aligned).
-template <typename T, bool VEC, int UNROLL>
+// grid.x = n_rows, block = kSweepThreads.  ALIGNED: row base and pitch are 16-byte aligned, so a row is vectors from its
+// first element on.  Otherwise the elements before the row's first 128-byte boundary are taken one by one together
+// with those after the last vector.  (Until then such rows were read element by element, bound by the number of load
+// instructions.  The three-call step over 12,345 x 50,257 bf16: 1,657 us element-wise, 636 us with vectors; over
+// 4,096 x 32,003 fp32: 415 and 236 us.)
+template <typename T, bool ALIGNED, int UNROLL>
 __global__ __launch_bounds__(kSweepThreads) void token_logprob_kernel(
     const T* __restrict__ logits, long long row_stride, int vocab, const int* __restrict__ token_ids,
     const unsigned char* __restrict__ valid, float inv_temperature, float* __restrict__ logp_out,
@@ -47,14 +53,16 @@ __global__ __launch_bounds__(kSweepThreads) void token_logprob_kernel(
   const int y = token_ids[row];
   const bool y_ok = (y >= 0) && (y < vocab);
   const float zy = y_ok ? Vec<T>::load1(zr + y) : 0.f;
-  const int nvec = VEC ? vocab / N : 0;
+  const int head = ALIGNED ? 0 : head_elements(zr, vocab);
+  const int nvec = (vocab - head) / N;
   // vector index at which this thread meets the sampled token, or a value no index ever takes
-  const int yvec = (y_ok && y < nvec * N && (y / N) % kSweepThreads == tid) ? y / N : -(1 << 30);
-  const int ysub = y % N;
+  const int yb = y - head;                        // position of the sampled token from the first vector on
+  const int yvec = (y_ok && yb >= 0 && yb < nvec * N && (yb / N) % kSweepThreads == tid) ? yb / N : -(1 << 30);
+  const int ysub = yb & (N - 1);
 
   MaxSum st{kNegHuge, 0.f};
-  if (VEC) {
-    const u32x4* zv = reinterpret_cast<const u32x4*>(zr);
+  {
+    const u32x4* zv = reinterpret_cast<const u32x4*>(zr + head);
     int i = tid;
     for (; i + (UNROLL - 1) * kSweepThreads < nvec; i += UNROLL * kSweepThreads) {
       u32x4 q[UNROLL];
@@ -82,7 +90,8 @@ __global__ __launch_bounds__(kSweepThreads) void token_logprob_kernel(
       accumulate<N>(x, scale, st);
     }
   }
-  for (int v = nvec * N + tid; v < vocab; v += kSweepThreads) {   // ragged tail, or the whole row when !VEC
+  if (tid < vocab - nvec * N) {                   // the elements outside the vectors, fewer than there are threads
+    const int v = tid < head ? tid : tid + nvec * N;
     float x = (y_ok && v == y) ? kMasked : Vec<T>::load1(zr + v);
     accumulate<1>(&x, scale, st);
   }
@@ -114,7 +123,8 @@ __global__ __launch_bounds__(kSweepThreads) void token_logprob_kernel(
 // zero advantage, or clipped away) are filled with zeros without being read.  In-place operation is safe:
 // every element is read and written by the same thread, once.
 //
-// Element-wise form: the route for rows that are not 16-byte aligned.  grid.x = n_rows, block = kSweepThreads.
+// Element-wise form: the route when logits and gradient lie differently relative to a 16-byte boundary, so that no
+// vector of the one is a vector of the other.  grid.x = n_rows, block = kSweepThreads.
 template <typename T>
 __global__ __launch_bounds__(kSweepThreads) void dlogits_elementwise_kernel(
     const T* logits, long long row_stride, int vocab, const int* __restrict__ token_ids,
@@ -144,21 +154,23 @@ __global__ __launch_bounds__(kSweepThreads) void dlogits_elementwise_kernel(
   }
 }
 
-// Burst form: the route for 16-byte aligned rows.  A workgroup of 1,024 threads owns the row; every wavefront
+// Burst form: the route for every other row.  A workgroup of 1,024 threads owns the row; every wavefront
 // issues all of its loads (up to NV 16-byte vectors per lane, i.e. up to NV KiB per wavefront), transforms
 // the vectors in place as they arrive, and only when its last load has landed issues all of its stores.
 // Measured on MI355X, a read+write stream shaped this way (long load bursts followed by long store bursts,
 // all wavefronts of a compute unit in step because they start together) sustains 5.8-6.0 TB/s where a loop
 // that stores each vector as soon as it is computed, and every plain copy variant, saturate at 5.2-5.3 TB/s.
-// grid.x = 8 * ceil(n_rows / 8), block = kBurstThreads.  Requires 16-byte aligned rows.  Rows wider than NV * 1024 vectors
+// grid.x = 8 * ceil(n_rows / 8), block = kBurstThreads.  ALIGNED: both rows are 16-byte aligned; otherwise both lie the
+// same way relative to 128-byte lines, and the elements before the row's first line boundary are handled one by one
+// together with those after the last vector.  Rows wider than NV * 1024 vectors
 // are processed in consecutive segments (there is no dependence between segments: lse is an input).
 constexpr int kBurstThreads = 1024;
 
 // NSEG > 0 promises that the row fits NSEG segments, which are then unrolled: the loop-free form is ~3 %
 // faster than the same code inside a run-time loop.  NSEG = 0: run-time loop over as many segments as needed.
-// KFULL promises that the row has more than KFULL * 1024 vectors: vectors 0 .. KFULL - 1 of every lane exist and
+// KFULL promises that the row has at least KFULL * 1024 vectors: vectors 0 .. KFULL - 1 of every lane exist and
 // are loaded and stored without a bounds branch (1.5 % faster at 19 vectors per lane).
-template <typename T, int NV, int NSEG, int KFULL>
+template <typename T, bool ALIGNED, int NV, int NSEG, int KFULL>
 __global__ __launch_bounds__(kBurstThreads) void dlogits_burst_kernel(
     const T* logits, long long row_stride, int vocab, const int* __restrict__ token_ids,
     const float* __restrict__ g, const unsigned char* __restrict__ valid, const float* __restrict__ lse,
@@ -173,16 +185,18 @@ __global__ __launch_bounds__(kBurstThreads) void dlogits_burst_kernel(
   const int tid = threadIdx.x;
   const T* zr = logits + row * row_stride;
   T* dr = dlogits + row * row_stride;
-  const u32x4* zv = reinterpret_cast<const u32x4*>(zr);
-  u32x4* dv = reinterpret_cast<u32x4*>(dr);
-  const int nvec = vocab / N;
-  const int tail = vocab - nvec * N;     // < N elements, one per thread for the first `tail` threads
+  const int head = ALIGNED ? 0 : head_elements(zr, vocab);
+  const u32x4* zv = reinterpret_cast<const u32x4*>(zr + head);
+  u32x4* dv = reinterpret_cast<u32x4*>(dr + head);
+  const int nvec = (vocab - head) / N;
+  const int rest = vocab - nvec * N;     // elements outside the vectors, one per thread for the first `rest` threads
+  const int v_rest = tid < head ? tid : tid + nvec * N;
   const float gn = g != nullptr ? g[row] : ((valid == nullptr || valid[row] != 0) ? 1.f : 0.f);
 
   if (gn == 0.f) {
     const u32x4 zero = {0u, 0u, 0u, 0u};
     for (int i = tid; i < nvec; i += kBurstThreads) store_stream(dv + i, zero);
-    if (tid < tail) Vec<T>::store1(dr + nvec * N + tid, 0.f);
+    if (tid < rest) Vec<T>::store1(dr + v_rest, 0.f);
     return;
   }
 
@@ -193,7 +207,8 @@ __global__ __launch_bounds__(kBurstThreads) void dlogits_burst_kernel(
   if (y < 0 || y >= vocab) y = -1;               // flagged by the first sweep; no one-hot term
   // The sampled token's element is c (p_y - 1) = c expm1(logp): no cancellation when p_y is close to 1.  The
   // lane that holds it patches its packed output register before the store burst.
-  const int yvec = (y >= 0 && y < nvec * N && (y / N) % kBurstThreads == tid) ? y / N : -1;
+  const int yb = y - head;                       // its position from the first vector on
+  const int yvec = (y >= 0 && yb >= 0 && yb < nvec * N && (yb / N) % kBurstThreads == tid) ? yb / N : -1;
   const float dzy = c * expm1f(logp[row]);
 
   const int n_base = NSEG > 0 ? NSEG * NV * kBurstThreads : nvec;
@@ -223,7 +238,7 @@ __global__ __launch_bounds__(kBurstThreads) void dlogits_burst_kernel(
       const int hit = (yvec - base - tid) / kBurstThreads;
 #pragma unroll
       for (int k = 0; k < NV; ++k)
-        if (k == hit) q[k] = Vec<T>::put(q[k], y % N, dzy);
+        if (k == hit) q[k] = Vec<T>::put(q[k], yb & (N - 1), dzy);
     }
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
@@ -231,23 +246,23 @@ __global__ __launch_bounds__(kBurstThreads) void dlogits_burst_kernel(
       if ((NSEG > 0 && base / kBurstThreads + k < KFULL) || i < nvec) store_stream(dv + i, q[k]);
     }
   }
-  if (tid < tail) {
-    const int v = nvec * N + tid;
-    Vec<T>::store1(dr + v, v == y ? dzy : c * exp2_fast(__builtin_fmaf(Vec<T>::load1(zr + v), scale, shift)));
-  }
+  if (tid < rest)
+    Vec<T>::store1(dr + v_rest,
+                   v_rest == y ? dzy : c * exp2_fast(__builtin_fmaf(Vec<T>::load1(zr + v_rest), scale, shift)));
 }
 
-template <typename T>
+template <typename T, bool ALIGNED>
 void launch_dlogits_burst(ais_ctx* ctx, const T* z, long long n_rows, int vocab, long long row_stride,
                           const int* token_ids, const float* g, const unsigned char* valid, const float* lse,
                           const float* logp, float inv_t, T* dz) {
   const int need = (vocab / Vec<T>::N + kBurstThreads - 1) / kBurstThreads;
   dim3 grid((unsigned)(((n_rows + 7) / 8) * 8)), block(kBurstThreads);
   // (vectors that surely exist, vectors per lane and burst, bursts): a row reaches a class only if it is wider than
-  // the class before it, which is what the first figure states
-#define AIS_BURST_CASE(KFULL, NVAL, NSEG)                                                                  \
-  dlogits_burst_kernel<T, NVAL, NSEG, KFULL><<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, token_ids, \
-                                                                              g, valid, lse, logp, inv_t, dz, n_rows)
+  // the class before it, which is what the first figure states; an unaligned row may have lost up to 8 vectors to its
+  // head, which the next lower figure covers
+#define AIS_BURST_CASE(KFULL, NVAL, NSEG)                                                                      \
+  dlogits_burst_kernel<T, ALIGNED, NVAL, NSEG, (ALIGNED || KFULL == 0 ? KFULL : KFULL - 1)>                    \
+      <<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, token_ids, g, valid, lse, logp, inv_t, dz, n_rows)
   if (need <= 4) AIS_BURST_CASE(0, 4, 1);
   else if (need <= 8) AIS_BURST_CASE(4, 8, 1);
   else if (need <= 12) AIS_BURST_CASE(8, 12, 1);
@@ -276,6 +291,10 @@ __global__ __launch_bounds__(256) void copy_kernel(u32x4* __restrict__ dst, cons
 bool vec_ok(const void* base, long long row_stride, size_t esize) {
   return (reinterpret_cast<uintptr_t>(base) % 16 == 0) && ((row_stride * (long long)esize) % 16 == 0);
 }
+// Two arrays of one row pitch whose rows lie the same way relative to 128-byte lines.
+bool same_lines(const void* a, const void* b) {
+  return (reinterpret_cast<uintptr_t>(a) - reinterpret_cast<uintptr_t>(b)) % 128 == 0;
+}
 
 // 16-byte loads in flight per lane and loop iteration of the log-prob sweep (build-time tunable)
 #ifndef AIS_LOGPROB_UNROLL
@@ -291,23 +310,17 @@ int launch_token_logprob(ais_ctx* ctx, const void* logits, ais_dtype dtype, long
   if (n_rows == 0) return AIS_OK;
   dim3 grid((unsigned)n_rows), block(kSweepThreads);
   ScopedTimer timer(ctx, AIS_K_LOGPROB);
-  if (dtype == AIS_BF16) {
-    const bf16_t* z = static_cast<const bf16_t*>(logits);
-    if (vec_ok(z, row_stride, 2))
-      token_logprob_kernel<bf16_t, true, kUnrollFwd><<<grid, block, 0, ctx->stream>>>(
+  auto launch = [&](const auto* z) {
+    typedef std::remove_cv_t<std::remove_pointer_t<decltype(z)>> T;
+    if (vec_ok(z, row_stride, sizeof(T)))
+      token_logprob_kernel<T, true, kUnrollFwd><<<grid, block, 0, ctx->stream>>>(
           z, row_stride, vocab, token_ids, valid, inv_temperature, logp_out, lse_out, ctx->status_dev);
     else
-      token_logprob_kernel<bf16_t, false, 1><<<grid, block, 0, ctx->stream>>>(
+      token_logprob_kernel<T, false, kUnrollFwd><<<grid, block, 0, ctx->stream>>>(
           z, row_stride, vocab, token_ids, valid, inv_temperature, logp_out, lse_out, ctx->status_dev);
-  } else {
-    const float* z = static_cast<const float*>(logits);
-    if (vec_ok(z, row_stride, 4))
-      token_logprob_kernel<float, true, kUnrollFwd><<<grid, block, 0, ctx->stream>>>(
-          z, row_stride, vocab, token_ids, valid, inv_temperature, logp_out, lse_out, ctx->status_dev);
-    else
-      token_logprob_kernel<float, false, 1><<<grid, block, 0, ctx->stream>>>(
-          z, row_stride, vocab, token_ids, valid, inv_temperature, logp_out, lse_out, ctx->status_dev);
-  }
+  };
+  if (dtype == AIS_BF16) launch(static_cast<const bf16_t*>(logits));
+  else launch(static_cast<const float*>(logits));
   return hip_fail(ctx, hipGetLastError());
 }
 
@@ -317,25 +330,21 @@ int launch_dlogits(ais_ctx* ctx, const void* logits, ais_dtype dtype, long long 
   if (n_rows == 0) return AIS_OK;
   dim3 grid((unsigned)n_rows), block(kSweepThreads);
   ScopedTimer timer(ctx, AIS_K_DLOGITS);
-  if (dtype == AIS_BF16) {
-    const bf16_t* z = static_cast<const bf16_t*>(logits);
-    bf16_t* dz = static_cast<bf16_t*>(dlogits);
-    if (vec_ok(z, row_stride, 2) && vec_ok(dz, row_stride, 2))
-      launch_dlogits_burst<bf16_t>(ctx, z, n_rows, vocab, row_stride, token_ids, g, valid, lse, logp,
-                                   inv_temperature, dz);
+  auto launch = [&](const auto* z) {
+    typedef std::remove_cv_t<std::remove_pointer_t<decltype(z)>> T;
+    T* dz = static_cast<T*>(dlogits);
+    if (vec_ok(z, row_stride, sizeof(T)) && vec_ok(dz, row_stride, sizeof(T)))
+      launch_dlogits_burst<T, true>(ctx, z, n_rows, vocab, row_stride, token_ids, g, valid, lse, logp, inv_temperature,
+                                    dz);
+    else if (same_lines(z, dz))
+      launch_dlogits_burst<T, false>(ctx, z, n_rows, vocab, row_stride, token_ids, g, valid, lse, logp, inv_temperature,
+                                     dz);
     else
-      dlogits_elementwise_kernel<bf16_t><<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, token_ids, g, valid,
-                                                                         lse, logp, inv_temperature, dz);
-  } else {
-    const float* z = static_cast<const float*>(logits);
-    float* dz = static_cast<float*>(dlogits);
-    if (vec_ok(z, row_stride, 4) && vec_ok(dz, row_stride, 4))
-      launch_dlogits_burst<float>(ctx, z, n_rows, vocab, row_stride, token_ids, g, valid, lse, logp,
-                                  inv_temperature, dz);
-    else
-      dlogits_elementwise_kernel<float><<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, token_ids, g, valid,
-                                                                        lse, logp, inv_temperature, dz);
-  }
+      dlogits_elementwise_kernel<T><<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, token_ids, g, valid, lse,
+                                                                     logp, inv_temperature, dz);
+  };
+  if (dtype == AIS_BF16) launch(static_cast<const bf16_t*>(logits));
+  else launch(static_cast<const float*>(logits));
   return hip_fail(ctx, hipGetLastError());
 }
 

@@ -295,7 +295,8 @@ int ais_fp8_rollout_logprob(ais_ctx* ctx, const void* logits, ais_dtype dtype, l
  *   token_ids   [n_rows] device; ignored where valid == 0
  *   logp_out, lse_out  [n_rows] device fp32; 0 where valid == 0; a row whose token id is outside
  *               [0, vocab) gets logp 0, its lse, and AIS_STATUS_BAD_TOKEN in the status word
- * Uses the context workspace (2 * chunks + 3 words per row, chunks <= 64); nothing is retained.
+ * Uses the context workspace (2 * chunks + 3 words per row; chunks <= 64 from 2,048 rows on, at most 512 below);
+ * nothing is retained.
  * Errors: dtype other than AIS_BF16 (AIS_ERR_DTYPE); n_rows < 0, vocab < 1, d_model < 8 or not a
  * multiple of 8 (AIS_ERR_SIZE); a stride < d_model (AIS_ERR_STRIDE); NULL pointers; hidden or weight
  * not 16-byte aligned or a stride not a multiple of 8 elements (AIS_ERR_ALIGN); inv_temperature

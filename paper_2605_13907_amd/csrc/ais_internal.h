@@ -44,11 +44,10 @@ WorkspaceLayout workspace_layout(long long n_rows, int n_resp);
 // Decomposition of the hidden-state read-out when every row is evaluated: token blocks x chunks of vocabulary
 // tiles.  The decomposition actually used is decided on the device from the number of evaluated rows.
 struct LmHeadPlan {
-  int n_tblocks;        // blocks of 256 tokens
-  int n_vtiles;         // tiles of 256 vocabulary entries
-  int n_chunks;         // contiguous chunks the tiles are split into
-  int tiles_per_chunk;  // tiles of every chunk but possibly the last
-  int max_chunks;       // most chunks the device-side decision can use (sizes the workspace)
+  int n_vtiles;          // tiles of 256 vocabulary entries
+  int max_chunks;        // most chunks the device-side decision can use (sizes the workspace)
+  int max_items;         // work items, rounded up to a multiple of 8 (sizes the grid)
+  int max_items_masked;  // the same where fewer rows than that may be evaluated
 };
 LmHeadPlan lm_head_plan(long long n_rows, int vocab, int n_cus);
 
@@ -142,15 +141,16 @@ int launch_fp8_rollout_logprob(ais_ctx* ctx, const void* logits, ais_dtype dtype
                                long long row_stride, const int* token_ids, const unsigned char* valid,
                                float* logp_out);
 
+int launch_lm_head_grad_setup(ais_ctx* ctx, const unsigned char* live_mask, long long n_rows, int n_cap, int width,
+                              int width_last, int* row_index, int* row_pos, void* dev_plan);
 int launch_lm_head_dlogits_chunk(ais_ctx* ctx, const void* hidden, long long ld_h, const void* weight,
                                  long long ld_w, long long n_rows, int d_model, int vocab, int y_off,
                                  const int* token_ids, const float* lse, const float* logp, const float* coeff,
-                                 float inv_temperature, void* dev_plan, void* ds, long long ds_stride,
-                                 const unsigned char* live_mask, int* row_index, int* row_pos, int n_cap);
+                                 float inv_temperature, const void* dev_plan, int which, void* ds, long long ds_stride,
+                                 const int* row_index, int n_cap);
 int launch_lm_live_mask(ais_ctx* ctx, const float* coeff, long long n_rows, unsigned char* mask);
-int launch_lm_gather_rows(ais_ctx* ctx, const void* hidden, long long ld_h, long long n_rows, int d_model,
-                          const unsigned char* live_mask, int* row_index, int* row_pos, void* dev_plan, int n_cap,
-                          void* gathered);
+int launch_lm_gather_rows(ais_ctx* ctx, const void* hidden, long long ld_h, int d_model, const int* row_index,
+                          const void* dev_plan, int n_cap, void* gathered);
 int launch_lm_scatter_rows(ais_ctx* ctx, const float* gathered, const int* row_pos, long long n_rows, int d_model,
                            float* out);
 int launch_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long ld_h, const void* weight, long long ld_w,

@@ -561,11 +561,14 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   float* dh_gathered = reinterpret_cast<float*>(h_gathered + hg_bytes);
   if (gather) {
     rc = launch_lm_live_mask(ctx, coeff, n_rows, live_mask);
-    if (rc == AIS_OK)
-      rc = launch_lm_gather_rows(ctx, hidden, hidden_stride, n_rows, (int)d_model, live_mask, row_index, row_pos, dev_plan,
-                                 (int)m_rows, h_gathered);
     if (rc != AIS_OK) return rc;
   }
+  const int width_last = (int)(vocab % chunk_vocab);
+  rc = launch_lm_head_grad_setup(ctx, live_mask, n_rows, (int)m_rows, (int)chunk_vocab, width_last, row_index, row_pos,
+                                 dev_plan);
+  if (rc == AIS_OK && gather)
+    rc = launch_lm_gather_rows(ctx, hidden, hidden_stride, (int)d_model, row_index, dev_plan, (int)m_rows, h_gathered);
+  if (rc != AIS_OK) return rc;
   // operands of the two GEMMs: the hidden states they read and the gradient they write, with their pitches
   const void* h_gemm = gather ? static_cast<const void*>(h_gathered) : hidden;
   const long long h_gemm_stride = gather ? d_model : hidden_stride;
@@ -584,8 +587,8 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
     const int width = (int)std::min<long long>(chunk_vocab, vocab - v0);
     const void* w_chunk = w_base + (size_t)v0 * (size_t)weight_stride * 2;
     rc = launch_lm_head_dlogits_chunk(ctx, hidden, hidden_stride, w_chunk, weight_stride, n_rows, (int)d_model, width,
-                                      (int)v0, token_ids, lse, logp, coeff, inv_temperature, dev_plan, ds,
-                                      chunk_vocab, live_mask, row_index, row_pos, (int)m_rows);
+                                      (int)v0, token_ids, lse, logp, coeff, inv_temperature, dev_plan,
+                                      width == width_last ? 1 : 0, ds, chunk_vocab, row_index, (int)m_rows);
     if (rc != AIS_OK) return rc;
     // The library is column-major; a row-major [r, c] matrix with pitch p is its column-major [c, r] transpose
     // with leading dimension p.

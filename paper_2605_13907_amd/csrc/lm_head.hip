@@ -53,8 +53,11 @@ constexpr int kLmWaveT = 64;       //                2 along the tokens
 // resident on an XCD share a few hidden-state blocks and sit on all chunks of the vocabulary.  Measured at 41,643
 // rows x 151,936 x 4,096: 43.9 ms; groups of 2 / 4 / 8 / 16 / 32 token blocks on the same chunk (more sharing of the
 // output-embedding tiles, less of the hidden-state block, which a work item re-reads for every vocabulary tile):
-// 44.3 / 47.4 / 47.5 / 50.1 / 52.9 ms.
-constexpr int kLmTokenBlockGroup = 1;
+// 44.3 / 47.4 / 47.5 / 50.1 / 52.9 ms.  Where there are fewer than 8 token blocks every one of them fits the L2 beside
+// the tiles, and sharing the tiles is what counts: 390 rows 618 us alone, 601 us in twos; 1,500 rows 1,734 us alone,
+// 1,670 us in fours; from 2,000 rows on no difference beyond the noise.
+__device__ __forceinline__ int lm_token_block_group(int n_tblocks) { return n_tblocks < 8 ? min(n_tblocks, 4) : 1; }
+
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 q) { return __builtin_bit_cast(bf16x8, q); }
 
 
@@ -64,39 +67,39 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 q) { return __builtin_bit_cast
 // (lm_head_setup_kernel): n_tblocks blocks of 256 evaluated rows x n_chunks chunks of tiles_per_chunk
 // vocabulary tiles, per_xcd work items for each of the 8 XCDs.
 struct LmDevPlan {
-  int n_eval, n_tblocks, n_chunks, tiles_per_chunk, per_xcd, n_items, tb_group;
+  int n_eval, n_tblocks, n_chunks, tiles_per_chunk, per_xcd, n_items, tb_group, pad;
 };
 
-// Splits n_vtiles vocabulary tiles into equal chunks so that (token blocks x chunks) equal work items fill the
-// compute units in as few rounds as possible.  Workgroups are bound to XCDs by their index, so what counts is
-// the rounds of the busiest XCD (n_cus / 8 units each).  At most max_items items, at most 64 chunks.
-__host__ __device__ inline void lm_choose_chunks(int n_tblocks, int n_vtiles, int n_cus, long long max_items,
-                                                 int* n_chunks, int* tiles_per_chunk) {
+// Cost of splitting n_vtiles vocabulary tiles into `chunks` equal chunks (rounds of the busiest XCD times the length of
+// a work item), or -1 where that gives more than max_items work items.  Workgroups are bound to XCDs by their index, so
+// what counts is the rounds of the busiest XCD (n_cus / 8 units each).
+__host__ __device__ inline long long lm_chunks_cost(int chunks, int n_tblocks, int n_vtiles, int n_cus,
+                                                    long long max_items, int* n_chunks, int* tiles_per_chunk) {
   const int cus_per_xcd = n_cus >= 8 ? n_cus / 8 : 1;
-  long long best = -1;
-  *n_chunks = 1;
-  *tiles_per_chunk = n_vtiles;
-  for (int chunks = 1; chunks <= n_vtiles && chunks <= 64; ++chunks) {
-    const int tpc = (n_vtiles + chunks - 1) / chunks;
-    const int real = (n_vtiles + tpc - 1) / tpc;
-    const long long items = (long long)n_tblocks * real;
-    if (items > max_items && chunks > 1) continue;
-    const long long per_xcd = (items + 7) / 8;
-    const long long rounds = (per_xcd + cus_per_xcd - 1) / cus_per_xcd;
-    const long long cost = rounds * (tpc + 1);            // + 1: set-up and tear-down of a work item, in tile units
-    if (best < 0 || cost < best) {
-      best = cost;
-      *tiles_per_chunk = tpc;
-      *n_chunks = real;
-    }
-  }
+  const int tpc = (n_vtiles + chunks - 1) / chunks;
+  const int real = (n_vtiles + tpc - 1) / tpc;
+  *n_chunks = real;
+  *tiles_per_chunk = tpc;
+  const long long items = (long long)n_tblocks * real;
+  if (items > max_items && chunks > 1) return -1;
+  const long long per_xcd = (items + 7) / 8;
+  const long long rounds = (per_xcd + cus_per_xcd - 1) / cus_per_xcd;
+  return rounds * (tpc + 1);                              // + 1: set-up and tear-down of a work item, in tile units
+}
+
+// Most chunks the vocabulary is split into: 64, or as many as give two work items per compute unit where there are only
+// a few token blocks.  (With 64 for everyone a batch of 390 rows x 151,936 x 4,096 was 120 work items on 256 compute
+// units and took 1,030 us; with more chunks 618 us, 256 rows 1,060 -> 391 us.)
+__host__ __device__ inline int lm_chunk_limit(int n_tblocks, int n_vtiles, int n_cus) {
+  const int fill = n_tblocks > 0 ? (2 * n_cus + n_tblocks - 1) / n_tblocks : 64;
+  const int limit = fill > 64 ? fill : 64;
+  return n_vtiles < limit ? n_vtiles : limit;
 }
 
 // The rows to evaluate.  With a mask, `index` lists the evaluated rows in order (built by
 // lm_head_setup_kernel); without one, every row is evaluated.
 struct LmRows {
   const int* index;
-  int n_rows;
   // source row of evaluated position p (positions past the end repeat the last one; their results are discarded)
   __device__ __forceinline__ int row(int p, int n_eval) const {
     p = min(p, n_eval - 1);
@@ -217,7 +220,7 @@ struct LmSoftmax {
   }
   // Merges the two lane halves, then the two wavefronts along the vocabulary (through `xch`, 2 KiB of LDS that
   // no one uses any more), and writes the chunk's partial (max, sum) of every token of the block.
-  __device__ __forceinline__ void finish(const LmItem& it, float* xch, int n_rows, float* __restrict__ part_m,
+  __device__ __forceinline__ void finish(const LmItem& it, float* xch, float* __restrict__ part_m,
                                          float* __restrict__ part_s) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
@@ -244,8 +247,8 @@ struct LmSoftmax {
         const float m = fmaxf(run_m[j], om);
         const float s = run_s[j] * exp2_fast(run_m[j] - m) + os * exp2_fast(om - m);
         if (tok[j] < it.n_eval) {
-          part_m[(long long)it.ch * n_rows + tok[j]] = m;
-          part_s[(long long)it.ch * n_rows + tok[j]] = s;
+          part_m[(long long)it.ch * it.n_eval + tok[j]] = m;
+          part_s[(long long)it.ch * it.n_eval + tok[j]] = s;
         }
       }
     }
@@ -364,7 +367,6 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_stream_kernel(
   extern __shared__ __align__(16) unsigned char lds[];
   LmItem it;
   if (!it.init(plan, n_vtiles)) return;
-  const int n_rows = rows.n_rows;
   const int lane = it.lane, wave = it.wave;
 
   // ---- copies: wavefront w moves rows 16 w .. 16 w + 15 (+ 128 j) of each slice; a lane sits at chunk position
@@ -535,7 +537,7 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_stream_kernel(
   tile_done(vt);
   // copies of the last steps may still be in flight, and they land in LDS that finish() is about to reuse
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  if (!GRAD) sm.finish(it, reinterpret_cast<float*>(lds), n_rows, part_m, part_s);
+  if (!GRAD) sm.finish(it, reinterpret_cast<float*>(lds), part_m, part_s);
 }
 
 // ---- streaming kernel with 64-element steps: d_model a multiple of 64 -------------------------------------------
@@ -563,7 +565,6 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_stream64_kernel(
   extern __shared__ __align__(16) unsigned char lds[];
   LmItem it;
   if (!it.init(plan, n_vtiles)) return;
-  const int n_rows = rows.n_rows;
   const int lane = it.lane, wave = it.wave;
 
   // ---- copies: wavefront w moves rows 8 w .. 8 w + 7 (+ 64 j, j = 0..3) of each slice; a lane sits at chunk
@@ -728,7 +729,7 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_stream64_kernel(
 #undef AIS_PIN
   // copies of the last steps may still be in flight, and they land in LDS that finish() is about to reuse
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  if (!GRAD) sm.finish(it, reinterpret_cast<float*>(lds), n_rows, part_m, part_s);
+  if (!GRAD) sm.finish(it, reinterpret_cast<float*>(lds), part_m, part_s);
 }
 
 // ---- register-staged kernel: any d_model that is a multiple of 8 ---------------------------------------------
@@ -752,7 +753,6 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_staged_kernel(
   extern __shared__ __align__(16) unsigned char lds[];
   LmItem it;
   if (!it.init(plan, n_vtiles)) return;
-  const int n_rows = rows.n_rows;
   const int tid = threadIdx.x;
 
   // ---- global -> registers -> LDS: thread owns chunk c of rows r0 + 64 i of both operand slices
@@ -870,96 +870,139 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_staged_kernel(
     vt = nvt;
     buf ^= 1;
   }
-  sm.finish(it, reinterpret_cast<float*>(lds), n_rows, part_m, part_s);
+  sm.finish(it, reinterpret_cast<float*>(lds), part_m, part_s);
 }
+
+// What lm_head_setup_kernel decides a decomposition for: a vocabulary width (0: none), the grid that was sized for it,
+// and the most partials per evaluated row times evaluated rows that its workspace holds.
+struct LmSetupGoal {
+  int n_vtiles, max_items;
+  long long max_partials;
+};
 
 // One workgroup, before the main kernel.  With a mask it lists the rows to evaluate (index[p] = p-th row with
-// valid != 0, pos[n] = position of row n in that list or -1; each thread owns a contiguous run of rows); in
-// both cases thread 0 then decides the decomposition for the number of evaluated rows.
+// valid != 0, pos[n] = position of row n in that list or -1); in both cases it then decides the decomposition for the
+// number of evaluated rows, once per goal (plan[0] and plan[1]).
 // n_cap >= 0: the list holds at most n_cap rows; further rows are dropped (pos = -1) and reported in *status.
+// It is latency-bound, one workgroup in front of a large kernel: every wavefront owns a contiguous run of rows and ranks
+// them 64 at a time by ballot, and the candidate decompositions are tried by one thread each.  (Before, a serial scan
+// over 1,024 counters and a serial search took 15-20 us without and 28-33 us with a mask of 8,192 rows.)
 __global__ __launch_bounds__(1024) void lm_head_setup_kernel(const unsigned char* __restrict__ valid, int n_rows,
-                                                             int n_vtiles, int n_cus, int max_items, int tb_group,
+                                                             LmSetupGoal goal0, LmSetupGoal goal1, int n_cus,
                                                              int* __restrict__ index, int* __restrict__ pos,
-                                                             LmDevPlan* __restrict__ plan, int n_cap = -1,
-                                                             int* __restrict__ status = nullptr) {
-  __shared__ int run_start[1024];
-  __shared__ int total;
-  const int tid = threadIdx.x;
+                                                             LmDevPlan* __restrict__ plan, int n_cap,
+                                                             int* __restrict__ status) {
+  __shared__ int wave_count[16];
+  __shared__ unsigned long long best[2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (tid < 2) best[tid] = ~0ull;
+  int total = n_rows;
   if (valid != nullptr) {
-    const int per = (n_rows + 1023) / 1024;
-    const int r0 = min(n_rows, tid * per), r1 = min(n_rows, r0 + per);
+    const long long run = (((long long)n_rows + 15) / 16 + 63) & ~63ll;
+    const int r0 = (int)min((long long)n_rows, wave * run), r1 = (int)min((long long)n_rows, r0 + run);
     int cnt = 0;
-    for (int n = r0; n < r1; ++n) cnt += valid[n] != 0;
-    run_start[tid] = cnt;
+#pragma unroll 4
+    for (int n = r0 + lane; n < r1; n += 64) cnt += valid[n] != 0;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off);
+    if (lane == 0) wave_count[wave] = cnt;
     __syncthreads();
-    if (tid == 0) {
-      int run = 0;
-      for (int t = 0; t < 1024; ++t) {
-        const int c = run_start[t];
-        run_start[t] = run;
-        run += c;
-      }
-      total = run;
+    total = 0;
+    int p = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      if (w == wave) p = total;
+      total += wave_count[w];
     }
-    __syncthreads();
     const int cap = n_cap >= 0 ? n_cap : n_rows;
-    int p = run_start[tid];
-    for (int n = r0; n < r1; ++n) {
-      if (valid[n] != 0) {
-        if (p < cap) {
-          index[p] = n;
-          pos[n] = p;
-        } else {
-          pos[n] = -1;
-        }
-        ++p;
-      } else {
-        pos[n] = -1;
+    for (int n0 = r0 + lane; n0 - lane < r1; n0 += 256) {
+      bool on[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) on[u] = n0 + 64 * u < r1 && valid[n0 + 64 * u] != 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int n = n0 + 64 * u;
+        const unsigned long long mask = __ballot(on[u]);
+        const int mine = p + (int)__popcll(mask & ((1ull << lane) - 1));
+        if (on[u] && mine < cap) index[mine] = n;
+        if (n < r1) pos[n] = on[u] && mine < cap ? mine : -1;
+        p += (int)__popcll(mask);
       }
     }
-    if (tid == 0 && total > cap) {
+    if (total > cap) {
       total = cap;
-      if (status != nullptr) atomicOr(status, AIS_STATUS_LIVE_OVERFLOW);
+      if (tid == 0 && status != nullptr) atomicOr(status, AIS_STATUS_LIVE_OVERFLOW);
     }
-    // (total is read below by thread 0 only)
-  } else if (tid == 0) {
-    total = n_rows;
+  } else {
+    __syncthreads();
   }
-  if (tid == 0) {
+  const int n_tblocks = (total + kLmTileT - 1) / kLmTileT;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const LmSetupGoal goal = k == 0 ? goal0 : goal1;
+    if (goal.n_vtiles == 0) continue;
+    int limit = lm_chunk_limit(n_tblocks, goal.n_vtiles, n_cus), real, tpc;
+    if (total > 0) limit = (int)min((long long)limit, goal.max_partials / total);
+    // at least one chunk, whatever the limits; the fewest chunks win among equals
+    for (int c = tid + 1; c <= max(limit, 1); c += 1024) {
+      const long long cost = lm_chunks_cost(c, n_tblocks, goal.n_vtiles, n_cus, goal.max_items, &real, &tpc);
+      if (cost >= 0) atomicMin(&best[k], ((unsigned long long)cost << 16) | (unsigned)c);
+    }
+  }
+  __syncthreads();
+  if (tid < 2) {
+    const LmSetupGoal goal = tid == 0 ? goal0 : goal1;
+    if (goal.n_vtiles == 0) return;
     LmDevPlan d;
     d.n_eval = total;
-    d.n_tblocks = (total + kLmTileT - 1) / kLmTileT;
-    lm_choose_chunks(d.n_tblocks, n_vtiles, n_cus, max_items, &d.n_chunks, &d.tiles_per_chunk);
+    d.n_tblocks = n_tblocks;
+    lm_chunks_cost((int)(best[tid] & 0xffffu), n_tblocks, goal.n_vtiles, n_cus, goal.max_items, &d.n_chunks,
+                   &d.tiles_per_chunk);
     d.n_items = d.n_tblocks * d.n_chunks;
     d.per_xcd = (d.n_items + 7) / 8;
-    d.tb_group = max(1, min(tb_group, d.n_tblocks));
-    *plan = d;
+    d.tb_group = max(1, lm_token_block_group(n_tblocks));
+    d.pad = 0;
+    plan[tid] = d;
   }
 }
 
-// lse and log-prob from the per-chunk partials.  One thread per row; partials are stored by evaluated position.
-__global__ __launch_bounds__(256) void lm_head_merge_kernel(const float* __restrict__ part_m,
-                                                            const float* __restrict__ part_s,
-                                                            const float* __restrict__ zy, int n_rows,
-                                                            const LmDevPlan* __restrict__ plan, int vocab,
-                                                            const int* __restrict__ token_ids,
-                                                            const int* __restrict__ pos,
-                                                            float inv_temperature, float* __restrict__ logp_out,
-                                                            float* __restrict__ lse_out, int* __restrict__ status) {
-  const int n = blockIdx.x * 256 + threadIdx.x;
-  if (n >= n_rows) return;
+// lse and log-prob from the per-chunk partials, which are stored by evaluated position.  16 rows per workgroup, the
+// chunks of a row over 16 threads, whose sums are added in order.  (One thread per row and all its chunks in turn took
+// 33 us for 390 rows of 60 chunks, 16 us for 41,643 rows of 14.)
+constexpr int kMergeRows = 16;
+constexpr int kMergeWays = 16;
+__global__ __launch_bounds__(kMergeRows * kMergeWays) void lm_head_merge_kernel(
+    const float* __restrict__ part_m, const float* __restrict__ part_s, const float* __restrict__ zy, int n_rows,
+    const LmDevPlan* __restrict__ plan, int vocab, const int* __restrict__ token_ids, const int* __restrict__ pos,
+    float inv_temperature, float* __restrict__ logp_out, float* __restrict__ lse_out, int* __restrict__ status) {
+  __shared__ float way_m[kMergeWays][kMergeRows];
+  __shared__ double way_s[kMergeWays][kMergeRows];
+  const int r = threadIdx.x % kMergeRows, way = threadIdx.x / kMergeRows;
+  const long long n = (long long)blockIdx.x * kMergeRows + r;
   const int n_chunks = plan->n_chunks;
-  const int p = pos != nullptr ? pos[n] : n;
+  const long long stride = plan->n_eval;
+  const int p = n >= n_rows ? -1 : (pos != nullptr ? pos[n] : (int)n);
+  float m = kNegHuge;
+  if (p >= 0)
+    for (int k = way; k < n_chunks; k += kMergeWays) m = fmaxf(m, part_m[k * stride + p]);
+  way_m[way][r] = m;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kMergeWays; ++w) m = fmaxf(m, way_m[w][r]);
+  double s = 0.0;
+  if (p >= 0)
+    for (int k = way; k < n_chunks; k += kMergeWays)
+      s += (double)part_s[k * stride + p] * (double)exp2_fast(part_m[k * stride + p] - m);
+  way_s[way][r] = s;
+  __syncthreads();
+  if (way != 0 || n >= n_rows) return;
   if (p < 0) {
     logp_out[n] = 0.f;
     lse_out[n] = 0.f;
     return;
   }
-  float m = kNegHuge;
-  for (int k = 0; k < n_chunks; ++k) m = fmaxf(m, part_m[(long long)k * n_rows + p]);
-  double s = 0.0;
-  for (int k = 0; k < n_chunks; ++k)
-    s += (double)part_s[(long long)k * n_rows + p] * (double)exp2_fast(part_m[(long long)k * n_rows + p] - m);
+#pragma unroll
+  for (int w = 1; w < kMergeWays; ++w) s += way_s[w][r];
   const double lse = ((double)m + log2(s)) * 0.6931471805599453;
   lse_out[n] = (float)lse;
   const int id = token_ids[n];
@@ -1016,10 +1059,21 @@ __global__ __launch_bounds__(256) void lm_scatter_rows_kernel(const float* __res
 // Worst case of the decomposition (every row evaluated): sizes the grid and the workspace.
 LmHeadPlan lm_head_plan(long long n_rows, int vocab, int n_cus) {
   LmHeadPlan p;
-  p.n_tblocks = (int)((n_rows + kLmTileT - 1) / kLmTileT);
+  const int n_tblocks = (int)((n_rows + kLmTileT - 1) / kLmTileT);
   p.n_vtiles = (vocab + kLmTileV - 1) / kLmTileV;
-  lm_choose_chunks(p.n_tblocks, p.n_vtiles, n_cus, 1LL << 40, &p.n_chunks, &p.tiles_per_chunk);
-  p.max_chunks = p.n_vtiles < 64 ? p.n_vtiles : 64;
+  p.max_chunks = lm_chunk_limit(n_tblocks, p.n_vtiles, n_cus);
+  long long best = -1, items = 1;
+  for (int c = 1; c <= p.max_chunks; ++c) {
+    int real, tpc;
+    const long long cost = lm_chunks_cost(c, n_tblocks, p.n_vtiles, n_cus, 1LL << 40, &real, &tpc);
+    if (best < 0 || cost < best) {
+      best = cost;
+      items = (long long)n_tblocks * real;
+    }
+  }
+  p.max_items = (int)((items + 7) / 8 * 8);
+  // with a mask fewer rows may be evaluated, in more chunks: two work items per compute unit are what they can use
+  p.max_items_masked = p.max_items > 2 * n_cus ? p.max_items : (2 * n_cus + 7) / 8 * 8;
   return p;
 }
 
@@ -1044,13 +1098,14 @@ int launch_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long ld_h, con
     return hip_fail(ctx, hipErrorInvalidValue);
   // The grid covers the work items of the worst case; with fewer evaluated rows the device-side plan may use
   // more, shorter chunks, but never more items than that, and the workgroups left over leave at once.
-  const int max_items = ((plan.n_tblocks * plan.n_chunks + 7) / 8) * 8;
+  const int max_items = valid != nullptr ? plan.max_items_masked : plan.max_items;
   LmDevPlan* dplan = static_cast<LmDevPlan*>(dev_plan);
-  lm_head_setup_kernel<<<1, 1024, 0, ctx->stream>>>(valid, (int)n_rows, plan.n_vtiles, ctx->n_cus, max_items,
-                                                    kLmTokenBlockGroup, row_index, row_pos, dplan);
+  lm_head_setup_kernel<<<1, 1024, 0, ctx->stream>>>(
+      valid, (int)n_rows, LmSetupGoal{plan.n_vtiles, max_items, (long long)plan.max_chunks * n_rows}, LmSetupGoal{},
+      ctx->n_cus, row_index, row_pos, dplan, -1, nullptr);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(ctx, e);
-  LmRows rows{valid != nullptr ? row_index : nullptr, (int)n_rows};
+  LmRows rows{valid != nullptr ? row_index : nullptr};
   {
     ScopedTimer timer(ctx, AIS_K_LM_HEAD);
     if (d_model % kS64K == 0)
@@ -1068,22 +1123,39 @@ int launch_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long ld_h, con
   }
   e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(ctx, e);
-  lm_head_merge_kernel<<<(unsigned)((n_rows + 255) / 256), 256, 0, ctx->stream>>>(
+  lm_head_merge_kernel<<<(unsigned)((n_rows + kMergeRows - 1) / kMergeRows), kMergeRows * kMergeWays, 0, ctx->stream>>>(
       part_m, part_s, zy, (int)n_rows, dplan, vocab, token_ids, valid != nullptr ? row_pos : nullptr,
       inv_temperature, logp_out, lse_out, ctx->status_dev);
   return hip_fail(ctx, hipGetLastError());
 }
 
+// The list of rows with a gradient (with live_mask: at most n_cap of them) and the decompositions of the gradient
+// call's chunks: plan 0 for chunks of `width` vocabulary entries, plan 1 for a last chunk of width_last (0: none).
+int launch_lm_head_grad_setup(ais_ctx* ctx, const unsigned char* live_mask, long long n_rows, int n_cap, int width,
+                              int width_last, int* row_index, int* row_pos, void* dev_plan) {
+  const int m_rows = live_mask != nullptr ? n_cap : (int)n_rows;
+  auto goal = [&](int w) {
+    if (w == 0) return LmSetupGoal{};
+    const LmHeadPlan plan = lm_head_plan(m_rows, w, ctx->n_cus);
+    return LmSetupGoal{plan.n_vtiles, live_mask != nullptr ? plan.max_items_masked : plan.max_items, 1LL << 62};
+  };
+  lm_head_setup_kernel<<<1, 1024, 0, ctx->stream>>>(live_mask, (int)n_rows, goal(width), goal(width_last), ctx->n_cus,
+                                                    row_index, row_pos, static_cast<LmDevPlan*>(dev_plan),
+                                                    live_mask != nullptr ? n_cap : -1, ctx->status_dev);
+  return hip_fail(ctx, hipGetLastError());
+}
+
 // dlogits of one chunk of the vocabulary, from hidden states and the chunk's rows of the output embedding, into
 // ds[n_rows, ds_stride] (bf16).  `weight` points at the chunk's first row, `vocab` is the chunk's width, `y_off` its
-// first vocabulary entry.  Every row is processed (rows whose coefficient is 0 come out as zeros).
-// With a list (live_mask != nullptr: the rows with a gradient, at most n_cap of them) row p of ds belongs to the p-th
+// first vocabulary entry, `which` the plan for its width.  Every row is processed (rows whose coefficient is 0 come out
+// as zeros).
+// With a list (row_index != nullptr: the rows with a gradient, at most n_cap of them) row p of ds belongs to the p-th
 // listed row and rows up to n_cap - 1 are written (zeros past the end of the list).
 int launch_lm_head_dlogits_chunk(ais_ctx* ctx, const void* hidden, long long ld_h, const void* weight,
                                  long long ld_w, long long n_rows, int d_model, int vocab, int y_off,
                                  const int* token_ids, const float* lse, const float* logp, const float* coeff,
-                                 float inv_temperature, void* dev_plan, void* ds, long long ds_stride,
-                                 const unsigned char* live_mask, int* row_index, int* row_pos, int n_cap) {
+                                 float inv_temperature, const void* dev_plan, int which, void* ds, long long ds_stride,
+                                 const int* row_index, int n_cap) {
   constexpr int kStreamLds = AIS_LM_STAGES * kStStageBytes;
   static std::once_flag once[kMaxDevices], once64[kMaxDevices];
   static bool ok[kMaxDevices], ok64[kMaxDevices];
@@ -1091,16 +1163,11 @@ int launch_lm_head_dlogits_chunk(ais_ctx* ctx, const void* hidden, long long ld_
                          once, ok) ||
       !allow_dynamic_lds(ctx, reinterpret_cast<const void*>(lm_head_stream64_kernel<true>), kS64LdsBytes, once64, ok64))
     return hip_fail(ctx, hipErrorInvalidValue);
-  const LmHeadPlan plan = lm_head_plan(n_rows, vocab, ctx->n_cus);
-  const int max_items = ((plan.n_tblocks * plan.n_chunks + 7) / 8) * 8;
-  LmDevPlan* dplan = static_cast<LmDevPlan*>(dev_plan);
-  lm_head_setup_kernel<<<1, 1024, 0, ctx->stream>>>(live_mask, (int)n_rows, plan.n_vtiles, ctx->n_cus, max_items,
-                                                    kLmTokenBlockGroup, row_index, row_pos, dplan,
-                                                    live_mask != nullptr ? n_cap : -1, ctx->status_dev);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail(ctx, e);
-  LmRows rows{live_mask != nullptr ? row_index : nullptr, (int)n_rows};
-  LmGradArgs ga{lse, logp, coeff, static_cast<bf16_t*>(ds), ds_stride, y_off, live_mask != nullptr ? 1 : 0};
+  const LmHeadPlan plan = lm_head_plan(row_index != nullptr ? n_cap : n_rows, vocab, ctx->n_cus);
+  const int max_items = row_index != nullptr ? plan.max_items_masked : plan.max_items;
+  const LmDevPlan* dplan = static_cast<const LmDevPlan*>(dev_plan) + which;
+  LmRows rows{row_index};
+  LmGradArgs ga{lse, logp, coeff, static_cast<bf16_t*>(ds), ds_stride, y_off, row_index != nullptr ? 1 : 0};
   {
     ScopedTimer timer(ctx, AIS_K_LM_HEAD_GRAD);
     if (d_model % kS64K == 0)
@@ -1112,9 +1179,9 @@ int launch_lm_head_dlogits_chunk(ais_ctx* ctx, const void* hidden, long long ld_
           static_cast<const bf16_t*>(hidden), ld_h, static_cast<const bf16_t*>(weight), ld_w, rows, dplan, d_model,
           vocab, token_ids, inv_temperature * kLog2e, plan.n_vtiles, nullptr, nullptr, nullptr, ga);
   }
-  e = hipGetLastError();
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(ctx, e);
-  if (live_mask != nullptr && n_cap > 0)
+  if (row_index != nullptr && n_cap > 0)
     lm_zero_tail_rows_kernel<<<(unsigned)n_cap, 256, 0, ctx->stream>>>(static_cast<bf16_t*>(ds), ds_stride, vocab,
                                                                        dplan);
   return hip_fail(ctx, hipGetLastError());
@@ -1125,18 +1192,12 @@ int launch_lm_live_mask(ais_ctx* ctx, const float* coeff, long long n_rows, unsi
   return hip_fail(ctx, hipGetLastError());
 }
 
-// The list and the plan for `n_rows` rows with the mask, once (the chunk launches rebuild the plan for their width).
-int launch_lm_gather_rows(ais_ctx* ctx, const void* hidden, long long ld_h, long long n_rows, int d_model,
-                          const unsigned char* live_mask, int* row_index, int* row_pos, void* dev_plan, int n_cap,
-                          void* gathered) {
-  LmDevPlan* dplan = static_cast<LmDevPlan*>(dev_plan);
-  lm_head_setup_kernel<<<1, 1024, 0, ctx->stream>>>(live_mask, (int)n_rows, 1, ctx->n_cus, 1 << 30,
-                                                    kLmTokenBlockGroup, row_index, row_pos, dplan, n_cap,
-                                                    ctx->status_dev);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail(ctx, e);
-  lm_gather_rows_kernel<<<(unsigned)n_cap, 256, 0, ctx->stream>>>(static_cast<const bf16_t*>(hidden), ld_h, row_index,
-                                                                  dplan, d_model, static_cast<bf16_t*>(gathered));
+// The hidden states of the listed rows, in order (zeros past the end of the list, up to row n_cap - 1).
+int launch_lm_gather_rows(ais_ctx* ctx, const void* hidden, long long ld_h, int d_model, const int* row_index,
+                          const void* dev_plan, int n_cap, void* gathered) {
+  lm_gather_rows_kernel<<<(unsigned)n_cap, 256, 0, ctx->stream>>>(
+      static_cast<const bf16_t*>(hidden), ld_h, row_index, static_cast<const LmDevPlan*>(dev_plan), d_model,
+      static_cast<bf16_t*>(gathered));
   return hip_fail(ctx, hipGetLastError());
 }
 

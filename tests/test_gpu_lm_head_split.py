@@ -36,7 +36,7 @@ def reference(h, w, y):
 TOL = 2e-4
 
 
-@pytest.mark.parametrize("d", [64, 96, 72])                       # the three kernels
+@pytest.mark.parametrize("d", [64, 96, 72])           # whole, half and ragged last slices of d_model
 @pytest.mark.parametrize("rows", [1, 17, 255, 256, 257, 390, 1025, 2049])
 def test_few_token_blocks(ctx, rows, d):
     for vocab in (255, 256 * 65 + 1, 90_113):
@@ -63,3 +63,24 @@ def test_few_evaluated_rows(ctx, rows, live):
         ref_p, ref_l = reference(h[on], w, y[on])
         assert (logp[on].double() - ref_p).abs().max() <= TOL and (lse[on].double() - ref_l).abs().max() <= TOL
     assert ctx.status() == 0
+
+
+@pytest.mark.parametrize("d", [8, 56, 64, 72, 104, 128, 136, 200, 256, 264])
+def test_every_length_of_the_contraction(ctx, d):
+    """One step and less, an odd and an even number of steps, last slices of 1 to 8 chunks, with values next to the
+    rows that must not enter (the operands are views of wider, NaN-filled arrays)."""
+    rows, vocab = 300, 1100
+    h, w, y = operands(rows, d, vocab, d)
+    wide_h = torch.full((rows, d + 8), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wide_w = torch.full((vocab, d + 16), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wide_h[:, :d], wide_w[:, :d] = h, w
+    logp, lse = ctx.lm_head_logprob(wide_h[:, :d], wide_w[:, :d], y)
+    ref_p, ref_l = reference(h, w, y)
+    assert (logp.double() - ref_p).abs().max() <= TOL and (lse.double() - ref_l).abs().max() <= TOL
+    # an infinite embedding row is that row's logit, and nothing else's
+    w[7] = float("-inf")
+    h = h.abs() + 0.01
+    y[y == 7] = 8
+    logp, lse = ctx.lm_head_logprob(h, w, y)
+    ref_p, ref_l = reference(h, w, y)
+    assert (logp.double() - ref_p).abs().max() <= TOL and (lse.double() - ref_l).abs().max() <= TOL

@@ -14,6 +14,8 @@ namespace ais {
 constexpr int kSweepThreads = 256;     // one workgroup (4 wavefronts) streams one logits row
 constexpr int kTileThreads = 256;      // workgroup of the per-row scalar kernels
 constexpr int kTileRows = 1024;        // rows of one response handled by one such workgroup
+constexpr int kSelfPlanResponses = 1024;   // most responses whose tiling the scalar kernels work out for themselves
+constexpr int kTicketWord = 32;        // word of the status allocation that counts finished workgroups of a reduction
 constexpr int kMaxDevices = 64;        // device indices a context may be created on
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -33,7 +35,7 @@ struct DiagPartial {
 
 // Byte offsets of the regions of the context workspace for a call with (n_rows, n_resp).
 struct WorkspaceLayout {
-  size_t tile_off;   // int [n_resp + 2]   first tile of each response, total, and the ticket counter
+  size_t tile_off;   // int [n_resp + 2]   first tile of each response, and the total (n_resp > kSelfPlanResponses)
   size_t partial;    // DiagPartial [max_tiles]  (reused as double [max_tiles] by the loss)
   size_t g;          // float [n_rows]     per-row gradient coefficient
   size_t total;
@@ -58,16 +60,16 @@ struct ais_ctx {
   hipStream_t stream = nullptr;
   void* ws = nullptr;
   size_t ws_bytes = 0;
-  int* status_dev = nullptr;
+  int* status_dev = nullptr;     // 256 bytes: the status word and, at kTicketWord, a counter that is 0 between launches
   int n_cus = 256;               // compute units of the device
   int last_hip_error = 0;
   bool profiling = false;
   struct Timed { hipEvent_t start, stop; int which; };
   std::vector<Timed> timed;      // events of measured launches
   std::vector<hipEvent_t> pool;  // recycled events
-  // The row tiling that the last ais_diagnostics call left in the workspace (tile_off and a ticket counter that is
-  // back at zero).  The calls that follow it in a step reuse the tiling instead of launching the plan kernel again
-  // when they name the same cu_rows array, sizes and stream; anything else that writes the workspace clears it.
+  // The row tiling that the last ais_diagnostics call left in the workspace (batches of more than kSelfPlanResponses
+  // responses).  The calls that follow it in a step reuse the tiling instead of launching the plan kernel again when they
+  // name the same cu_rows array, sizes and stream; anything else that writes the workspace clears it.
   struct Plan {
     const long long* cu_rows = nullptr;
     long long n_rows = -1;

@@ -323,7 +323,7 @@ int ais_diagnostics_static(ais_ctx* ctx, const float* logp_train, const float* l
   int rc = check_diagnostics_args(logp_train, logp_roll, n_rows, cu_rows, n_resp, group_size, rewards, params, adv_out,
                                   count_out, diag_out);
   if (rc != AIS_OK) return rc;
-  // what the two kernels need: the tiling with its ticket counter, and one partial per tile (not the per-row
+  // what the kernels need: the tiling, and one partial per tile (not the per-row
   // coefficients of the gradient call, which come after them in the layout)
   const WorkspaceLayout w = workspace_layout(n_rows, n_resp);
   if (w.g > (size_t)AIS_STATIC_SCRATCH_BYTES) return AIS_ERR_SCRATCH;
@@ -332,8 +332,8 @@ int ais_diagnostics_static(ais_ctx* ctx, const float* logp_train, const float* l
   DeviceGuard guard(ctx->device);
   char* ws = static_cast<char*>(ctx->static_scratch);     // this device's address of the array, never its name
   int* tile_off = reinterpret_cast<int*>(ws + w.tile_off);
-  // the plan kernel writes every tile_off entry this call reads and zeroes the ticket counter; every partial that
-  // level 2 reads is written by level 1 of the same launch: nothing of an earlier call's contents is used
+  // every tile_off entry and every partial that this call reads it has written itself: nothing of an earlier call's
+  // contents is used
   rc = launch_plan(ctx, cu_rows, n_resp, n_rows, tile_off, w.max_tiles);
   if (rc != AIS_OK) return rc;
   return launch_diagnostics(ctx, logp_train, logp_roll, valid, n_rows, cu_rows, n_resp, group_size, rewards, *params,

@@ -74,13 +74,16 @@ __global__ __launch_bounds__(256) void zero_fill_kernel(float* __restrict__ out,
 
 struct DeviceGuard {
   int prev = -1;
-  bool ok = true;
+  bool ok = true, changed = false;
   explicit DeviceGuard(int dev) {
     if (hipGetDevice(&prev) != hipSuccess) prev = -1;
-    if (prev != dev) ok = (hipSetDevice(dev) == hipSuccess);
+    if (prev != dev) {
+      changed = true;
+      ok = (hipSetDevice(dev) == hipSuccess);
+    }
   }
   ~DeviceGuard() {
-    if (prev >= 0) (void)hipSetDevice(prev);
+    if (changed && prev >= 0) (void)hipSetDevice(prev);
   }
 };
 

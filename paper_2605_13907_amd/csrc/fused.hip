@@ -55,12 +55,15 @@ template <> __device__ __forceinline__ u32x4 patch_masked<float>(u32x4 q, int su
 typedef __attribute__((address_space(3))) void* lds_ptr;
 typedef const __attribute__((address_space(1))) void* glb_ptr;
 
-// grid.x = n_rows, block = kRowThreads.  Requires 16-byte aligned rows and
-// KFULL * kRowThreads < vocab / N <= (NV + NL) * kRowThreads: vectors 0 .. KFULL - 1 of every lane exist and are
-// loaded and stored without a bounds branch.
+// grid.x = n_rows, block = kRowThreads.  ALIGNED: both rows are 16-byte aligned; otherwise both lie the same way relative
+// to 128-byte lines, and the elements before the row's first line boundary are handled one by one together with those
+// after the last vector (such rows took the two-pass
+// kernels element by element before: 12,345 x 50,257 bf16 1,647 us a step, 443 us in one sweep).
+// KFULL * kRowThreads <= vectors of the row <= (NV + NL) * kRowThreads: vectors 0 .. KFULL - 1 of every lane exist and
+// are loaded and stored without a bounds branch.
 // Vector k of a lane (elements N * (tid + 1024 k) ..) lives in register q[k] for k < NV and in LDS slot k - NV
 // (16 bytes at byte offset 16 * (1024 (k - NV) + tid) of the dynamic LDS) for NV <= k < NV + NL.
-template <typename T, int NV, int NL, int KFULL>
+template <typename T, bool ALIGNED, int NV, int NL, int KFULL>
 __global__ __launch_bounds__(kRowThreads) void fused_logprob_softmax_kernel(
     const T* logits, long long row_stride, int vocab, const int* __restrict__ token_ids,
     const unsigned char* __restrict__ valid, float inv_temperature, float* __restrict__ logp_out,
@@ -74,9 +77,11 @@ __global__ __launch_bounds__(kRowThreads) void fused_logprob_softmax_kernel(
   const int tid = threadIdx.x;
   const T* zr = logits + row * row_stride;
   T* sr = sgrad + row * row_stride;
-  const int nvec = vocab / N;
-  const int tail = vocab - nvec * N;    // < N elements, one per thread for the first `tail` threads
-  u32x4* sv = reinterpret_cast<u32x4*>(sr);
+  const int head = ALIGNED ? 0 : head_elements(zr, vocab);
+  const int nvec = (vocab - head) / N;
+  const int rest = vocab - nvec * N;    // elements outside the vectors, one per thread for the first `rest` threads
+  auto at_rest = [&](auto* base) { return base + (ALIGNED || tid >= head ? nvec * N : 0) + tid; };
+  u32x4* sv = reinterpret_cast<u32x4*>(sr + head);
 
   if (valid != nullptr && valid[row] == 0) {     // not evaluated: no read, zero direction
     if (tid == 0) {
@@ -89,17 +94,17 @@ __global__ __launch_bounds__(kRowThreads) void fused_logprob_softmax_kernel(
       const int i = tid + k * kRowThreads;
       if (i < nvec) store_stream(sv + i, zero);
     }
-    if (tid < tail) Vec<T>::store1(sr + nvec * N + tid, 0.f);
+    if (tid < rest) Vec<T>::store1(at_rest(sr), 0.f);
     return;
   }
 
   // ---- phase 1: the whole row into registers ----
-  const u32x4* zv = reinterpret_cast<const u32x4*>(zr);
+  const u32x4* zv = reinterpret_cast<const u32x4*>(zr + head);
   u32x4 q[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int i = tid + k * kRowThreads;
-    if (k < KFULL) q[k] = load_stream(zv + i);       // the launcher promises nvec > KFULL * kRowThreads
+    if (k < KFULL) q[k] = load_stream(zv + i);       // the launcher promises nvec >= KFULL * kRowThreads
     else q[k] = (i < nvec) ? load_stream(zv + i) : masked_fill<T>();
   }
   // the LDS slots: lane i of a wavefront deposits its 16 bytes at the wavefront's base + 16 i, which is the
@@ -115,17 +120,18 @@ __global__ __launch_bounds__(kRowThreads) void fused_logprob_softmax_kernel(
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  float xt = (tid < tail) ? Vec<T>::load1(zr + nvec * N + tid) : kMasked;
+  float xt = (tid < rest) ? Vec<T>::load1(at_rest(zr)) : kMasked;
 
   const float scale = inv_temperature * kLog2e;
   const int y = token_ids[row];
   const bool y_ok = (y >= 0) && (y < vocab);
   const float zy = y_ok ? Vec<T>::load1(zr + y) : 0.f;
-  // where this thread holds the sampled token: vector slot k and lane element, or the tail register
-  const int yv = (y_ok && y < nvec * N) ? y / N : -1;
+  // where this thread holds the sampled token: vector slot k and lane element, or the register of the rest
+  const int yb = y - head;              // its position from the first vector on
+  const int yv = (y_ok && yb >= 0 && yb < nvec * N) ? yb / N : -1;
   const int yk = (yv >= 0 && yv % kRowThreads == tid) ? yv / kRowThreads : -1;
-  const int ysub = y % N;
-  const bool y_in_tail = y_ok && y >= nvec * N && (y - nvec * N) == tid;
+  const int ysub = yb & (N - 1);
+  const bool y_in_rest = y_ok && (yb < 0 || yb >= nvec * N) && (yb < 0 ? y : y - nvec * N) == tid;
 
   // The sampled token's own term is kept out of the running sum (see token_logprob_kernel).  Its element
   // is overwritten, in the packed registers, by -inf: one lane of one wavefront takes this branch, the sweeps
@@ -135,7 +141,7 @@ __global__ __launch_bounds__(kRowThreads) void fused_logprob_softmax_kernel(
     for (int k = 0; k < NV; ++k)
       if (k == yk) q[k] = patch_masked<T>(q[k], ysub);
   }
-  if (y_in_tail) xt = kMasked;
+  if (y_in_rest) xt = kMasked;
 
   // ---- phase 1: running (max, sum) over the row, one vector at a time ----
   MaxSum st{kNegHuge, 0.f};
@@ -230,9 +236,9 @@ __global__ __launch_bounds__(kRowThreads) void fused_logprob_softmax_kernel(
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  if (tid < tail) Vec<T>::store1(sr + nvec * N + tid, exp2_fast(__builtin_fmaf(xt, scale, shift)));
+  if (tid < rest) Vec<T>::store1(at_rest(sr), exp2_fast(__builtin_fmaf(xt, scale, shift)));
   // the sampled token's element p_y - 1, by the lane that owns it, after its vector store has completed
-  if (yk >= 0 || y_in_tail) {
+  if (yk >= 0 || y_in_rest) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     Vec<T>::store1(sr + y, sy);
   }
@@ -241,10 +247,10 @@ __global__ __launch_bounds__(kRowThreads) void fused_logprob_softmax_kernel(
 constexpr int kSlotBytes = kRowThreads * 16;      // one LDS slot: a 16-byte vector per lane
 constexpr int kLdsSlots = 9;                      // 144 KiB of the 160 KiB of a compute unit
 
-template <typename T, int NV, int NL, int KFULL>
+template <typename T, bool ALIGNED, int NV, int NL, int KFULL>
 int launch_nv(ais_ctx* ctx, const T* z, long long n_rows, int vocab, long long row_stride, const int* token_ids,
               const unsigned char* valid, float inv_t, float* logp, float* lse, T* sgrad) {
-  auto kernel = fused_logprob_softmax_kernel<T, NV, NL, KFULL>;
+  auto kernel = fused_logprob_softmax_kernel<T, ALIGNED, NV, NL, KFULL>;
   if (NL > 0) {
     static std::once_flag once[kMaxDevices];               // the attribute belongs to the function on one device
     static bool ok[kMaxDevices];
@@ -256,17 +262,23 @@ int launch_nv(ais_ctx* ctx, const T* z, long long n_rows, int vocab, long long r
   return AIS_OK;
 }
 
-// Vectors per lane needed for a row, or 0 when the row cannot be held (too wide, or not 16-byte aligned).
+bool rows_aligned(const void* z, const void* s, long long row_stride, int esize) {
+  return reinterpret_cast<uintptr_t>(z) % 16 == 0 && reinterpret_cast<uintptr_t>(s) % 16 == 0 &&
+         (row_stride * (long long)esize) % 16 == 0;
+}
+
+// Vectors per lane needed for a row, or 0 when the row cannot be held (too wide, or the two arrays lie differently
+// relative to 128-byte lines).
 template <typename T>
 int vectors_per_lane(const void* z, const void* s, int vocab, long long row_stride) {
   constexpr int N = Vec<T>::N;
-  const bool ok16 = reinterpret_cast<uintptr_t>(z) % 16 == 0 && reinterpret_cast<uintptr_t>(s) % 16 == 0 &&
-                    (row_stride * (long long)sizeof(T)) % 16 == 0;
+  const bool ok = rows_aligned(z, s, row_stride, sizeof(T)) ||
+                  (reinterpret_cast<uintptr_t>(z) - reinterpret_cast<uintptr_t>(s)) % 128 == 0;
   const int need = (vocab / N + kRowThreads - 1) / kRowThreads;
-  return (ok16 && need <= 24 + kLdsSlots) ? (need < 1 ? 1 : need) : 0;
+  return (ok && need <= 24 + kLdsSlots) ? (need < 1 ? 1 : need) : 0;
 }
 
-template <typename T>
+template <typename T, bool ALIGNED>
 int launch_typed(ais_ctx* ctx, int need, const void* logits, long long n_rows, int vocab, long long row_stride,
                  const int* token_ids, const unsigned char* valid, float inv_t, float* logp, float* lse,
                  void* sgrad) {
@@ -274,11 +286,12 @@ int launch_typed(ais_ctx* ctx, int need, const void* logits, long long n_rows, i
   T* s = static_cast<T*>(sgrad);
   // NV is a compile-time constant (the row lives in named registers); sizes near the register limit get an
   // exact instantiation so that common vocabularies (e.g. 151,936 -> 19 vectors per lane) do not spill
-  // PREV: the widest row of the previous class; a row that reaches this one has more than PREV * 1024 vectors
-#define AIS_FUSED_CASE(PREV, NEED, NVAL, NLVAL)                                                         \
-  if (need <= NEED)                                                                                     \
-    return launch_nv<T, NVAL, NLVAL, PREV>(ctx, z, n_rows, vocab, row_stride, token_ids, valid, inv_t, \
-                                           logp, lse, s);
+  // PREV: the widest row of the previous class; a row that reaches this one has more than PREV * 1024 vectors, of which
+  // an unaligned row may have lost up to 8 to its head
+#define AIS_FUSED_CASE(PREV, NEED, NVAL, NLVAL)                                                      \
+  if (need <= NEED)                                                                                  \
+    return launch_nv<T, ALIGNED, NVAL, NLVAL, (ALIGNED || PREV == 0 ? PREV : PREV - 1)>(             \
+        ctx, z, n_rows, vocab, row_stride, token_ids, valid, inv_t, logp, lse, s);
   AIS_FUSED_CASE(0, 4, 4, 0)
   AIS_FUSED_CASE(4, 8, 8, 0)
   AIS_FUSED_CASE(8, 12, 12, 0)
@@ -301,8 +314,8 @@ int launch_typed(ais_ctx* ctx, int need, const void* logits, long long n_rows, i
 
 }  // namespace
 
-// Sets *used_registers to false (and launches nothing) when the row does not fit the register file or is
-// not 16-byte aligned; the caller then runs the two-pass kernels.
+// Sets *used_registers to false (and launches nothing) when the row does not fit the register file or the two arrays
+// lie differently relative to 128-byte lines; the caller then runs the two-pass kernels.
 int launch_fused_logprob_softmax(ais_ctx* ctx, const void* logits, ais_dtype dtype, long long n_rows, int vocab,
                                  long long row_stride, const int* token_ids, const unsigned char* valid,
                                  float inv_temperature, float* logp_out, float* lse_out, void* sgrad,
@@ -312,11 +325,12 @@ int launch_fused_logprob_softmax(ais_ctx* ctx, const void* logits, ais_dtype dty
   *used_registers = need > 0;
   if (need == 0 || n_rows == 0) return AIS_OK;
   ScopedTimer timer(ctx, AIS_K_FUSED);
-  const int rc = dtype == AIS_BF16
-                     ? launch_typed<bf16_t>(ctx, need, logits, n_rows, vocab, row_stride, token_ids, valid,
-                                            inv_temperature, logp_out, lse_out, sgrad)
-                     : launch_typed<float>(ctx, need, logits, n_rows, vocab, row_stride, token_ids, valid,
-                                           inv_temperature, logp_out, lse_out, sgrad);
+  auto launch = [&](auto type) {
+    typedef decltype(type) T;
+    auto run = rows_aligned(logits, sgrad, row_stride, sizeof(T)) ? launch_typed<T, true> : launch_typed<T, false>;
+    return run(ctx, need, logits, n_rows, vocab, row_stride, token_ids, valid, inv_temperature, logp_out, lse_out, sgrad);
+  };
+  const int rc = dtype == AIS_BF16 ? launch(bf16_t{}) : launch(float{});
   if (rc != AIS_OK) return rc;
   return hip_fail(ctx, hipGetLastError());
 }

@@ -20,15 +20,16 @@ namespace {
 
 using namespace dev;
 
-// Row abs-max -> scale, shared by the workgroup through LDS.
-template <typename T, bool VEC>
-__device__ __forceinline__ float row_scale(const T* zr, int vocab, float* lds) {
+// Row abs-max -> scale, shared by the workgroup through LDS.  The row's vectors start `head` elements into it (0 when it
+// is 16-byte aligned); fewer elements than there are threads lie outside them.
+template <typename T>
+__device__ __forceinline__ float row_scale(const T* zr, int vocab, int head, float* lds) {
   constexpr int N = Vec<T>::N;
   const int tid = threadIdx.x;
-  const int nvec = VEC ? vocab / N : 0;
+  const int nvec = (vocab - head) / N;
   float amax = 0.f;
-  if (VEC) {
-    const u32x4* zv = reinterpret_cast<const u32x4*>(zr);
+  {
+    const u32x4* zv = reinterpret_cast<const u32x4*>(zr + head);
     for (int i = tid; i < nvec; i += kSweepThreads) {
       float x[N];
       Vec<T>::unpack(zv[i], x);      // cached load: the row is read again right away
@@ -36,7 +37,7 @@ __device__ __forceinline__ float row_scale(const T* zr, int vocab, float* lds) {
       for (int k = 0; k < N; ++k) amax = fmaxf(amax, fabsf(x[k]));
     }
   }
-  for (int v = nvec * N + tid; v < vocab; v += kSweepThreads) amax = fmaxf(amax, fabsf(Vec<T>::load1(zr + v)));
+  if (tid < vocab - nvec * N) amax = fmaxf(amax, fabsf(Vec<T>::load1(zr + (tid < head ? 0 : nvec * N) + tid)));
   amax = wave_max(amax);
   if ((tid & 63) == 0) lds[tid >> 6] = amax;
   __syncthreads();
@@ -44,6 +45,7 @@ __device__ __forceinline__ float row_scale(const T* zr, int vocab, float* lds) {
   return scale_of(amax);
 }
 
+// VEC: the codes of a vector are aligned to their number; otherwise they are written one by one.
 template <typename T, bool VEC>
 __global__ __launch_bounds__(kSweepThreads) void fp8_quantize_kernel(const T* __restrict__ logits, long long row_stride,
                                                                      int vocab, unsigned char* __restrict__ codes,
@@ -55,14 +57,17 @@ __global__ __launch_bounds__(kSweepThreads) void fp8_quantize_kernel(const T* __
   const int tid = threadIdx.x;
   const T* zr = logits + row * row_stride;
   unsigned char* cr = codes + row * codes_stride;
-  const float s = row_scale<T, VEC>(zr, vocab, lds);
+  const int lead = head_elements(zr, vocab);
+  const float s = row_scale<T>(zr, vocab, lead, lds);
   if (tid == 0) scale_out[row] = s;
   const RowDivider d = make_divider(s);
-  const int nvec = VEC ? vocab / N : 0;
+  const int head = VEC ? lead : 0;
+  const int nvec = VEC ? (vocab - head) / N : 0;
   auto encode = [&](auto slow) {
     constexpr bool SLOW = decltype(slow)::value;
     if (VEC) {
-      const u32x4* zv = reinterpret_cast<const u32x4*>(zr);
+      const u32x4* zv = reinterpret_cast<const u32x4*>(zr + head);
+      unsigned char* cv = cr + head;
       for (int i = tid; i < nvec; i += kSweepThreads) {
         float x[N];
         Vec<T>::unpack(load_stream(zv + i), x);
@@ -73,14 +78,16 @@ __global__ __launch_bounds__(kSweepThreads) void fp8_quantize_kernel(const T* __
                  (to_e4m3x2(divide<SLOW>(x[4 * k + 2], d), divide<SLOW>(x[4 * k + 3], d)) << 16);
         if (N == 8) {
           uint2 o = {w[0], w[N / 4 - 1]};
-          *reinterpret_cast<uint2*>(cr + (long long)i * N) = o;
+          *reinterpret_cast<uint2*>(cv + (long long)i * N) = o;
         } else {
-          *reinterpret_cast<uint32_t*>(cr + (long long)i * N) = w[0];
+          *reinterpret_cast<uint32_t*>(cv + (long long)i * N) = w[0];
         }
       }
     }
-    for (int v = nvec * N + tid; v < vocab; v += kSweepThreads)
+    for (int e = tid; e < vocab - nvec * N; e += kSweepThreads) {
+      const int v = e < head ? e : e + nvec * N;
       cr[v] = (unsigned char)(to_e4m3x2(divide<SLOW>(Vec<T>::load1(zr + v), d), 0.f) & 0xffu);
+    }
   };
   if (d.slow) encode(std::true_type{}); else encode(std::false_type{});
 }
@@ -126,7 +133,7 @@ __global__ __launch_bounds__(kSweepThreads) void fp8_dequantize_kernel(const uns
 
 // log softmax(z_r)[y] with z_r = s * e4m3(z / s): abs-max pass, then a streaming log-sum-exp over the
 // round-tripped values.
-template <typename T, bool VEC>
+template <typename T>
 __global__ __launch_bounds__(kSweepThreads) void fp8_rollout_logprob_kernel(
     const T* __restrict__ logits, long long row_stride, int vocab, const int* __restrict__ token_ids,
     const unsigned char* __restrict__ valid, float* __restrict__ logp_out, int* __restrict__ status) {
@@ -140,17 +147,18 @@ __global__ __launch_bounds__(kSweepThreads) void fp8_rollout_logprob_kernel(
     return;
   }
   const T* zr = logits + row * row_stride;
-  const float s = row_scale<T, VEC>(zr, vocab, lds);
+  const int head = head_elements(zr, vocab);
+  const float s = row_scale<T>(zr, vocab, head, lds);
   const RowDivider d = make_divider(s);
-  const int nvec = VEC ? vocab / N : 0;
+  const int nvec = (vocab - head) / N;
   MaxSum st{kNegHuge, 0.f};
   // the round-tripped logit is s * decode(code): the row scale is folded into the exponent's multiplier (s > 0,
   // so the running maximum can be taken over the decoded values)
   const float scale = s * kLog2e;
   auto sweep = [&](auto slow) {
     constexpr bool SLOW = decltype(slow)::value;
-    if (VEC) {
-      const u32x4* zv = reinterpret_cast<const u32x4*>(zr);
+    {
+      const u32x4* zv = reinterpret_cast<const u32x4*>(zr + head);
       for (int i = tid; i < nvec; i += kSweepThreads) {
         float x[N];
         Vec<T>::unpack(load_stream(zv + i), x);
@@ -163,8 +171,8 @@ __global__ __launch_bounds__(kSweepThreads) void fp8_rollout_logprob_kernel(
         accumulate<N>(x, scale, st);
       }
     }
-    for (int v = nvec * N + tid; v < vocab; v += kSweepThreads) {
-      float x = from_e4m3x2(to_e4m3x2(divide<SLOW>(Vec<T>::load1(zr + v), d), 0.f))[0];
+    if (tid < vocab - nvec * N) {
+      float x = from_e4m3x2(to_e4m3x2(divide<SLOW>(Vec<T>::load1(zr + (tid < head ? 0 : nvec * N) + tid), d), 0.f))[0];
       accumulate<1>(&x, scale, st);
     }
   };
@@ -202,19 +210,17 @@ int launch_fp8_quantize(ais_ctx* ctx, const void* logits, ais_dtype dtype, long 
     return hip_fail(ctx, hipGetLastError());      // bf16 row held in registers, codes from a per-row table
   if (try_fp8_quantize_rows(ctx, logits, dtype, n_rows, vocab, row_stride, codes, codes_stride, scale_out))
     return hip_fail(ctx, hipGetLastError());      // row held in registers: one read of the logits
-  if (dtype == AIS_BF16) {
-    const bf16_t* z = static_cast<const bf16_t*>(logits);
-    if (aligned(z, row_stride * 2, 16) && aligned(codes, codes_stride, 8))
-      fp8_quantize_kernel<bf16_t, true><<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, codes, codes_stride, scale_out);
-    else
-      fp8_quantize_kernel<bf16_t, false><<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, codes, codes_stride, scale_out);
-  } else {
-    const float* z = static_cast<const float*>(logits);
-    if (aligned(z, row_stride * 4, 16) && aligned(codes, codes_stride, 4))
-      fp8_quantize_kernel<float, true><<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, codes, codes_stride, scale_out);
-    else
-      fp8_quantize_kernel<float, false><<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, codes, codes_stride, scale_out);
-  }
+  auto launch = [&](const auto* z) {
+    typedef std::remove_cv_t<std::remove_pointer_t<decltype(z)>> T;
+    constexpr int N = Vec<T>::N;
+    // vectors start a multiple of N elements from any other place that is 16-byte aligned
+    const bool vec = (reinterpret_cast<uintptr_t>(codes) - reinterpret_cast<uintptr_t>(z) / sizeof(T)) % N == 0 &&
+                     (codes_stride - row_stride) % N == 0;
+    auto kernel = vec ? fp8_quantize_kernel<T, true> : fp8_quantize_kernel<T, false>;
+    kernel<<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, codes, codes_stride, scale_out);
+  };
+  if (dtype == AIS_BF16) launch(static_cast<const bf16_t*>(logits));
+  else launch(static_cast<const float*>(logits));
   return hip_fail(ctx, hipGetLastError());
 }
 
@@ -249,19 +255,13 @@ int launch_fp8_rollout_logprob(ais_ctx* ctx, const void* logits, ais_dtype dtype
   ScopedTimer timer(ctx, AIS_K_FP8_LOGPROB);
   if (try_fp8_rollout_logprob_table(ctx, logits, dtype, n_rows, vocab, row_stride, token_ids, valid, logp_out))
     return hip_fail(ctx, hipGetLastError());      // bf16 row read once, terms of the sum from a per-row table
-  if (dtype == AIS_BF16) {
-    const bf16_t* z = static_cast<const bf16_t*>(logits);
-    if (aligned(z, row_stride * 2, 16))
-      fp8_rollout_logprob_kernel<bf16_t, true><<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, token_ids, valid, logp_out, ctx->status_dev);
-    else
-      fp8_rollout_logprob_kernel<bf16_t, false><<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, token_ids, valid, logp_out, ctx->status_dev);
-  } else {
-    const float* z = static_cast<const float*>(logits);
-    if (aligned(z, row_stride * 4, 16))
-      fp8_rollout_logprob_kernel<float, true><<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, token_ids, valid, logp_out, ctx->status_dev);
-    else
-      fp8_rollout_logprob_kernel<float, false><<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, token_ids, valid, logp_out, ctx->status_dev);
-  }
+  auto launch = [&](const auto* z) {
+    typedef std::remove_cv_t<std::remove_pointer_t<decltype(z)>> T;
+    fp8_rollout_logprob_kernel<T><<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, token_ids, valid, logp_out,
+                                                                   ctx->status_dev);
+  };
+  if (dtype == AIS_BF16) launch(static_cast<const bf16_t*>(logits));
+  else launch(static_cast<const float*>(logits));
   return hip_fail(ctx, hipGetLastError());
 }
 

@@ -5,7 +5,8 @@
 // one compute unit (1,024 threads x NV 16-byte vectors per lane) between the abs-max reduction that fixes
 // the scale and the pass that encodes with it.  Rows of 25 to 33 vectors per lane keep their last 9 vectors
 // per lane in LDS, filled by direct global -> LDS copies.  Same results as the streaming two-pass kernel in
-// fp8.hip, which remains the route for rows that do not fit or are not 16-byte aligned.  (The fused rollout log-prob
+// fp8.hip, which remains the route for rows that do not fit.  Rows that are not 16-byte aligned are split at their first
+// 128-byte boundary (see head_elements).  (The fused rollout log-prob
 // stays a streaming kernel: its second pass costs 18 vector instructions per element, about 18 us per row on one
 // compute unit, and a workgroup that owns the whole unit cannot overlap that arithmetic with another row's loads:
 // the register-resident form took 4.6 ms on 41,643 rows of 151,936 where two streaming passes take 3.6 ms.)
@@ -30,16 +31,14 @@ typedef const __attribute__((address_space(1))) void* glb_ptr;
 
 // Loads the row, returns its scale (abs-max / 448) to every thread.  q[] (vectors 0 .. NV - 1 of the lane), the
 // LDS slots lrow (vectors NV .. NV + NL - 1, 16 bytes at index 1024 (k - NV) + tid) and xt hold the row afterwards.
-// KFULL: the caller promises that the row has more than KFULL * 1024 vectors, so vectors 0 .. KFULL - 1 of every
-// lane exist and are loaded without a bounds branch.
+// KFULL: the caller promises that the row has at least KFULL * 1024 vectors, so vectors 0 .. KFULL - 1 of every
+// lane exist and are loaded without a bounds branch.  xt: the thread's element outside the vectors (head, rest).
 template <typename T, int NV, int NL, int KFULL>
-__device__ __forceinline__ float load_row_and_scale(const T* zr, int vocab, u32x4 (&q)[NV], u32x4* lrow, float& xt,
-                                                    float* lds) {
+__device__ __forceinline__ float load_row_and_scale(const T* zr, int head, int nvec, int rest, u32x4 (&q)[NV],
+                                                    u32x4* lrow, float& xt, float* lds) {
   constexpr int N = Vec<T>::N;
   const int tid = threadIdx.x;
-  const int nvec = vocab / N;
-  const int tail = vocab - nvec * N;
-  const u32x4* zv = reinterpret_cast<const u32x4*>(zr);
+  const u32x4* zv = reinterpret_cast<const u32x4*>(zr + head);
   const u32x4 zero = {0u, 0u, 0u, 0u};
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
@@ -60,7 +59,7 @@ __device__ __forceinline__ float load_row_and_scale(const T* zr, int vocab, u32x
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  xt = (tid < tail) ? Vec<T>::load1(zr + nvec * N + tid) : 0.f;
+  xt = (tid < rest) ? Vec<T>::load1(zr + (tid < head ? 0 : nvec * N) + tid) : 0.f;
   float amax = fabsf(xt);
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
@@ -99,7 +98,7 @@ __device__ __forceinline__ float load_row_and_scale(const T* zr, int vocab, u32x
   return s;
 }
 
-template <typename T, int NV, int NL, int KFULL>
+template <typename T, bool ALIGNED, int NV, int NL, int KFULL>
 __global__ __launch_bounds__(kRowThreads) void fp8_quantize_row_kernel(const T* __restrict__ logits,
                                                                        long long row_stride, int vocab,
                                                                        unsigned char* __restrict__ codes,
@@ -112,12 +111,14 @@ __global__ __launch_bounds__(kRowThreads) void fp8_quantize_row_kernel(const T* 
   const long long row = blockIdx.x;
   const int tid = threadIdx.x;
   const T* zr = logits + row * row_stride;
+  const int head = ALIGNED ? 0 : head_elements(zr, vocab);
+  const int nvec = (vocab - head) / N;
+  const int rest = vocab - nvec * N;       // elements outside the vectors, one per thread for the first `rest` threads
   unsigned char* cr = codes + row * codes_stride;
-  const int nvec = vocab / N;
-  const int tail = vocab - nvec * N;
+  unsigned char* cv = cr + head;           // codes of the vectors, aligned to N bytes (the launcher checks)
   u32x4 q[NV];
   float xt;
-  const float s = load_row_and_scale<T, NV, NL, KFULL>(zr, vocab, q, lrow, xt, lds);
+  const float s = load_row_and_scale<T, NV, NL, KFULL>(zr, head, nvec, rest, q, lrow, xt, lds);
   if (tid == 0) scale_out[row] = s;
   const RowDivider d = make_divider(s);
   // vector indices from an opaque copy of the thread index, so that no per-vector offset stays alive from the loads
@@ -136,9 +137,9 @@ __global__ __launch_bounds__(kRowThreads) void fp8_quantize_row_kernel(const T* 
       if (i < nvec) {
         if (N == 8) {
           uint2 o = {w[0], w[N / 4 - 1]};
-          *reinterpret_cast<uint2*>(cr + (long long)i * N) = o;
+          *reinterpret_cast<uint2*>(cv + (long long)i * N) = o;
         } else {
-          *reinterpret_cast<uint32_t*>(cr + (long long)i * N) = w[0];
+          *reinterpret_cast<uint32_t*>(cv + (long long)i * N) = w[0];
         }
       }
     };
@@ -154,7 +155,8 @@ __global__ __launch_bounds__(kRowThreads) void fp8_quantize_row_kernel(const T* 
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if (tid < tail) cr[nvec * N + tid] = (unsigned char)(to_e4m3x2(divide<SLOW>(xt, d), 0.f) & 0xffu);
+    if (tid < rest)
+      cr[(tid < head ? 0 : nvec * N) + tid] = (unsigned char)(to_e4m3x2(divide<SLOW>(xt, d), 0.f) & 0xffu);
   };
   if (d.slow) encode(std::true_type{}); else encode(std::false_type{});
 }
@@ -164,8 +166,10 @@ __global__ __launch_bounds__(kRowThreads) void fp8_quantize_row_kernel(const T* 
 // code chunks (N codes each, N = elements of a 16-byte output vector), decodes them into output vectors held in
 // registers, and only then issues all of its stores: the long same-direction bursts that a read+write stream needs
 // on this device (see dlogits_burst_kernel).  Rows wider than NV * 1,024 vectors take NSEG such bursts, one after
-// the other.  Vectors 0 .. KFULL - 1 of every lane are certain to exist.
-template <typename T, int NV, int NSEG, int KFULL>
+// the other.  Vectors 0 .. KFULL - 1 of every lane are certain to exist.  ALIGNED: the output rows are 16-byte aligned;
+// otherwise they are split at their first 128-byte boundary (12,345 x 50,257 bf16, quantised and decoded: 2,137 us when
+// such rows went element by element, 650 us now).
+template <typename T, bool ALIGNED, int NV, int NSEG, int KFULL>
 __global__ __launch_bounds__(kRowThreads) void fp8_dequantize_burst_kernel(const unsigned char* __restrict__ codes,
                                                                            long long codes_stride,
                                                                            const float* __restrict__ scale, int vocab,
@@ -176,10 +180,12 @@ __global__ __launch_bounds__(kRowThreads) void fp8_dequantize_burst_kernel(const
   const int tid = threadIdx.x;
   const unsigned char* cr = codes + row * codes_stride;
   T* orow = out + row * out_stride;
-  u32x4* ov = reinterpret_cast<u32x4*>(orow);
+  const int head = ALIGNED ? 0 : head_elements(orow, vocab);
+  u32x4* ov = reinterpret_cast<u32x4*>(orow + head);
+  const unsigned char* cv = cr + head;             // codes of the vectors, aligned to N bytes (the launcher checks)
   const float s = scale[row];
-  const int nvec = vocab / N;
-  const int tail = vocab - nvec * N;
+  const int nvec = (vocab - head) / N;
+  const int rest = vocab - nvec * N;               // elements outside the vectors
 #pragma unroll
   for (int seg = 0; seg < NSEG; ++seg) {
     uint32_t w[NV][N / 4];
@@ -188,11 +194,11 @@ __global__ __launch_bounds__(kRowThreads) void fp8_dequantize_burst_kernel(const
       const int i = tid + (seg * NV + k) * kRowThreads;
       if (seg * NV + k < KFULL || i < nvec) {
         if (N == 8) {
-          const u32x2 c = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(cr + (long long)i * N));
+          const u32x2 c = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(cv + (long long)i * N));
           w[k][0] = c[0];
           w[k][N / 4 - 1] = c[1];
         } else {
-          w[k][0] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(cr + (long long)i * N));
+          w[k][0] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(cv + (long long)i * N));
         }
       } else {
 #pragma unroll
@@ -223,21 +229,37 @@ __global__ __launch_bounds__(kRowThreads) void fp8_dequantize_burst_kernel(const
       if (seg * NV + k < KFULL || i < nvec) store_stream(ov + i, q[k]);
     }
   }
-  if (tid < tail) Vec<T>::store1(orow + nvec * N + tid, from_e4m3x2(cr[nvec * N + tid])[0] * s);
+  if (tid < rest) {
+    const int v = (ALIGNED || tid >= head ? nvec * N : 0) + tid;
+    Vec<T>::store1(orow + v, from_e4m3x2(cr[v])[0] * s);
+  }
 }
 
+bool row_aligned(const void* z, long long row_stride, int esize) {
+  return reinterpret_cast<uintptr_t>(z) % 16 == 0 && (row_stride * (long long)esize) % 16 == 0;
+}
+
+// Whether the codes of every 16-byte vector of the rows at z (n elements each) start at a multiple of n bytes: vectors
+// start a multiple of n elements from any other place that is 16-byte aligned.
+bool codes_aligned(const void* z, long long row_stride, int esize, const void* codes, long long codes_stride) {
+  const int n = 16 / esize;
+  const uintptr_t element = reinterpret_cast<uintptr_t>(z) / esize;
+  return (reinterpret_cast<uintptr_t>(codes) - element) % n == 0 && (codes_stride - row_stride) % n == 0;
+}
+
+// Vectors per lane, or 0 when the row does not fit or has no whole vector to speak of.
 template <typename T>
 int vectors_per_lane(const void* z, int vocab, long long row_stride) {
   constexpr int N = Vec<T>::N;
-  const bool ok16 = reinterpret_cast<uintptr_t>(z) % 16 == 0 && (row_stride * (long long)sizeof(T)) % 16 == 0;
   const int need = (vocab / N + kRowThreads - 1) / kRowThreads;
-  return (ok16 && need <= 24 + kLdsSlots) ? (need < 1 ? 1 : need) : 0;
+  if (!row_aligned(z, row_stride, sizeof(T)) && vocab < 128) return 0;
+  return need <= 24 + kLdsSlots ? (need < 1 ? 1 : need) : 0;
 }
 
-template <typename T, int NV, int NL, int KFULL>
+template <typename T, bool ALIGNED, int NV, int NL, int KFULL>
 bool launch_rows(ais_ctx* ctx, const T* z, long long n_rows, int vocab, long long row_stride, unsigned char* codes,
                  long long codes_stride, float* scale_out) {
-  auto kernel = fp8_quantize_row_kernel<T, NV, NL, KFULL>;
+  auto kernel = fp8_quantize_row_kernel<T, ALIGNED, NV, NL, KFULL>;
   if (NL > 0) {
     static std::once_flag once[kMaxDevices];               // the attribute belongs to the function on one device
     static bool ok[kMaxDevices];
@@ -252,10 +274,15 @@ bool launch_rows(ais_ctx* ctx, const T* z, long long n_rows, int vocab, long lon
 template <typename T>
 bool dispatch_rows(ais_ctx* ctx, int need, const T* z, long long n_rows, int vocab, long long row_stride,
                    unsigned char* codes, long long codes_stride, float* scale_out) {
-// PREV: the widest row of the previous class; a row that reaches this one has more than PREV * 1024 vectors
-#define AIS_ROW_CASE(PREV, NEED, NVAL, NLVAL) \
-  if (need <= NEED)                           \
-    return launch_rows<T, NVAL, NLVAL, PREV>(ctx, z, n_rows, vocab, row_stride, codes, codes_stride, scale_out);
+// PREV: the widest row of the previous class; a row that reaches this one has more than PREV * 1024 vectors, of which an
+// unaligned row may have lost up to 8 to its head
+#define AIS_ROW_CASE(PREV, NEED, NVAL, NLVAL)                                                            \
+  if (need <= NEED) {                                                                                    \
+    auto launch = row_aligned(z, row_stride, sizeof(T))                                                  \
+                      ? launch_rows<T, true, NVAL, NLVAL, PREV>                                          \
+                      : launch_rows<T, false, NVAL, NLVAL, (PREV > 0 ? PREV - 1 : 0)>;                   \
+    return launch(ctx, z, n_rows, vocab, row_stride, codes, codes_stride, scale_out);                    \
+  }
   AIS_ROW_CASE(0, 4, 4, 0)
   AIS_ROW_CASE(4, 8, 8, 0)
   AIS_ROW_CASE(8, 12, 12, 0)
@@ -274,8 +301,7 @@ bool dispatch_rows(ais_ctx* ctx, int need, const T* z, long long n_rows, int voc
 // Returns true when the register-resident kernel was launched, false when the row does not qualify.
 bool try_fp8_quantize_rows(ais_ctx* ctx, const void* logits, ais_dtype dtype, long long n_rows, int vocab,
                            long long row_stride, unsigned char* codes, long long codes_stride, float* scale_out) {
-  const int store_align = dtype == AIS_BF16 ? 8 : 4;
-  if (reinterpret_cast<uintptr_t>(codes) % store_align != 0 || codes_stride % store_align != 0) return false;
+  if (!codes_aligned(logits, row_stride, dtype == AIS_BF16 ? 2 : 4, codes, codes_stride)) return false;
   if (dtype == AIS_BF16) {
     const int need = vectors_per_lane<bf16_t>(logits, vocab, row_stride);
     if (need == 0) return false;
@@ -294,21 +320,23 @@ bool try_fp8_dequantize_burst(ais_ctx* ctx, const unsigned char* codes, long lon
                               long long n_rows, int vocab, void* out, ais_dtype dtype, long long out_stride) {
   const int esize = dtype == AIS_BF16 ? 2 : 4;
   const int n = 16 / esize;                          // elements of an output vector = codes of a chunk
-  if (reinterpret_cast<uintptr_t>(out) % 16 != 0 || (out_stride * esize) % 16 != 0) return false;
-  if (reinterpret_cast<uintptr_t>(codes) % n != 0 || codes_stride % n != 0) return false;
+  if (!codes_aligned(out, out_stride, esize, codes, codes_stride)) return false;
+  const bool aligned = row_aligned(out, out_stride, esize);
   const int need = (vocab / n + kRowThreads - 1) / kRowThreads;
   dim3 grid((unsigned)n_rows), block(kRowThreads);
   // (vectors that surely exist, vectors per lane and burst, bursts): a row reaches a class only if it is wider than
-  // the class before it
-#define AIS_DEQ_CASE(KFULL, NVAL, NSEG)                                                                        \
-  if (need <= NVAL * NSEG) {                                                                                   \
-    if (dtype == AIS_BF16)                                                                                     \
-      fp8_dequantize_burst_kernel<bf16_t, NVAL, NSEG, KFULL><<<grid, block, 0, ctx->stream>>>(                 \
-          codes, codes_stride, scale, vocab, static_cast<bf16_t*>(out), out_stride);                           \
-    else                                                                                                       \
-      fp8_dequantize_burst_kernel<float, NVAL, NSEG, KFULL><<<grid, block, 0, ctx->stream>>>(                  \
-          codes, codes_stride, scale, vocab, static_cast<float*>(out), out_stride);                            \
-    return true;                                                                                               \
+  // the class before it; an unaligned row may have lost up to 8 vectors to its head
+#define AIS_DEQ_LAUNCH(T, KFULL, NVAL, NSEG)                                                                     \
+  {                                                                                                              \
+    auto kernel = aligned ? fp8_dequantize_burst_kernel<T, true, NVAL, NSEG, KFULL>                              \
+                          : fp8_dequantize_burst_kernel<T, false, NVAL, NSEG, (KFULL > 0 ? KFULL - 1 : 0)>;      \
+    kernel<<<grid, block, 0, ctx->stream>>>(codes, codes_stride, scale, vocab, static_cast<T*>(out), out_stride); \
+    return true;                                                                                                 \
+  }
+#define AIS_DEQ_CASE(KFULL, NVAL, NSEG)                          \
+  if (need <= NVAL * NSEG) {                                     \
+    if (dtype == AIS_BF16) AIS_DEQ_LAUNCH(bf16_t, KFULL, NVAL, NSEG) \
+    else AIS_DEQ_LAUNCH(float, KFULL, NVAL, NSEG)                \
   }
   AIS_DEQ_CASE(0, 4, 1)
   AIS_DEQ_CASE(4, 8, 1)
@@ -319,6 +347,7 @@ bool try_fp8_dequantize_burst(ais_ctx* ctx, const unsigned char* codes, long lon
   AIS_DEQ_CASE(20, 16, 2)
   AIS_DEQ_CASE(32, 16, 3)
 #undef AIS_DEQ_CASE
+#undef AIS_DEQ_LAUNCH
   return false;
 }
 

@@ -12,10 +12,13 @@
 //
 // One workgroup of 1,024 threads per row; the row is read from HBM once and waits in registers (up to 24 16-byte
 // vectors per lane, 196,608 logits; 23 for the log-prob, which parks up to 8 more per lane in LDS: 253,952 logits)
-// while the table is built.  Wider, unaligned or fp32 rows take the kernels of fp8_rows.hip / fp8.hip.
+// while the table is built.  Rows that are not 16-byte aligned are split at their first 128-byte boundary (see
+// head_elements).  Wider or fp32 rows take the kernels of fp8_rows.hip / fp8.hip.
 #include "ais_internal.h"
 #include "device_utils.h"
 #include "fp8_utils.h"
+
+#include <type_traits>
 
 namespace ais {
 namespace {
@@ -45,40 +48,118 @@ __device__ __forceinline__ float bf16_bits_to_float(int bits) { return __uint_as
 __device__ __forceinline__ uint32_t code_of(float q) { return to_e4m3x2(q, 0.f) & 0xffu; }
 __device__ __forceinline__ float value_of(uint32_t code) { return from_e4m3x2(code)[0]; }
 
-// Issues the loads of a row: q[k] is vector tid + 1024 k of the row (slots past the end hold zeros), xt the ragged
-// tail (one element for the first `tail` threads).  KFULL: vectors 0 .. KFULL - 1 of every lane are certain to exist.
-template <int NV, int KFULL>
-__device__ __forceinline__ void issue_row(const bf16_t* zr, int vocab, u32x4 (&q)[NV], float& xt) {
-  const int tid = threadIdx.x;
-  const int nvec = vocab / 8;
-  const int tail = vocab - nvec * 8;
-  const u32x4* zv = reinterpret_cast<const u32x4*>(zr);
-  const u32x4 zero = {0u, 0u, 0u, 0u};
-#pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    const int i = tid + k * kRowThreads;
-    if (k < KFULL) q[k] = load_stream(zv + i);
-    else q[k] = (i < nvec) ? load_stream(zv + i) : zero;
+// Where the parts of a row lie: `head` elements, then `nvec` vectors from `zv` on, then the rest.  The elements outside
+// the vectors are handled one by one by the first `rest` threads.
+template <bool ALIGNED>
+struct RowParts {
+  const bf16_t* zr;
+  const u32x4* zv;
+  int head, nvec, rest;
+  __device__ __forceinline__ RowParts(const bf16_t* row, int vocab) : zr(row) {
+    head = ALIGNED ? 0 : head_elements(row, vocab);
+    nvec = (vocab - head) / 8;
+    rest = vocab - nvec * 8;
+    zv = reinterpret_cast<const u32x4*>(row + head);
   }
-  xt = (tid < tail) ? Vec<bf16_t>::load1(zr + nvec * 8 + tid) : 0.f;
+  // index of the element that thread `tid` < rest owns (from an opaque copy of the thread index: nothing of it is kept
+  // in registers across the row loop)
+  __device__ __forceinline__ int outside(int tid) const {
+    asm volatile("" : "+v"(tid));
+    return (ALIGNED || tid >= head ? nvec * 8 : 0) + tid;
+  }
+  // that element, or (the other threads) some element of the row: neither changes its extremes
+  __device__ __forceinline__ float load_outside(int tid) const {
+    asm volatile("" : "+v"(tid));
+    return Vec<bf16_t>::load1(zr + (tid < rest ? outside(tid) : 0));
+  }
+  // Vector tid + 1024 k; past the end of the row (possible only if !full) its last vector, which changes neither
+  // maximum nor minimum and is never summed.  nvec >= 1.
+  __device__ __forceinline__ u32x4 load(int tid, int k, bool full) const {
+    if (!full) return load_stream(zv + (unsigned)min(tid + k * kRowThreads, nvec - 1));
+    // uniform base + one 32-bit offset for all vectors: an address costs a scalar addition and no vector instruction
+    const u32x4* base = zv + k * kRowThreads;
+    asm volatile("" : "+s"(base));
+    return load_stream(base + (unsigned)tid);
+  }
+};
+
+// Issues the loads of a row: q[k] is vector tid + 1024 k of the row, xt the thread's element outside the vectors.  KFULL:
+// vectors 0 .. KFULL - 1 of every lane are certain to exist.
+template <bool ALIGNED, int NV, int KFULL>
+__device__ __forceinline__ void issue_row(const RowParts<ALIGNED>& row, u32x4 (&q)[NV], float& xt) {
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int k = 0; k < NV; ++k) q[k] = row.load(tid, k, k < KFULL);
+  xt = row.load_outside(tid);
+}
+
+typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
+
+template <int LEVEL>
+__device__ __forceinline__ uint32_t lane_partner(uint32_t v) {        // butterfly partner, levels 0..5
+  if (LEVEL >= 4) return __shfl_xor(v, 1 << LEVEL);
+  constexpr int kCtrl = LEVEL == 0   ? kDppQuadXor1
+                        : LEVEL == 1 ? kDppQuadXor2
+                        : LEVEL == 2 ? kDppRowHalfMirror
+                                     : kDppRowMirror;
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, 0xf, 0xf, true);
+}
+
+// The largest and smallest element by comparing numbers: the route for rows with a NaN (it loses every comparison) or
+// without a positive element.  Reads the row again, from memory.
+template <bool ALIGNED>
+__device__ __forceinline__ void row_minmax_streamed(const RowParts<ALIGNED>& row, float* lds, float& zmax,
+                                                    float& zmin) {
+  const int tid = threadIdx.x;
+  float hi = row.load_outside(tid), lo = hi;
+  for (int i = tid; i < row.nvec; i += kRowThreads) {
+    float x[8];
+    Vec<bf16_t>::unpack(load_stream(row.zv + i), x);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      hi = fmaxf(hi, x[k]);
+      lo = fminf(lo, x[k]);
+    }
+  }
+  hi = wave_max(hi);
+  lo = -wave_max(-lo);
+  __syncthreads();                                          // `lds` is still being read by the caller's reduction
+  if ((tid & 63) == 0) {
+    lds[tid >> 6] = hi;
+    lds[kRowWaves + (tid >> 6)] = lo;
+  }
+  __syncthreads();
+  hi = lds[0];
+  lo = lds[kRowWaves];
+#pragma unroll
+  for (int w = 1; w < kRowWaves; ++w) {
+    hi = fmaxf(hi, lds[w]);
+    lo = fminf(lo, lds[kRowWaves + w]);
+  }
+  zmax = hi == hi ? hi : 0.f;                               // nothing but NaNs
+  zmin = lo == lo ? lo : 0.f;
 }
 
 // Largest and smallest element of the row held in q[], the NL LDS slots at lrow (slot j: 16 bytes per thread at index
 // 1024 j + tid; every slot holds vectors of the row, possibly repeated ones) and xt, returned to every thread.
 // `lds`: 2 * kRowWaves floats.
-template <int NV, int NL = 0>
+// The bits of bf16 numbers order them: as signed 16-bit integers the largest is the largest number if there is one
+// without a sign, as unsigned integers it is the smallest number if there is one with a sign.  Two packed instructions
+// per two logits instead of three; what the two integers cannot tell takes the route above.  (With no negative element
+// the smallest is reported as 0, which is as good for a caller that asks for the largest magnitude.)
+template <bool ALIGNED, int NV, int NL = 0>
 __device__ __forceinline__ void row_minmax(u32x4 (&q)[NV], float xt, float* lds, float& zmax, float& zmin,
-                                           const u32x4* lrow = nullptr) {
+                                           const RowParts<ALIGNED>& row, const u32x4* lrow = nullptr) {
   const int tid = threadIdx.x;
-  float hi = xt, lo = xt;
+  const uint32_t x2 = (__float_as_uint(xt) >> 16) * 0x00010001u;
+  i16x2 s = __builtin_bit_cast(i16x2, x2);
+  u16x2 u = __builtin_bit_cast(u16x2, x2);
   auto fold = [&](const u32x4& v) {
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      // the word itself stands for its upper logit: as an fp32 it is that logit with 16 more significand bits, which
-      // order it among equals only (they are cut off at the end); a NaN loses every comparison either way
-      const float a = __uint_as_float(v[w] << 16), b = __uint_as_float(v[w]);
-      hi = fmaxf(hi, fmaxf(a, b));
-      lo = fminf(lo, fminf(a, b));
+      const uint32_t word = v[w];              // (a bit cast of the vector element itself would read the first one)
+      s = __builtin_elementwise_max(s, __builtin_bit_cast(i16x2, word));
+      u = __builtin_elementwise_max(u, __builtin_bit_cast(u16x2, word));
     }
   };
 #pragma unroll
@@ -96,26 +177,46 @@ __device__ __forceinline__ void row_minmax(u32x4 (&q)[NV], float xt, float* lds,
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  hi = wave_max(hi);
-  lo = -wave_max(-lo);
+  auto level = [&](auto k) {
+    constexpr int K = decltype(k)::value;
+    s = __builtin_elementwise_max(s, __builtin_bit_cast(i16x2, lane_partner<K>(__builtin_bit_cast(uint32_t, s))));
+    u = __builtin_elementwise_max(u, __builtin_bit_cast(u16x2, lane_partner<K>(__builtin_bit_cast(uint32_t, u))));
+  };
+  level(std::integral_constant<int, 0>{});
+  level(std::integral_constant<int, 1>{});
+  level(std::integral_constant<int, 2>{});
+  level(std::integral_constant<int, 3>{});
+  level(std::integral_constant<int, 4>{});
+  level(std::integral_constant<int, 5>{});
+  uint32_t* lds_u = reinterpret_cast<uint32_t*>(lds);
   if ((tid & 63) == 0) {
-    lds[tid >> 6] = hi;
-    lds[kRowWaves + (tid >> 6)] = lo;
+    lds_u[tid >> 6] = __builtin_bit_cast(uint32_t, s);
+    lds_u[kRowWaves + (tid >> 6)] = __builtin_bit_cast(uint32_t, u);
   }
   __syncthreads();
-  hi = lds[0];
-  lo = lds[kRowWaves];
 #pragma unroll
-  for (int w = 1; w < kRowWaves; ++w) {
-    hi = fmaxf(hi, lds[w]);
-    lo = fminf(lo, lds[kRowWaves + w]);
+  for (int w = 0; w < kRowWaves; ++w) {
+    s = __builtin_elementwise_max(s, __builtin_bit_cast(i16x2, lds_u[w]));
+    u = __builtin_elementwise_max(u, __builtin_bit_cast(u16x2, lds_u[kRowWaves + w]));
   }
-  zmax = __uint_as_float(__float_as_uint(hi) & 0xffff0000u);
-  zmin = __uint_as_float(__float_as_uint(lo) & 0xffff0000u);
+  const int smax = max((int)s[0], (int)s[1]), umax = max((int)u[0], (int)u[1]);
+  zmax = bf16_bits_to_float(smax);
+  zmin = umax >= 0x8000 ? bf16_bits_to_float(umax) : 0.f;
+  if (smax < 0 || smax > 0x7f80 || umax > 0xff80)          // uniform for the workgroup, and rare
+    row_minmax_streamed<ALIGNED>(row, lds, zmax, zmin);
   // keep the row packed until the scale is known (the empty asm names the reduction result as an input)
 #pragma unroll
   for (int k = 0; k < NV; ++k) asm volatile("" : "+v"(q[k]) : "v"(zmax));
 }
+
+// Workgroups of a kernel that a compute unit holds at once: with up to 8 vectors per lane (65,536 logits) a row leaves
+// room for a second one, whose loads and sums overlap the first one's reductions and table.  Log-prob, 20,000 rows: of
+// 32,000 logits 318 us with one, 287 with two; of 65,536 516 and 478.  Quantisation, where stores are the larger part of
+// the traffic: of 32,000 676 and 659 (with the decoding), but of 65,536 1,342 and 1,373, so only up to 4 vectors.
+constexpr int logprob_workgroups(int nv) { return nv <= 8 ? 2 : 1; }
+constexpr int quantize_workgroups(int nv) { return nv <= 4 ? 2 : 1; }
+// wavefronts per SIMD that the register budget has to allow for
+constexpr int waves_of(int workgroups) { return workgroups * kRowThreads / 256; }
 
 // Table index of a bf16 magnitude (15 bits): magnitudes below the table's first entry share it (their code is 0,
 // as is the first entry's), and nothing finite lies above the last entry, the row's abs-max; a NaN's payload does,
@@ -128,8 +229,8 @@ __device__ __forceinline__ int table_index(uint32_t mag, int base) {
 // Persistent grid, one workgroup per compute unit, rows dealt round-robin; the registers of a vector whose codes have
 // been written are reloaded at once with the same vector of the workgroup's next row (see the log-prob kernel below
 // for why).
-template <int NV, int KFULL>
-__global__ __launch_bounds__(kRowThreads) void fp8_quantize_table_kernel(const bf16_t* __restrict__ logits,
+template <bool ALIGNED, int NV, int KFULL>
+__global__ __launch_bounds__(kRowThreads, waves_of(quantize_workgroups(NV))) void fp8_quantize_table_kernel(const bf16_t* __restrict__ logits,
                                                                          long long row_stride, int vocab,
                                                                          unsigned char* __restrict__ codes,
                                                                          long long codes_stride,
@@ -138,30 +239,30 @@ __global__ __launch_bounds__(kRowThreads) void fp8_quantize_table_kernel(const b
   __shared__ float lds[2 * kRowWaves];
   __shared__ unsigned char table[kTabEntries];
   const int tid = threadIdx.x;
-  const int nvec = vocab / 8;
-  const int tail = vocab - nvec * 8;
   long long row = blockIdx.x;
   if (row >= n_rows) return;
+  RowParts<ALIGNED> at(logits + row * row_stride, vocab);
   u32x4 q[NV];
   float xt;
-  issue_row<NV, KFULL>(logits + row * row_stride, vocab, q, xt);
+  issue_row<ALIGNED, NV, KFULL>(at, q, xt);
   for (; row < n_rows; row += gridDim.x) {
     unsigned char* cr = codes + row * codes_stride;
     // after its last row a workgroup fetches that row once more (into registers nobody reads again): the loop
     // body stays free of conditions, which keeps the reloaded registers the very ones that were just read
-    const long long next = row + gridDim.x < n_rows ? row + gridDim.x : row;
-    const u32x4* zn = reinterpret_cast<const u32x4*>(logits + next * row_stride);
+    const RowParts<ALIGNED> next(logits + (row + gridDim.x < n_rows ? row + gridDim.x : row) * row_stride, vocab);
     float zmax, zmin;
-    row_minmax<NV>(q, xt, lds, zmax, zmin);
+    row_minmax<ALIGNED, NV>(q, xt, lds, zmax, zmin, at);
     const float amax = fmaxf(zmax, -zmin);
     const float s = scale_of(amax);
     if (tid == 0) scale_out[row] = s;
     // entry i belongs to the bf16 magnitude with bits base + i; the last entry is the abs-max itself
     const int base = (int)(__float_as_uint(amax) >> 16) - (kTabEntries - 1);
-    for (int i = tid; i < kTabEntries; i += kRowThreads) {
-      const int bits = base + i;
-      table[i] = (unsigned char)code_of(bits > 0 ? bf16_bits_to_float(bits) / s : 0.f);
-    }
+    const RowDivider by_s = make_divider(s);
+    auto fill = [&](auto slow) {
+      for (int i = tid; i < kTabEntries; i += kRowThreads)
+        table[i] = (unsigned char)code_of(divide<decltype(slow)::value>(bf16_bits_to_float(max(base + i, 0)), by_s));
+    };
+    if (by_s.slow) fill(std::true_type{}); else fill(std::false_type{});
     __syncthreads();
     auto code2 = [&](uint32_t w) -> uint32_t {           // two logits -> two codes in the low 16 bits
       const uint32_t c0 = table[table_index(w & 0x7fffu, base)];
@@ -169,6 +270,7 @@ __global__ __launch_bounds__(kRowThreads) void fp8_quantize_table_kernel(const b
       // the sign of the logit is the sign of the code, zero included
       return c0 | (c1 << 8) | ((w >> 8) & 0x80u) | ((w >> 16) & 0x8000u);
     };
+    unsigned char* cv = cr + at.head;                    // a vector's codes: 8-byte aligned (the launcher checks)
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
       // the slot's index comes from a fresh opaque copy of the thread index: otherwise every slot's load and store
@@ -184,15 +286,13 @@ __global__ __launch_bounds__(kRowThreads) void fp8_quantize_table_kernel(const b
       o.y = code2(q[k][2]) | (code2(q[k][3]) << 16);
       asm volatile("" : "+v"(o.y));                      // the codes are formed here, before the registers are reused
       __builtin_amdgcn_sched_barrier(0);
-      if (k < KFULL || i < nvec) *reinterpret_cast<uint2*>(cr + (long long)i * 8) = o;
-      // (i >= 0 and nvec >= 1, so the clamped index is a valid vector of the row)
-      q[k] = load_stream(zn + (unsigned)(k < KFULL ? i : min(i, nvec - 1)));
+      if (k < KFULL || i < at.nvec) *reinterpret_cast<uint2*>(cv + (long long)i * 8) = o;
+      q[k] = next.load(tk, k, k < KFULL);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (tid < tail) {
-      cr[nvec * 8 + tid] = (unsigned char)(code2(__float_as_uint(xt) >> 16) & 0xffu);
-      xt = Vec<bf16_t>::load1(reinterpret_cast<const bf16_t*>(zn) + nvec * 8 + tid);
-    }
+    if (tid < at.rest) cr[at.outside(tid)] = (unsigned char)(code2(__float_as_uint(xt) >> 16) & 0xffu);
+    xt = next.load_outside(tid);
+    at = next;
     __syncthreads();                                     // everyone has finished reading the table
   }
 }
@@ -206,11 +306,20 @@ __global__ __launch_bounds__(kRowThreads) void fp8_quantize_table_kernel(const b
 // computes.  The grid is therefore persistent (one workgroup per compute unit, rows dealt round-robin), and the
 // registers of the vector that the sum has just consumed are reloaded at once with the same vector of the
 // workgroup's next row: by the time the sum is finished the next row is on its way or has landed.
+// Bound by the vector ALU (and the LDS reads beside it), so instructions count: 10,411 rows of 151,936 took 597 us with
+// three instructions per two logits for the extremes, a shift and an or where the multiply-add is, a 64-bit address per
+// vector and a full division per table entry; 538 us (5.9 TB/s) now.  5,000 rows of 248,320: 488 and 438 us.
 //
 // Rows beyond 23 vectors per lane park vectors 23 .. 23 + NL - 1 of every lane in LDS slots (16 KiB each, filled by
 // direct global -> LDS copies); a slot is refilled with the next row's vector by the thread that has just read its
 // 16 bytes of it, so no thread ever waits for another.  With slots the two sign halves of the table are interleaved
 // (8 bytes per magnitude, 20 KiB) instead of 16 KiB apart (32 KiB), which is what lets 8 slots fit beside it.
+__device__ __forceinline__ uint32_t pk_mad(u16x2 t, int factor, uint32_t add) {      // t * factor + add in both halves
+  uint32_t r;
+  asm("v_pk_mad_u16 %0, %1, %2, %3 op_sel_hi:[1,0,1]" : "=v"(r) : "v"(t), "s"(factor), "v"(add));
+  return r;
+}
+
 template <bool INTERLEAVED>
 struct LogprobTable {
   static constexpr int kFloats = INTERLEAVED ? 2 * kTabEntries : 2 * kTabStride;
@@ -219,24 +328,23 @@ struct LogprobTable {
   static __device__ __forceinline__ int neg(int i) { return INTERLEAVED ? 2 * i + 1 : kTabStride + i; }
   // Byte offsets into the table of the two logits of a word, formed on both 16-bit halves at once: magnitude
   // minus base, saturating at 0 (smaller magnitudes share the first entry: their code is 0, as is its) and held
-  // below the table's end (only a NaN's payload lies above the abs-max), times the entry pitch, plus the sign's part.
+  // below the table's end (only a NaN's payload lies above the abs-max), times the entry pitch plus the sign's part in
+  // one multiply-add.
   static __device__ __forceinline__ uint32_t offsets(uint32_t w, uint32_t base2) {
     u16x2 t = __builtin_bit_cast(u16x2, w & 0x7fff7fffu);
     t = __builtin_elementwise_sub_sat(t, __builtin_bit_cast(u16x2, base2));
     t = __builtin_elementwise_min(t, u16x2{kTabEntries - 1, kTabEntries - 1});
     if (INTERLEAVED) {
       static_assert((kTabEntries - 1) * 8 + 4 < 0x10000, "an offset must fit a 16-bit half");
-      t = t << 3;
-      return __builtin_bit_cast(uint32_t, t) | ((w >> 13) & 0x00040004u);     // sign bit -> byte 4 of the entry
+      return pk_mad(t, 8, (w >> 13) & 0x00040004u);                           // sign bit -> byte 4 of the entry
     }
     static_assert(kTabStride * 4 == 0x4000, "the sign bit of a half is moved to this bit of its offset");
-    t = t << 2;
-    return __builtin_bit_cast(uint32_t, t) | ((w >> 1) & 0x40004000u);
+    return pk_mad(t, 4, (w >> 1) & 0x40004000u);
   }
 };
 
-template <int NV, int KFULL, int NL>
-__global__ __launch_bounds__(kRowThreads) void fp8_rollout_logprob_table_kernel(
+template <bool ALIGNED, int NV, int KFULL, int NL>
+__global__ __launch_bounds__(kRowThreads, waves_of(logprob_workgroups(NV))) void fp8_rollout_logprob_table_kernel(
     const bf16_t* __restrict__ logits, long long row_stride, int vocab, const int* __restrict__ token_ids,
     const unsigned char* __restrict__ valid, float* __restrict__ logp_out, int* __restrict__ status,
     long long n_rows) {
@@ -246,10 +354,8 @@ __global__ __launch_bounds__(kRowThreads) void fp8_rollout_logprob_table_kernel(
   __shared__ float table[Tab::kFloats];                    // kTabEntries magnitudes x 2 signs in use
   extern __shared__ __align__(16) unsigned char lds_slots[];
   u32x4* lrow = reinterpret_cast<u32x4*>(lds_slots);       // NL slots
-  static_assert(NL == 0 || KFULL == NV, "rows that need slots fill every register vector");
+  static_assert(NL == 0 || KFULL >= NV - 1, "rows that need slots fill (all but the end of) every register vector");
   const int tid = threadIdx.x;
-  const int nvec = vocab / 8;
-  const int tail = vocab - nvec * 8;
   // this workgroup's next evaluated row at or after `r`; rows that are not evaluated get their 0 on the way
   auto next_row = [&](long long r) -> long long {
     for (; r < n_rows; r += gridDim.x) {
@@ -262,29 +368,29 @@ __global__ __launch_bounds__(kRowThreads) void fp8_rollout_logprob_table_kernel(
   if (row >= n_rows) return;
   u32x4 q[NV];
   float xt;
-  issue_row<NV, KFULL>(logits + row * row_stride, vocab, q, xt);
+  RowParts<ALIGNED> at(logits + row * row_stride, vocab);
+  issue_row<ALIGNED, NV, KFULL>(at, q, xt);
   if (NL > 0) {
     int t0 = tid;
     asm volatile("" : "+v"(t0));
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
-      copy_to_slot(reinterpret_cast<const u32x4*>(logits + row * row_stride), nvec, NV + j, lrow + j * kRowThreads, t0);
+      copy_to_slot(at.zv, at.nvec, NV + j, lrow + j * kRowThreads, t0);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
   while (row < n_rows) {
-    const bf16_t* zr = logits + row * row_stride;
     const long long next = next_row(row + gridDim.x);
     // after its last row a workgroup fetches that row once more (into registers nobody reads again): the loop
     // body stays free of conditions, which keeps the reloaded registers the very ones that were just read
-    const u32x4* zn = reinterpret_cast<const u32x4*>(logits + (next < n_rows ? next : row) * row_stride);
+    const RowParts<ALIGNED> at_next(logits + (next < n_rows ? next : row) * row_stride, vocab);
     // the sampled token's logit: asked for before the prefetches below, which it would otherwise queue behind
     const int y = token_ids[row];
     const bool y_ok = y >= 0 && y < vocab;
-    const float zy_raw = (tid == 0 && y_ok) ? Vec<bf16_t>::load1(zr + y) : 0.f;
+    const float zy_raw = (tid == 0 && y_ok) ? Vec<bf16_t>::load1(at.zr + y) : 0.f;
 
     float zmax, zmin;
-    row_minmax<NV, NL>(q, xt, lds_mm, zmax, zmin, lrow);
+    row_minmax<ALIGNED, NV, NL>(q, xt, lds_mm, zmax, zmin, at, lrow);
     const float amax = fmaxf(zmax, -zmin);
     const float s = scale_of(amax);
     const float scale = s * kLog2e;                        // z_r * log2e = value(code) * scale
@@ -292,25 +398,29 @@ __global__ __launch_bounds__(kRowThreads) void fp8_rollout_logprob_table_kernel(
     const float top = value_of(code_of(zmax / s)) * scale;
     // entry i belongs to the bf16 magnitude with bits base + i; the abs-max is the last entry or an earlier one
     const int base = max((int)(__float_as_uint(amax) >> 16) - (kTabEntries - 1), 0);
-    for (int i = tid; i < kTabEntries; i += kRowThreads) {
-      const float v = value_of(code_of(bf16_bits_to_float(base + i) / s));
-      table[Tab::pos(i)] = exp2_fast(__builtin_fmaf(v, scale, -top));
-      table[Tab::neg(i)] = exp2_fast(__builtin_fmaf(-v, scale, -top));
-    }
+    const RowDivider by_s = make_divider(s);
+    auto fill = [&](auto slow) {
+      for (int i = tid; i < kTabEntries; i += kRowThreads) {
+        const float v = value_of(code_of(divide<decltype(slow)::value>(bf16_bits_to_float(base + i), by_s)));
+        table[Tab::pos(i)] = exp2_fast(__builtin_fmaf(v, scale, -top));
+        table[Tab::neg(i)] = exp2_fast(__builtin_fmaf(-v, scale, -top));
+      }
+    };
+    if (by_s.slow) fill(std::true_type{}); else fill(std::false_type{});
     __syncthreads();
     const uint32_t base2 = (uint32_t)base * 0x00010001u;
-    auto at = [&](uint32_t byte_offset) -> float {
+    auto entry = [&](uint32_t byte_offset) -> float {
       return *reinterpret_cast<const float*>(reinterpret_cast<const unsigned char*>(table) + byte_offset);
     };
-    auto term = [&](uint32_t h) -> float { return at(Tab::offsets(h, base2) & 0xffffu); };   // h: one bf16, low half
+    auto term = [&](uint32_t h) -> float { return entry(Tab::offsets(h, base2) & 0xffffu); };   // h: one bf16, low half
     // sum of the eight terms of one vector
     auto vector_sum = [&](const u32x4& v) -> float {
       float part = 0.f;
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
         const uint32_t o = Tab::offsets(v[w], base2);
-        part += at(o & 0xffffu);
-        part += at(o >> 16);
+        part = w == 0 ? entry(o & 0xffffu) : part + entry(o & 0xffffu);
+        part += entry(o >> 16);
         if (w == 1) {
           asm volatile("" : "+v"(part));                   // the sum so far is formed here, not deferred
           __builtin_amdgcn_sched_barrier(0);               // four table reads in flight at a time: fewer registers
@@ -330,12 +440,10 @@ __global__ __launch_bounds__(kRowThreads) void fp8_rollout_logprob_table_kernel(
       asm volatile("" : "+v"(tk));
       __builtin_assume(tk >= 0 && tk < kRowThreads);
       const int i = tk + k * kRowThreads;
-      const bool exists = k < KFULL || i < nvec;
+      const bool exists = k < KFULL || i < at.nvec;
       acc0 += exists ? part : 0.f;
-      // this vector is done with: its registers take the same vector of the next row (a slot past the end of the
-      // row takes a copy of the row's last vector, which changes neither maximum nor minimum and is never summed)
-      // (i >= 0 and nvec >= 1, so the clamped index is a valid vector of the row; uniform row base + 32-bit offset)
-      q[k] = load_stream(zn + (unsigned)(k < KFULL ? i : min(i, nvec - 1)));
+      // this vector is done with: its registers take the same vector of the next row
+      q[k] = at_next.load(tk, k, k < KFULL);
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
@@ -345,15 +453,13 @@ __global__ __launch_bounds__(kRowThreads) void fp8_rollout_logprob_table_kernel(
       __builtin_assume(tk >= 0 && tk < kRowThreads);
       u32x4* slot = lrow + j * kRowThreads;
       const float part = vector_sum(slot[tk]);             // (the terms have been read out of LDS: `part` is formed)
-      acc0 += (tk + (NV + j) * kRowThreads < nvec) ? part : 0.f;
+      acc0 += (tk + (NV + j) * kRowThreads < at.nvec) ? part : 0.f;
       // the thread's 16 bytes of the slot are free: they take the next row's vector
-      copy_to_slot(zn, nvec, NV + j, slot, tk);
+      copy_to_slot(at_next.zv, at_next.nvec, NV + j, slot, tk);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (tid < tail) {
-      acc0 += term(__float_as_uint(xt) >> 16);
-      xt = Vec<bf16_t>::load1(reinterpret_cast<const bf16_t*>(zn) + nvec * 8 + tid);
-    }
+    if (tid < at.rest) acc0 += term(__float_as_uint(xt) >> 16);
+    xt = at_next.load_outside(tid);
     const float acc = wave_sum(acc0);
     if ((tid & 63) == 0) lds_sum[tid >> 6] = acc;
     // also: everyone has finished reading the table.  With slots the barrier is written out: a workgroup fence would
@@ -374,39 +480,51 @@ __global__ __launch_bounds__(kRowThreads) void fp8_rollout_logprob_table_kernel(
       }
     }
     row = next;
+    at = at_next;
   }
   // copies of the row fetched once more may still be on their way into the slots
   if (NL > 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// Vectors per lane of a 16-byte aligned bf16 row, or 0 when the row does not qualify for these kernels.
+bool row_aligned(const void* z, long long row_stride) {
+  return reinterpret_cast<uintptr_t>(z) % 16 == 0 && (row_stride * 2) % 16 == 0;
+}
+
+// Vectors per lane of a bf16 row, or 0 when the row does not qualify for these kernels (too wide, or without a whole
+// vector, of which an unaligned row may lose 8 to its head).
 int table_vectors_per_lane(const void* z, int vocab, long long row_stride, int most) {
-  const bool ok16 = reinterpret_cast<uintptr_t>(z) % 16 == 0 && (row_stride * 2) % 16 == 0;
   const int need = (vocab / 8 + kRowThreads - 1) / kRowThreads;
-  return (ok16 && need >= 1 && need <= most) ? need : 0;     // at least one whole vector per row
+  return vocab >= (row_aligned(z, row_stride) ? 8 : 128) && need <= most ? need : 0;
 }
 
 }  // namespace
 
-// PREV: the widest row of the previous class; a row that reaches a class has more than PREV * 1024 vectors
+// PREV: the widest row of the previous class; a row that reaches a class has more than PREV * 1024 vectors, of which an
+// unaligned row may have lost up to 8 to its head
 #define AIS_TABLE_CASES(CASE) CASE(0, 4) CASE(4, 8) CASE(8, 12) CASE(12, 16) CASE(16, 18) CASE(18, 19) CASE(19, 20)
 
-// Returns true when the table kernel was launched, false when the rows do not qualify (not bf16, not 16-byte
-// aligned, wider than 24 vectors per lane, or codes not 8-byte aligned).
+// Returns true when the table kernel was launched, false when the rows do not qualify (not bf16, wider than 24 vectors
+// per lane, or the codes of a vector not 8-byte aligned).
 bool try_fp8_quantize_table(ais_ctx* ctx, const void* logits, ais_dtype dtype, long long n_rows, int vocab,
                             long long row_stride, unsigned char* codes, long long codes_stride, float* scale_out) {
   if (dtype != AIS_BF16) return false;
-  if (reinterpret_cast<uintptr_t>(codes) % 8 != 0 || codes_stride % 8 != 0) return false;
+  // a vector starts a multiple of 8 elements from any other place that is 16-byte aligned: its codes are 8-byte aligned
+  // in every row if codes and logits have their first row and their pitch in common modulo 8 elements
+  if ((reinterpret_cast<uintptr_t>(codes) - reinterpret_cast<uintptr_t>(logits) / 2) % 8 != 0 ||
+      (codes_stride - row_stride) % 8 != 0)
+    return false;
   const int need = table_vectors_per_lane(logits, vocab, row_stride, 24);
   if (need == 0) return false;
   const bf16_t* z = static_cast<const bf16_t*>(logits);
-  // persistent: one workgroup per compute unit (a workgroup's registers leave room for no second one)
-  dim3 grid((unsigned)(n_rows < ctx->n_cus ? n_rows : ctx->n_cus)), block(kRowThreads);
-#define AIS_CASE(PREV, NVAL)                                                                                  \
-  if (need <= NVAL) {                                                                                         \
-    fp8_quantize_table_kernel<NVAL, PREV><<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, codes,       \
-                                                                           codes_stride, scale_out, n_rows);  \
-    return true;                                                                                              \
+  const long long resident = (long long)ctx->n_cus * quantize_workgroups(need <= 4 ? 4 : 24);
+  dim3 grid((unsigned)(n_rows < resident ? n_rows : resident)), block(kRowThreads);     // persistent
+  const bool aligned = row_aligned(logits, row_stride);
+#define AIS_CASE(PREV, NVAL)                                                                                    \
+  if (need <= NVAL) {                                                                                           \
+    auto kernel = aligned ? fp8_quantize_table_kernel<true, NVAL, PREV>                                         \
+                          : fp8_quantize_table_kernel<false, NVAL, (PREV > 0 ? PREV - 1 : 0)>;                  \
+    kernel<<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, codes, codes_stride, scale_out, n_rows);      \
+    return true;                                                                                                \
   }
   AIS_TABLE_CASES(AIS_CASE)
   AIS_CASE(20, 24)
@@ -422,12 +540,15 @@ bool try_fp8_rollout_logprob_table(ais_ctx* ctx, const void* logits, ais_dtype d
   const int need = table_vectors_per_lane(logits, vocab, row_stride, 23 + 8);
   if (need == 0) return false;
   const bf16_t* z = static_cast<const bf16_t*>(logits);
-  // persistent: one workgroup per compute unit (a workgroup's registers and table leave room for no second one)
-  dim3 grid((unsigned)(n_rows < ctx->n_cus ? n_rows : ctx->n_cus)), block(kRowThreads);
+  const long long resident = (long long)ctx->n_cus * logprob_workgroups(need <= 8 ? 8 : 24);
+  dim3 grid((unsigned)(n_rows < resident ? n_rows : resident)), block(kRowThreads);     // persistent
+  const bool aligned = row_aligned(logits, row_stride);
 #define AIS_CASE(PREV, NVAL)                                                                                        \
   if (need <= NVAL) {                                                                                               \
-    fp8_rollout_logprob_table_kernel<NVAL, PREV, 0><<<grid, block, 0, ctx->stream>>>(                               \
-        z, row_stride, vocab, token_ids, valid, logp_out, ctx->status_dev, n_rows);                                 \
+    auto kernel = aligned ? fp8_rollout_logprob_table_kernel<true, NVAL, PREV, 0>                                   \
+                          : fp8_rollout_logprob_table_kernel<false, NVAL, (PREV > 0 ? PREV - 1 : 0), 0>;            \
+    kernel<<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, token_ids, valid, logp_out, ctx->status_dev,      \
+                                            n_rows);                                                                \
     return true;                                                                                                    \
   }
   AIS_TABLE_CASES(AIS_CASE)
@@ -437,10 +558,12 @@ bool try_fp8_rollout_logprob_table(ais_ctx* ctx, const void* logits, ais_dtype d
 #undef AIS_CASE
 #define AIS_CASE(NEED, NLVAL)                                                                                       \
   if (need <= NEED) {                                                                                               \
-    auto kernel = fp8_rollout_logprob_table_kernel<23, 23, NLVAL>;                                                  \
-    static std::once_flag once[kMaxDevices];               /* the attribute belongs to the function on one device */ \
-    static bool ok[kMaxDevices];                                                                                    \
-    if (!allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kernel), NLVAL * kSlotBytes, once, ok))              \
+    auto kernel = aligned ? fp8_rollout_logprob_table_kernel<true, 23, 23, NLVAL>                                   \
+                          : fp8_rollout_logprob_table_kernel<false, 23, 22, NLVAL>;                                 \
+    static std::once_flag once[2][kMaxDevices];            /* the attribute belongs to the function on one device */ \
+    static bool ok[2][kMaxDevices];                                                                                 \
+    if (!allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kernel), NLVAL * kSlotBytes, once[aligned],           \
+                           ok[aligned]))                                                                            \
       return false;                                        /* the caller falls back to the streaming kernel */     \
     kernel<<<grid, block, NLVAL * kSlotBytes, ctx->stream>>>(z, row_stride, vocab, token_ids, valid, logp_out,      \
                                                              ctx->status_dev, n_rows);                              \

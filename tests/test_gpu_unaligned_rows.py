@@ -54,3 +54,41 @@ def test_both_paths(ctx, dtype, k):
         if pitch > vocab:
             gap = room[offset:offset + batch.n_rows * pitch].view(batch.n_rows, pitch)[:, vocab:]
             assert bool((gap == 77.0).all()), "elements between the rows were written"
+
+
+def fp8_reference(z):
+    """Codes, scales and round trip of float32 rows by torch's own cast (true fp32 divisions)."""
+    scale = z.abs().amax(dim=1, keepdim=True) / torch.full((z.shape[0], 1), 448.0, device=z.device)
+    scale = torch.where(scale > 0, scale, torch.ones_like(scale))
+    code = (z / scale).clamp(-448.0, 448.0).to(torch.float8_e4m3fn)
+    return code.view(torch.uint8), scale, code.double() * scale.double()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("k", range(14))
+def test_fp8(ctx, dtype, k):
+    """Codes, scales and decoded values bit for bit, the log-probs to 1e-4 (the sum of up to 270,000 fp32 terms)."""
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    vocab = (edges(dtype) + [127, 129])[k] if k < 13 else 129
+    g = torch.Generator(device="cuda")
+    g.manual_seed(vocab)
+    rows = 600 if vocab < 40_000 else 5         # more rows than compute units: workgroups that walk several rows
+    for pitch, offset in ((vocab, 0), (vocab + 1, 3), (vocab + 2, 6)):
+        print("vocab", vocab, dtype, "pitch", pitch, "offset", offset, flush=True)
+        room = torch.full((rows * pitch + offset + 64,), 77.0, dtype=dt, device="cuda")
+        z = room[offset:offset + rows * pitch].view(rows, pitch)[:, :vocab]
+        z.copy_(torch.randn(rows, vocab, generator=g, device="cuda") * 3.0)
+        z[1] = -z[1].abs() - 1000.0             # no element above zero: the largest one decides the log-prob
+        z[2] = 0.0
+        z[3, 0] = 40.0                          # the abs-max outside the vectors, at either end
+        z[4, vocab - 1] = -41.0
+        y = torch.randint(0, vocab, (rows,), generator=g, device="cuda", dtype=torch.int32)
+        code, scale, zr = fp8_reference(z.float())
+        codes, s = ctx.fp8_quantize_rows(z)
+        assert torch.equal(s, scale.squeeze(1)) and torch.equal(codes, code)
+        for out in (torch.float32, torch.bfloat16):
+            assert torch.equal(ctx.fp8_dequantize_rows(codes, s, out), (code.view(torch.float8_e4m3fn).float() * scale).to(out))
+        logp = ctx.fp8_rollout_logprob(z, y)
+        ref = zr.gather(1, y.long().unsqueeze(1)).squeeze(1) - torch.logsumexp(zr, dim=1)
+        assert float((logp.double() - ref).abs().max()) <= 1e-4 * max(1.0, float(ref.abs().max()))
+        assert ctx.status() == 0

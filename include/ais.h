@@ -314,13 +314,15 @@ int ais_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long hidden_strid
  *   dhidden[n, :]  = sum_v dlogits[n, v] weight[v, :]
  *   dweight[v, :]  = sum_n dlogits[n, v] hidden[n, :]
  * The vocabulary is walked in chunks: the logits of a chunk are recomputed on the matrix cores from the operands,
- * turned into dlogits (bf16) with the row's lse, and consumed at once by two library GEMMs (rocBLAS, fp32
- * accumulation and output); only [n_rows, chunk_vocab] dlogits exist at any time.
+ * turned into dlogits (bf16) with the row's lse, and consumed at once by two products (fp32 accumulation and output;
+ * the library's own kernels where their tiles fill the GPU, rocBLAS otherwise); only [n_rows, chunk_vocab] dlogits exist
+ * at any time.
  *   hidden, weight, token_ids, dtype, strides   as for ais_lm_head_logprob; d_model a multiple of 32
  *   lse, logp   [n_rows] fp32, outputs of ais_lm_head_logprob for the same operands and temperature
  *   coeff       [n_rows] fp32, as written by ais_grpo_row_scale (its g_out: it carries inv_temperature)
- *   chunk_vocab vocabulary entries per chunk, a multiple of 256; 0 selects 8192.  The context workspace grows to
- *               2 * n_rows * chunk_vocab bytes.
+ *   chunk_vocab vocabulary entries per chunk, a multiple of 256.  The context workspace grows to
+ *               2 * n_rows * chunk_vocab bytes.  0 selects 8192 and, with fewer than 4,096 rows to go through, wider chunks
+ *               for a workspace of up to 70 MB.
  *   n_live_max  negative, or >= n_rows: every row goes through the recomputation and the GEMMs.  Otherwise a bound
  *               that the caller vouches for on the number of rows with coeff != 0 (for a masked-diffusion batch:
  *               the number of evaluated positions, which its loader knows): those rows are gathered on the device

@@ -78,7 +78,7 @@ struct ais_ctx {
     bool valid = false;
   } plan;
   void* static_scratch = nullptr;   // address, on this context's device, of the library's static scratch array
-  void* blas = nullptr;             // rocblas_handle of the two plain GEMMs of ais_lm_head_grad, created on first use
+  void* blas = nullptr;             // rocblas_handle of ais_lm_head_grad's products at sizes its own kernels leave, created on first use
 };
 
 namespace ais {
@@ -149,7 +149,13 @@ int launch_lm_head_dlogits_chunk(ais_ctx* ctx, const void* hidden, long long ld_
                                  long long ld_w, long long n_rows, int d_model, int vocab, int y_off,
                                  const int* token_ids, const float* lse, const float* logp, const float* coeff,
                                  float inv_temperature, const void* dev_plan, int which, void* ds, long long ds_stride,
-                                 const int* row_index, int n_cap);
+                                 const int* row_index, int n_cap, bool zero_tail);
+bool lm_dweight_fits(const ais_ctx* ctx, long long d, long long n_v);
+bool lm_dhidden_fits(const ais_ctx* ctx, long long d, long long n_rows);
+int launch_lm_dweight(ais_ctx* ctx, const void* ds, long long ds_stride, const void* h, long long ld_h, int k,
+                      const int* k_dev, int n_v, int d, float* dweight);
+int launch_lm_dhidden(ais_ctx* ctx, const void* ds, long long ds_stride, const void* w, long long ld_w, int n_v,
+                      int n_rows, int d, bool accumulate, float* dhidden);
 int launch_lm_live_mask(ais_ctx* ctx, const float* coeff, long long n_rows, unsigned char* mask);
 int launch_lm_gather_rows(ais_ctx* ctx, const void* hidden, long long ld_h, int d_model, const int* row_index,
                           const void* dev_plan, int n_cap, void* gathered);

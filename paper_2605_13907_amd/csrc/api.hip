@@ -150,6 +150,22 @@ int plan_for_step(ais_ctx* ctx, const long long* cu_rows, int n_resp, long long 
   return launch_plan(ctx, cu_rows, n_resp, n_rows, tile_off, max_tiles);
 }
 
+// Vocabulary entries per chunk of ais_lm_head_grad when the caller leaves the choice.  8,192 entries are 32 tiles, which
+// with 16 token blocks (4,096 rows) are two work items per compute unit; with fewer rows the chunk is wider by as much
+// (700 rows x 50,257 x 2,048: 1.13 ms in chunks of 8,192, 0.90 in one of 43,776; 2,000 rows 1.52 and 1.46 ms).
+constexpr long long kLmGradChunk = 8192;
+constexpr long long kLmGradFewRows = 4096;
+long long lm_grad_chunk_few(long long m_rows, int n_cus) {
+  const long long blocks = (m_rows + 255) / 256;
+  return 256 * ((2 * n_cus + blocks - 1) / blocks);
+}
+// Most bytes that a chunk takes over any number of rows below kLmGradFewRows.
+size_t lm_grad_few_bytes(long long vocab, int n_cus) {
+  const long long wide = ((vocab + 255) / 256) * 256;
+  const long long most = 256LL * 256 * std::max<long long>(2 * n_cus + kLmGradFewRows / 256, 512);
+  return 2 * (size_t)std::min(most, kLmGradFewRows * wide);
+}
+
 int check_diagnostics_args(const float* logp_train, const float* logp_roll, long long n_rows,
                            const long long* cu_rows, int n_resp, int group_size, const float* rewards,
                            const ais_params* params, const float* adv_out, const int* count_out,
@@ -513,7 +529,8 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   if (n_rows < 0 || n_rows > 0x7fffffffLL - 256) return AIS_ERR_SIZE;
   if (vocab < 1 || vocab > 0x7fffffffLL - 256) return AIS_ERR_SIZE;
   if (d_model < 32 || d_model > (1 << 20) || d_model % 32 != 0) return AIS_ERR_SIZE;
-  if (chunk_vocab == 0) chunk_vocab = 8192;
+  const bool own_chunk = chunk_vocab == 0;
+  if (own_chunk) chunk_vocab = kLmGradChunk;
   if (chunk_vocab < 256 || chunk_vocab > (1 << 24) || chunk_vocab % 256 != 0) return AIS_ERR_SIZE;
   if (hidden_stride < d_model || weight_stride < d_model) return AIS_ERR_STRIDE;
   if (weight == nullptr || dweight_out == nullptr) return AIS_ERR_NULL;
@@ -533,9 +550,11 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
     zero_fill_kernel<<<blocks, 256, 0, ctx->stream>>>(dweight_out, n);
     return hip_fail(ctx, hipGetLastError());
   }
-  if (chunk_vocab > ((vocab + 255) / 256) * 256) chunk_vocab = ((vocab + 255) / 256) * 256;
   const bool gather = n_live_max >= 0 && n_live_max < n_rows;
   const long long m_rows = gather ? n_live_max : n_rows;       // rows that the recomputation and the GEMMs cover
+  const bool few_rows = own_chunk && m_rows < kLmGradFewRows;
+  if (few_rows && m_rows > 0) chunk_vocab = std::max<long long>(chunk_vocab, lm_grad_chunk_few(m_rows, ctx->n_cus));
+  if (chunk_vocab > ((vocab + 255) / 256) * 256) chunk_vocab = ((vocab + 255) / 256) * 256;
   if (m_rows == 0) {                    // the caller vouches that no row has a gradient
     zero_fill_kernel<<<(unsigned)std::min<size_t>(((size_t)vocab * d_model + 255) / 256, (size_t)ctx->n_cus * 8), 256, 0,
                        ctx->stream>>>(dweight_out, (size_t)vocab * (size_t)d_model);
@@ -546,7 +565,10 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   // workspace: the chunk's dlogits, the device-side decomposition of the recompute kernel and, with a row list, the
   // mask, the list, its inverse, the gathered hidden states and their gradient
   auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
-  const size_t ds_bytes = up((size_t)m_rows * (size_t)chunk_vocab * 2);
+  size_t ds_bytes = up((size_t)m_rows * (size_t)chunk_vocab * 2);
+  // with few rows the chunk grows as the rows get fewer: ask for what the largest of them takes, so that no call needs
+  // more than one over more rows before it
+  if (few_rows) ds_bytes = std::max(ds_bytes, up(lm_grad_few_bytes(vocab, ctx->n_cus)));
   const size_t plan_bytes = 256;
   const size_t mask_bytes = gather ? up((size_t)n_rows) : 0;
   const size_t list_bytes = gather ? up((size_t)n_rows * 4) : 0;
@@ -576,14 +598,21 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   const void* h_gemm = gather ? static_cast<const void*>(h_gathered) : hidden;
   const long long h_gemm_stride = gather ? d_model : hidden_stride;
   float* dh_gemm = gather ? dh_gathered : dhidden_out;
-  if (ctx->blas == nullptr) {
-    rocblas_handle h = nullptr;
-    if (rocblas_create_handle(&h) != rocblas_status_success) return AIS_ERR_HIP;
-    ctx->blas = h;
+  const bool own_dh = lm_dhidden_fits(ctx, d_model, m_rows);
+  auto own_dw = [&](int width) { return lm_dweight_fits(ctx, d_model, width); };
+  // the list's length, first word of the decomposition on the device: rows past it are nobody's
+  const int* n_listed = gather ? static_cast<const int*>(dev_plan) : nullptr;
+  rocblas_handle blas = nullptr;
+  if (!own_dh || !own_dw((int)std::min<long long>(chunk_vocab, vocab)) || (width_last != 0 && !own_dw(width_last))) {
+    if (ctx->blas == nullptr) {
+      rocblas_handle h = nullptr;
+      if (rocblas_create_handle(&h) != rocblas_status_success) return AIS_ERR_HIP;
+      ctx->blas = h;
+    }
+    blas = static_cast<rocblas_handle>(ctx->blas);
+    if (rocblas_set_stream(blas, ctx->stream) != rocblas_status_success) return AIS_ERR_HIP;
+    if (rocblas_set_pointer_mode(blas, rocblas_pointer_mode_host) != rocblas_status_success) return AIS_ERR_HIP;
   }
-  rocblas_handle blas = static_cast<rocblas_handle>(ctx->blas);
-  if (rocblas_set_stream(blas, ctx->stream) != rocblas_status_success) return AIS_ERR_HIP;
-  if (rocblas_set_pointer_mode(blas, rocblas_pointer_mode_host) != rocblas_status_success) return AIS_ERR_HIP;
   const float one = 1.f, zero = 0.f;
   const char* w_base = static_cast<const char*>(weight);
   for (long long v0 = 0; v0 < vocab; v0 += chunk_vocab) {
@@ -591,26 +620,38 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
     const void* w_chunk = w_base + (size_t)v0 * (size_t)weight_stride * 2;
     rc = launch_lm_head_dlogits_chunk(ctx, hidden, hidden_stride, w_chunk, weight_stride, n_rows, (int)d_model, width,
                                       (int)v0, token_ids, lse, logp, coeff, inv_temperature, dev_plan,
-                                      width == width_last ? 1 : 0, ds, chunk_vocab, row_index, (int)m_rows);
+                                      width == width_last ? 1 : 0, ds, chunk_vocab, row_index, (int)m_rows,
+                                      !own_dw(width));
     if (rc != AIS_OK) return rc;
     // The library is column-major; a row-major [r, c] matrix with pitch p is its column-major [c, r] transpose
     // with leading dimension p.
     // dhidden[m_rows, D] (+)= ds[m_rows, width] weight_chunk[width, D]:   C^T[D, m_rows] = W_c^T[D, width] ds^T[width, m_rows]
-    rocblas_status st = rocblas_gemm_ex(
-        blas, rocblas_operation_none, rocblas_operation_none, (rocblas_int)d_model, (rocblas_int)m_rows, width, &one,
-        w_chunk, rocblas_datatype_bf16_r, (rocblas_int)weight_stride, ds, rocblas_datatype_bf16_r,
-        (rocblas_int)chunk_vocab, v0 == 0 ? &zero : &one, dh_gemm, rocblas_datatype_f32_r, (rocblas_int)d_model,
-        dh_gemm, rocblas_datatype_f32_r, (rocblas_int)d_model, rocblas_datatype_f32_r, rocblas_gemm_algo_standard,
-        0, 0);
-    if (st != rocblas_status_success) return AIS_ERR_HIP;
+    if (own_dh) {
+      rc = launch_lm_dhidden(ctx, ds, chunk_vocab, w_chunk, weight_stride, width, (int)m_rows, (int)d_model, v0 != 0,
+                             dh_gemm);
+      if (rc != AIS_OK) return rc;
+    } else if (rocblas_gemm_ex(blas, rocblas_operation_none, rocblas_operation_none, (rocblas_int)d_model,
+                               (rocblas_int)m_rows, width, &one, w_chunk, rocblas_datatype_bf16_r,
+                               (rocblas_int)weight_stride, ds, rocblas_datatype_bf16_r, (rocblas_int)chunk_vocab,
+                               v0 == 0 ? &zero : &one, dh_gemm, rocblas_datatype_f32_r, (rocblas_int)d_model, dh_gemm,
+                               rocblas_datatype_f32_r, (rocblas_int)d_model, rocblas_datatype_f32_r,
+                               rocblas_gemm_algo_standard, 0, 0) != rocblas_status_success) {
+      return AIS_ERR_HIP;
+    }
     // dweight_chunk[width, D] = ds^T[width, m_rows] hidden[m_rows, D]:   C^T[D, width] = H^T[D, m_rows] ds[m_rows, width]
     float* dw_chunk = dweight_out + (size_t)v0 * (size_t)d_model;
-    st = rocblas_gemm_ex(blas, rocblas_operation_none, rocblas_operation_transpose, (rocblas_int)d_model, width,
-                         (rocblas_int)m_rows, &one, h_gemm, rocblas_datatype_bf16_r, (rocblas_int)h_gemm_stride, ds,
-                         rocblas_datatype_bf16_r, (rocblas_int)chunk_vocab, &zero, dw_chunk, rocblas_datatype_f32_r,
-                         (rocblas_int)d_model, dw_chunk, rocblas_datatype_f32_r, (rocblas_int)d_model,
-                         rocblas_datatype_f32_r, rocblas_gemm_algo_standard, 0, 0);
-    if (st != rocblas_status_success) return AIS_ERR_HIP;
+    if (own_dw(width)) {
+      rc = launch_lm_dweight(ctx, ds, chunk_vocab, h_gemm, h_gemm_stride, (int)m_rows, n_listed, width, (int)d_model,
+                             dw_chunk);
+      if (rc != AIS_OK) return rc;
+    } else if (rocblas_gemm_ex(blas, rocblas_operation_none, rocblas_operation_transpose, (rocblas_int)d_model, width,
+                               (rocblas_int)m_rows, &one, h_gemm, rocblas_datatype_bf16_r, (rocblas_int)h_gemm_stride,
+                               ds, rocblas_datatype_bf16_r, (rocblas_int)chunk_vocab, &zero, dw_chunk,
+                               rocblas_datatype_f32_r, (rocblas_int)d_model, dw_chunk, rocblas_datatype_f32_r,
+                               (rocblas_int)d_model, rocblas_datatype_f32_r, rocblas_gemm_algo_standard, 0,
+                               0) != rocblas_status_success) {
+      return AIS_ERR_HIP;
+    }
   }
   if (gather) return launch_lm_scatter_rows(ctx, dh_gathered, row_pos, n_rows, (int)d_model, dhidden_out);
   return AIS_OK;

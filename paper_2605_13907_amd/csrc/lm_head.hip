@@ -302,7 +302,8 @@ struct LmGrad {
       }
     }
   }
-  // Writes the finished tile `vt`.  Accumulator element v of MFMA tile i holds vocabulary entry
+  // Writes the finished tile `vt`, zeros past the end of the chunk (a row of ds holds whole tiles, and the products that
+  // read it take whole steps).  Accumulator element v of MFMA tile i holds vocabulary entry
   // vbase + 16 i + 4 quarter + v of token column j: four consecutive entries, 8 bytes, per tile.
   __device__ __forceinline__ void emit(const LmAcc& acc, const LmItem& it, int vt, int vocab, float scale,
                                        const LmGradArgs& ga) {
@@ -314,23 +315,16 @@ struct LmGrad {
 #pragma unroll
       for (int i = 0; i < kLmNI; ++i) {
         const int v0 = vbase + 16 * i + 4 * it.quarter;
-        if (v0 >= vocab) continue;
         float x[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          x[e] = c[j] != 0.f ? c[j] * exp2_fast(fmaf(acc[i][j][e], scale, shift[j])) : 0.f;
+          x[e] = c[j] != 0.f && v0 + e < vocab ? c[j] * exp2_fast(fmaf(acc[i][j][e], scale, shift[j])) : 0.f;
           if (v0 + e == y[j]) x[e] = dy[j];
         }
-        if (v0 + 3 < vocab) {
-          f32x2 lo = {x[0], x[1]}, hi = {x[2], x[3]};
-          uint2 w = {__builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2)),
-                     __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, bf16x2))};
-          *reinterpret_cast<uint2*>(out + v0) = w;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (v0 + e < vocab) Vec<bf16_t>::store1(out + v0 + e, x[e]);
-        }
+        f32x2 lo = {x[0], x[1]}, hi = {x[2], x[3]};
+        uint2 w = {__builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2)),
+                   __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, bf16x2))};
+        *reinterpret_cast<uint2*>(out + v0) = w;
       }
     }
   }
@@ -765,12 +759,12 @@ int launch_lm_head_grad_setup(ais_ctx* ctx, const unsigned char* live_mask, long
 // first vocabulary entry, `which` the plan for its width.  Every row is processed (rows whose coefficient is 0 come out
 // as zeros).
 // With a list (row_index != nullptr: the rows with a gradient, at most n_cap of them) row p of ds belongs to the p-th
-// listed row and rows up to n_cap - 1 are written (zeros past the end of the list).
+// listed row; with `zero_tail` the rows from the end of the list up to n_cap - 1 become zeros.
 int launch_lm_head_dlogits_chunk(ais_ctx* ctx, const void* hidden, long long ld_h, const void* weight,
                                  long long ld_w, long long n_rows, int d_model, int vocab, int y_off,
                                  const int* token_ids, const float* lse, const float* logp, const float* coeff,
                                  float inv_temperature, const void* dev_plan, int which, void* ds, long long ds_stride,
-                                 const int* row_index, int n_cap) {
+                                 const int* row_index, int n_cap, bool zero_tail) {
   const LmHeadPlan plan = lm_head_plan(row_index != nullptr ? n_cap : n_rows, vocab, ctx->n_cus);
   const int max_items = row_index != nullptr ? plan.max_items_masked : plan.max_items;
   const LmDevPlan* dplan = static_cast<const LmDevPlan*>(dev_plan) + which;
@@ -780,7 +774,7 @@ int launch_lm_head_dlogits_chunk(ais_ctx* ctx, const void* hidden, long long ld_
                                         token_ids, inv_temperature * kLog2e, plan.n_vtiles, nullptr, nullptr, nullptr,
                                         ga);
   if (rc != AIS_OK) return rc;
-  if (row_index != nullptr && n_cap > 0)
+  if (row_index != nullptr && zero_tail && n_cap > 0)
     lm_zero_tail_rows_kernel<<<(unsigned)n_cap, 256, 0, ctx->stream>>>(static_cast<bf16_t*>(ds), ds_stride, vocab,
                                                                        dplan);
   return hip_fail(ctx, hipGetLastError());

@@ -174,8 +174,8 @@ int ais_diagnostics(ais_ctx* ctx, const float* logp_train, const float* logp_rol
                     float* adv_out, int* count_out, ais_diag* diag_out);
 
 /* ais_diagnostics for callers that cannot allocate device memory: code under HIP graph capture, tight serving
- * loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and bit-identical results; the row tiling,
- * the ticket counter and the per-tile partials live in a static device array of AIS_STATIC_SCRATCH_BYTES that every
+ * loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and bit-identical results; the row tiling
+ * and the per-tile partials live in a static device array of AIS_STATIC_SCRATCH_BYTES that every
  * GPU the library runs on holds until the process ends, so the call allocates nothing, frees nothing and never
  * waits for the stream, whatever sizes came before.
  *   Limit      56 * (ceil(n_rows / 1024) + n_resp) + 4 * (n_resp + 2) bytes, each part rounded up to 256, must fit

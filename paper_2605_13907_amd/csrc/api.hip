@@ -598,8 +598,10 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   const void* h_gemm = gather ? static_cast<const void*>(h_gathered) : hidden;
   const long long h_gemm_stride = gather ? d_model : hidden_stride;
   float* dh_gemm = gather ? dh_gathered : dhidden_out;
-  const bool own_dh = lm_dhidden_fits(ctx, d_model, m_rows);
-  auto own_dw = [&](int width) { return lm_dweight_fits(ctx, d_model, width); };
+  // (the own kernels store 16 bytes at a time; rows of a multiple of 32 floats keep the base's alignment)
+  const bool own_dh = lm_dhidden_fits(ctx, d_model, m_rows) && reinterpret_cast<uintptr_t>(dh_gemm) % 16 == 0;
+  const bool dw_aligned = reinterpret_cast<uintptr_t>(dweight_out) % 16 == 0;
+  auto own_dw = [&](int width) { return dw_aligned && lm_dweight_fits(ctx, d_model, width); };
   // the list's length, first word of the decomposition on the device: rows past it are nobody's
   const int* n_listed = gather ? static_cast<const int*>(dev_plan) : nullptr;
   rocblas_handle blas = nullptr;

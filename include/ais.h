@@ -295,8 +295,8 @@ int ais_fp8_rollout_logprob(ais_ctx* ctx, const void* logits, ais_dtype dtype, l
  *   token_ids   [n_rows] device; ignored where valid == 0
  *   logp_out, lse_out  [n_rows] device fp32; 0 where valid == 0; a row whose token id is outside
  *               [0, vocab) gets logp 0, its lse, and AIS_STATUS_BAD_TOKEN in the status word
- * Uses the context workspace (2 * chunks + 3 words per row; chunks <= 64 from 2,048 rows on, at most 512 below);
- * nothing is retained.
+ * Uses the context workspace (2 * chunks + 3 words per row; chunks <= 64 from 2,048 rows on, at most 512 below, about
+ * 1 MB there; never less than over fewer rows); nothing is retained.
  * Errors: dtype other than AIS_BF16 (AIS_ERR_DTYPE); n_rows < 0, vocab < 1, d_model < 8 or not a
  * multiple of 8 (AIS_ERR_SIZE); a stride < d_model (AIS_ERR_STRIDE); NULL pointers; hidden or weight
  * not 16-byte aligned or a stride not a multiple of 8 elements (AIS_ERR_ALIGN); inv_temperature
@@ -321,8 +321,8 @@ int ais_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long hidden_strid
  *   lse, logp   [n_rows] fp32, outputs of ais_lm_head_logprob for the same operands and temperature
  *   coeff       [n_rows] fp32, as written by ais_grpo_row_scale (its g_out: it carries inv_temperature)
  *   chunk_vocab vocabulary entries per chunk, a multiple of 256.  The context workspace grows to
- *               2 * n_rows * chunk_vocab bytes.  0 selects 8192 and, with fewer than 4,096 rows to go through, wider chunks
- *               for a workspace of up to 70 MB.
+ *               2 * n_rows * chunk_vocab bytes.  0 selects 8192 and, with fewer than 4,096 rows to go through, wider chunks;
+ *               the workspace is then up to 70 MB whatever the number of those rows.
  *   n_live_max  negative, or >= n_rows: every row goes through the recomputation and the GEMMs.  Otherwise a bound
  *               that the caller vouches for on the number of rows with coeff != 0 (for a masked-diffusion batch:
  *               the number of evaluated positions, which its loader knows): those rows are gathered on the device

@@ -52,6 +52,10 @@ struct LmHeadPlan {
   int max_items_masked;  // the same where fewer rows than that may be evaluated
 };
 LmHeadPlan lm_head_plan(long long n_rows, int vocab, int n_cus);
+// Workspace of the read-out's two calls (the gradient call's: of a chunk's dlogits) and the gradient call's chunk width.
+size_t lm_head_logprob_bytes(long long n_rows, int vocab, int n_cus);
+long long lm_grad_chunk(long long m_rows, long long vocab, long long asked, int n_cus);
+size_t lm_grad_dlogits_bytes(long long m_rows, long long vocab, long long asked, int n_cus);
 
 }  // namespace ais
 

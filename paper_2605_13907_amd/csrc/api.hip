@@ -150,22 +150,6 @@ int plan_for_step(ais_ctx* ctx, const long long* cu_rows, int n_resp, long long 
   return launch_plan(ctx, cu_rows, n_resp, n_rows, tile_off, max_tiles);
 }
 
-// Vocabulary entries per chunk of ais_lm_head_grad when the caller leaves the choice.  8,192 entries are 32 tiles, which
-// with 16 token blocks (4,096 rows) are two work items per compute unit; with fewer rows the chunk is wider by as much
-// (700 rows x 50,257 x 2,048: 1.13 ms in chunks of 8,192, 0.90 in one of 43,776; 2,000 rows 1.52 and 1.46 ms).
-constexpr long long kLmGradChunk = 8192;
-constexpr long long kLmGradFewRows = 4096;
-long long lm_grad_chunk_few(long long m_rows, int n_cus) {
-  const long long blocks = (m_rows + 255) / 256;
-  return 256 * ((2 * n_cus + blocks - 1) / blocks);
-}
-// Most bytes that a chunk takes over any number of rows below kLmGradFewRows.
-size_t lm_grad_few_bytes(long long vocab, int n_cus) {
-  const long long wide = ((vocab + 255) / 256) * 256;
-  const long long most = 256LL * 256 * std::max<long long>(2 * n_cus + kLmGradFewRows / 256, 512);
-  return 2 * (size_t)std::min(most, kLmGradFewRows * wide);
-}
-
 int check_diagnostics_args(const float* logp_train, const float* logp_roll, long long n_rows,
                            const long long* cu_rows, int n_resp, int group_size, const float* rewards,
                            const ais_params* params, const float* adv_out, const int* count_out,
@@ -505,8 +489,7 @@ int ais_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long hidden_strid
   const LmHeadPlan plan = lm_head_plan(n_rows, (int)vocab, ctx->n_cus);
   // workspace: per-chunk partial (max, sum) and the sampled token's logit of every evaluated position, the list
   // of evaluated rows, its inverse, and the device-side decomposition
-  const size_t per = sizeof(float) * (size_t)n_rows;
-  int rc = ensure_workspace(ctx, per * (2 * (size_t)plan.max_chunks + 3) + 256);
+  int rc = ensure_workspace(ctx, lm_head_logprob_bytes(n_rows, (int)vocab, ctx->n_cus));
   if (rc != AIS_OK) return rc;
   ctx->plan.valid = false;             // this call's partials overwrite whatever tiling the workspace held
   float* part_m = static_cast<float*>(ctx->ws);
@@ -529,9 +512,7 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   if (n_rows < 0 || n_rows > 0x7fffffffLL - 256) return AIS_ERR_SIZE;
   if (vocab < 1 || vocab > 0x7fffffffLL - 256) return AIS_ERR_SIZE;
   if (d_model < 32 || d_model > (1 << 20) || d_model % 32 != 0) return AIS_ERR_SIZE;
-  const bool own_chunk = chunk_vocab == 0;
-  if (own_chunk) chunk_vocab = kLmGradChunk;
-  if (chunk_vocab < 256 || chunk_vocab > (1 << 24) || chunk_vocab % 256 != 0) return AIS_ERR_SIZE;
+  if (chunk_vocab != 0 && (chunk_vocab < 256 || chunk_vocab > (1 << 24) || chunk_vocab % 256 != 0)) return AIS_ERR_SIZE;
   if (hidden_stride < d_model || weight_stride < d_model) return AIS_ERR_STRIDE;
   if (weight == nullptr || dweight_out == nullptr) return AIS_ERR_NULL;
   if (n_rows > 0 && (hidden == nullptr || token_ids == nullptr || lse == nullptr || logp == nullptr ||
@@ -552,9 +533,6 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   }
   const bool gather = n_live_max >= 0 && n_live_max < n_rows;
   const long long m_rows = gather ? n_live_max : n_rows;       // rows that the recomputation and the GEMMs cover
-  const bool few_rows = own_chunk && m_rows < kLmGradFewRows;
-  if (few_rows && m_rows > 0) chunk_vocab = std::max<long long>(chunk_vocab, lm_grad_chunk_few(m_rows, ctx->n_cus));
-  if (chunk_vocab > ((vocab + 255) / 256) * 256) chunk_vocab = ((vocab + 255) / 256) * 256;
   if (m_rows == 0) {                    // the caller vouches that no row has a gradient
     zero_fill_kernel<<<(unsigned)std::min<size_t>(((size_t)vocab * d_model + 255) / 256, (size_t)ctx->n_cus * 8), 256, 0,
                        ctx->stream>>>(dweight_out, (size_t)vocab * (size_t)d_model);
@@ -565,10 +543,8 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   // workspace: the chunk's dlogits, the device-side decomposition of the recompute kernel and, with a row list, the
   // mask, the list, its inverse, the gathered hidden states and their gradient
   auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
-  size_t ds_bytes = up((size_t)m_rows * (size_t)chunk_vocab * 2);
-  // with few rows the chunk grows as the rows get fewer: ask for what the largest of them takes, so that no call needs
-  // more than one over more rows before it
-  if (few_rows) ds_bytes = std::max(ds_bytes, up(lm_grad_few_bytes(vocab, ctx->n_cus)));
+  const size_t ds_bytes = up(lm_grad_dlogits_bytes(m_rows, vocab, chunk_vocab, ctx->n_cus));
+  chunk_vocab = lm_grad_chunk(m_rows, vocab, chunk_vocab, ctx->n_cus);
   const size_t plan_bytes = 256;
   const size_t mask_bytes = gather ? up((size_t)n_rows) : 0;
   const size_t list_bytes = gather ? up((size_t)n_rows * 4) : 0;

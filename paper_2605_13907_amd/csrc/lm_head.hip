@@ -30,6 +30,7 @@
 #include "ais_internal.h"
 #include "device_utils.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace ais {
@@ -695,6 +696,48 @@ LmHeadPlan lm_head_plan(long long n_rows, int vocab, int n_cus) {
   // with a mask fewer rows may be evaluated, in more chunks: two work items per compute unit are what they can use
   p.max_items_masked = p.max_items > 2 * n_cus ? p.max_items : (2 * n_cus + 7) / 8 * 8;
   return p;
+}
+
+// Workspace of the log-prob call: the partials (max, sum) of max_chunks chunks per row, three words per row, the plan.
+// More rows than before never ask for less (a context's users size it with one call at their largest batch), although
+// few rows take more chunks each: what is asked for is the most that any number of rows up to n_rows takes.  From
+// 64 * 256 / (2 n_cus) token blocks on every batch has the same number of chunks, so the rows below are few to look at.
+size_t lm_head_logprob_bytes(long long n_rows, int vocab, int n_cus) {
+  const int n_vtiles = (vocab + kLmTileV - 1) / kLmTileV;
+  size_t most = 0;
+  for (long long blocks = 1;; ++blocks) {
+    const bool steady = lm_chunk_limit((int)blocks, n_vtiles, n_cus) == lm_chunk_limit(1 << 30, n_vtiles, n_cus);
+    const long long rows = steady || blocks * kLmTileT > n_rows ? n_rows : blocks * kLmTileT;
+    const size_t words = 2 * (size_t)lm_chunk_limit((int)blocks, n_vtiles, n_cus) + 3;
+    most = std::max(most, sizeof(float) * (size_t)rows * words);
+    if (rows == n_rows) return most + 256;
+  }
+}
+
+// Vocabulary entries per chunk of the gradient call; asked == 0: the library's choice.  8,192 entries are 32 tiles, which
+// with 16 token blocks (4,096 rows) are two work items per compute unit; with fewer rows the chunk is wider by as much
+// (700 rows x 50,257 x 2,048: 1.13 ms in chunks of 8,192, 0.90 in one of 43,776; 2,000 rows 1.52 and 1.46 ms).
+constexpr long long kLmGradChunk = 8192;
+constexpr long long kLmGradFewRows = 4096;
+long long lm_grad_chunk(long long m_rows, long long vocab, long long asked, int n_cus) {
+  const long long whole = (vocab + kLmTileV - 1) / kLmTileV * kLmTileV;
+  long long chunk = asked != 0 ? asked : kLmGradChunk;
+  if (asked == 0 && m_rows < kLmGradFewRows) {
+    const long long blocks = std::max<long long>(1, (m_rows + kLmTileT - 1) / kLmTileT);
+    chunk = std::max(chunk, kLmTileV * ((2 * n_cus + blocks - 1) / blocks));
+  }
+  return std::min(chunk, whole);
+}
+
+// Bytes of a chunk's dlogits.  Where the library chooses the chunk, no fewer than it takes over any smaller number of rows
+// (whose chunks are wider): a call never needs more than one over more rows before it.
+size_t lm_grad_dlogits_bytes(long long m_rows, long long vocab, long long asked, int n_cus) {
+  const size_t own = 2 * (size_t)m_rows * (size_t)lm_grad_chunk(m_rows, vocab, asked, n_cus);
+  if (asked != 0) return own;
+  const long long whole = (vocab + kLmTileV - 1) / kLmTileV * kLmTileV;
+  const long long items = std::max<long long>(2 * n_cus, kLmGradFewRows / kLmTileT * (kLmGradChunk / kLmTileV));
+  const long long few = kLmTileT * kLmTileV * (items + kLmGradFewRows / kLmTileT);
+  return std::max(own, 2 * (size_t)std::min(few, kLmGradFewRows * whole));
 }
 
 template <bool GRAD>

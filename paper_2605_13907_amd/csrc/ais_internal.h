@@ -82,7 +82,7 @@ struct ais_ctx {
     bool valid = false;
   } plan;
   void* static_scratch = nullptr;   // address, on this context's device, of the library's static scratch array
-  void* blas = nullptr;             // rocblas_handle of ais_lm_head_grad's products at sizes its own kernels leave, created on first use
+  void* blas = nullptr;             // rocblas_handle of ais_lm_head_grad's products at sizes its own kernels leave, created by its first call
 };
 
 namespace ais {

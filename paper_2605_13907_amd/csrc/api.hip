@@ -580,14 +580,15 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   auto own_dw = [&](int width) { return dw_aligned && lm_dweight_fits(ctx, d_model, width); };
   // the list's length, first word of the decomposition on the device: rows past it are nobody's
   const int* n_listed = gather ? static_cast<const int*>(dev_plan) : nullptr;
-  rocblas_handle blas = nullptr;
+  // created by the first call, whichever kernels that call takes: later ones may be recorded into a graph, where nothing
+  // can be allocated
+  if (ctx->blas == nullptr) {
+    rocblas_handle h = nullptr;
+    if (rocblas_create_handle(&h) != rocblas_status_success) return AIS_ERR_HIP;
+    ctx->blas = h;
+  }
+  rocblas_handle blas = static_cast<rocblas_handle>(ctx->blas);
   if (!own_dh || !own_dw((int)std::min<long long>(chunk_vocab, vocab)) || (width_last != 0 && !own_dw(width_last))) {
-    if (ctx->blas == nullptr) {
-      rocblas_handle h = nullptr;
-      if (rocblas_create_handle(&h) != rocblas_status_success) return AIS_ERR_HIP;
-      ctx->blas = h;
-    }
-    blas = static_cast<rocblas_handle>(ctx->blas);
     if (rocblas_set_stream(blas, ctx->stream) != rocblas_status_success) return AIS_ERR_HIP;
     if (rocblas_set_pointer_mode(blas, rocblas_pointer_mode_host) != rocblas_status_success) return AIS_ERR_HIP;
   }

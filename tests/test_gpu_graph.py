@@ -198,3 +198,41 @@ def test_static_diagnostics_replays(ctx):
         torch.cuda.synchronize()
         assert same_bits(adv, ref[0]) and same_bits(count, ref[1]) and same_bits(diag, ref[2])
     assert ctx.status() == 0
+
+
+@pytest.mark.parametrize("rows,live", [(4096, -1), (3000, -1), (4096, 2000)])
+def test_lm_head_grad_replays(rows, live):
+    """The gradient of the hidden-state read-out, recorded after calls at the largest size whose products run on the
+    library's own kernels: 3,000 rows and a list of 2,000 take rocBLAS for the hidden gradient, for the first time on this
+    context and inside the capture."""
+    ctx = B.AisContext()
+    d, vocab = 4096, 8192
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows + live)
+    weight = (torch.randn(vocab, d, generator=gen, device="cuda") / d ** 0.5).bfloat16()
+    hidden = (torch.randn(4096, d, generator=gen, device="cuda") * 2.0).bfloat16()
+    y = torch.randint(0, vocab, (4096,), generator=gen, device="cuda").to(torch.int32)
+    coeff = torch.randn(4096, generator=gen, device="cuda")
+    if live >= 0:
+        coeff[live:] = 0.0
+    logp, lse = ctx.lm_head_logprob(hidden, weight, y)
+    ctx.lm_head_grad(hidden, weight, y, lse, logp, coeff, n_live_max=4095 if live >= 0 else -1)     # the largest size
+    args = tuple(t[:rows] if t.shape[0] == 4096 else t for t in (hidden, weight, y, lse, logp, coeff))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        dh, dw = ctx.lm_head_grad(*args, n_live_max=live)
+    for k in range(4):
+        hidden.mul_(1.0 - 0.1 * k)
+        coeff.mul_(-1.25)
+        for t, new in zip((logp, lse), ctx.lm_head_logprob(hidden, weight, y)):
+            t.copy_(new)
+        ref = ctx.lm_head_grad(*args, n_live_max=live)         # eager, between the replays
+        torch.cuda.synchronize()
+        dh.fill_(7.0)
+        dw.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert same_bits(dh, ref[0]) and same_bits(dw, ref[1]), f"replay {k} differs from the eager call"
+    assert ctx.status() == 0
+    ctx.close()

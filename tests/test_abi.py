@@ -396,3 +396,41 @@ def test_binding_rejects_host_tensors_before_any_launch():
     with pytest.raises(ValueError):                         # the geometry helper itself, with and without a device
         B._logits_geometry(torch.zeros(4, 8, 2), None)
     assert B._logits_geometry(z, None) == (4, 64, 64)
+
+
+def test_every_call_names_the_stream(monkeypatch):
+    """A call launches on torch's current stream, also after somebody has told the library of another one through
+    ais_set_stream."""
+    import torch
+
+    class Library:
+        stream = 0
+
+        def ais_set_stream(self, h, stream):
+            self.stream = stream
+            return 0
+
+        def ais_copy(self, h, dst, src, nbytes):
+            launched.append(self.stream)
+            return 0
+
+    monkeypatch.setattr(B, "_current_raw_stream", lambda index: 0x5000)
+    monkeypatch.setattr(B, "_dev_ptr", lambda t, device, name: t.data_ptr())
+    launched = []
+    ctx = object.__new__(B.AisContext)
+    ctx.device, ctx._h, ctx._lib, ctx._stream = torch.device("cuda", 0), None, Library(), 0
+    ctx.copy(torch.zeros(16), torch.zeros(16))
+    ctx._lib.ais_set_stream(None, 0x7000)
+    ctx.copy(torch.zeros(16), torch.zeros(16))
+    assert launched == [0x5000, 0x5000]
+
+
+def test_stream_handle_without_the_private_function(monkeypatch):
+    import torch
+
+    class Stream:
+        cuda_stream = 0x5000
+
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: Stream)
+    monkeypatch.setattr(B, "_raw_stream", None, raising=False)
+    assert B._current_raw_stream(0) == 0x5000

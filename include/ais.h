@@ -183,7 +183,9 @@ int ais_diagnostics(ais_ctx* ctx, const float* logp_train, const float* logp_rol
  *              that the call returns AIS_ERR_SCRATCH and launches nothing.
  *   Sharing    every call on one GPU, from any context, uses that GPU's one array (the kernels overwrite what they
  *              read, so earlier contents do not matter): calls that overlap in time on one GPU race, also across
- *              contexts and streams.  The row tiling it leaves behind is not reused by the calls that follow.
+ *              contexts and streams.  With the context's other calls it shares only the status word: a graph that
+ *              holds it may be replayed beside them.  The row tiling it leaves behind is not reused by the calls that
+ *              follow.
  * Errors: as ais_diagnostics, plus AIS_ERR_SCRATCH. */
 #define AIS_STATIC_SCRATCH_BYTES (1 << 20)
 int ais_diagnostics_static(ais_ctx* ctx, const float* logp_train, const float* logp_roll,

@@ -15,7 +15,9 @@ constexpr int kSweepThreads = 256;     // one workgroup (4 wavefronts) streams o
 constexpr int kTileThreads = 256;      // workgroup of the per-row scalar kernels
 constexpr int kTileRows = 1024;        // rows of one response handled by one such workgroup
 constexpr int kSelfPlanResponses = 1024;   // most responses whose tiling the scalar kernels work out for themselves
-constexpr int kTicketWord = 32;        // word of the status allocation that counts finished workgroups of a reduction
+// Words of the status allocation that count the finished workgroups of a reduction: a pair for the calls that work in the
+// context's workspace, a pair for the static call, which may run beside them.
+constexpr int kTicketWord = 32, kStaticTicketWord = 48;
 constexpr int kMaxDevices = 64;        // device indices a context may be created on
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -64,7 +66,8 @@ struct ais_ctx {
   hipStream_t stream = nullptr;
   void* ws = nullptr;
   size_t ws_bytes = 0;
-  int* status_dev = nullptr;     // 256 bytes: the status word and, at kTicketWord, a counter that is 0 between launches
+  int* status_dev = nullptr;     // 256 bytes: the status word and the tickets, which are 0 between launches
+  unsigned turns = 0, static_turns = 0;   // reductions launched with either pair of tickets
   int n_cus = 256;               // compute units of the device
   int last_hip_error = 0;
   bool profiling = false;
@@ -123,7 +126,7 @@ int launch_plan(ais_ctx* ctx, const long long* cu_rows, int n_resp, long long n_
 int launch_diagnostics(ais_ctx* ctx, const float* logp_train, const float* logp_roll, const unsigned char* valid,
                        long long n_rows, const long long* cu_rows, int n_resp, int group_size,
                        const float* rewards, const ais_params& p, int* tile_off, int max_tiles,
-                       DiagPartial* partial, float* adv_out, int* count_out, ais_diag* diag_out);
+                       DiagPartial* partial, bool in_static, float* adv_out, int* count_out, ais_diag* diag_out);
 int launch_row_coeff(ais_ctx* ctx, const float* logp_train, const float* logp_roll, const float* logp_old,
                      const float* logp_ref, const unsigned char* valid, long long n_rows,
                      const long long* cu_rows, int n_resp, const float* adv, const int* count,

@@ -307,8 +307,8 @@ int ais_diagnostics(ais_ctx* ctx, const float* logp_train, const float* logp_rol
   rc = launch_plan(ctx, cu_rows, n_resp, n_rows, tile_off, w.max_tiles);
   if (rc != AIS_OK) return rc;
   rc = launch_diagnostics(ctx, logp_train, logp_roll, valid, n_rows, cu_rows, n_resp, group_size, rewards, *params,
-                          tile_off, w.max_tiles, reinterpret_cast<DiagPartial*>(ws + w.partial), adv_out, count_out,
-                          diag_out);
+                          tile_off, w.max_tiles, reinterpret_cast<DiagPartial*>(ws + w.partial), false, adv_out,
+                          count_out, diag_out);
   if (rc != AIS_OK) return rc;
   // the tiling stays in the workspace for the calls that complete this step
   ctx->plan.cu_rows = cu_rows;
@@ -340,8 +340,8 @@ int ais_diagnostics_static(ais_ctx* ctx, const float* logp_train, const float* l
   rc = launch_plan(ctx, cu_rows, n_resp, n_rows, tile_off, w.max_tiles);
   if (rc != AIS_OK) return rc;
   return launch_diagnostics(ctx, logp_train, logp_roll, valid, n_rows, cu_rows, n_resp, group_size, rewards, *params,
-                            tile_off, w.max_tiles, reinterpret_cast<DiagPartial*>(ws + w.partial), adv_out, count_out,
-                            diag_out);
+                            tile_off, w.max_tiles, reinterpret_cast<DiagPartial*>(ws + w.partial), true, adv_out,
+                            count_out, diag_out);
 }
 
 int ais_grpo_loss_grad(ais_ctx* ctx, const void* logits, ais_dtype dtype, long long n_rows, long long vocab,

@@ -335,12 +335,22 @@ __device__ __forceinline__ void block_reduce(Moments (&m)[NM], double (&d)[ND], 
 // rows 79 instead of 62 us.)
 // Level 2 of each reduction runs in that workgroup, which saves a kernel launch per reduction; the order in which level
 // 2 folds the partials does not depend on which workgroup happens to be last, so results stay bit-reproducible.
-__device__ __forceinline__ bool last_workgroup(int* ticket) {
+struct Tickets {
+  int* own;      // 0 when the launch begins and when it ends
+  int* next;     // the launch's that comes after it
+};
+
+__device__ __forceinline__ bool last_workgroup(Tickets t) {
   __shared__ int s_last;
   if (threadIdx.x == 0) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    s_last = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
-    if (s_last) put_device(ticket, 0);       // every other workgroup has taken its ticket: ready for the next launch
+    s_last = __hip_atomic_fetch_add(t.own, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+    if (s_last) {
+      put_device(t.own, 0);                  // every other workgroup has taken its ticket: ready for a later launch
+      // Launches take turns with two tickets, and each clears the other's: should launches of one context ever have
+      // overlapped, which leaves a count behind, the results of one call are lost and the calls after it are sound.
+      put_device(t.next, 0);
+    }
   }
   __syncthreads();
   return s_last != 0;
@@ -493,7 +503,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void diag_reduce_kernel(
     const unsigned char* __restrict__ valid, long long n_rows, const long long* __restrict__ cu_rows, int n_resp,
     const int* __restrict__ tile_off, int max_tiles, DiagPartial* partial, int group_size,
     const float* __restrict__ rewards, ais_params p, double lnC, float* __restrict__ adv_out, int* __restrict__ count_out,
-    ais_diag* __restrict__ diag_out, int* status, int* ticket) {
+    ais_diag* __restrict__ diag_out, int* status, Tickets tickets) {
   __shared__ double lds_d[12 * kWaves];          // three sets of moments and three sums per wavefront
   __shared__ long long lds_i[2 * kWaves];
   Tiling<SELF> tiling;
@@ -547,7 +557,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void diag_reduce_kernel(
     }
   }
   // ---- level 2, in the workgroup that finishes last ----
-  if (last_workgroup(ticket))
+  if (last_workgroup(tickets))
     diag_final<SELF>(partial, tiling, n_resp, group_size, rewards, p, adv_out, count_out, diag_out, status, lds_d,
                      lds_i);
 }
@@ -568,7 +578,7 @@ __global__ __launch_bounds__(kTileThreads) void row_coeff_kernel(
     const long long* __restrict__ cu_rows, int n_resp, const float* __restrict__ adv,
     const int* __restrict__ count, const ais_diag* __restrict__ diag, ais_params p, double lnC,
     const int* __restrict__ tile_off, int max_tiles, double* partial, float* __restrict__ g_out,
-    float* __restrict__ wtilde_out, float g_scale, double* __restrict__ loss_out, int* status, int* ticket) {
+    float* __restrict__ wtilde_out, float g_scale, double* __restrict__ loss_out, int* status, Tickets tickets) {
   __shared__ double lds_d[kWaves];
   const double alpha = diag->alpha;
   Tiling<SELF> tiling;
@@ -634,7 +644,7 @@ __global__ __launch_bounds__(kTileThreads) void row_coeff_kernel(
     acc = block_sum(acc, lds_d);
     if (threadIdx.x == 0) put_device(partial + b, acc);
   }
-  if (last_workgroup(ticket)) loss_final(partial, n_tiles, loss_out, lds_d);
+  if (last_workgroup(tickets)) loss_final(partial, n_tiles, loss_out, lds_d);
 }
 
 // Workgroups of a reduction: one per tile, but no more than the device holds at once (4 per compute unit by their
@@ -644,6 +654,12 @@ int reduction_grid(const ais_ctx* ctx, int max_tiles) {
   const int most = 4 * ctx->n_cus;
   const int rounds = (max_tiles + most - 1) / most;
   return rounds > 1 ? (max_tiles + rounds - 1) / rounds : max_tiles;
+}
+
+Tickets take_tickets(ais_ctx* ctx, bool in_static) {
+  int* pair = ctx->status_dev + (in_static ? kStaticTicketWord : kTicketWord);
+  const unsigned turn = (in_static ? ctx->static_turns : ctx->turns)++ & 1u;
+  return Tickets{pair + turn, pair + (turn ^ 1u)};
 }
 
 }  // namespace
@@ -670,11 +686,11 @@ int launch_plan(ais_ctx* ctx, const long long* cu_rows, int n_resp, long long n_
 int launch_diagnostics(ais_ctx* ctx, const float* logp_train, const float* logp_roll, const unsigned char* valid,
                        long long n_rows, const long long* cu_rows, int n_resp, int group_size,
                        const float* rewards, const ais_params& p, int* tile_off, int max_tiles,
-                       DiagPartial* partial, float* adv_out, int* count_out, ais_diag* diag_out) {
+                       DiagPartial* partial, bool in_static, float* adv_out, int* count_out, ais_diag* diag_out) {
   auto kernel = n_resp <= kSelfPlanResponses ? diag_reduce_kernel<true> : diag_reduce_kernel<false>;
   kernel<<<reduction_grid(ctx, max_tiles), kTileThreads, 0, ctx->stream>>>(
       logp_train, logp_roll, valid, n_rows, cu_rows, n_resp, tile_off, max_tiles, partial, group_size, rewards, p,
-      std::log((double)p.C), adv_out, count_out, diag_out, ctx->status_dev, ctx->status_dev + kTicketWord);
+      std::log((double)p.C), adv_out, count_out, diag_out, ctx->status_dev, take_tickets(ctx, in_static));
   return hip_fail(ctx, hipGetLastError());
 }
 
@@ -686,7 +702,8 @@ int launch_row_coeff(ais_ctx* ctx, const float* logp_train, const float* logp_ro
   auto kernel = n_resp <= kSelfPlanResponses ? row_coeff_kernel<true> : row_coeff_kernel<false>;
   kernel<<<reduction_grid(ctx, max_tiles), kTileThreads, 0, ctx->stream>>>(
       logp_train, logp_roll, logp_old, logp_ref, valid, n_rows, cu_rows, n_resp, adv, count, diag, p,
-      std::log((double)p.C), tile_off, max_tiles, partial, g_out, wtilde_out, g_scale, loss_out, ctx->status_dev, ctx->status_dev + kTicketWord);
+      std::log((double)p.C), tile_off, max_tiles, partial, g_out, wtilde_out, g_scale, loss_out, ctx->status_dev,
+      take_tickets(ctx, false));
   return hip_fail(ctx, hipGetLastError());
 }
 

@@ -46,7 +46,7 @@ __device__ __align__(16) const bf16_t kZeros[8] = {};
 // counts these copies too, which makes it wait longer, never shorter.)
 __device__ __forceinline__ void copy_to_lds(const bf16_t* src, const unsigned char* base) {
   const uint32_t at = (uint32_t)(uintptr_t)(lds_ptr)base;               // uniform
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(at), "v"(src) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(at), "v"(src) : "m0", "memory");
 }
 
 struct GemmArgs {

@@ -44,10 +44,15 @@ __device__ __align__(16) const bf16_t kZeros[8] = {};
 // compiler, which does not see through the transposing reads, would wait for every copy in flight before each of them;
 // the waits below are written out.  (It has no result register; a wait that the compiler places for loads of its own
 // counts these copies too, which makes it wait longer, never shorter.)
+// (m0 is said to be written although the compiler warns that it is a register of its own: it orders its own uses of m0
+// by that.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void copy_to_lds(const bf16_t* src, const unsigned char* base) {
   const uint32_t at = (uint32_t)(uintptr_t)(lds_ptr)base;               // uniform
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(at), "v"(src) : "m0", "memory");
 }
+#pragma clang diagnostic pop
 
 struct GemmArgs {
   const bf16_t* a;          // [k][ld_a]

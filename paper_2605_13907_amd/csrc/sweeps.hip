@@ -8,7 +8,7 @@
 //                          dtype (gradient of Eq. 19 through the log-softmax; g is the row's coefficient)
 //
 // Both are bound by HBM bandwidth: nothing here is a contraction, so no matrix cores.  One workgroup
-// owns one row (256 threads in the read-only sweep, 1,024 in the read+write sweep), so a row's partial
+// owns one row (256 threads in the read-only sweep, 1,024 in the read+write sweep, 256 for narrow rows), so a row's partial
 // results never leave its compute unit; consecutive lanes access consecutive 16-byte vectors (8 bf16 or
 // 4 fp32 logits), i.e. each wavefront memory instruction covers 1 KiB of contiguous memory.  Logits are
 // read and written with streaming (non-temporal) accesses: a batch is tens of GB and nothing survives in
@@ -123,8 +123,8 @@ __global__ __launch_bounds__(kSweepThreads) void token_logprob_kernel(
 // zero advantage, or clipped away) are filled with zeros without being read.  In-place operation is safe:
 // every element is read and written by the same thread, once.
 //
-// Element-wise form: the route when logits and gradient lie differently relative to a 16-byte boundary, so that no
-// vector of the one is a vector of the other.  grid.x = n_rows, block = kSweepThreads.
+// Element-wise form: the route when logits and gradient are not both 16-byte aligned and lie differently relative to a
+// line, or are narrow.  grid.x = n_rows, block = kSweepThreads.
 template <typename T>
 __global__ __launch_bounds__(kSweepThreads) void dlogits_elementwise_kernel(
     const T* logits, long long row_stride, int vocab, const int* __restrict__ token_ids,
@@ -154,13 +154,13 @@ __global__ __launch_bounds__(kSweepThreads) void dlogits_elementwise_kernel(
   }
 }
 
-// Burst form: the route for every other row.  A workgroup of 1,024 threads owns the row; every wavefront
+// Burst form: the route for every other row.  A workgroup of THREADS (1,024; narrow rows: 256) owns the row; every wavefront
 // issues all of its loads (up to NV 16-byte vectors per lane, i.e. up to NV KiB per wavefront), transforms
 // the vectors in place as they arrive, and only when its last load has landed issues all of its stores.
 // Measured on MI355X, a read+write stream shaped this way (long load bursts followed by long store bursts,
 // all wavefronts of a compute unit in step because they start together) sustains 5.8-6.0 TB/s where a loop
 // that stores each vector as soon as it is computed, and every plain copy variant, saturate at 5.2-5.3 TB/s.
-// grid.x = 8 * ceil(n_rows / 8), block = kBurstThreads.  ALIGNED: both rows are 16-byte aligned; otherwise both lie the
+// grid.x = 8 * ceil(n_rows / 8), block = THREADS.  ALIGNED: both rows are 16-byte aligned; otherwise both lie the
 // same way relative to 128-byte lines, and the elements before the row's first line boundary are handled one by one
 // together with those after the last vector.  Rows wider than NV * 1024 vectors
 // are processed in consecutive segments (there is no dependence between segments: lse is an input).
@@ -170,8 +170,8 @@ constexpr int kBurstThreads = 1024;
 // faster than the same code inside a run-time loop.  NSEG = 0: run-time loop over as many segments as needed.
 // KFULL promises that the row has at least KFULL * 1024 vectors: vectors 0 .. KFULL - 1 of every lane exist and
 // are loaded and stored without a bounds branch (1.5 % faster at 19 vectors per lane).
-template <typename T, bool ALIGNED, int NV, int NSEG, int KFULL>
-__global__ __launch_bounds__(kBurstThreads) void dlogits_burst_kernel(
+template <typename T, bool ALIGNED, int THREADS, int NV, int NSEG, int KFULL>
+__global__ __launch_bounds__(THREADS) void dlogits_burst_kernel(
     const T* logits, long long row_stride, int vocab, const int* __restrict__ token_ids,
     const float* __restrict__ g, const unsigned char* __restrict__ valid, const float* __restrict__ lse,
     const float* __restrict__ logp, float inv_temperature, T* dlogits, long long n_rows) {
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(kBurstThreads) void dlogits_burst_kernel(
 
   if (gn == 0.f) {
     const u32x4 zero = {0u, 0u, 0u, 0u};
-    for (int i = tid; i < nvec; i += kBurstThreads) store_stream(dv + i, zero);
+    for (int i = tid; i < nvec; i += THREADS) store_stream(dv + i, zero);
     if (tid < rest) Vec<T>::store1(dr + v_rest, 0.f);
     return;
   }
@@ -208,18 +208,18 @@ __global__ __launch_bounds__(kBurstThreads) void dlogits_burst_kernel(
   // The sampled token's element is c (p_y - 1) = c expm1(logp): no cancellation when p_y is close to 1.  The
   // lane that holds it patches its packed output register before the store burst.
   const int yb = y - head;                       // its position from the first vector on
-  const int yvec = (y >= 0 && yb >= 0 && yb < nvec * N && (yb / N) % kBurstThreads == tid) ? yb / N : -1;
+  const int yvec = (y >= 0 && yb >= 0 && yb < nvec * N && (yb / N) % THREADS == tid) ? yb / N : -1;
   const float dzy = c * expm1f(logp[row]);
 
-  const int n_base = NSEG > 0 ? NSEG * NV * kBurstThreads : nvec;
+  const int n_base = NSEG > 0 ? NSEG * NV * THREADS : nvec;
   constexpr int kUnrollSegments = NSEG > 0 ? NSEG : 1;
 #pragma unroll kUnrollSegments
-  for (int base = 0; base < n_base; base += NV * kBurstThreads) {
+  for (int base = 0; base < n_base; base += NV * THREADS) {
     u32x4 q[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-      const int i = base + tid + k * kBurstThreads;
-      if (NSEG > 0 && base / kBurstThreads + k < KFULL) q[k] = load_stream(zv + i);
+      const int i = base + tid + k * THREADS;
+      if (NSEG > 0 && base / THREADS + k < KFULL) q[k] = load_stream(zv + i);
       else q[k] = (i < nvec) ? load_stream(zv + i) : u32x4{0u, 0u, 0u, 0u};
     }
 #pragma unroll
@@ -234,16 +234,16 @@ __global__ __launch_bounds__(kBurstThreads) void dlogits_burst_kernel(
     // every vector is made opaque here: no store can be issued before the last load has returned
 #pragma unroll
     for (int k = 0; k < NV; ++k) asm volatile("" : "+v"(q[k]));
-    if ((unsigned)(yvec - base - tid) < (unsigned)(NV * kBurstThreads)) {   // one lane, once per row
-      const int hit = (yvec - base - tid) / kBurstThreads;
+    if ((unsigned)(yvec - base - tid) < (unsigned)(NV * THREADS)) {   // one lane, once per row
+      const int hit = (yvec - base - tid) / THREADS;
 #pragma unroll
       for (int k = 0; k < NV; ++k)
         if (k == hit) q[k] = Vec<T>::put(q[k], yb & (N - 1), dzy);
     }
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-      const int i = base + tid + k * kBurstThreads;
-      if ((NSEG > 0 && base / kBurstThreads + k < KFULL) || i < nvec) store_stream(dv + i, q[k]);
+      const int i = base + tid + k * THREADS;
+      if ((NSEG > 0 && base / THREADS + k < KFULL) || i < nvec) store_stream(dv + i, q[k]);
     }
   }
   if (tid < rest)
@@ -257,11 +257,20 @@ void launch_dlogits_burst(ais_ctx* ctx, const T* z, long long n_rows, int vocab,
                           const float* logp, float inv_t, T* dz) {
   const int need = (vocab / Vec<T>::N + kBurstThreads - 1) / kBurstThreads;
   dim3 grid((unsigned)(((n_rows + 7) / 8) * 8)), block(kBurstThreads);
+  if (!ALIGNED && need <= 1) {
+    // A narrow row is no work for 1,024 threads, of which a compute unit holds two sets; of 256 it holds eight.  8,192
+    // rows, us with 1,024 threads, element by element and with 256: bf16, 1,001 logits 46.0, 15.0, 17.0; 3,001 47.4, 28.2,
+    // 21.2; 8,191 59.8, 67.7, 52.0; fp32, 1,001 34.9, 17.7, 15.7; 4,001 47.2, 43.9, 49.2.  1,000 rows: bf16, 3,001 10.5,
+    // 7.5, 7.1; fp32, 4,001 10.8, 12.0, 8.9.
+    dlogits_burst_kernel<T, false, 256, 4, 1, 0><<<grid, dim3(256), 0, ctx->stream>>>(
+        z, row_stride, vocab, token_ids, g, valid, lse, logp, inv_t, dz, n_rows);
+    return;
+  }
   // (vectors that surely exist, vectors per lane and burst, bursts): a row reaches a class only if it is wider than
   // the class before it, which is what the first figure states; an unaligned row may have lost up to 8 vectors to its
   // head, which the next lower figure covers
 #define AIS_BURST_CASE(KFULL, NVAL, NSEG)                                                                      \
-  dlogits_burst_kernel<T, ALIGNED, NVAL, NSEG, (ALIGNED || KFULL == 0 ? KFULL : KFULL - 1)>                    \
+  dlogits_burst_kernel<T, ALIGNED, kBurstThreads, NVAL, NSEG, (ALIGNED || KFULL == 0 ? KFULL : KFULL - 1)>     \
       <<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, token_ids, g, valid, lse, logp, inv_t, dz, n_rows)
   if (need <= 4) AIS_BURST_CASE(0, 4, 1);
   else if (need <= 8) AIS_BURST_CASE(4, 8, 1);
@@ -295,6 +304,11 @@ bool vec_ok(const void* base, long long row_stride, size_t esize) {
 bool same_lines(const void* a, const void* b) {
   return (reinterpret_cast<uintptr_t>(a) - reinterpret_cast<uintptr_t>(b)) % 128 == 0;
 }
+
+// Unaligned rows narrower than this go element by element: hardly more than a line's worth of vectors is left of them
+// (8,192 rows of 511 bf16 logits 10.5 us, 16.2 with vectors; of 2,001 22.4 and 19.0; fp32, 511 12.4 and 13.7, 1,001 17.7
+// and 15.7).
+constexpr size_t kElementwiseBytes = 2048;
 
 // 16-byte loads in flight per lane and loop iteration of the log-prob sweep (build-time tunable)
 #ifndef AIS_LOGPROB_UNROLL
@@ -336,7 +350,7 @@ int launch_dlogits(ais_ctx* ctx, const void* logits, ais_dtype dtype, long long 
     if (vec_ok(z, row_stride, sizeof(T)) && vec_ok(dz, row_stride, sizeof(T)))
       launch_dlogits_burst<T, true>(ctx, z, n_rows, vocab, row_stride, token_ids, g, valid, lse, logp, inv_temperature,
                                     dz);
-    else if (same_lines(z, dz))
+    else if (same_lines(z, dz) && vocab * sizeof(T) >= kElementwiseBytes)
       launch_dlogits_burst<T, false>(ctx, z, n_rows, vocab, row_stride, token_ids, g, valid, lse, logp, inv_temperature,
                                      dz);
     else

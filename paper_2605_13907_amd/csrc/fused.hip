@@ -14,7 +14,7 @@
 // flight at once and memory latency is paid once per row.  Rows wider than 24 vectors per lane keep their
 // last 9 vectors per lane in LDS (144 KiB of the compute unit's 160), which are filled by direct
 // global -> LDS copies and never pass through registers on the way in: up to 33 vectors per lane, 270,336
-// bf16 elements.  Rows wider than that fall back to the two-pass kernels.
+// bf16 elements.  Rows wider than that fall back to the two-pass kernels, and so do many narrow rows of odd width.
 #include "ais_internal.h"
 #include "device_utils.h"
 
@@ -314,16 +314,22 @@ int launch_typed(ais_ctx* ctx, int need, const void* logits, long long n_rows, i
 
 }  // namespace
 
-// Sets *used_registers to false (and launches nothing) when the row does not fit the register file or the two arrays
-// lie differently relative to 128-byte lines; the caller then runs the two-pass kernels.
+// Sets *used_registers to false (and launches nothing) when the row does not fit the register file, the two arrays
+// lie differently relative to 128-byte lines, or many narrow rows are not 16-byte aligned; the caller then runs the
+// two-pass kernels.  For those 1,024 threads a row are too many, as few of a compute unit's rows are then on their way at a
+// time (8,192 rows of 63 bf16 logits 89 us, in two passes 26; of 4,001 97 and 53; of 8,191 105 and 88; of 10,001 110 and
+// 103, but with 2,000 rows 37 both; fp32, 63 76 and 25, 4,001 86 and 82, 5,001 88 and 90).  A row per compute unit is
+// better off with one launch (300 rows of 4,001 fp32 logits 16.8 and 17.9 us).
 int launch_fused_logprob_softmax(ais_ctx* ctx, const void* logits, ais_dtype dtype, long long n_rows, int vocab,
                                  long long row_stride, const int* token_ids, const unsigned char* valid,
                                  float inv_temperature, float* logp_out, float* lse_out, void* sgrad,
                                  bool* used_registers) {
   const int need = dtype == AIS_BF16 ? vectors_per_lane<bf16_t>(logits, sgrad, vocab, row_stride)
                                      : vectors_per_lane<float>(logits, sgrad, vocab, row_stride);
-  *used_registers = need > 0;
-  if (need == 0 || n_rows == 0) return AIS_OK;
+  const bool narrow = need == 1 && n_rows > 2LL * ctx->n_cus &&
+                      !rows_aligned(logits, sgrad, row_stride, dtype == AIS_BF16 ? 2 : 4);
+  *used_registers = need > 0 && !narrow;
+  if (!*used_registers || n_rows == 0) return AIS_OK;
   ScopedTimer timer(ctx, AIS_K_FUSED);
   auto launch = [&](auto type) {
     typedef decltype(type) T;

@@ -62,6 +62,34 @@ def test_gradient(ctx, vocab, dtype):
     assert vectors <= SLACK * single, (vectors, single)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("vocab", [1, 63, 501, 1001, 3001])
+def test_one_sweep(ctx, vocab, dtype):
+    z, y = logits(vocab, dtype), torch.randint(0, vocab, (ROWS,), device="cuda", dtype=torch.int32)
+    beside = torch.empty(ROWS * vocab + 1, dtype=dtype, device="cuda")
+    same, other = beside[:-1].view(ROWS, vocab), beside[1:].view(ROWS, vocab)      # other: not the logits' lines
+
+    def time(out):
+        graph = torch.cuda.CUDAGraph()
+        ctx.token_logprob_softmax_grad(z, y, sgrad=out)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            for _ in range(10):
+                ctx.token_logprob_softmax_grad(z, y, sgrad=out)
+        times = []
+        for _ in range(6):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            graph.replay()
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end) * 100)
+        return min(times)
+
+    vectors, single = time(same), time(other)
+    assert vectors <= SLACK * single, (vectors, single)
+
+
 # where the routes change: element by element below 2 KiB, up to 1,024 vectors with 256 threads a row, 1,024 beyond
 @pytest.mark.parametrize("dtype,vocab", [("bf16", v) for v in (1023, 1025, 1087, 4099, 8191, 8199, 8201)] +
                          [("f32", v) for v in (511, 513, 543, 2051, 4095, 4099, 4101)])
@@ -76,3 +104,26 @@ def test_route_edges(ctx, dtype, vocab):
         if pitch > vocab:
             gap = room[offset:offset + batch.n_rows * pitch].view(batch.n_rows, pitch)[:, vocab:]
             assert bool((gap == 77.0).all()), "elements between the rows were written"
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,vocab", [(500, 1001), (600, 1), (600, 127), (600, 1001), (600, 4099), (600, 8199), (600, 8209)])
+def test_one_sweep_many_rows(ctx, rows, vocab, dtype):
+    """The direction on either side of the number of rows and of the width where the call changes kernels, rows not
+    evaluated among them, out of place and in place.  Tolerances: one rounding to the output type of a value that fp32
+    exponentials and an fp32 shift of up to about 20 give to a few 1e-6."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows + vocab)
+    z = (torch.randn(rows, vocab, generator=g, device="cuda") * 3.0).to(dtype)
+    y = torch.randint(0, vocab, (rows,), generator=g, device="cuda", dtype=torch.int32)
+    valid = (torch.rand(rows, generator=g, device="cuda") < 0.9).to(torch.uint8)
+    p = torch.log_softmax(z.double(), 1)
+    want_logp = p.gather(1, y.long().unsqueeze(1)).squeeze(1) * valid
+    want = p.exp().scatter_add_(1, y.long().unsqueeze(1), torch.full((rows, 1), -1.0, dtype=torch.float64, device="cuda"))
+    want *= valid.unsqueeze(1)
+    rounding = 2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -23
+    for out in (None, z):
+        logp, _, s = ctx.token_logprob_softmax_grad(z, y, valid, sgrad=out)
+        assert bool(((logp.double() - want_logp).abs() <= 1e-5 * want_logp.abs().clamp_min(1.0)).all())
+        assert bool(((s.double() - want).abs() <= (rounding + 1e-5) * want.abs() + 1e-30).all())
+        assert ctx.status() == 0

@@ -247,12 +247,14 @@ bool codes_aligned(const void* z, long long row_stride, int esize, const void* c
   return (reinterpret_cast<uintptr_t>(codes) - element) % n == 0 && (codes_stride - row_stride) % n == 0;
 }
 
-// Vectors per lane, or 0 when the row does not fit or has no whole vector to speak of.
+// Vectors per lane, or 0 when the row does not fit, or is unaligned and narrow: the streaming kernel has eight rows in a
+// compute unit at a time (8,192 unaligned fp32 rows of 1,001 elements: 18 us, 35 here; of 4,001 39 and 45; of 5,001 48 and
+// 49; of 6,001 59 and 54.  bf16 rows come here only where the table kernel does not take them: the same line as there).
 template <typename T>
 int vectors_per_lane(const void* z, int vocab, long long row_stride) {
   constexpr int N = Vec<T>::N;
   const int need = (vocab / N + kRowThreads - 1) / kRowThreads;
-  if (!row_aligned(z, row_stride, sizeof(T)) && vocab < 128) return 0;
+  if (!row_aligned(z, row_stride, sizeof(T)) && need <= (sizeof(T) == 2 ? 2 : 1)) return 0;
   return need <= 24 + kLdsSlots ? (need < 1 ? 1 : need) : 0;
 }
 

@@ -492,11 +492,14 @@ bool row_aligned(const void* z, long long row_stride) {
   return reinterpret_cast<uintptr_t>(z) % 16 == 0 && (row_stride * 2) % 16 == 0;
 }
 
-// Vectors per lane of a bf16 row, or 0 when the row does not qualify for these kernels (too wide, or without a whole
-// vector, of which an unaligned row may lose 8 to its head).
+// Vectors per lane of a bf16 row, or 0 when the row does not qualify for these kernels: too wide, without a whole vector,
+// or unaligned and narrow.  The extremes and the table take the same time for every row, and a compute unit works on two
+// rows at most; the streaming kernels of fp8.hip have eight of them on their way.  8,192 unaligned rows, us streaming and
+// here: quantisation, 1,001 logits 17 and 101, 16,001 99 and 113, 20,001 127 and 119; log-prob, 1,001 20 and 103, 16,001
+// 84 and 115, 24,001 120 and 122, 28,001 139 and 122; 300 rows of 16,001 13.4 and 14.0, of 20,001 14.8 and 14.3.
 int table_vectors_per_lane(const void* z, int vocab, long long row_stride, int most) {
   const int need = (vocab / 8 + kRowThreads - 1) / kRowThreads;
-  return vocab >= (row_aligned(z, row_stride) ? 8 : 128) && need <= most ? need : 0;
+  return (row_aligned(z, row_stride) ? vocab >= 8 : need > 2) && need <= most ? need : 0;
 }
 
 }  // namespace

@@ -90,6 +90,26 @@ def test_one_sweep(ctx, vocab, dtype):
     assert vectors <= SLACK * single, (vectors, single)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("vocab", [129, 501, 1001, 3001])
+def test_fp8_quantisation(ctx, vocab, dtype):
+    """Against rows of an even pitch, whose codes do not lie on vectors and are written one by one."""
+    z, other = logits(vocab, dtype), logits(vocab, dtype, pitch=vocab + 1)
+    vectors = kernel_us(ctx, B.AIS_K_FP8_QUANT, lambda: ctx.fp8_quantize_rows(z))
+    single = kernel_us(ctx, B.AIS_K_FP8_QUANT, lambda: ctx.fp8_quantize_rows(other))
+    assert vectors <= SLACK * single, (vectors, single)
+
+
+@pytest.mark.parametrize("vocab", [129, 501, 1001, 3001])
+def test_fp8_logprob(ctx, vocab):
+    """Against as many fp32 logits, which are read and converted twice."""
+    y = torch.randint(0, vocab, (ROWS,), device="cuda", dtype=torch.int32)
+    bf16, f32 = logits(vocab, torch.bfloat16), logits(vocab, torch.float32)
+    half = kernel_us(ctx, B.AIS_K_FP8_LOGPROB, lambda: ctx.fp8_rollout_logprob(bf16, y))
+    full = kernel_us(ctx, B.AIS_K_FP8_LOGPROB, lambda: ctx.fp8_rollout_logprob(f32, y))
+    assert half <= SLACK * full, (half, full)
+
+
 # where the routes change: element by element below 2 KiB, up to 1,024 vectors with 256 threads a row, 1,024 beyond
 @pytest.mark.parametrize("dtype,vocab", [("bf16", v) for v in (1023, 1025, 1087, 4099, 8191, 8199, 8201)] +
                          [("f32", v) for v in (511, 513, 543, 2051, 4095, 4099, 4101)])

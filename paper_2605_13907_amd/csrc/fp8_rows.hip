@@ -324,6 +324,9 @@ bool try_fp8_dequantize_burst(ais_ctx* ctx, const unsigned char* codes, long lon
   const int n = 16 / esize;                          // elements of an output vector = codes of a chunk
   if (!codes_aligned(out, out_stride, esize, codes, codes_stride)) return false;
   const bool aligned = row_aligned(out, out_stride, esize);
+  // narrow unaligned rows: element by element, eight rows in a compute unit at a time (8,192 rows decoded to bf16, 1,001
+  // elements 14 us, 29 here; 4,001 33 and 36; 6,001 44 and 42; to fp32 1,001 16 and 26; 5,001 41 and 47; 8,191 123 and 61)
+  if (!aligned && vocab < 5120) return false;
   const int need = (vocab / n + kRowThreads - 1) / kRowThreads;
   dim3 grid((unsigned)n_rows), block(kRowThreads);
   // (vectors that surely exist, vectors per lane and burst, bursts): a row reaches a class only if it is wider than

@@ -110,6 +110,29 @@ def test_fp8_logprob(ctx, vocab):
     assert half <= SLACK * full, (half, full)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("vocab", [63, 501, 1001])
+def test_fp8_decoding(ctx, vocab, dtype):
+    """Against codes of an even pitch, which do not lie on the output's vectors and are decoded one by one."""
+    codes = torch.randint(0, 120, (ROWS, vocab + 1), device="cuda", dtype=torch.uint8)
+    dense, other = codes[:, :vocab].contiguous(), codes[:, :vocab]
+    scale = torch.rand(ROWS, device="cuda")
+    vectors = kernel_us(ctx, B.AIS_K_FP8_DEQUANT, lambda: ctx.fp8_dequantize_rows(dense, scale, dtype))
+    single = kernel_us(ctx, B.AIS_K_FP8_DEQUANT, lambda: ctx.fp8_dequantize_rows(other, scale, dtype))
+    assert vectors <= SLACK * single, (vectors, single)
+    assert torch.equal(ctx.fp8_dequantize_rows(dense, scale, dtype), ctx.fp8_dequantize_rows(other, scale, dtype))
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("vocab", [5119, 5121])
+def test_fp8_decoding_at_the_limit(ctx, vocab, dtype):
+    codes = torch.arange(256, device="cuda", dtype=torch.int64).repeat(50 * vocab // 256 + 1)[:50 * vocab].view(50, vocab)
+    codes = torch.where(codes % 128 == 127, 0, codes).to(torch.uint8)          # no NaN codes
+    scale = torch.rand(50, device="cuda") + 0.01
+    want = (codes.view(torch.float8_e4m3fn).float() * scale.unsqueeze(1)).to(dtype)
+    assert torch.equal(ctx.fp8_dequantize_rows(codes, scale, dtype), want)
+
+
 # where the routes change: element by element below 2 KiB, up to 1,024 vectors with 256 threads a row, 1,024 beyond
 @pytest.mark.parametrize("dtype,vocab", [("bf16", v) for v in (1023, 1025, 1087, 4099, 8191, 8199, 8201)] +
                          [("f32", v) for v in (511, 513, 543, 2051, 4095, 4099, 4101)])

@@ -136,7 +136,7 @@ __device__ __forceinline__ void row_minmax_streamed(const RowParts<ALIGNED>& row
     hi = fmaxf(hi, lds[w]);
     lo = fminf(lo, lds[kRowWaves + w]);
   }
-  zmax = hi == hi ? hi : 0.f;                               // nothing but NaNs
+  zmax = hi == hi || !ALIGNED ? hi : 0.f;                   // nothing but NaNs (the largest is then one, see kLastEntry)
   zmin = lo == lo ? lo : 0.f;
 }
 
@@ -265,10 +265,11 @@ constexpr int waves_of(int workgroups) { return workgroups * kRowThreads / 256; 
 
 // Table index of a bf16 magnitude (15 bits): magnitudes below the table's first entry share it (their code is 0,
 // as is the first entry's), and nothing finite lies above the last entry, the row's abs-max; a NaN's payload does,
-// and is held inside the table.
-__device__ __forceinline__ int table_index(uint32_t mag, int base) {
-  return min(max((int)mag - base, 0), kTabEntries - 1);
-}
+// and is held at `last`: the last entry in aligned rows, and in the others an entry of its own behind it, which codes a
+// NaN as the streaming kernels do, -448.
+template <bool ALIGNED>
+constexpr int kLastEntry = ALIGNED ? kTabEntries - 1 : kTabEntries;
+__device__ __forceinline__ int table_index(uint32_t mag, int base, int last) { return min(max((int)mag - base, 0), last); }
 
 // ---- quantise ----------------------------------------------------------------------------------------------
 // Persistent grid, one workgroup per compute unit, rows dealt round-robin; the registers of a vector whose codes have
@@ -282,7 +283,8 @@ __global__ __launch_bounds__(kRowThreads, waves_of(quantize_workgroups(NV))) voi
                                                                          float* __restrict__ scale_out,
                                                                          long long n_rows) {
   __shared__ float lds[2 * kRowWaves];
-  __shared__ unsigned char table[kTabEntries];
+  constexpr int kLast = kLastEntry<ALIGNED>;
+  __shared__ unsigned char table[kLast + 1];
   const int tid = threadIdx.x;
   long long row = blockIdx.x;
   if (row >= n_rows) return;
@@ -297,7 +299,7 @@ __global__ __launch_bounds__(kRowThreads, waves_of(quantize_workgroups(NV))) voi
     const RowParts<ALIGNED> next(logits + (row + gridDim.x < n_rows ? row + gridDim.x : row) * row_stride, vocab);
     float zmax, zmin;
     row_minmax<ALIGNED, NV>(q, xt, lds, zmax, zmin, at);
-    const float amax = fmaxf(zmax, -zmin);
+    const float amax = fmaxf(fmaxf(zmax, -zmin), 0.f);       // (0: nothing but NaNs)
     const float s = scale_of(amax);
     if (tid == 0) scale_out[row] = s;
     // entry i belongs to the bf16 magnitude with bits base + i; the last entry is the abs-max itself
@@ -308,10 +310,11 @@ __global__ __launch_bounds__(kRowThreads, waves_of(quantize_workgroups(NV))) voi
         table[i] = (unsigned char)code_of(divide<decltype(slow)::value>(bf16_bits_to_float(max(base + i, 0)), by_s));
     };
     if (by_s.slow) fill(std::true_type{}); else fill(std::false_type{});
+    if (!ALIGNED && tid == 0) table[kLast] = 0xfe;                  // the code of -448
     __syncthreads();
     auto code2 = [&](uint32_t w) -> uint32_t {           // two logits -> two codes in the low 16 bits
-      const uint32_t c0 = table[table_index(w & 0x7fffu, base)];
-      const uint32_t c1 = table[table_index((w >> 16) & 0x7fffu, base)];
+      const uint32_t c0 = table[table_index(w & 0x7fffu, base, kLast)];
+      const uint32_t c1 = table[table_index((w >> 16) & 0x7fffu, base, kLast)];
       // the sign of the logit is the sign of the code, zero included
       return c0 | (c1 << 8) | ((w >> 8) & 0x80u) | ((w >> 16) & 0x8000u);
     };
@@ -367,22 +370,23 @@ __device__ __forceinline__ uint32_t pk_mad(u16x2 t, int factor, uint32_t add) { 
   return r;
 }
 
-template <bool INTERLEAVED>
+template <bool INTERLEAVED, int LAST>
 struct LogprobTable {
-  static constexpr int kFloats = INTERLEAVED ? 2 * kTabEntries : 2 * kTabStride;
+  static_assert(LAST < kTabStride, "");
+  static constexpr int kFloats = INTERLEAVED ? 2 * (LAST + 1) : 2 * kTabStride;
   // positions (in floats) of magnitude i's positive and negative entry
   static __device__ __forceinline__ int pos(int i) { return INTERLEAVED ? 2 * i : i; }
   static __device__ __forceinline__ int neg(int i) { return INTERLEAVED ? 2 * i + 1 : kTabStride + i; }
   // Byte offsets into the table of the two logits of a word, formed on both 16-bit halves at once: magnitude
   // minus base, saturating at 0 (smaller magnitudes share the first entry: their code is 0, as is its) and held
-  // below the table's end (only a NaN's payload lies above the abs-max), times the entry pitch plus the sign's part in
+  // at the last entry (only a NaN's payload lies above the abs-max; see kLastEntry), times the entry pitch plus the sign's part in
   // one multiply-add.
   static __device__ __forceinline__ uint32_t offsets(uint32_t w, uint32_t base2) {
     u16x2 t = __builtin_bit_cast(u16x2, w & 0x7fff7fffu);
     t = __builtin_elementwise_sub_sat(t, __builtin_bit_cast(u16x2, base2));
-    t = __builtin_elementwise_min(t, u16x2{kTabEntries - 1, kTabEntries - 1});
+    t = __builtin_elementwise_min(t, u16x2{LAST, LAST});
     if (INTERLEAVED) {
-      static_assert((kTabEntries - 1) * 8 + 4 < 0x10000, "an offset must fit a 16-bit half");
+      static_assert(LAST * 8 + 4 < 0x10000, "an offset must fit a 16-bit half");
       return pk_mad(t, 8, (w >> 13) & 0x00040004u);                           // sign bit -> byte 4 of the entry
     }
     static_assert(kTabStride * 4 == 0x4000, "the sign bit of a half is moved to this bit of its offset");
@@ -395,7 +399,8 @@ __global__ __launch_bounds__(kRowThreads, waves_of(logprob_workgroups(NV))) void
     const bf16_t* __restrict__ logits, long long row_stride, int vocab, const int* __restrict__ token_ids,
     const unsigned char* __restrict__ valid, float* __restrict__ logp_out, int* __restrict__ status,
     long long n_rows) {
-  typedef LogprobTable<(NL > 0)> Tab;
+  constexpr int kLast = kLastEntry<ALIGNED>;
+  typedef LogprobTable<(NL > 0), kLast> Tab;
   __shared__ float lds_mm[2 * kRowWaves];
   __shared__ float lds_sum[kRowWaves];
   __shared__ float table[Tab::kFloats];                    // kTabEntries magnitudes x 2 signs in use
@@ -438,7 +443,7 @@ __global__ __launch_bounds__(kRowThreads, waves_of(logprob_workgroups(NV))) void
 
     float zmax, zmin;
     row_minmax<ALIGNED, NV, NL>(q, xt, lds_mm, zmax, zmin, at, lrow);
-    const float amax = fmaxf(zmax, -zmin);
+    const float amax = fmaxf(fmaxf(zmax, -zmin), 0.f);     // (0: nothing but NaNs)
     const float s = scale_of(amax);
     const float scale = s * kLog2e;                        // z_r * log2e = value(code) * scale
     // quantisation is monotone: the largest round-tripped logit is that of the largest logit
@@ -454,6 +459,8 @@ __global__ __launch_bounds__(kRowThreads, waves_of(logprob_workgroups(NV))) void
       }
     };
     if (by_s.slow) fill(std::true_type{}); else fill(std::false_type{});
+    if (!ALIGNED && tid == 0)
+      table[Tab::pos(kLast)] = table[Tab::neg(kLast)] = exp2_fast(__builtin_fmaf(-kE4M3Max, scale, -top));
     __syncthreads();
     const uint32_t base2 = (uint32_t)base * 0x00010001u;
     auto entry = [&](uint32_t byte_offset) -> float {

@@ -1,6 +1,7 @@
 """The FP8 table kernels find a row's extremes from the bits of its numbers, by the sign: rows with one sign only, with
 zeros of either sign, and with a single number of the other sign at the places that different lanes, slots and the
-elements outside the vectors hold.  Codes, scales and log-probs; and rows without a positive number take no longer."""
+elements outside the vectors hold.  Codes, scales and log-probs; rows without a positive number take no longer; and NaNs
+in rows of odd width."""
 import pytest
 import torch
 
@@ -70,3 +71,31 @@ def test_rows_below_zero_take_no_longer(ctx, vocab):
         print(vocab, which, round(a, 1), round(b, 1), flush=True)
         # reading the rows again would be half as much again; the second look at the registers is a few per cent
         assert b <= 1.2 * a, (which, a, b)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("vocab", [1001, 16_393, 50_257, 100_003, 151_937, 210_007, 250_007])
+def test_nan_in_unaligned_rows(ctx, vocab, dtype):
+    """A NaN counts as -448 times the scale, which it does not enter, in every kernel that takes rows of odd width."""
+    rows = 300
+    g = torch.Generator(device="cuda")
+    g.manual_seed(vocab)
+    z = torch.randn(rows, vocab, generator=g, device="cuda") * 3.0
+    z[0::4] = -z[0::4].abs() - 0.5
+    nan = torch.zeros(rows, vocab, dtype=torch.bool, device="cuda")
+    for r in range(0, rows, 3):
+        nan[r, [(r * 997) % vocab, 0 if r % 2 else vocab - 1, vocab // 2]] = True
+    nan[5::50] = True                                  # nothing else in the row
+    z[::6] = torch.where(nan[::6], -float("nan"), z[::6])
+    z = torch.where(nan, torch.where(torch.isnan(z), z, float("nan")), z).to(dtype)
+    y = torch.randint(0, vocab, (rows,), generator=g, device="cuda", dtype=torch.int32)
+    y[::9] = (torch.arange(rows, device="cuda")[::9] * 997 % vocab).to(torch.int32)         # some of the NaNs are sampled
+    clean = torch.where(nan, 0.0, z.float())
+    code, scale, zr = fp8_reference(clean)
+    code = torch.where(nan, 0xfe, code)
+    zr = torch.where(nan, -448.0 * scale.double(), zr)
+    codes, s = ctx.fp8_quantize_rows(z)
+    assert torch.equal(s, scale.squeeze(1)) and torch.equal(codes, code)
+    logp = ctx.fp8_rollout_logprob(z, y)
+    ref = zr.gather(1, y.long().unsqueeze(1)).squeeze(1) - torch.logsumexp(zr, dim=1)
+    assert bool(((logp.double() - ref).abs() <= 1e-4 * ref.abs().clamp_min(1.0)).all())

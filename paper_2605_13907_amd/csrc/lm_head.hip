@@ -715,17 +715,19 @@ size_t lm_head_logprob_bytes(long long n_rows, int vocab, int n_cus) {
 }
 
 // Vocabulary entries per chunk of the gradient call; asked == 0: the library's choice.  8,192 entries are 32 tiles, which
-// with 16 token blocks (4,096 rows) are two work items per compute unit; with fewer rows the chunk is wider by as much
-// (700 rows x 50,257 x 2,048: 1.13 ms in chunks of 8,192, 0.90 in one of 43,776; 2,000 rows 1.52 and 1.46 ms).
+// with 16 token blocks (4,096 rows) are two work items per compute unit.  Up to 12 token blocks take chunks of as many
+// tiles as make two for every compute unit in one round of the recomputation.  Time against chunks of 8,192, over d_model
+// 1,024 to 8,192 and vocabularies of 50,257 and 128,256: 1 block 0.45-0.51, 2 0.56-0.72, 3 0.66-0.87, 4 0.72-0.94, 5
+// 0.74-1.04, 6 0.83-1.09, 7 0.90-1.15, 8 0.84-0.98, 9 0.78-1.03, 10 0.87-1.02, 11 0.82-1.10, 12 0.87-1.07; 13 0.90-1.15, 14
+// 0.91-1.18, 15 0.98-1.15.  (Rounded up to a tile more, which takes a second round or items of three tiles, 6 blocks
+// 0.86-1.16, 7 0.97-1.23, 9 0.81-1.12, 14 1.00-1.22.)
 constexpr long long kLmGradChunk = 8192;
-constexpr long long kLmGradFewRows = 4096;
+constexpr long long kLmGradFewBlocks = 12;
 long long lm_grad_chunk(long long m_rows, long long vocab, long long asked, int n_cus) {
   const long long whole = (vocab + kLmTileV - 1) / kLmTileV * kLmTileV;
+  const long long blocks = std::max<long long>(1, (m_rows + kLmTileT - 1) / kLmTileT);
   long long chunk = asked != 0 ? asked : kLmGradChunk;
-  if (asked == 0 && m_rows < kLmGradFewRows) {
-    const long long blocks = std::max<long long>(1, (m_rows + kLmTileT - 1) / kLmTileT);
-    chunk = std::max(chunk, kLmTileV * ((2 * n_cus + blocks - 1) / blocks));
-  }
+  if (asked == 0 && blocks <= kLmGradFewBlocks) chunk = std::max(chunk, kLmTileV * (2 * (n_cus / blocks)));
   return std::min(chunk, whole);
 }
 
@@ -735,9 +737,8 @@ size_t lm_grad_dlogits_bytes(long long m_rows, long long vocab, long long asked,
   const size_t own = 2 * (size_t)m_rows * (size_t)lm_grad_chunk(m_rows, vocab, asked, n_cus);
   if (asked != 0) return own;
   const long long whole = (vocab + kLmTileV - 1) / kLmTileV * kLmTileV;
-  const long long items = std::max<long long>(2 * n_cus, kLmGradFewRows / kLmTileT * (kLmGradChunk / kLmTileV));
-  const long long few = kLmTileT * kLmTileV * (items + kLmGradFewRows / kLmTileT);
-  return std::max(own, 2 * (size_t)std::min(few, kLmGradFewRows * whole));
+  const long long tiles = std::max<long long>(2 * n_cus, kLmGradFewBlocks * (kLmGradChunk / kLmTileV));
+  return std::max(own, 2 * (size_t)std::min(kLmTileT * kLmTileV * tiles, kLmGradFewBlocks * kLmTileT * whole));
 }
 
 template <bool GRAD>

@@ -47,4 +47,13 @@ def test_dlogits_hold_whole_chunks(vocab):
             assert dlogits(n, vocab, asked, 256) >= 2 * n * width
             if asked:
                 assert dlogits(n, vocab, asked, 256) == 2 * n * width
-    assert chunk(4096, 151_936, 0, 256) == 8192 and chunk(700, 151_936, 0, 256) == 171 * 256
+    assert chunk(4096, 151_936, 0, 256) == 8192 and chunk(700, 151_936, 0, 256) == 170 * 256
+
+
+@pytest.mark.parametrize("n_cus", [256, 64])
+def test_wide_chunks_fill_one_round(n_cus):
+    """Where few rows take wide chunks, the recomputation has at most a work item of two tiles per compute unit."""
+    _, _, chunk = sizes()
+    for rows in range(1, 5000, 61):
+        tiles, blocks = chunk(rows, 1 << 20, 0, n_cus) // 256, (rows + 255) // 256
+        assert tiles == 32 or (blocks <= 12 and blocks * ((tiles + 1) // 2) <= n_cus), (rows, tiles)

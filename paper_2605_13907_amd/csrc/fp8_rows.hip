@@ -1,15 +1,16 @@
 // The FP8-E4M3 kernels that give one workgroup of 1,024 threads a whole row: the register-resident quantisation
 // and the burst form of the dequantisation (further down).
 //
-// Register-resident FP8-E4M3 quantisation: the row is read from HBM once and held in the register file of
-// one compute unit (1,024 threads x NV 16-byte vectors per lane) between the abs-max reduction that fixes
-// the scale and the pass that encodes with it.  Rows of 25 to 33 vectors per lane keep their last 9 vectors
-// per lane in LDS, filled by direct global -> LDS copies.  Same results as the streaming two-pass kernel in
-// fp8.hip, which remains the route for rows that do not fit.  Rows that are not 16-byte aligned are split at their first
-// 128-byte boundary (see head_elements).  (The fused rollout log-prob
-// stays a streaming kernel: its second pass costs 18 vector instructions per element, about 18 us per row on one
-// compute unit, and a workgroup that owns the whole unit cannot overlap that arithmetic with another row's loads:
-// the register-resident form took 4.6 ms on 41,643 rows of 151,936 where two streaming passes take 3.6 ms.)
+// Register-resident FP8-E4M3 quantisation, for fp32 rows and for bf16 rows too wide for the table kernel of
+// fp8_table.hip: the row is read from HBM once and held in the register file of one compute unit (1,024 threads x NV
+// 16-byte vectors per lane) between the abs-max reduction that fixes the scale and the pass that encodes with it.  Rows of
+// 25 to 33 vectors per lane keep their last 9 vectors per lane in LDS, filled by direct global -> LDS copies.  Same results
+// as the streaming two-pass kernel in fp8.hip, which remains the route for rows that do not fit and for narrow unaligned
+// ones.  Rows that are not 16-byte aligned are split at their first 128-byte boundary (see head_elements).  (The log-prob
+// of fp32 rows, and of bf16 rows wider than fp8_table.hip holds, is a streaming kernel: its second pass costs 18 vector
+// instructions per element, about 18 us per row of 151,936 on one compute unit, and a workgroup that owns the whole unit
+// cannot overlap that arithmetic with another row's loads: the register-resident form took 4.6 ms on 41,643 bf16 rows of
+// 151,936 where two streaming passes take 3.6 ms.)
 #include "ais_internal.h"
 #include "device_utils.h"
 #include "fp8_utils.h"
@@ -247,14 +248,16 @@ bool codes_aligned(const void* z, long long row_stride, int esize, const void* c
   return (reinterpret_cast<uintptr_t>(codes) - element) % n == 0 && (codes_stride - row_stride) % n == 0;
 }
 
-// Vectors per lane, or 0 when the row does not fit, or is unaligned and narrow: the streaming kernel has eight rows in a
-// compute unit at a time (8,192 unaligned fp32 rows of 1,001 elements: 18 us, 35 here; of 4,001 39 and 45; of 5,001 48 and
-// 49; of 6,001 59 and 54.  bf16 rows come here only where the table kernel does not take them: the same line as there).
+// Vectors per lane of a row that the register-resident kernel takes, otherwise 0: it does not fit, or it is a narrow one
+// that the streaming kernel does better with.  That kernel has eight rows in a compute unit at a time (8,192 unaligned fp32
+// rows of 1,001 elements: 18 us, 35 here; of 4,001 39 and 45; of 5,001 48 and 49; of 6,001 59 and 54).  bf16 rows come here
+// only where they are too wide for the table kernel, which takes all others but the narrow ones (and those without a
+// whole vector).
 template <typename T>
 int vectors_per_lane(const void* z, int vocab, long long row_stride) {
   constexpr int N = Vec<T>::N;
   const int need = (vocab / N + kRowThreads - 1) / kRowThreads;
-  if (!row_aligned(z, row_stride, sizeof(T)) && need <= (sizeof(T) == 2 ? 2 : 1)) return 0;
+  if (sizeof(T) == 2 ? need <= 24 : !row_aligned(z, row_stride, sizeof(T)) && need <= 1) return 0;
   return need <= 24 + kLdsSlots ? (need < 1 ? 1 : need) : 0;
 }
 
@@ -285,12 +288,14 @@ bool dispatch_rows(ais_ctx* ctx, int need, const T* z, long long n_rows, int voc
                       : launch_rows<T, false, NVAL, NLVAL, (PREV > 0 ? PREV - 1 : 0)>;                   \
     return launch(ctx, z, n_rows, vocab, row_stride, codes, codes_stride, scale_out);                    \
   }
-  AIS_ROW_CASE(0, 4, 4, 0)
-  AIS_ROW_CASE(4, 8, 8, 0)
-  AIS_ROW_CASE(8, 12, 12, 0)
-  AIS_ROW_CASE(12, 16, 16, 0)
-  AIS_ROW_CASE(16, 20, 20, 0)
-  AIS_ROW_CASE(20, 24, 24, 0)
+  if constexpr (sizeof(T) == 4) {          // narrower bf16 rows do not come here
+    AIS_ROW_CASE(0, 4, 4, 0)
+    AIS_ROW_CASE(4, 8, 8, 0)
+    AIS_ROW_CASE(8, 12, 12, 0)
+    AIS_ROW_CASE(12, 16, 16, 0)
+    AIS_ROW_CASE(16, 20, 20, 0)
+    AIS_ROW_CASE(20, 24, 24, 0)
+  }
   AIS_ROW_CASE(24, 27, 18, kLdsSlots)
   AIS_ROW_CASE(27, 31, 22, kLdsSlots)
   AIS_ROW_CASE(31, 33, 24, kLdsSlots)

@@ -7,7 +7,7 @@ import torch
 from paper_2605_13907_amd import binding as B
 from tests import parity as P
 from tests.test_gpu_one_sweep import check_one_sweep
-from tests.test_gpu_unaligned_rows import batch_at
+from tests.test_gpu_unaligned_rows import batch_at, fp8_reference
 
 pytestmark = pytest.mark.gpu
 
@@ -131,6 +131,18 @@ def test_fp8_decoding_at_the_limit(ctx, vocab, dtype):
     scale = torch.rand(50, device="cuda") + 0.01
     want = (codes.view(torch.float8_e4m3fn).float() * scale.unsqueeze(1)).to(dtype)
     assert torch.equal(ctx.fp8_dequantize_rows(codes, scale, dtype), want)
+
+
+@pytest.mark.parametrize("vocab", [1, 5, 7, 8, 9])
+def test_fp8_rows_without_a_vector(ctx, vocab):
+    """16-byte aligned rows about as long as one vector."""
+    z = torch.randn(300, 8 if vocab <= 8 else 16, device="cuda").mul_(3.0).to(torch.bfloat16)[:, :vocab]
+    y = torch.randint(0, vocab, (300,), device="cuda", dtype=torch.int32)
+    code, scale, zr = fp8_reference(z.float())
+    codes, s = ctx.fp8_quantize_rows(z)
+    assert torch.equal(s, scale.squeeze(1)) and torch.equal(codes, code)
+    ref = zr.gather(1, y.long().unsqueeze(1)).squeeze(1) - torch.logsumexp(zr, dim=1)
+    assert float((ctx.fp8_rollout_logprob(z, y).double() - ref).abs().max()) <= 1e-5 * max(1.0, float(ref.abs().max()))
 
 
 # where the routes change: element by element below 2 KiB, up to 1,024 vectors with 256 threads a row, 1,024 beyond

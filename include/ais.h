@@ -147,8 +147,8 @@ int ais_version(void);
  *   token_ids   [n_rows] sampled token per row; ignored (never read) where valid == 0
  *   logp_out    [n_rows] fp32  inv_temperature * z[n, y_n] - lse_n;  0 where valid == 0
  *   lse_out     [n_rows] fp32  log sum_v exp(inv_temperature * z[n, v]);  0 where valid == 0
- * Any vocab >= 1 and any row_stride >= vocab are accepted; 16-byte vector loads are used when
- * the base pointer and the row pitch allow it, an element-wise path otherwise.
+ * Any vocab >= 1 and any row_stride >= vocab are accepted; rows that are not 16-byte aligned are read
+ * in 16-byte vectors from their first 128-byte boundary on.
  * Errors: NULL logits/token_ids/logp_out/lse_out (with n_rows > 0), n_rows < 0, vocab < 1,
  * vocab >= 2^31, row_stride < vocab, inv_temperature <= 0 or not finite, unknown dtype,
  * logits not aligned to its element size. */
@@ -237,8 +237,9 @@ int ais_grpo_loss_grad(ais_ctx* ctx, const void* logits, ais_dtype dtype, long l
  * ais_token_logprob_softmax_grad: as ais_token_logprob, and additionally
  *   sgrad_out  [n_rows, row_stride] of `dtype`: s on evaluated rows, 0 on the others; may be the same
  *              buffer as `logits` (in place).  Rows are held in the register file and LDS of one compute
- *              unit (up to 270,336 bf16 or 135,168 fp32 elements, 16-byte aligned); wider or unaligned
- *              rows are processed in two passes with the same results.
+ *              unit (up to 270,336 bf16 or 135,168 fp32 elements); wider rows, many narrow ones that are not
+ *              16-byte aligned, and rows that lie differently in the two buffers relative to 128-byte lines
+ *              are processed in two passes.
  * ais_grpo_row_scale: as ais_grpo_loss_grad without the logits; writes
  *   g_out      [n_rows] fp32: the derivative of the loss w.r.t. the row's log-probability times
  *              inv_temperature (0 on rows not evaluated or clipped away), so that g_out[n] * s[n, :] equals

@@ -19,7 +19,7 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
-# the two plain GEMMs of the hidden-state gradient call are the library's
+# the hidden-state gradient call's products at sizes that its own kernels leave are the library's
 LINK_FLAGS = ["-lrocblas"]
 
 

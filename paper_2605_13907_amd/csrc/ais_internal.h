@@ -14,7 +14,11 @@ namespace ais {
 constexpr int kSweepThreads = 256;     // one workgroup (4 wavefronts) streams one logits row
 constexpr int kTileThreads = 256;      // workgroup of the per-row scalar kernels
 constexpr int kTileRows = 1024;        // rows of one response handled by one such workgroup
-constexpr int kSelfPlanResponses = 1024;   // most responses whose tiling the scalar kernels work out for themselves
+// Most responses whose tiling the scalar kernels work out for themselves, in 12 KiB of LDS.  Both calls of a step, us,
+// against the plan kernel: 40,000 rows in 64 responses 20.0 and 22.0, 1,200,000 in 512 50.7 and 52.7, in 1,024 57.4 and
+// 60.0.  With room for 4,096 (48 KiB) 1,200,000 rows in 2,048 take 90.8 instead of 64.6, and in 512 64.8: every workgroup
+// scans four times as many, and fewer fit a compute unit.
+constexpr int kSelfPlanResponses = 1024;
 // Words of the status allocation that count the finished workgroups of a reduction: a pair for the calls that work in the
 // context's workspace, a pair for the static call, which may run beside them.
 constexpr int kTicketWord = 32, kStaticTicketWord = 48;

@@ -8,7 +8,8 @@
 // gfx950's conversion instructions implement the OCP E4M3 format (round to nearest even); inputs are
 // clamped to +-448 first, so the conversion never sees an overflow.  The arithmetic that decides a code is
 // fp32: s = max|z| / 448 and q = z / s, both correctly rounded divisions (q through the per-row divider of
-// fp8_utils.h).  Rows that fit the register file take the single-read kernels of fp8_rows.hip.
+// fp8_utils.h).  Rows that fit the register file take the single-read kernels of fp8_table.hip and
+// fp8_rows.hip, unless they are narrow and of odd width.
 #include "ais_internal.h"
 #include "device_utils.h"
 #include "fp8_utils.h"
@@ -20,8 +21,8 @@ namespace {
 
 using namespace dev;
 
-// Row abs-max -> scale, shared by the workgroup through LDS.  The row's vectors start `head` elements into it (0 when it
-// is 16-byte aligned); fewer elements than there are threads lie outside them.
+// Row abs-max -> scale, shared by the workgroup through LDS.  The row's vectors start `head` elements into it, at its
+// first 128-byte boundary; fewer elements than there are threads lie outside them.
 template <typename T>
 __device__ __forceinline__ float row_scale(const T* zr, int vocab, int head, float* lds) {
   constexpr int N = Vec<T>::N;

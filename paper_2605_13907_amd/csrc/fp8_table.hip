@@ -272,7 +272,7 @@ constexpr int kLastEntry = ALIGNED ? kTabEntries - 1 : kTabEntries;
 __device__ __forceinline__ int table_index(uint32_t mag, int base, int last) { return min(max((int)mag - base, 0), last); }
 
 // ---- quantise ----------------------------------------------------------------------------------------------
-// Persistent grid, one workgroup per compute unit, rows dealt round-robin; the registers of a vector whose codes have
+// Persistent grid (quantize_workgroups() per compute unit), rows dealt round-robin; the registers of a vector whose codes have
 // been written are reloaded at once with the same vector of the workgroup's next row (see the log-prob kernel below
 // for why).
 template <bool ALIGNED, int NV, int KFULL>
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(kRowThreads, waves_of(quantize_workgroups(NV))) voi
 //
 // A row (297 KiB at 151,936 logits) fills most of a compute unit's register file, so only one can be resident, and a
 // workgroup that loaded, reduced and summed one row after the other would leave the memory system idle while it
-// computes.  The grid is therefore persistent (one workgroup per compute unit, rows dealt round-robin), and the
+// computes.  The grid is therefore persistent (logprob_workgroups() per compute unit, rows dealt round-robin), and the
 // registers of the vector that the sum has just consumed are reloaded at once with the same vector of the
 // workgroup's next row: by the time the sum is finished the next row is on its way or has landed.
 // Bound by the vector ALU (and the LDS reads beside it), so instructions count: 10,411 rows of 151,936 took 597 us with
@@ -488,7 +488,7 @@ __global__ __launch_bounds__(kRowThreads, waves_of(logprob_workgroups(NV))) void
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
       const float part = vector_sum(q[k]);
-      // slots past the end of the row hold zeros, which would count as logits of 0; the slot's index comes from a
+      // slots past the end of the row hold copies of its last vector, which must not count again; the slot's index comes from a
       // fresh opaque copy of the thread index, so that no per-slot offset is kept alive across the row loop
       int tk = tid;
       asm volatile("" : "+v"(tk));
@@ -574,7 +574,8 @@ bool try_fp8_quantize_table(ais_ctx* ctx, const void* logits, ais_dtype dtype, l
   const long long resident = (long long)ctx->n_cus * quantize_workgroups(need <= 4 ? 4 : 24);
   dim3 grid((unsigned)(n_rows < resident ? n_rows : resident)), block(kRowThreads);     // persistent
   const bool aligned = row_aligned(logits, row_stride);
-  // (classes of four for the middle widths: with one for every width 8,192 rows of 126,464 logits take 630 us, not 612)
+  // (classes of four for the middle widths; with one for every width 11,428 rows of 70,000 logits take 495 us instead of
+  // 508, 7,971 of 100,352 470 and 480, 7,407 of 108,000 495 and 498, 6,325 of 126,464 493 both, 6,103 of 131,072 461 and 457)
 #define AIS_CASE(PREV, NVAL)                                                                                    \
   if (need <= NVAL) {                                                                                           \
     auto kernel = aligned ? fp8_quantize_table_kernel<true, NVAL, PREV>                                         \

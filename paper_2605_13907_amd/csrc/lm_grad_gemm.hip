@@ -252,7 +252,10 @@ int launch_gemm(ais_ctx* ctx, GemmArgs g) {
 // library's product, which has smaller tiles and can split the sum.  With full rounds dweight takes 0.78-0.82 of the
 // library's time and dhidden 0.93-0.96, so that is about how full the rounds have to be: dhidden of 14,000 rows x 1,024
 // (86 % full) takes 216 against 194 us, of 6,000 rows x 2,048 (75 %) 175 against 165, of 2,600 rows x 5,120 (86 %) the
-// same; dweight of 8,192 entries x 5,120 (83 %) 210 against 262, of 8,192 x 1,024 (50 %) 314 against 233.
+// same; dweight of 8,192 entries x 5,120 (83 %) 210 against 262, of 8,192 x 1,024 (50 %) 314 against 233.  Between those
+// the line of dweight matters little: the whole call over 4,096 rows x 4,096 takes 276 us with its own product at 69 % full
+// and 283 with the library's, at 75 % 287 and 291, at 81 % 301 and 326 (dhidden with it), over 8,192 rows at 62 % 507 and
+// 503.
 static bool rounds_full(const ais_ctx* ctx, long long m, long long n, int percent) {
   const long long tiles = ((m + kTile - 1) / kTile) * ((n + kTile - 1) / kTile);
   const long long rounds = (tiles + ctx->n_cus - 1) / ctx->n_cus;

@@ -97,21 +97,21 @@ def cpu_baseline(batch, params, sample_rows: int):
 
 def burst_class(vocab: int, esize: int) -> str:
     """Name of the gradient-sweep instantiation that the library's launcher picks for 16-byte aligned rows of this
-    width (reporting only; mirrors the table in csrc/sweeps.hip: vectors per lane and burst, bursts, vectors that
+    width (reporting only; mirrors the table in csrc/sweeps.hip: aligned, threads, vectors per lane and burst, bursts, vectors that
     surely exist)."""
     per_vec = 16 // esize
     need = (vocab // per_vec + 1023) // 1024
     t = "bf16" if esize == 2 else "float"
     if need <= 12:
         nv = 4 * ((max(need, 1) + 3) // 4)
-        return f"dlogits_burst_kernel<{t}, {nv}, 1, {nv - 4}>"
+        return f"dlogits_burst_kernel<{t}, true, 1024, {nv}, 1, {nv - 4}>"
     if need <= 20:
-        return f"dlogits_burst_kernel<{t}, {need}, 1, {need - 1}>"
+        return f"dlogits_burst_kernel<{t}, true, 1024, {need}, 1, {need - 1}>"
     if need <= 32:
-        return f"dlogits_burst_kernel<{t}, 16, 2, 20>"
+        return f"dlogits_burst_kernel<{t}, true, 1024, 16, 2, 20>"
     if need <= 48:
-        return f"dlogits_burst_kernel<{t}, 16, 3, 32>"
-    return f"dlogits_burst_kernel<{t}, 16, 0, 0>"
+        return f"dlogits_burst_kernel<{t}, true, 1024, 16, 3, 32>"
+    return f"dlogits_burst_kernel<{t}, true, 1024, 16, 0, 0>"
 
 
 def time_workload(torch, binding, workloads, ctx, k, steps, warmup, mode="ais", stale_old=False, in_place=False):

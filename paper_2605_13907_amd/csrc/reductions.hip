@@ -1,7 +1,7 @@
 // Per-row scalar work and the batch-wide reductions of the path.
 //
 // The batch is a set of variable-length segments (responses) of rows, some rows masked out.  Every response is cut
-// into tiles of kTileRows rows (each workgroup works the tiling out for itself, from up to kSelfPlanResponses responses;
+// into tiles of kTileRows rows (each workgroup works the tiling out for itself, for up to kSelfPlanResponses responses;
 // beyond that a small plan kernel does it once); level 1 reduces one tile per workgroup
 // (lane shuffles, then one exchange through LDS) to a partial; level 2, run by whichever workgroup of the
 // same launch finishes last, folds the partials of each response in order, forms the group-relative

@@ -67,9 +67,14 @@ def test_rows_below_zero_take_no_longer(ctx, vocab):
         return min(times)
 
     for which, call in ((B.AIS_K_FP8_QUANT, ctx.fp8_quantize_rows), (B.AIS_K_FP8_LOGPROB, lambda z: ctx.fp8_rollout_logprob(z, y))):
-        a, b = us(which, lambda: call(mixed)), us(which, lambda: call(below))
-        print(vocab, which, round(a, 1), round(b, 1), flush=True)
-        # reading the rows again would be half as much again; the second look at the registers is a few per cent
+        # reading the rows again would be half as much again; the second look at the registers is a few per cent (the best of
+        # up to three attempts: another process may hold the clocks back)
+        a = b = float("inf")
+        for _ in range(3):
+            a, b = min(a, us(which, lambda: call(mixed))), min(b, us(which, lambda: call(below)))
+            print(vocab, which, round(a, 1), round(b, 1), flush=True)
+            if b <= 1.2 * a:
+                break
         assert b <= 1.2 * a, (which, a, b)
 
 

@@ -15,6 +15,16 @@ ROWS = 8192
 SLACK = 1.35            # routes that are equally good differ by less
 
 
+def assert_no_slower(this, other):
+    """this() <= SLACK other(), the best of each over up to three attempts: another process may hold the clocks back."""
+    a = b = float("inf")
+    for _ in range(3):
+        a, b = min(a, this()), min(b, other())
+        if a <= SLACK * b:
+            return
+    raise AssertionError((a, b))
+
+
 @pytest.fixture(scope="module")
 def ctx():
     c = B.AisContext()
@@ -58,8 +68,7 @@ def test_gradient(ctx, vocab, dtype):
         return kernel_us(ctx, B.AIS_K_DLOGITS, lambda: ctx.grpo_loss_grad(z, y, None, cu, logp, lse, logp, adv, count, diag,
                                                                           dlogits=out))
 
-    vectors, single = time(same), time(other)
-    assert vectors <= SLACK * single, (vectors, single)
+    assert_no_slower(lambda: time(same), lambda: time(other))
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
@@ -86,8 +95,7 @@ def test_one_sweep(ctx, vocab, dtype):
             times.append(start.elapsed_time(end) * 100)
         return min(times)
 
-    vectors, single = time(same), time(other)
-    assert vectors <= SLACK * single, (vectors, single)
+    assert_no_slower(lambda: time(same), lambda: time(other))
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
@@ -95,9 +103,8 @@ def test_one_sweep(ctx, vocab, dtype):
 def test_fp8_quantisation(ctx, vocab, dtype):
     """Against rows of an even pitch, whose codes do not lie on vectors and are written one by one."""
     z, other = logits(vocab, dtype), logits(vocab, dtype, pitch=vocab + 1)
-    vectors = kernel_us(ctx, B.AIS_K_FP8_QUANT, lambda: ctx.fp8_quantize_rows(z))
-    single = kernel_us(ctx, B.AIS_K_FP8_QUANT, lambda: ctx.fp8_quantize_rows(other))
-    assert vectors <= SLACK * single, (vectors, single)
+    assert_no_slower(lambda: kernel_us(ctx, B.AIS_K_FP8_QUANT, lambda: ctx.fp8_quantize_rows(z)),
+                     lambda: kernel_us(ctx, B.AIS_K_FP8_QUANT, lambda: ctx.fp8_quantize_rows(other)))
 
 
 @pytest.mark.parametrize("vocab", [129, 501, 1001, 3001])
@@ -105,9 +112,8 @@ def test_fp8_logprob(ctx, vocab):
     """Against as many fp32 logits, which are read and converted twice."""
     y = torch.randint(0, vocab, (ROWS,), device="cuda", dtype=torch.int32)
     bf16, f32 = logits(vocab, torch.bfloat16), logits(vocab, torch.float32)
-    half = kernel_us(ctx, B.AIS_K_FP8_LOGPROB, lambda: ctx.fp8_rollout_logprob(bf16, y))
-    full = kernel_us(ctx, B.AIS_K_FP8_LOGPROB, lambda: ctx.fp8_rollout_logprob(f32, y))
-    assert half <= SLACK * full, (half, full)
+    assert_no_slower(lambda: kernel_us(ctx, B.AIS_K_FP8_LOGPROB, lambda: ctx.fp8_rollout_logprob(bf16, y)),
+                     lambda: kernel_us(ctx, B.AIS_K_FP8_LOGPROB, lambda: ctx.fp8_rollout_logprob(f32, y)))
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
@@ -117,9 +123,8 @@ def test_fp8_decoding(ctx, vocab, dtype):
     codes = torch.randint(0, 120, (ROWS, vocab + 1), device="cuda", dtype=torch.uint8)
     dense, other = codes[:, :vocab].contiguous(), codes[:, :vocab]
     scale = torch.rand(ROWS, device="cuda")
-    vectors = kernel_us(ctx, B.AIS_K_FP8_DEQUANT, lambda: ctx.fp8_dequantize_rows(dense, scale, dtype))
-    single = kernel_us(ctx, B.AIS_K_FP8_DEQUANT, lambda: ctx.fp8_dequantize_rows(other, scale, dtype))
-    assert vectors <= SLACK * single, (vectors, single)
+    assert_no_slower(lambda: kernel_us(ctx, B.AIS_K_FP8_DEQUANT, lambda: ctx.fp8_dequantize_rows(dense, scale, dtype)),
+                     lambda: kernel_us(ctx, B.AIS_K_FP8_DEQUANT, lambda: ctx.fp8_dequantize_rows(other, scale, dtype)))
     assert torch.equal(ctx.fp8_dequantize_rows(dense, scale, dtype), ctx.fp8_dequantize_rows(other, scale, dtype))
 
 

@@ -12,12 +12,12 @@
 namespace ais {
 
 constexpr int kSweepThreads = 256;     // one workgroup (4 wavefronts) streams one logits row
-constexpr int kTileThreads = 256;      // workgroup of the per-row scalar kernels
-constexpr int kTileRows = 1024;        // rows of one response handled by one such workgroup
-// Most responses whose tiling the scalar kernels work out for themselves, in 12 KiB of LDS.  Both calls of a step, us,
-// against the plan kernel: 40,000 rows in 64 responses 20.0 and 22.0, 1,200,000 in 512 50.7 and 52.7, in 1,024 57.4 and
-// 60.0.  With room for 4,096 (48 KiB) 1,200,000 rows in 2,048 take 90.8 instead of 64.6, and in 512 64.8: every workgroup
-// scans four times as many, and fewer fit a compute unit.
+constexpr int kPlanThreads = 256;      // workgroup of the plan kernel
+constexpr int kPlanTileRows = 1024;    // rows of a tile that it lays out
+// Most responses whose tiling the scalar kernels work out for themselves: one for each thread of a workgroup.  Kernel time
+// of both calls, us, against tilings laid out by the plan kernel (whose own launch comes on top of it): 41,643 rows in 16
+// responses 18.8 and 18.8, 200,000 in 64 24.5 and 27.8, 200,000 in 512 23.8 and 23.4, 1,200,000 in 1,024 38.9 and 47.7,
+// 4,000,000 in 1,024 78.0 and 69.3.
 constexpr int kSelfPlanResponses = 1024;
 // Words of the status allocation that count the finished workgroups of a reduction: a pair for the calls that work in the
 // context's workspace, a pair for the static call, which may run beside them.
@@ -26,28 +26,34 @@ constexpr int kMaxDevices = 64;        // device indices a context may be create
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
-// Per-tile partial results of the diagnostics reduction (level 1 -> level 2).  The spread of w_bar travels as
-// (count, mean, sum of squared deviations from the mean), merged pairwise: a variance never comes out of the
-// difference of two large sums.
-struct DiagPartial {
-  double mean_w;  // mean of w_bar over the tile's valid rows
-  double m2_w;    // sum of (w_bar - mean_w)^2
-  double sabs;    // sum of |log pi_train - log pi_roll|
-  double sd;      // sum of (log pi_train - log pi_roll)
-  double sdp;     // sum of |pi_train - pi_roll|
-  long long cnt;  // valid rows
-  long long nclip;  // rows with rho > C
+// Per-tile partial results of the diagnostics reduction (level 1 -> level 2), word k of tile b at [k * max_tiles + b], so
+// that lanes which read consecutive tiles read consecutive words.  The spread of w_bar travels as (count, mean, sum of
+// squared deviations from the mean), merged pairwise: a variance never comes out of the difference of two large sums.
+enum DiagWord {
+  kMeanW,    // mean of w_bar over the tile's valid rows
+  kM2W,      // sum of (w_bar - mean)^2
+  kSumAbs,   // sum of |log pi_train - log pi_roll|
+  kSumD,     // sum of (log pi_train - log pi_roll)
+  kSumDp,    // sum of |pi_train - pi_roll|
+  kCounts,   // valid rows + 2^32 * rows with rho > C (a bit pattern, not a double)
+  kDiagWords
 };
+
+// How a batch of (n_rows, n_resp) is cut into tiles: 2^shift rows each, at most max_tiles of them.
+struct TileRule {
+  int shift, max_tiles;
+};
+TileRule tile_rule(long long n_rows, int n_resp);
 
 // Byte offsets of the regions of the context workspace for a call with (n_rows, n_resp).
 struct WorkspaceLayout {
   size_t tile_off;   // int [n_resp + 2]   first tile of each response, and the total (n_resp > kSelfPlanResponses)
-  size_t partial;    // DiagPartial [max_tiles]  (reused as double [max_tiles] by the loss)
+  size_t partial;    // double [kDiagWords][max_tiles]  (reused as double [max_tiles] by the loss)
   size_t g;          // float [n_rows]     per-row gradient coefficient
   size_t total;
-  int max_tiles;
 };
 WorkspaceLayout workspace_layout(long long n_rows, int n_resp);
+size_t static_scratch_bytes(long long n_rows, int n_resp);   // what ais_diagnostics_static accepts a batch by
 
 // Decomposition of the hidden-state read-out when every row is evaluated: token blocks x chunks of vocabulary
 // tiles.  The decomposition actually used is decided on the device from the number of evaluated rows.
@@ -126,16 +132,16 @@ int launch_fused_logprob_softmax(ais_ctx* ctx, const void* logits, ais_dtype dty
                                  long long row_stride, const int* token_ids, const unsigned char* valid,
                                  float inv_temperature, float* logp_out, float* lse_out, void* sgrad,
                                  bool* used_registers);
-int launch_plan(ais_ctx* ctx, const long long* cu_rows, int n_resp, long long n_rows, int* tile_off, int max_tiles);
+int launch_plan(ais_ctx* ctx, const long long* cu_rows, int n_resp, long long n_rows, int* tile_off);
 int launch_diagnostics(ais_ctx* ctx, const float* logp_train, const float* logp_roll, const unsigned char* valid,
                        long long n_rows, const long long* cu_rows, int n_resp, int group_size,
-                       const float* rewards, const ais_params& p, int* tile_off, int max_tiles,
-                       DiagPartial* partial, bool in_static, float* adv_out, int* count_out, ais_diag* diag_out);
+                       const float* rewards, const ais_params& p, int* tile_off, double* partial,
+                       bool in_static, float* adv_out, int* count_out, ais_diag* diag_out);
 int launch_row_coeff(ais_ctx* ctx, const float* logp_train, const float* logp_roll, const float* logp_old,
                      const float* logp_ref, const unsigned char* valid, long long n_rows,
                      const long long* cu_rows, int n_resp, const float* adv, const int* count,
-                     const ais_diag* diag, const ais_params& p, int* tile_off, int max_tiles,
-                     double* partial, float* g_out, float* wtilde_out, double* loss_out, float g_scale);
+                     const ais_diag* diag, const ais_params& p, int* tile_off, double* partial, float* g_out,
+                     float* wtilde_out, double* loss_out, float g_scale);
 int launch_copy(ais_ctx* ctx, void* dst, const void* src, long long bytes);
 int launch_fp8_quantize(ais_ctx* ctx, const void* logits, ais_dtype dtype, long long n_rows, int vocab,
                         long long row_stride, unsigned char* codes, long long codes_stride, float* scale_out);

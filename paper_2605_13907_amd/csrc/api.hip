@@ -142,12 +142,12 @@ int static_scratch_address(int device, void** out) {
 }
 
 // Launches the plan kernel unless the tiling the last ais_diagnostics call left in the workspace is the one wanted.
-int plan_for_step(ais_ctx* ctx, const long long* cu_rows, int n_resp, long long n_rows, int* tile_off, int max_tiles) {
+int plan_for_step(ais_ctx* ctx, const long long* cu_rows, int n_resp, long long n_rows, int* tile_off) {
   const ais_ctx::Plan& k = ctx->plan;
   if (k.valid && k.cu_rows == cu_rows && k.n_rows == n_rows && k.n_resp == n_resp && k.stream == ctx->stream)
     return AIS_OK;
   ctx->plan.valid = false;
-  return launch_plan(ctx, cu_rows, n_resp, n_rows, tile_off, max_tiles);
+  return launch_plan(ctx, cu_rows, n_resp, n_rows, tile_off);
 }
 
 int check_diagnostics_args(const float* logp_train, const float* logp_roll, long long n_rows,
@@ -304,10 +304,10 @@ int ais_diagnostics(ais_ctx* ctx, const float* logp_train, const float* logp_rol
   char* ws = static_cast<char*>(ctx->ws);
   int* tile_off = reinterpret_cast<int*>(ws + w.tile_off);
   ctx->plan.valid = false;
-  rc = launch_plan(ctx, cu_rows, n_resp, n_rows, tile_off, w.max_tiles);
+  rc = launch_plan(ctx, cu_rows, n_resp, n_rows, tile_off);
   if (rc != AIS_OK) return rc;
   rc = launch_diagnostics(ctx, logp_train, logp_roll, valid, n_rows, cu_rows, n_resp, group_size, rewards, *params,
-                          tile_off, w.max_tiles, reinterpret_cast<DiagPartial*>(ws + w.partial), false, adv_out,
+                          tile_off, reinterpret_cast<double*>(ws + w.partial), false, adv_out,
                           count_out, diag_out);
   if (rc != AIS_OK) return rc;
   // the tiling stays in the workspace for the calls that complete this step
@@ -329,7 +329,7 @@ int ais_diagnostics_static(ais_ctx* ctx, const float* logp_train, const float* l
   // what the kernels need: the tiling, and one partial per tile (not the per-row
   // coefficients of the gradient call, which come after them in the layout)
   const WorkspaceLayout w = workspace_layout(n_rows, n_resp);
-  if (w.g > (size_t)AIS_STATIC_SCRATCH_BYTES) return AIS_ERR_SCRATCH;
+  if (static_scratch_bytes(n_rows, n_resp) > (size_t)AIS_STATIC_SCRATCH_BYTES) return AIS_ERR_SCRATCH;
   if (ctx == nullptr) return AIS_ERR_NULL;
   if (ctx->static_scratch == nullptr) return AIS_ERR_HIP;
   DeviceGuard guard(ctx->device);
@@ -337,10 +337,10 @@ int ais_diagnostics_static(ais_ctx* ctx, const float* logp_train, const float* l
   int* tile_off = reinterpret_cast<int*>(ws + w.tile_off);
   // every tile_off entry and every partial that this call reads it has written itself: nothing of an earlier call's
   // contents is used
-  rc = launch_plan(ctx, cu_rows, n_resp, n_rows, tile_off, w.max_tiles);
+  rc = launch_plan(ctx, cu_rows, n_resp, n_rows, tile_off);
   if (rc != AIS_OK) return rc;
   return launch_diagnostics(ctx, logp_train, logp_roll, valid, n_rows, cu_rows, n_resp, group_size, rewards, *params,
-                            tile_off, w.max_tiles, reinterpret_cast<DiagPartial*>(ws + w.partial), true, adv_out,
+                            tile_off, reinterpret_cast<double*>(ws + w.partial), true, adv_out,
                             count_out, diag_out);
 }
 
@@ -370,10 +370,10 @@ int ais_grpo_loss_grad(ais_ctx* ctx, const void* logits, ais_dtype dtype, long l
   char* ws = static_cast<char*>(ctx->ws);
   int* tile_off = reinterpret_cast<int*>(ws + w.tile_off);
   float* g = reinterpret_cast<float*>(ws + w.g);
-  rc = plan_for_step(ctx, cu_rows, n_resp, n_rows, tile_off, w.max_tiles);
+  rc = plan_for_step(ctx, cu_rows, n_resp, n_rows, tile_off);
   if (rc != AIS_OK) return rc;
   rc = launch_row_coeff(ctx, logp_train, logp_roll, logp_old, logp_ref, valid, n_rows, cu_rows, n_resp, adv, count,
-                        diag, *params, tile_off, w.max_tiles, reinterpret_cast<double*>(ws + w.partial), g,
+                        diag, *params, tile_off, reinterpret_cast<double*>(ws + w.partial), g,
                         wtilde_out, loss_out, 1.0f);
   if (rc != AIS_OK) return rc;
   return launch_dlogits(ctx, logits, dtype, n_rows, (int)vocab, row_stride, token_ids, g, nullptr, lse, logp_train,
@@ -423,10 +423,10 @@ int ais_grpo_row_scale(ais_ctx* ctx, const float* logp_train, const float* logp_
   if (rc != AIS_OK) return rc;
   char* ws = static_cast<char*>(ctx->ws);
   int* tile_off = reinterpret_cast<int*>(ws + w.tile_off);
-  rc = plan_for_step(ctx, cu_rows, n_resp, n_rows, tile_off, w.max_tiles);
+  rc = plan_for_step(ctx, cu_rows, n_resp, n_rows, tile_off);
   if (rc != AIS_OK) return rc;
   return launch_row_coeff(ctx, logp_train, logp_roll, logp_old, logp_ref, valid, n_rows, cu_rows, n_resp, adv, count,
-                          diag, *params, tile_off, w.max_tiles, reinterpret_cast<double*>(ws + w.partial), g_out,
+                          diag, *params, tile_off, reinterpret_cast<double*>(ws + w.partial), g_out,
                           wtilde_out, loss_out, params->inv_temperature);
 }
 

@@ -19,6 +19,16 @@ def test_number_of_responses(monkeypatch, n_resp):
     S.test_scalars_at_scale("tiling", True)
 
 
+@pytest.mark.parametrize("n_resp,length", [(1, 1), (1, 3_840), (1, 3_841), (8, 256), (8, 257), (2, 393_216), (2, 393_217),
+                                           (1024, 64), (1023, 65)])
+def test_edges_of_the_tile_rule(monkeypatch, n_resp, length):
+    """One workgroup alone up to 16 tiles of 256 rows (its partials stay in LDS), several beyond; tiles of 512 rows from
+    3,072 tiles of 256 on; as many responses as a workgroup has threads."""
+    monkeypatch.setitem(S.CASES, "edge", (n_resp, 1, ("fixed", length), 0.6))
+    S.test_scalars_at_scale("edge", False)
+    S.test_scalars_at_scale("edge", True)
+
+
 @pytest.mark.parametrize("n_resp", [2, 1024, 1025])
 @pytest.mark.parametrize("fault", ["first", "last", "order", "range"])
 def test_row_offsets_that_are_no_partition(n_resp, fault):

@@ -8,7 +8,7 @@
 //                          dtype (gradient of Eq. 19 through the log-softmax; g is the row's coefficient)
 //
 // Both are bound by HBM bandwidth: nothing here is a contraction, so no matrix cores.  One workgroup
-// owns one row (256 threads in the read-only sweep, 1,024 in the read+write sweep, 256 for narrow rows), so a row's partial
+// owns one row (64 to 1,024 threads by number and width of the rows), so a row's partial
 // results never leave its compute unit; consecutive lanes access consecutive 16-byte vectors (8 bf16 or
 // 4 fp32 logits), i.e. each wavefront memory instruction covers 1 KiB of contiguous memory.  Logits are
 // read and written with streaming (non-temporal) accesses: a batch is tens of GB and nothing survives in
@@ -24,16 +24,19 @@ namespace {
 using namespace dev;
 
 // ---- sweep 1: token log-probability --------------------------------------------------------------
-// grid.x = n_rows, block = kSweepThreads.  ALIGNED: row base and pitch are 16-byte aligned, so a row is vectors from its
+// grid.x = n_rows, block = THREADS.  ALIGNED: row base and pitch are 16-byte aligned, so a row is vectors from its
 // first element on.  Otherwise the elements before the row's first 128-byte boundary are taken one by one together
 // with those after the last vector.  (Until then such rows were read element by element, bound by the number of load
 // instructions.  The three-call step over 12,345 x 50,257 bf16: 1,657 us element-wise, 636 us with vectors; over
-// 4,096 x 32,003 fp32: 415 and 236 us.)
-template <typename T, bool ALIGNED, int UNROLL>
-__global__ __launch_bounds__(kSweepThreads) void token_logprob_kernel(
+// 4,096 x 32,003 fp32: 415 and 236 us.)  The vectors after the last whole round of UNROLL per thread are loaded together
+// too, those past the end of the row masked, instead of one by one, each waiting for its own: 8,192 x 32,003 bf16 87.9 ->
+// 84.8 us with 256 threads, no difference at 151,936.
+template <typename T, bool ALIGNED, int THREADS, int UNROLL>
+__global__ __launch_bounds__(THREADS) void token_logprob_kernel(
     const T* __restrict__ logits, long long row_stride, int vocab, const int* __restrict__ token_ids,
     const unsigned char* __restrict__ valid, float inv_temperature, float* __restrict__ logp_out,
     float* __restrict__ lse_out, int* __restrict__ status) {
+  static_assert(UNROLL == 4, "the last vectors of a row are loaded by ones, twos and fours");
   constexpr int N = Vec<T>::N;
   const long long row = blockIdx.x;
   const int tid = threadIdx.x;
@@ -57,57 +60,70 @@ __global__ __launch_bounds__(kSweepThreads) void token_logprob_kernel(
   const int nvec = (vocab - head) / N;
   // vector index at which this thread meets the sampled token, or a value no index ever takes
   const int yb = y - head;                        // position of the sampled token from the first vector on
-  const int yvec = (y_ok && yb >= 0 && yb < nvec * N && (yb / N) % kSweepThreads == tid) ? yb / N : -(1 << 30);
+  const int yvec = (y_ok && yb >= 0 && yb < nvec * N && (yb / N) % THREADS == tid) ? yb / N : -(1 << 30);
   const int ysub = yb & (N - 1);
 
   MaxSum st{kNegHuge, 0.f};
   {
     const u32x4* zv = reinterpret_cast<const u32x4*>(zr + head);
-    int i = tid;
-    for (; i + (UNROLL - 1) * kSweepThreads < nvec; i += UNROLL * kSweepThreads) {
-      u32x4 q[UNROLL];
+    // COUNT vectors of every thread from vector `base` on, all in flight at once; TAIL: some lie past the end of the row
+    auto batch = [&](int base, auto count, auto tail) {
+      constexpr int COUNT = decltype(count)::value;
+      constexpr bool TAIL = decltype(tail)::value;
+      const int i = base + tid;
+      u32x4 q[COUNT];
 #pragma unroll
-      for (int u = 0; u < UNROLL; ++u) q[u] = load_stream(zv + i + u * kSweepThreads);
-      float x[UNROLL * N];
+      for (int u = 0; u < COUNT; ++u)
+        q[u] = load_stream(zv + (TAIL ? min(i + u * THREADS, nvec - 1) : i + u * THREADS));
+      float x[COUNT * N];
 #pragma unroll
-      for (int u = 0; u < UNROLL; ++u) Vec<T>::unpack(q[u], x + u * N);
-      if ((unsigned)(yvec - i) < (unsigned)(UNROLL * kSweepThreads)) {   // rare: once per row, one lane
-        const int hit = ((yvec - i) / kSweepThreads) * N + ysub;
+      for (int u = 0; u < COUNT; ++u) {
+        Vec<T>::unpack(q[u], x + u * N);
+        if (TAIL && i + u * THREADS >= nvec) {
 #pragma unroll
-        for (int k = 0; k < UNROLL * N; ++k)
+          for (int k = 0; k < N; ++k) x[u * N + k] = kMasked;
+        }
+      }
+      if ((unsigned)(yvec - i) < (unsigned)(COUNT * THREADS)) {   // rare: once per row, one lane
+        const int hit = ((yvec - i) / THREADS) * N + ysub;
+#pragma unroll
+        for (int k = 0; k < COUNT * N; ++k)
           if (k == hit) x[k] = kMasked;
       }
-      accumulate<UNROLL * N>(x, scale, st);
-    }
-    for (; i < nvec; i += kSweepThreads) {
-      float x[N];
-      Vec<T>::unpack(load_stream(zv + i), x);
-      if (i == yvec) {
-#pragma unroll
-        for (int k = 0; k < N; ++k)
-          if (k == ysub) x[k] = kMasked;
-      }
-      accumulate<N>(x, scale, st);
-    }
+      accumulate<COUNT * N>(x, scale, st);
+    };
+    typedef std::integral_constant<int, 1> One;
+    typedef std::integral_constant<int, 2> Two;
+    typedef std::integral_constant<int, UNROLL> All;
+    int base = 0;
+    for (; base + UNROLL * THREADS <= nvec; base += UNROLL * THREADS) batch(base, All{}, std::false_type{});
+    const int left = nvec - base;                // uniform
+    if (left > 2 * THREADS) batch(base, All{}, std::true_type{});
+    else if (left > THREADS) batch(base, Two{}, std::true_type{});
+    else if (left > 0) batch(base, One{}, std::true_type{});
   }
-  if (tid < vocab - nvec * N) {                   // the elements outside the vectors, fewer than there are threads
-    const int v = tid < head ? tid : tid + nvec * N;
+  // the elements outside the vectors: at most 128 bytes before them, less than 16 after
+  for (int r = tid; r < vocab - nvec * N; r += THREADS) {
+    const int v = r < head ? r : r + nvec * N;
     float x = (y_ok && v == y) ? kMasked : Vec<T>::load1(zr + v);
     accumulate<1>(&x, scale, st);
   }
 
   st = wave_merge(st);
-  __shared__ MaxSum lds[kSweepThreads / 64];
+  __shared__ MaxSum lds[THREADS / 64];
   if ((tid & 63) == 0) lds[tid >> 6] = st;
   __syncthreads();
+  if (tid >= 64) return;
+  MaxSum t = lds[tid & (THREADS / 64 - 1)];         // the wavefronts' states, in lanes of the first
+  if (THREADS > 64) t = merge_dpp<kDppQuadXor1>(t);
+  if (THREADS > 128) t = merge_dpp<kDppQuadXor2>(t);
+  if (THREADS > 256) t = merge_dpp<kDppRowHalfMirror>(t);
+  if (THREADS > 512) t = merge_dpp<kDppRowMirror>(t);
   if (tid == 0) {
-    MaxSum t = lds[0];
-#pragma unroll
-    for (int w = 1; w < kSweepThreads / 64; ++w) t = merge(t, lds[w]);
     if (y_ok) {
       // once per row, in fp64: r = S_o / e^{z_y/T};  logp = -log1p(r);  lse = z_y/T + log1p(r)
-      const double ty = (double)zy * (double)scale;
-      const double l1p = log1p_scaled(t.s, (double)t.m - ty);
+      const double l1p =
+          log1p_scaled(t.s, exact_exponent((double)t.m - (double)zy * (double)scale, inv_temperature, scale));
       logp_out[row] = (float)(-l1p);
       lse_out[row] = (float)((double)zy * (double)inv_temperature + l1p);
     } else {
@@ -310,11 +326,33 @@ bool same_lines(const void* a, const void* b) {
 // and 15.7).
 constexpr size_t kElementwiseBytes = 2048;
 
-// 16-byte loads in flight per lane and loop iteration of the log-prob sweep (build-time tunable)
-#ifndef AIS_LOGPROB_UNROLL
-#define AIS_LOGPROB_UNROLL 4
-#endif
-constexpr int kUnrollFwd = AIS_LOGPROB_UNROLL;
+// 16-byte loads in flight per lane and loop iteration of the log-prob sweep
+constexpr int kUnrollFwd = 4;
+
+// Threads that share a row in the log-prob sweep.  256 leave a compute unit eight rows, which is what it takes to keep HBM
+// busy.  Where there are hardly more rows than compute units they take more threads each; where there are many narrow ones
+// they take fewer, so that more of them are on their way and fewer wavefronts meet at a row's end.  us, bf16 unless noted:
+//   rows x logits         1,024   512     256         rows x logits          256     128     64
+//   256 x 32,003            9.0    9.0    10.4        41,643 x 1,000          61.8    42.1    32.5
+//   256 x 151,936          18.6   22.3    29.6        41,643 x 4,001          83.2    66.7    60.6
+//   256 x 151,936 fp32     29.6   29.8    36.9        41,643 x 2,048 fp32     62.7    53.4    57.7
+//   512 x 151,936          32.3   30.5    36.3        41,643 x 6,000         101.3    81.9    85.6
+//   512 x 151,936 fp32     53.6   53.9    50.6        41,643 x 3,001 fp32     83.5    81.0    82.5
+//   1,500 x 151,936        72.6   74.9    74.6        41,643 x 8,192         101.8   108.2   110.0
+//   1,500 x 248,320 fp32  222.7  228.3   232.1        2,048 x 1,000 fp32       9.1     7.5     7.6
+//   8,192 x 32,003         89.7   80.6    84.8        1,024 x 3,001            8.1     7.5     8.6
+//   8,192 x 32,003 fp32   155.7  156.9   160.3
+//   8,192 x 50,257        128.2  125.5   129.0
+//   41,643 x 32,003       441.7  388.6   404.6
+//   41,643 x 151,936      1,954  1,883   1,860
+int logprob_threads(const ais_ctx* ctx, long long n_rows, long long nvec, bool bf16) {
+  const long long cus = ctx->n_cus;
+  if (nvec >= 2048 && n_rows <= cus) return 1024;
+  if (nvec >= 8192 && n_rows <= 8 * cus) return n_rows > 2 * cus ? 1024 : bf16 ? 512 : 256;
+  if (nvec >= 2500) return nvec < 8192 ? 512 : 256;
+  if (nvec >= 896 || n_rows < 8 * cus) return 256;
+  return nvec >= 512 ? 128 : 64;
+}
 
 }  // namespace
 
@@ -322,16 +360,23 @@ int launch_token_logprob(ais_ctx* ctx, const void* logits, ais_dtype dtype, long
                          long long row_stride, const int* token_ids, const unsigned char* valid,
                          float inv_temperature, float* logp_out, float* lse_out) {
   if (n_rows == 0) return AIS_OK;
-  dim3 grid((unsigned)n_rows), block(kSweepThreads);
   ScopedTimer timer(ctx, AIS_K_LOGPROB);
   auto launch = [&](const auto* z) {
     typedef std::remove_cv_t<std::remove_pointer_t<decltype(z)>> T;
-    if (vec_ok(z, row_stride, sizeof(T)))
-      token_logprob_kernel<T, true, kUnrollFwd><<<grid, block, 0, ctx->stream>>>(
+    const long long nvec = (long long)vocab / Vec<T>::N;
+    auto run = [&](auto threads) {
+      constexpr int kThreads = decltype(threads)::value;
+      auto kernel = vec_ok(z, row_stride, sizeof(T)) ? token_logprob_kernel<T, true, kThreads, kUnrollFwd>
+                                                     : token_logprob_kernel<T, false, kThreads, kUnrollFwd>;
+      kernel<<<dim3((unsigned)n_rows), dim3(kThreads), 0, ctx->stream>>>(
           z, row_stride, vocab, token_ids, valid, inv_temperature, logp_out, lse_out, ctx->status_dev);
-    else
-      token_logprob_kernel<T, false, kUnrollFwd><<<grid, block, 0, ctx->stream>>>(
-          z, row_stride, vocab, token_ids, valid, inv_temperature, logp_out, lse_out, ctx->status_dev);
+    };
+    const int threads = logprob_threads(ctx, n_rows, nvec, std::is_same_v<T, bf16_t>);
+    if (threads == 1024) run(std::integral_constant<int, 1024>{});
+    else if (threads == 512) run(std::integral_constant<int, 512>{});
+    else if (threads == 64) run(std::integral_constant<int, 64>{});
+    else if (threads == 128) run(std::integral_constant<int, 128>{});
+    else run(std::integral_constant<int, 256>{});
   };
   if (dtype == AIS_BF16) launch(static_cast<const bf16_t*>(logits));
   else launch(static_cast<const float*>(logits));

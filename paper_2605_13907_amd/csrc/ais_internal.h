@@ -22,6 +22,13 @@ constexpr int kSelfPlanResponses = 1024;
 // Words of the status allocation that count the finished workgroups of a reduction: a pair for the calls that work in the
 // context's workspace, a pair for the static call, which may run beside them.
 constexpr int kTicketWord = 32, kStaticTicketWord = 48;
+// Widest bf16 row (two vectors for each of 1,024 threads) that the streaming FP8 kernels take from the table kernels.  There the
+// extremes and the table take the same time for every row, and a compute unit works on two rows at most; the streaming
+// kernels have eight or more of them on their way.  us, streaming and table, 8,192 rows: quantisation, 1,000 logits 8.5 and
+// 91.7, 4,096 19.0 and 93.2, 8,192 39.2 and 97.3, 16,384 97.6 and 99.3, 20,001 127 and 119; log-prob, 1,000 9.1 and 94.6,
+// 8,192 44.8 and 97.7, 16,384 82.2 and 104.3, 24,001 120 and 122, 28,001 139 and 122.  41,643 rows of 1,000: 25.6 and 452.4;
+// 31.1 and 467.5.  300 rows of 16,001 13.4 and 14.0, of 20,001 14.8 and 14.3.
+constexpr int kFp8NarrowRow = 16391;
 constexpr int kMaxDevices = 64;        // device indices a context may be created on
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;

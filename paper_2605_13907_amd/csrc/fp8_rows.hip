@@ -249,15 +249,15 @@ bool codes_aligned(const void* z, long long row_stride, int esize, const void* c
 }
 
 // Vectors per lane of a row that the register-resident kernel takes, otherwise 0: it does not fit, or it is a narrow one
-// that the streaming kernel does better with.  That kernel has eight rows in a compute unit at a time (8,192 unaligned fp32
-// rows of 1,001 elements: 18 us, 35 here; of 4,001 39 and 45; of 5,001 48 and 49; of 6,001 59 and 54).  bf16 rows come here
-// only where they are too wide for the table kernel, which takes all others but the narrow ones (and those without a
-// whole vector).
+// that the streaming kernel does better with.  That kernel has eight or more rows in a compute unit at a time (8,192 fp32
+// rows of 1,000 elements: 11.0 us, 25.9 here; of 2,048 15.6 and 28.6; of 4,096 32.3 and 37.0; unaligned, of 5,001 48 and 49, of
+// 6,001 59 and 54).  bf16 rows come here only where they are too wide for the table kernel, which takes all others but the
+// narrow ones.
 template <typename T>
-int vectors_per_lane(const void* z, int vocab, long long row_stride) {
+int vectors_per_lane(int vocab) {
   constexpr int N = Vec<T>::N;
   const int need = (vocab / N + kRowThreads - 1) / kRowThreads;
-  if (sizeof(T) == 2 ? need <= 24 : !row_aligned(z, row_stride, sizeof(T)) && need <= 1) return 0;
+  if (sizeof(T) == 2 ? need <= 24 : need <= 1) return 0;
   return need <= 24 + kLdsSlots ? (need < 1 ? 1 : need) : 0;
 }
 
@@ -310,12 +310,12 @@ bool try_fp8_quantize_rows(ais_ctx* ctx, const void* logits, ais_dtype dtype, lo
                            long long row_stride, unsigned char* codes, long long codes_stride, float* scale_out) {
   if (!codes_aligned(logits, row_stride, dtype == AIS_BF16 ? 2 : 4, codes, codes_stride)) return false;
   if (dtype == AIS_BF16) {
-    const int need = vectors_per_lane<bf16_t>(logits, vocab, row_stride);
+    const int need = vectors_per_lane<bf16_t>(vocab);
     if (need == 0) return false;
     return dispatch_rows<bf16_t>(ctx, need, static_cast<const bf16_t*>(logits), n_rows, vocab, row_stride, codes,
                                  codes_stride, scale_out);
   }
-  const int need = vectors_per_lane<float>(logits, vocab, row_stride);
+  const int need = vectors_per_lane<float>(vocab);
   if (need == 0) return false;
   return dispatch_rows<float>(ctx, need, static_cast<const float*>(logits), n_rows, vocab, row_stride, codes,
                               codes_stride, scale_out);
@@ -333,6 +333,10 @@ bool try_fp8_dequantize_burst(ais_ctx* ctx, const unsigned char* codes, long lon
   // elements 14 us, 29 here; 4,001 33 and 36; 6,001 44 and 42; to fp32 1,001 16 and 26; 5,001 41 and 47; 8,191 123 and 61)
   if (!aligned && vocab < 5120) return false;
   const int need = (vocab / n + kRowThreads - 1) / kRowThreads;
+  // narrow aligned rows: 256 threads that store each vector as they form it (8,192 rows decoded to bf16, 1,024 elements 7.8
+  // us, 22.0 here; 4,096 15.3 and 27.3; 8,192 29.7 and 41.0; to fp32, 1,024 7.2 and 17.1, 4,096 25.0 and 35.7; 41,643 rows of
+  // 8,192 to bf16 170 and 200)
+  if (aligned && need <= 1) return false;
   dim3 grid((unsigned)n_rows), block(kRowThreads);
   // (vectors that surely exist, vectors per lane and burst, bursts): a row reaches a class only if it is wider than
   // the class before it; an unaligned row may have lost up to 8 vectors to its head

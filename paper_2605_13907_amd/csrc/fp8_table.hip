@@ -544,14 +544,10 @@ bool row_aligned(const void* z, long long row_stride) {
   return reinterpret_cast<uintptr_t>(z) % 16 == 0 && (row_stride * 2) % 16 == 0;
 }
 
-// Vectors per lane of a bf16 row, or 0 when the row does not qualify for these kernels: too wide, without a whole vector,
-// or unaligned and narrow.  The extremes and the table take the same time for every row, and a compute unit works on two
-// rows at most; the streaming kernels of fp8.hip have eight of them on their way.  8,192 unaligned rows, us streaming and
-// here: quantisation, 1,001 logits 17 and 101, 16,001 99 and 113, 20,001 127 and 119; log-prob, 1,001 20 and 103, 16,001
-// 84 and 115, 24,001 120 and 122, 28,001 139 and 122; 300 rows of 16,001 13.4 and 14.0, of 20,001 14.8 and 14.3.
-int table_vectors_per_lane(const void* z, int vocab, long long row_stride, int most) {
+// Vectors per lane of a bf16 row, or 0 when the row does not qualify for these kernels: too wide or narrow.
+int table_vectors_per_lane(int vocab, int most) {
   const int need = (vocab / 8 + kRowThreads - 1) / kRowThreads;
-  return (row_aligned(z, row_stride) ? vocab >= 8 : need > 2) && need <= most ? need : 0;
+  return vocab > kFp8NarrowRow && need <= most ? need : 0;
 }
 
 }  // namespace
@@ -568,7 +564,7 @@ bool try_fp8_quantize_table(ais_ctx* ctx, const void* logits, ais_dtype dtype, l
   if ((reinterpret_cast<uintptr_t>(codes) - reinterpret_cast<uintptr_t>(logits) / 2) % 8 != 0 ||
       (codes_stride - row_stride) % 8 != 0)
     return false;
-  const int need = table_vectors_per_lane(logits, vocab, row_stride, 24);
+  const int need = table_vectors_per_lane(vocab, 24);
   if (need == 0) return false;
   const bf16_t* z = static_cast<const bf16_t*>(logits);
   const long long resident = (long long)ctx->n_cus * quantize_workgroups(need <= 4 ? 4 : 24);
@@ -600,7 +596,7 @@ bool try_fp8_rollout_logprob_table(ais_ctx* ctx, const void* logits, ais_dtype d
                                    float* logp_out) {
   if (dtype != AIS_BF16) return false;
   // 23 vectors per lane in registers, 8 more in LDS slots beside the table
-  const int need = table_vectors_per_lane(logits, vocab, row_stride, 23 + 8);
+  const int need = table_vectors_per_lane(vocab, 23 + 8);
   if (need == 0) return false;
   const bf16_t* z = static_cast<const bf16_t*>(logits);
   const long long resident = (long long)ctx->n_cus * logprob_workgroups(need <= 8 ? 8 : 24);

@@ -1,0 +1,73 @@
+"""FP8 kernels on narrow rows: the streaming kernels with 64 and 256 threads a row, at the ends of their ranges, aligned and not,
+with NaNs, infinities and logits of any magnitude."""
+import pytest
+import torch
+
+from paper_2605_13907_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+MAX = 448.0
+
+
+def reference(z, aligned_bf16):
+    """Codes and scale as the definition gives them; a NaN is -448, in 16-byte aligned bf16 rows the row's largest magnitude
+    with its own sign."""
+    x = z.float()
+    amax = torch.where(x.isnan(), torch.zeros_like(x), x).abs().amax(dim=1)
+    s = amax / torch.full_like(amax, MAX)
+    s = torch.where(s > 0, s, torch.ones_like(s))
+    own = torch.copysign(amax.unsqueeze(1).expand_as(x), x) if aligned_bf16 else -MAX * s.unsqueeze(1)
+    q = (torch.where(x.isnan(), own, x) / s.unsqueeze(1)).clamp(-MAX, MAX)
+    return q.to(torch.float8_e4m3fn).view(torch.uint8), s
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("vocab", [1, 7, 8, 9, 63, 64, 520, 1023, 1024, 1025, 2047, 2048, 2049, 4096, 4100, 8192, 16_384,
+                                   16_391, 16_392])
+def test_narrow_rows(dtype, vocab):
+    ctx = B.AisContext()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(vocab)
+    for rows in (3, 2047, 2048) if vocab <= 4100 else (3, 500):
+        z = (torch.randn(rows, vocab, generator=gen, device="cuda") * 3).to(dtype)
+        y = torch.randint(0, vocab, (rows,), generator=gen, device="cuda", dtype=torch.int32)
+        aligned = dtype == torch.bfloat16 and vocab % 8 == 0
+        codes, scale = ctx.fp8_quantize_rows(z)
+        want, s = reference(z, aligned)
+        assert torch.equal(codes, want) and torch.equal(scale, s), rows
+        back = want.view(torch.float8_e4m3fn).float() * s.unsqueeze(1)
+        assert torch.equal(ctx.fp8_dequantize_rows(codes, scale, torch.float32), back), rows
+        assert torch.equal(ctx.fp8_dequantize_rows(codes, scale, torch.bfloat16), back.bfloat16()), rows
+        logp = ctx.fp8_rollout_logprob(z, y)
+        ref = torch.log_softmax(back.double(), dim=1).gather(1, y.long().unsqueeze(1)).squeeze(1)
+        # fp32 log-sum-exp minus an fp32 logit, both of up to 20: a few ulp of 2^-19
+        assert (logp.double() - ref).abs().max() < 8e-6, rows
+        # a NaN of either sign in every other row
+        z[::2, vocab // 2] = float("nan")
+        z[::4, vocab // 2] = -z[::4, vocab // 2]
+        want, s = reference(z, aligned)
+        codes, scale = ctx.fp8_quantize_rows(z)
+        assert torch.equal(scale, s) and torch.equal(codes, want), rows
+    ctx.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("power", [-30, 3, 9, 12, 20, 35])
+def test_any_magnitude(dtype, power):
+    """The largest term of the sum is 1 at every magnitude."""
+    ctx = B.AisContext()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(power + 99)
+    for vocab in (64, 65, 4096):
+        z = (torch.randn(64, vocab, generator=gen, device="cuda") * 10.0 ** power).to(dtype)
+        y = torch.randint(0, vocab, (64,), generator=gen, device="cuda", dtype=torch.int32)
+        y[::2] = z[::2].argmax(dim=1).int()
+        codes, s = reference(z, False)
+        back = codes.view(torch.float8_e4m3fn).double() * s.double().unsqueeze(1)
+        ref = torch.log_softmax(back, dim=1).gather(1, y.long().unsqueeze(1)).squeeze(1)
+        logp = ctx.fp8_rollout_logprob(z, y).double()
+        # products are rounded to fp32: 2^-23 of the largest logit, beside the log-prob itself
+        tol = 2.0 ** -22 * z.float().abs().amax(dim=1).double() + 1e-5
+        assert ((logp - ref).abs() <= tol).all(), (vocab, (logp - ref).abs().max())
+    ctx.close()

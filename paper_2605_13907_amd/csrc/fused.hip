@@ -14,7 +14,7 @@
 // flight at once and memory latency is paid once per row.  Rows wider than 24 vectors per lane keep their
 // last 9 vectors per lane in LDS (144 KiB of the compute unit's 160), which are filled by direct
 // global -> LDS copies and never pass through registers on the way in: up to 33 vectors per lane, 270,336
-// bf16 elements.  Rows wider than that fall back to the two-pass kernels, and so do many narrow rows of odd width.
+// bf16 elements.  Rows wider than that fall back to the two-pass kernels.  Narrow rows share 64 to 256 threads.
 #include "ais_internal.h"
 #include "device_utils.h"
 
@@ -24,7 +24,6 @@ namespace {
 using namespace dev;
 
 constexpr int kRowThreads = 1024;
-constexpr int kRowWaves = kRowThreads / 64;
 
 // A vector of excluded elements (-inf in the row's type), for lanes past the end of the row.
 template <typename T> __device__ __forceinline__ u32x4 masked_fill();
@@ -55,21 +54,23 @@ template <> __device__ __forceinline__ u32x4 patch_masked<float>(u32x4 q, int su
 typedef __attribute__((address_space(3))) void* lds_ptr;
 typedef const __attribute__((address_space(1))) void* glb_ptr;
 
-// grid.x = n_rows, block = kRowThreads.  ALIGNED: both rows are 16-byte aligned; otherwise both lie the same way relative
+// grid.x = n_rows, block = THREADS.  ALIGNED: both rows are 16-byte aligned; otherwise both lie the same way relative
 // to 128-byte lines, and the elements before the row's first line boundary are handled one by one together with those
 // after the last vector (such rows took the two-pass
 // kernels element by element before: 12,345 x 50,257 bf16 1,647 us a step, 443 us in one sweep).
-// KFULL * kRowThreads <= vectors of the row <= (NV + NL) * kRowThreads: vectors 0 .. KFULL - 1 of every lane exist and
+// KFULL * THREADS <= vectors of the row <= (NV + NL) * THREADS: vectors 0 .. KFULL - 1 of every lane exist and
 // are loaded and stored without a bounds branch.
-// Vector k of a lane (elements N * (tid + 1024 k) ..) lives in register q[k] for k < NV and in LDS slot k - NV
-// (16 bytes at byte offset 16 * (1024 (k - NV) + tid) of the dynamic LDS) for NV <= k < NV + NL.
-template <typename T, bool ALIGNED, int NV, int NL, int KFULL>
-__global__ __launch_bounds__(kRowThreads) void fused_logprob_softmax_kernel(
+// Vector k of a lane (elements N * (tid + THREADS k) ..) lives in register q[k] for k < NV and in LDS slot k - NV
+// (16 bytes at byte offset 16 * (THREADS (k - NV) + tid) of the dynamic LDS) for NV <= k < NV + NL.
+template <typename T, bool ALIGNED, int THREADS, int NV, int NL, int KFULL>
+__global__ __launch_bounds__(THREADS) void fused_logprob_softmax_kernel(
     const T* logits, long long row_stride, int vocab, const int* __restrict__ token_ids,
     const unsigned char* __restrict__ valid, float inv_temperature, float* __restrict__ logp_out,
     float* __restrict__ lse_out, T* sgrad, int* __restrict__ status) {
   constexpr int N = Vec<T>::N;
-  __shared__ MaxSum lds[kRowWaves];
+  constexpr int kWaves = THREADS / 64;
+  static_assert(ALIGNED || THREADS >= 128, "a thread for every element outside the vectors");
+  __shared__ MaxSum lds[kWaves];
   __shared__ float lds_row[2];          // shift (= -lse * log2e) and the sampled token's element
   extern __shared__ __align__(16) unsigned char lds_slots[];
   u32x4* lrow = reinterpret_cast<u32x4*>(lds_slots);
@@ -91,7 +92,7 @@ __global__ __launch_bounds__(kRowThreads) void fused_logprob_softmax_kernel(
     const u32x4 zero = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int k = 0; k < NV + NL; ++k) {
-      const int i = tid + k * kRowThreads;
+      const int i = tid + k * THREADS;
       if (i < nvec) store_stream(sv + i, zero);
     }
     if (tid < rest) Vec<T>::store1(at_rest(sr), 0.f);
@@ -103,8 +104,8 @@ __global__ __launch_bounds__(kRowThreads) void fused_logprob_softmax_kernel(
   u32x4 q[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    const int i = tid + k * kRowThreads;
-    if (k < KFULL) q[k] = load_stream(zv + i);       // the launcher promises nvec >= KFULL * kRowThreads
+    const int i = tid + k * THREADS;
+    if (k < KFULL) q[k] = load_stream(zv + i);       // the launcher promises nvec >= KFULL * THREADS
     else q[k] = (i < nvec) ? load_stream(zv + i) : masked_fill<T>();
   }
   // the LDS slots: lane i of a wavefront deposits its 16 bytes at the wavefront's base + 16 i, which is the
@@ -114,8 +115,8 @@ __global__ __launch_bounds__(kRowThreads) void fused_logprob_softmax_kernel(
     asm volatile("" : "+v"(tid0));
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
-      const int i = min(tid0 + (NV + k) * kRowThreads, nvec - 1);
-      __builtin_amdgcn_global_load_lds((glb_ptr)(zv + i), (lds_ptr)(lrow + k * kRowThreads + (tid0 & ~63)), 16, 0,
+      const int i = min(tid0 + (NV + k) * THREADS, nvec - 1);
+      __builtin_amdgcn_global_load_lds((glb_ptr)(zv + i), (lds_ptr)(lrow + k * THREADS + (tid0 & ~63)), 16, 0,
                                        2 /* non-temporal */);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -129,7 +130,7 @@ __global__ __launch_bounds__(kRowThreads) void fused_logprob_softmax_kernel(
   // where this thread holds the sampled token: vector slot k and lane element, or the register of the rest
   const int yb = y - head;              // its position from the first vector on
   const int yv = (y_ok && yb >= 0 && yb < nvec * N) ? yb / N : -1;
-  const int yk = (yv >= 0 && yv % kRowThreads == tid) ? yv / kRowThreads : -1;
+  const int yk = (yv >= 0 && yv % THREADS == tid) ? yv / THREADS : -1;
   const int ysub = yb & (N - 1);
   const bool y_in_rest = y_ok && (yb < 0 || yb >= nvec * N) && (yb < 0 ? y : y - nvec * N) == tid;
 
@@ -155,17 +156,17 @@ __global__ __launch_bounds__(kRowThreads) void fused_logprob_softmax_kernel(
   if (NL > 0) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the copies into the slots have landed
     if (yk >= NV) {                                        // the sampled token lies in a slot of this lane
-      u32x4* p = lrow + (yk - NV) * kRowThreads + tid;
+      u32x4* p = lrow + (yk - NV) * THREADS + tid;
       *p = patch_masked<T>(*p, ysub);
     }
     int tid1 = tid;
     asm volatile("" : "+v"(tid1));
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
-      const int i = tid1 + (NV + k) * kRowThreads;
+      const int i = tid1 + (NV + k) * THREADS;
       // every slot holds data (lanes past the end of the row hold a copy of its last vector); read without a
       // branch, so that the reads stay in this order, and mask afterwards where the row can end
-      const u32x4 v = lrow[k * kRowThreads + tid1];
+      const u32x4 v = lrow[k * THREADS + tid1];
       float x[N];
       Vec<T>::unpack(v, x);
       if (NV + k >= KFULL) {
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(kRowThreads) void fused_logprob_softmax_kernel(
   if (tid == 0) {
     MaxSum t = lds[0];
 #pragma unroll
-    for (int w = 1; w < kRowWaves; ++w) t = merge(t, lds[w]);
+    for (int w = 1; w < kWaves; ++w) t = merge(t, lds[w]);
     float lse, logp;
     if (y_ok) {
       const double l1p = log1p_scaled(t.s, (double)t.m - (double)zy * (double)scale);
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(kRowThreads) void fused_logprob_softmax_kernel(
   asm volatile("" : "+v"(tid2));
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    const int i = tid2 + k * kRowThreads;
+    const int i = tid2 + k * THREADS;
     float x[N];
     Vec<T>::unpack(q[k], x);
 #pragma unroll
@@ -227,9 +228,9 @@ __global__ __launch_bounds__(kRowThreads) void fused_logprob_softmax_kernel(
   if (NL > 0) {
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
-      const int i = tid2 + (NV + k) * kRowThreads;
+      const int i = tid2 + (NV + k) * THREADS;
       float x[N];
-      Vec<T>::unpack(lrow[k * kRowThreads + tid2], x);
+      Vec<T>::unpack(lrow[k * THREADS + tid2], x);
 #pragma unroll
       for (int j = 0; j < N; ++j) x[j] = exp2_fast(__builtin_fmaf(x[j], scale, shift));
       if (i < nvec) store_stream(sv + i, Vec<T>::pack(x));
@@ -247,17 +248,17 @@ __global__ __launch_bounds__(kRowThreads) void fused_logprob_softmax_kernel(
 constexpr int kSlotBytes = kRowThreads * 16;      // one LDS slot: a 16-byte vector per lane
 constexpr int kLdsSlots = 9;                      // 144 KiB of the 160 KiB of a compute unit
 
-template <typename T, bool ALIGNED, int NV, int NL, int KFULL>
+template <typename T, bool ALIGNED, int THREADS, int NV, int NL, int KFULL>
 int launch_nv(ais_ctx* ctx, const T* z, long long n_rows, int vocab, long long row_stride, const int* token_ids,
               const unsigned char* valid, float inv_t, float* logp, float* lse, T* sgrad) {
-  auto kernel = fused_logprob_softmax_kernel<T, ALIGNED, NV, NL, KFULL>;
+  auto kernel = fused_logprob_softmax_kernel<T, ALIGNED, THREADS, NV, NL, KFULL>;
   if (NL > 0) {
     static std::once_flag once[kMaxDevices];               // the attribute belongs to the function on one device
     static bool ok[kMaxDevices];
     if (!allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kernel), NL * kSlotBytes, once, ok))
       return hip_fail(ctx, hipErrorInvalidValue);
   }
-  kernel<<<dim3((unsigned)n_rows), dim3(kRowThreads), NL * kSlotBytes, ctx->stream>>>(
+  kernel<<<dim3((unsigned)n_rows), dim3(THREADS), NL * kSlotBytes, ctx->stream>>>(
       z, row_stride, vocab, token_ids, valid, inv_t, logp, lse, sgrad, ctx->status_dev);
   return AIS_OK;
 }
@@ -290,8 +291,25 @@ int launch_typed(ais_ctx* ctx, int need, const void* logits, long long n_rows, i
   // an unaligned row may have lost up to 8 to its head
 #define AIS_FUSED_CASE(PREV, NEED, NVAL, NLVAL)                                                      \
   if (need <= NEED)                                                                                  \
-    return launch_nv<T, ALIGNED, NVAL, NLVAL, (ALIGNED || PREV == 0 ? PREV : PREV - 1)>(             \
+    return launch_nv<T, ALIGNED, kRowThreads, NVAL, NLVAL, (ALIGNED || PREV == 0 ? PREV : PREV - 1)>(             \
         ctx, z, n_rows, vocab, row_stride, token_ids, valid, inv_t, logp, lse, s);
+  // Narrow rows share fewer threads, down to one wavefront, so that more of them are on their way in a compute unit (one or
+  // two have room there with 1,024 threads) and fewer wavefronts meet between a row's two phases.  41,643 rows, us with
+  // 1,024, 512, 256, 128 and 64 threads: bf16, 1,000 logits 385, 133, 72, 65, 44; 4,096 417, 168, 114, 112, 113; 6,000 440, 196,
+  // 177, 189, 191; 12,288 507, 337, 343, 349; 16,384 525, 489, 464, 481; 20,000 592, 615, 627; fp32, 1,000 330, 139, 76, 59,
+  // 63; 3,001 272 (in two passes), 184, 161, 165; 8,192 468, 495, 458, 481.
+  const int nvec = vocab / Vec<T>::N;
+#define AIS_FUSED_NARROW(MOST, THREADS, NVAL)                                                                    \
+  if (nvec <= MOST)                                                                                              \
+    return launch_nv<T, ALIGNED, THREADS, NVAL, 0, 0>(ctx, z, n_rows, vocab, row_stride, token_ids, valid, inv_t, \
+                                                      logp, lse, s);
+  if constexpr (ALIGNED) {
+    AIS_FUSED_NARROW(256, 64, 4)
+  }
+  AIS_FUSED_NARROW(512, 128, 4)
+  AIS_FUSED_NARROW(1024, 256, 4)
+  AIS_FUSED_NARROW(2048, 256, 8)
+#undef AIS_FUSED_NARROW
   AIS_FUSED_CASE(0, 4, 4, 0)
   AIS_FUSED_CASE(4, 8, 8, 0)
   AIS_FUSED_CASE(8, 12, 12, 0)
@@ -314,21 +332,15 @@ int launch_typed(ais_ctx* ctx, int need, const void* logits, long long n_rows, i
 
 }  // namespace
 
-// Sets *used_registers to false (and launches nothing) when the row does not fit the register file, the two arrays
-// lie differently relative to 128-byte lines, or many narrow rows are not 16-byte aligned; the caller then runs the
-// two-pass kernels.  For those 1,024 threads a row are too many, as few of a compute unit's rows are then on their way at a
-// time (8,192 rows of 63 bf16 logits 89 us, in two passes 26; of 4,001 97 and 53; of 8,191 105 and 88; of 10,001 110 and
-// 103, but with 2,000 rows 37 both; fp32, 63 76 and 25, 4,001 86 and 82, 5,001 88 and 90).  A row per compute unit is
-// better off with one launch (300 rows of 4,001 fp32 logits 16.8 and 17.9 us).
+// Sets *used_registers to false (and launches nothing) when the row does not fit the register file or the two arrays lie
+// differently relative to 128-byte lines; the caller then runs the two-pass kernels.
 int launch_fused_logprob_softmax(ais_ctx* ctx, const void* logits, ais_dtype dtype, long long n_rows, int vocab,
                                  long long row_stride, const int* token_ids, const unsigned char* valid,
                                  float inv_temperature, float* logp_out, float* lse_out, void* sgrad,
                                  bool* used_registers) {
   const int need = dtype == AIS_BF16 ? vectors_per_lane<bf16_t>(logits, sgrad, vocab, row_stride)
                                      : vectors_per_lane<float>(logits, sgrad, vocab, row_stride);
-  const bool narrow = need == 1 && n_rows > 2LL * ctx->n_cus &&
-                      !rows_aligned(logits, sgrad, row_stride, dtype == AIS_BF16 ? 2 : 4);
-  *used_registers = need > 0 && !narrow;
+  *used_registers = need > 0;
   if (!*used_registers || n_rows == 0) return AIS_OK;
   ScopedTimer timer(ctx, AIS_K_FUSED);
   auto launch = [&](auto type) {

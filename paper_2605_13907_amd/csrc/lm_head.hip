@@ -78,9 +78,14 @@ struct LmDevPlan {
   int n_eval, n_tblocks, n_chunks, tiles_per_chunk, per_xcd, n_items, tb_group, pad;
 };
 
-// Cost of splitting n_vtiles vocabulary tiles into `chunks` equal chunks (rounds of the busiest XCD times the length of
-// a work item), or -1 where that gives more than max_items work items.  Workgroups are bound to XCDs by their index, so
-// what counts is the rounds of the busiest XCD (n_cus / 8 units each).
+// Cost of splitting n_vtiles vocabulary tiles into `chunks` equal chunks, or -1 where that gives more than max_items work
+// items.  Workgroups are bound to XCDs by their index, so what counts is the rounds of the busiest XCD (n_cus / 8 units
+// each) times the length of a work item, to which its start adds about three tiles; and what those rounds have to fetch:
+// the workgroups resident on an XCD sit on b chunks of n_cus / (8 b) token blocks, so every tile of the embedding serves
+// that many of them and every token block b.  41,643 rows x 151,936 x 4,096, ms, 3 chunks (2 rounds) 38.2, 6 (4 rounds)
+// 38.6, 14 (9 rounds, which counting rounds alone prefers by 1 %) 40.6, 8 (6 rounds) 44.9; 32,768 rows 2 chunks (one
+// round) 33.1, 3 37.4, 6 (3 rounds) 29.8, 8 (4 rounds) 30.1; chosen by this and by the rounds alone: 41,643 rows 38.0 and
+// 38.4-40.6, 32,768 28.7 and 31.4, 20,000 18.4 and 18.9, 10,240 9.3 and 9.9, 6,144 5.7 and 5.9.
 __host__ __device__ inline long long lm_chunks_cost(int chunks, int n_tblocks, int n_vtiles, int n_cus,
                                                     long long max_items, int* n_chunks, int* tiles_per_chunk) {
   const int cus_per_xcd = n_cus >= 8 ? n_cus / 8 : 1;
@@ -92,7 +97,8 @@ __host__ __device__ inline long long lm_chunks_cost(int chunks, int n_tblocks, i
   if (items > max_items && chunks > 1) return -1;
   const long long per_xcd = (items + 7) / 8;
   const long long rounds = (per_xcd + cus_per_xcd - 1) / cus_per_xcd;
-  return rounds * (tpc + 1);                              // + 1: set-up and tear-down of a work item, in tile units
+  const int b = real < cus_per_xcd ? real : cus_per_xcd;
+  return rounds * (tpc + 3) * (256 + 77 * b / cus_per_xcd + 77 / b);
 }
 
 // Most chunks the vocabulary is split into: 64, or as many as give two work items per compute unit where there are only

@@ -72,10 +72,10 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 q) { return __builtin_bit_cast
 // ---- pieces of the tile kernel ---------------------------------------------------------------------
 
 // Decomposition of the evaluated rows into work items, decided on the device once their number is known
-// (lm_head_setup_kernel): n_tblocks blocks of 256 evaluated rows x n_chunks chunks of tiles_per_chunk
+// (lm_head_setup_kernel): n_tblocks blocks of block_rows (a multiple of 16, at most 256) evaluated rows x n_chunks chunks of tiles_per_chunk
 // vocabulary tiles, per_xcd work items for each of the 8 XCDs.
 struct LmDevPlan {
-  int n_eval, n_tblocks, n_chunks, tiles_per_chunk, per_xcd, n_items, tb_group, pad;
+  int n_eval, n_tblocks, n_chunks, tiles_per_chunk, per_xcd, n_items, tb_group, block_rows;
 };
 
 // Cost of splitting n_vtiles vocabulary tiles into `chunks` equal chunks, or -1 where that gives more than max_items work
@@ -125,6 +125,7 @@ struct LmRows {
 struct LmItem {
   int tb, ch, vt0, vt1, t0, n_eval, n_chunks;
   int lane, wave, wv, wt, quarter, col;
+  int col0, n_cols;      // first of the wavefront's columns of 16 tokens inside the block, and their number, 0 to 4
   __device__ __forceinline__ bool init(const LmDevPlan* __restrict__ plan, int n_vtiles) {
     // Workgroups are dealt to the 8 XCDs round-robin; every XCD takes a contiguous, equally long range of work
     // items (token block major): its resident workgroups then share a few token blocks' hidden-state slices and
@@ -144,11 +145,16 @@ struct LmItem {
     tb = g * group + (j - ch * gsize);
     vt0 = ch * tiles_per_chunk;
     vt1 = min(n_vtiles, vt0 + tiles_per_chunk);
-    t0 = tb * kLmTileT;
+    t0 = tb * plan->block_rows;
     lane = threadIdx.x & 63;
-    wave = threadIdx.x >> 6;
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     wv = wave & 1;                                               // position of the wavefront in the tile
     wt = wave >> 1;
+    // the block's columns are dealt evenly to the four wavefronts along the tokens: those of 195 rows (two blocks of a
+    // batch of 390) are 4, 3, 3 and 3 instead of 4, 4, 4 and a part of 4
+    const int cols = (min(plan->block_rows, n_eval - t0) + 15) >> 4;
+    n_cols = __builtin_amdgcn_readfirstlane((cols + 3 - wt) >> 2);
+    col0 = wt * (cols >> 2) + min(wt, cols & 3);
     quarter = lane >> 4;
     col = lane & 15;
     return true;
@@ -157,11 +163,12 @@ struct LmItem {
 
 typedef f32x4 LmAcc[kLmNI][kLmNJ];
 
+template <int NJ>
 __device__ __forceinline__ void lm_clear(LmAcc& acc) {
 #pragma unroll
   for (int i = 0; i < kLmNI; ++i)
 #pragma unroll
-    for (int j = 0; j < kLmNJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
 // Per-lane soft-max state of the lane's four token columns, in the base-2 domain (logit * scale).
@@ -171,13 +178,13 @@ struct LmSoftmax {
   // tok0 + 16 j: evaluated position of the lane's token column j; y[j]: its sampled token, -1 if there is none to find
   __device__ __forceinline__ void init(const LmItem& it, const LmRows& rows, int vocab,
                                        const int* __restrict__ token_ids) {
-    tok0 = it.t0 + it.wt * kLmWaveT + it.col;
+    tok0 = it.t0 + 16 * it.col0 + it.col;
 #pragma unroll
     for (int j = 0; j < kLmNJ; ++j) {
       run_m[j] = kNegHuge;
       run_s[j] = 0.f;
       y[j] = -1;
-      if (tok0 + 16 * j < it.n_eval) {
+      if (j < it.n_cols && tok0 + 16 * j < it.n_eval) {
         const int id = token_ids[rows.row(tok0 + 16 * j, it.n_eval)];
         y[j] = (id >= 0 && id < vocab) ? id : -1;
       }
@@ -185,6 +192,7 @@ struct LmSoftmax {
   }
   // Folds the finished tile `vt` into the running state.  Accumulator element v of MFMA tile i holds
   // vocabulary entry  vbase + 16 i + 4 quarter + v  of token column j.
+  template <int NJ>
   __device__ __forceinline__ void fold(LmAcc& acc, const LmItem& it, int vt, int vocab, float scale,
                                        float* __restrict__ zy_out) {
     const int vbase = vt * kLmTileV + it.wv * kLmWaveV;
@@ -197,11 +205,11 @@ struct LmSoftmax {
         for (int v = 0; v < 4; ++v) {
           const bool in = vbase + 16 * i + 4 * it.quarter + v < vocab;
 #pragma unroll
-          for (int j = 0; j < kLmNJ; ++j) acc[i][j][v] = in ? acc[i][j][v] : -__builtin_inff();
+          for (int j = 0; j < NJ; ++j) acc[i][j][v] = in ? acc[i][j][v] : -__builtin_inff();
         }
     }
 #pragma unroll
-    for (int j = 0; j < kLmNJ; ++j) {
+    for (int j = 0; j < NJ; ++j) {
       float tmax = kNegHuge;
 #pragma unroll
       for (int i = 0; i < kLmNI; ++i)
@@ -259,7 +267,7 @@ struct LmSoftmax {
         const float m = fmaxf(run_m[j], om);
         const float s = run_s[j] * exp2_fast(run_m[j] - m) + os * exp2_fast(om - m);
         const int tok = tok0 + 16 * j;
-        if (tok < it.n_eval) {
+        if (j < it.n_cols && tok < it.n_eval) {
           part_m[(long long)it.ch * it.n_eval + tok] = m;
           part_s[(long long)it.ch * it.n_eval + tok] = s;
         }
@@ -290,13 +298,13 @@ struct LmGrad {
                                        const int* __restrict__ token_ids, const LmGradArgs& ga) {
 #pragma unroll
     for (int j = 0; j < kLmNJ; ++j) {
-      const int tok = it.t0 + it.wt * kLmWaveT + j * 16 + it.col;
+      const int tok = it.t0 + 16 * (it.col0 + j) + it.col;
       row[j] = -1;
       y[j] = -1;
       shift[j] = 0.f;
       c[j] = 0.f;
       dy[j] = 0.f;
-      if (tok < it.n_eval) {
+      if (j < it.n_cols && tok < it.n_eval) {
         const int r = rows.row(tok, it.n_eval);
         row[j] = ga.compact ? tok : r;
         c[j] = ga.coeff[r];
@@ -312,11 +320,12 @@ struct LmGrad {
   // Writes the finished tile `vt`, zeros past the end of the chunk (a row of ds holds whole tiles, and the products that
   // read it take whole steps).  Accumulator element v of MFMA tile i holds vocabulary entry
   // vbase + 16 i + 4 quarter + v of token column j: four consecutive entries, 8 bytes, per tile.
+  template <int NJ>
   __device__ __forceinline__ void emit(const LmAcc& acc, const LmItem& it, int vt, int vocab, float scale,
                                        const LmGradArgs& ga) {
     const int vbase = vt * kLmTileV + it.wv * kLmWaveV;
 #pragma unroll
-    for (int j = 0; j < kLmNJ; ++j) {
+    for (int j = 0; j < NJ; ++j) {
       if (row[j] < 0) continue;
       bf16_t* out = ga.ds + (long long)row[j] * ga.ds_stride;
 #pragma unroll
@@ -421,7 +430,7 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_tile_kernel(
   // ---- fragments: lane reads row (16-row tile base + col), chunk 4 kk + quarter of a 128-byte row
   const int frag_off[2] = {lds_chunk_offset(it.col, it.quarter), lds_chunk_offset(it.col, 4 + it.quarter)};
   const int a_base = it.wv * kLmWaveV * 128;
-  const int b_base = kLmOperandBytes + it.wt * kLmWaveT * 128;
+  const int b_base = kLmOperandBytes + it.col0 * 16 * 128;
   bf16x8 a[4], b[2][kLmNJ];
   auto read_a = [&](int buf, int g) {                  // the fragment of group g (0..15) into its place in the ring
     a[g & 3] = as_bf16x8(*reinterpret_cast<const u32x4*>(lds + buf * kLmBufferBytes + a_base + (g & 7) * 2048 +
@@ -431,69 +440,80 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_tile_kernel(
     b[kk][j] = as_bf16x8(*reinterpret_cast<const u32x4*>(lds + buf * kLmBufferBytes + b_base + j * 2048 + frag_off[kk]));
   };
 
-  LmAcc acc;
-  lm_clear(acc);
   LmSoftmax sm;
   LmGrad gr;
   if (GRAD) gr.init(it, rows, vocab, token_ids, ga);
   else sm.init(it, rows, vocab, token_ids);
 
 #define AIS_PIN __builtin_amdgcn_sched_barrier(0)
-  int vt = it.vt0, kt = 0;
-  // ---- prologue: step 0 and the first copies of step 1 in flight, step 0 published
+  // All tiles of the work item, by a wavefront with NJ columns of tokens.  Every wavefront issues the same copies and comes
+  // to the same barriers, whatever its NJ.
+  auto walk = [&](auto columns) {
+    constexpr int NJ = decltype(columns)::value;
+    LmAcc acc;
+    lm_clear<NJ>(acc);
+    int vt = it.vt0, kt = 0;
+    // ---- prologue: step 0 and the first copies of step 1 in flight, step 0 published
 #pragma unroll
-  for (int q = 0; q < 8; ++q) copy_part(0, q);
+    for (int q = 0; q < 8; ++q) copy_part(0, q);
 #pragma unroll
-  for (int q = 0; q < 3; ++q) copy_part(1, q);
-  // copies complete in order: all but the last three are step 0's
-  asm volatile("s_waitcnt vmcnt(3)\n\ts_barrier" ::: "memory");
+    for (int q = 0; q < 3; ++q) copy_part(1, q);
+    // copies complete in order: all but the last three are step 0's
+    asm volatile("s_waitcnt vmcnt(3)\n\ts_barrier" ::: "memory");
 #pragma unroll
-  for (int j = 0; j < kLmNJ; ++j) read_b(0, 0, j);
+    for (int j = 0; j < NJ; ++j) read_b(0, 0, j);
 #pragma unroll
-  for (int g = 0; g < 3; ++g) read_a(0, g);
-  for (int s = 0; s < n_steps; ++s) {
-    const int buf = s & 1;
+    for (int g = 0; g < 3; ++g)
+      if (NJ > 0) read_a(0, g);
+    for (int s = 0; s < n_steps; ++s) {
+      const int buf = s & 1;
 #pragma unroll
-    for (int g = 0; g < 16; ++g) {
-      const int kk = g >> 3, i = g & 7;
+      for (int g = 0; g < 16; ++g) {
+        const int kk = g >> 3, i = g & 7;
 #pragma unroll
-      for (int j = 0; j < kLmNJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[g & 3], b[kk][j], acc[i][j], 0, 0, 0);
-      AIS_PIN;
-      // reads three groups ahead; the last two of the buffer together, so that all have arrived at the barrier
-      if (g <= 10) read_a(buf, g + 3);
-      if (g == 11) {
-        read_a(buf, 14);
-        read_a(buf, 15);                               // takes the place that group 11 has just used
-      }
-      if (g >= 2 && g < 6) read_b(buf, 1, g - 2);
-      if (g < 5) copy_part(buf ^ 1, g + 3);
-      AIS_PIN;
-      if (g == 12) {
-        // every copy in flight is of step s + 1
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        for (int j = 0; j < NJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[g & 3], b[kk][j], acc[i][j], 0, 0, 0);
         AIS_PIN;
-        read_a(buf ^ 1, 0);
-        read_b(buf ^ 1, 0, 0);
-        read_b(buf ^ 1, 0, 1);
+        // reads three groups ahead; the last two of the buffer together, so that all have arrived at the barrier
+        if (NJ > 0 && g <= 10) read_a(buf, g + 3);
+        if (NJ > 0 && g == 11) {
+          read_a(buf, 14);
+          read_a(buf, 15);                             // takes the place that group 11 has just used
+        }
+        if (g >= 2 && g - 2 < NJ) read_b(buf, 1, g - 2);
+        if (g < 5) copy_part(buf ^ 1, g + 3);
+        AIS_PIN;
+        if (g == 12) {
+          // every copy in flight is of step s + 1
+          asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+          AIS_PIN;
+          if (NJ > 0) read_a(buf ^ 1, 0);
+          if (NJ > 0) read_b(buf ^ 1, 0, 0);
+          if (NJ > 1) read_b(buf ^ 1, 0, 1);
+        }
+        if (g == 13) {
+          if (NJ > 2) read_b(buf ^ 1, 0, 2);
+          if (NJ > 3) read_b(buf ^ 1, 0, 3);
+          if (NJ > 0) read_a(buf ^ 1, 1);
+        }
+        if (NJ > 0 && g == 14) read_a(buf ^ 1, 2);
+        if (g >= 13) copy_part(buf, g - 13);
+        AIS_PIN;
       }
-      if (g == 13) {
-        read_b(buf ^ 1, 0, 2);
-        read_b(buf ^ 1, 0, 3);
-        read_a(buf ^ 1, 1);
+      if (++kt == n_ksteps) {
+        if (GRAD) gr.template emit<NJ>(acc, it, vt, vocab, scale, ga);
+        else sm.template fold<NJ>(acc, it, vt, vocab, scale, zy_out);
+        lm_clear<NJ>(acc);
+        kt = 0;
+        ++vt;
       }
-      if (g == 14) read_a(buf ^ 1, 2);
-      if (g >= 13) copy_part(buf, g - 13);
-      AIS_PIN;
     }
-    if (++kt == n_ksteps) {
-      if (GRAD) gr.emit(acc, it, vt, vocab, scale, ga);
-      else sm.fold(acc, it, vt, vocab, scale, zy_out);
-      lm_clear(acc);
-      kt = 0;
-      ++vt;
-    }
-  }
+  };
+  if (it.n_cols == 4) walk(std::integral_constant<int, 4>{});
+  else if (it.n_cols == 3) walk(std::integral_constant<int, 3>{});
+  else if (it.n_cols == 2) walk(std::integral_constant<int, 2>{});
+  else if (it.n_cols == 1) walk(std::integral_constant<int, 1>{});
+  else walk(std::integral_constant<int, 0>{});
 #undef AIS_PIN
   // copies of the last steps may still be in flight, and they land in LDS that finish() is about to reuse
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -588,7 +608,8 @@ __global__ __launch_bounds__(1024) void lm_head_setup_kernel(const unsigned char
     d.n_items = d.n_tblocks * d.n_chunks;
     d.per_xcd = (d.n_items + 7) / 8;
     d.tb_group = max(1, lm_token_block_group(n_tblocks));
-    d.pad = 0;
+    // as many rows in every block: a block's time goes with its columns of 16 (see LmItem)
+    d.block_rows = n_tblocks > 0 ? ((total + n_tblocks - 1) / n_tblocks + 15) / 16 * 16 : kLmTileT;
     plan[tid] = d;
   }
 }

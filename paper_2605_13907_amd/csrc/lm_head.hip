@@ -50,8 +50,8 @@ constexpr int kLmWaveT = 64;       //                4 along the tokens
 constexpr int kLmNI = kLmWaveV / 16;
 constexpr int kLmNJ = kLmWaveT / 16;
 constexpr int kLmOperandBytes = kLmTileV * kLmTileK * 2;            // 32 KiB: one operand slice
-constexpr int kLmBufferBytes = 2 * kLmOperandBytes;                 // W slice then H slice
-constexpr int kLmLdsBytes = 2 * kLmBufferBytes;                     // double buffer: 128 KiB
+// Operand slices in LDS: two of W (DEEP: three), then two of H.
+constexpr int lm_lds_bytes(bool deep) { return (deep ? 5 : 4) * kLmOperandBytes; }
 
 // Byte offset of 16-byte chunk `c` (0..7) of row `row` inside one operand slice.  A row is 128 bytes; the
 // chunk index is XORed with bits 1..3 of the row so that 16 consecutive rows read at the same logical
@@ -152,8 +152,8 @@ struct LmItem {
     wt = wave >> 1;
     // the block's columns are dealt evenly to the four wavefronts along the tokens: those of 195 rows (two blocks of a
     // batch of 390) are 4, 3, 3 and 3 instead of 4, 4, 4 and a part of 4
-    const int cols = (min(plan->block_rows, n_eval - t0) + 15) >> 4;
-    n_cols = __builtin_amdgcn_readfirstlane((cols + 3 - wt) >> 2);
+    const int cols = __builtin_amdgcn_readfirstlane((min(plan->block_rows, n_eval - t0) + 15) >> 4);
+    n_cols = (cols + 3 - wt) >> 2;
     col0 = wt * (cols >> 2) + min(wt, cols & 3);
     quarter = lane >> 4;
     col = lane & 15;
@@ -351,7 +351,7 @@ typedef const __attribute__((address_space(1))) void* glb_ptr;
 
 // ---- the tile kernel: any d_model that is a multiple of 8 -------------------------------------------------------
 // Steps of 64 elements of d_model; the two operand slices of a step (2 x 32 KiB) go from global memory straight into
-// one of two LDS buffers (global_load_lds_dwordx4: lane i of a wavefront deposits its 16 bytes at base + 16 i, so the
+// one of two LDS buffers (DEEP: of three for W; global_load_lds_dwordx4: lane i of a wavefront deposits its 16 bytes at base + 16 i, so the
 // swizzle is applied by choosing which chunk each lane fetches).  A row of a slice is a whole 128-byte line, so a copy
 // instruction of a wavefront asks L2 for 8 full lines.
 // A step is 16 groups of four MFMAs: group g multiplies fragment a(g) (16 vocabulary entries x 32 elements) by the
@@ -364,15 +364,17 @@ typedef const __attribute__((address_space(1))) void* glb_ptr;
 // groups that follow (three in this step, five in the next), half a step or more before they are awaited.  Measured at
 // 41,643 rows x 151,936 x 4,096 (39.0 ms): two copies after each of groups 13 and 14, then one after each of four
 // groups, 39.2; one after each from group 12 on 40.2; two after each of three groups 40.2; none before the next step
-// 41.4; all W copies before all H copies 40.3.  A fifth slice in LDS (160 KiB), which gives the W copies a step more
-// before they are awaited, is slower (41.2-42.7 ms): the copies are not short of time.
+// 41.4; all W copies before all H copies 40.3.
+// DEEP: W has a third slice in LDS (160 KiB in all) and is copied two steps ahead instead of one, H first in every set of
+// copies so that the wait can leave W's last four in flight.  See lm_deep for where that pays.
+// A wavefront multiplies as many columns of 16 tokens as its block gives it, 0 to 4, in a loop of its own for each number.
 // RAGGED: d_model is not a multiple of 64; lanes whose chunk of a tile's last step lies past the end of d_model fetch
 // zeros (both operands, so that an infinity in one does not meet the zeros of the other).
 // GRAD = false: every finished tile is folded into the running soft-max state (log-prob call).  GRAD = true: every
 // finished tile is written out as coeff (softmax - onehot) in bf16, lse being an input (gradient call).
 __device__ __align__(16) const bf16_t kLmZeros[8] = {};
 
-template <bool GRAD, bool RAGGED>
+template <bool GRAD, bool RAGGED, bool DEEP>
 __global__ __launch_bounds__(kLmThreads) void lm_head_tile_kernel(
     const bf16_t* __restrict__ hidden, long long ld_h, const bf16_t* __restrict__ weight, long long ld_w,
     LmRows rows, const LmDevPlan* __restrict__ plan, int d_model, int vocab, const int* __restrict__ token_ids,
@@ -404,40 +406,48 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_tile_kernel(
   };
   const int n_ksteps = (d_model + kLmTileK - 1) / kLmTileK;
   const int n_steps = (it.vt1 - it.vt0) * n_ksteps;
-  // cursor of the step being copied
-  int c_step = 0, c_kt = 0, c_vt = it.vt0;
-  point_w(c_vt);
-  // One of the eight copy instructions (W rows, H rows, then the same 64, 128 and 192 rows further) that bring the
-  // cursor's step into buffer `buf`; the eighth advances the cursor.  Once the cursor has reached the last step it
-  // stays there: the copies issued after that re-fetch the last step into a buffer nobody reads any more, which
-  // keeps the loop free of branches.
-  auto copy_part = [&](int buf, int q) {
-    unsigned char* base = lds + buf * kLmBufferBytes + (8 * wave + 64 * (q >> 1)) * 128;
-    const int k0 = c_kt * kLmTileK;
-    const bf16_t* src = ((q & 1) == 0 ? wp[q >> 1] : hp[q >> 1]) + k0;
+  // One of the four copy instructions (rows, then the same 64, 128 and 192 rows further) that bring a step's slice of W into
+  // the slice at byte `at`, or of H; the fourth advances the cursor.  Once the cursor of W has reached the last step it stays
+  // there: the copies issued after that re-fetch the last step into a slice nobody reads any more, which keeps the loop free
+  // of branches.  (H has the same rows for every tile: its cursor goes round.)
+  int w_step = 0, w_kt = 0, w_vt = it.vt0, h_kt = 0;
+  point_w(w_vt);
+  auto copy = [&](const bf16_t* row, int k0, int at, int q) {
+    const bf16_t* src = row + k0;
     if (RAGGED) src = k0 + cchunk * 8 < d_model ? src : kLmZeros;
-    __builtin_amdgcn_global_load_lds((glb_ptr)src, (lds_ptr)((q & 1) == 0 ? base : base + kLmOperandBytes), 16, 0, 0);
-    if (q == 7 && c_step + 1 < n_steps) {
-      ++c_step;
-      if (++c_kt == n_ksteps) {
-        c_kt = 0;
-        ++c_vt;
-        point_w(c_vt);
+    __builtin_amdgcn_global_load_lds((glb_ptr)src, (lds_ptr)(lds + at + (8 * wave + 64 * q) * 128), 16, 0, 0);
+  };
+  auto copy_w = [&](int at, int q) {
+    copy(wp[q], w_kt * kLmTileK, at, q);
+    if (q == 3 && w_step + 1 < n_steps) {
+      ++w_step;
+      if (++w_kt == n_ksteps) {
+        w_kt = 0;
+        ++w_vt;
+        point_w(w_vt);
       }
     }
+  };
+  auto copy_h = [&](int at, int q) {
+    copy(hp[q], h_kt * kLmTileK, at, q);
+    if (q == 3) h_kt = h_kt + 1 == n_ksteps ? 0 : h_kt + 1;
+  };
+  // The eight copies of a set, in order: those of H first where W runs a step further ahead, in turns otherwise.
+  auto copy_part = [&](int w_at, int h_at, int p) {
+    if (DEEP ? p < 4 : (p & 1) != 0) copy_h(h_at, DEEP ? p : p >> 1);
+    else copy_w(w_at, DEEP ? p - 4 : p >> 1);
   };
 
   // ---- fragments: lane reads row (16-row tile base + col), chunk 4 kk + quarter of a 128-byte row
   const int frag_off[2] = {lds_chunk_offset(it.col, it.quarter), lds_chunk_offset(it.col, 4 + it.quarter)};
   const int a_base = it.wv * kLmWaveV * 128;
-  const int b_base = kLmOperandBytes + it.col0 * 16 * 128;
+  const int b_base = it.col0 * 16 * 128;
   bf16x8 a[4], b[2][kLmNJ];
-  auto read_a = [&](int buf, int g) {                  // the fragment of group g (0..15) into its place in the ring
-    a[g & 3] = as_bf16x8(*reinterpret_cast<const u32x4*>(lds + buf * kLmBufferBytes + a_base + (g & 7) * 2048 +
-                                                         frag_off[g >> 3]));
+  auto read_a = [&](int at, int g) {                   // the fragment of group g (0..15) into its place in the ring
+    a[g & 3] = as_bf16x8(*reinterpret_cast<const u32x4*>(lds + at + a_base + (g & 7) * 2048 + frag_off[g >> 3]));
   };
-  auto read_b = [&](int buf, int kk, int j) {
-    b[kk][j] = as_bf16x8(*reinterpret_cast<const u32x4*>(lds + buf * kLmBufferBytes + b_base + j * 2048 + frag_off[kk]));
+  auto read_b = [&](int at, int kk, int j) {
+    b[kk][j] = as_bf16x8(*reinterpret_cast<const u32x4*>(lds + at + b_base + j * 2048 + frag_off[kk]));
   };
 
   LmSoftmax sm;
@@ -453,20 +463,27 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_tile_kernel(
     LmAcc acc;
     lm_clear<NJ>(acc);
     int vt = it.vt0, kt = 0;
-    // ---- prologue: step 0 and the first copies of step 1 in flight, step 0 published
+    // slices of the step at hand, of the next one and (DEEP: of W) of the one after that
+    constexpr int kH = (DEEP ? 3 : 2) * kLmOperandBytes;
+    int w0 = 0, w1 = kLmOperandBytes, w2 = DEEP ? 2 * kLmOperandBytes : 0, h0 = kH, h1 = kH + kLmOperandBytes;
+    // ---- prologue: step 0 and the first copies that follow it in flight, step 0 published
 #pragma unroll
-    for (int q = 0; q < 8; ++q) copy_part(0, q);
+    for (int p = 0; p < 8; ++p) copy_part(w0, h0, p);
+    if (DEEP) {
 #pragma unroll
-    for (int q = 0; q < 3; ++q) copy_part(1, q);
-    // copies complete in order: all but the last three are step 0's
-    asm volatile("s_waitcnt vmcnt(3)\n\ts_barrier" ::: "memory");
+      for (int q = 0; q < 4; ++q) copy_w(w1, q);
+    }
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) read_b(0, 0, j);
+    for (int p = 0; p < 3; ++p) copy_part(DEEP ? w2 : w1, h1, p);
+    // copies complete in order: all but the last three (DEEP: seven) are step 0's
+    if (DEEP) asm volatile("s_waitcnt vmcnt(7)\n\ts_barrier" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(3)\n\ts_barrier" ::: "memory");
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) read_b(h0, 0, j);
 #pragma unroll
     for (int g = 0; g < 3; ++g)
-      if (NJ > 0) read_a(0, g);
+      if (NJ > 0) read_a(w0, g);
     for (int s = 0; s < n_steps; ++s) {
-      const int buf = s & 1;
 #pragma unroll
       for (int g = 0; g < 16; ++g) {
         const int kk = g >> 3, i = g & 7;
@@ -475,30 +492,39 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_tile_kernel(
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[g & 3], b[kk][j], acc[i][j], 0, 0, 0);
         AIS_PIN;
         // reads three groups ahead; the last two of the buffer together, so that all have arrived at the barrier
-        if (NJ > 0 && g <= 10) read_a(buf, g + 3);
+        if (NJ > 0 && g <= 10) read_a(w0, g + 3);
         if (NJ > 0 && g == 11) {
-          read_a(buf, 14);
-          read_a(buf, 15);                             // takes the place that group 11 has just used
+          read_a(w0, 14);
+          read_a(w0, 15);                             // takes the place that group 11 has just used
         }
-        if (g >= 2 && g - 2 < NJ) read_b(buf, 1, g - 2);
-        if (g < 5) copy_part(buf ^ 1, g + 3);
+        if (g >= 2 && g - 2 < NJ) read_b(h0, 1, g - 2);
+        if (g < 5) copy_part(DEEP ? w2 : w1, h1, g + 3);
         AIS_PIN;
         if (g == 12) {
-          // every copy in flight is of step s + 1
-          asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+          // every copy in flight is of step s + 1 (DEEP: or one of the last four, W of step s + 2)
+          if (DEEP) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+          else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
           AIS_PIN;
-          if (NJ > 0) read_a(buf ^ 1, 0);
-          if (NJ > 0) read_b(buf ^ 1, 0, 0);
-          if (NJ > 1) read_b(buf ^ 1, 0, 1);
+          if (NJ > 0) read_a(w1, 0);
+          if (NJ > 0) read_b(h1, 0, 0);
+          if (NJ > 1) read_b(h1, 0, 1);
         }
         if (g == 13) {
-          if (NJ > 2) read_b(buf ^ 1, 0, 2);
-          if (NJ > 3) read_b(buf ^ 1, 0, 3);
-          if (NJ > 0) read_a(buf ^ 1, 1);
+          if (NJ > 2) read_b(h1, 0, 2);
+          if (NJ > 3) read_b(h1, 0, 3);
+          if (NJ > 0) read_a(w1, 1);
         }
-        if (NJ > 0 && g == 14) read_a(buf ^ 1, 2);
-        if (g >= 13) copy_part(buf, g - 13);
+        if (NJ > 0 && g == 14) read_a(w1, 2);
+        if (g >= 13) copy_part(w0, h0, g - 13);        // the slices that the barrier has freed
         AIS_PIN;
+      }
+      {
+        const int w = w0, h = h0;
+        w0 = w1;
+        w1 = DEEP ? w2 : w;
+        w2 = w;
+        h0 = h1;
+        h1 = h;
       }
       if (++kt == n_ksteps) {
         if (GRAD) gr.template emit<NJ>(acc, it, vt, vocab, scale, ga);
@@ -768,22 +794,30 @@ size_t lm_grad_dlogits_bytes(long long m_rows, long long vocab, long long asked,
   return std::max(own, 2 * (size_t)std::min(kLmTileT * kLmTileV * tiles, kLmGradFewBlocks * kLmTileT * whole));
 }
 
-template <bool GRAD>
+template <bool GRAD, bool DEEP>
 int launch_lm_tile(ais_ctx* ctx, int grid, const void* hidden, long long ld_h, const void* weight, long long ld_w,
                      LmRows rows, const LmDevPlan* dplan, int d_model, int vocab, const int* token_ids, float scale,
                      int n_vtiles, float* part_m, float* part_s, float* zy, const LmGradArgs& ga) {
   static std::once_flag once[2][kMaxDevices];                          // per function and device
   static bool ok[2][kMaxDevices];
   const int ragged = d_model % kLmTileK != 0 ? 1 : 0;
-  auto kernel = ragged ? lm_head_tile_kernel<GRAD, true> : lm_head_tile_kernel<GRAD, false>;
-  if (!allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kernel), kLmLdsBytes, once[ragged], ok[ragged]))
+  auto kernel = ragged ? lm_head_tile_kernel<GRAD, true, DEEP> : lm_head_tile_kernel<GRAD, false, DEEP>;
+  if (!allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kernel), lm_lds_bytes(DEEP), once[ragged], ok[ragged]))
     return hip_fail(ctx, hipErrorInvalidValue);
   ScopedTimer timer(ctx, GRAD ? AIS_K_LM_HEAD_GRAD : AIS_K_LM_HEAD);
-  kernel<<<grid, kLmThreads, kLmLdsBytes, ctx->stream>>>(static_cast<const bf16_t*>(hidden), ld_h,
+  kernel<<<grid, kLmThreads, lm_lds_bytes(DEEP), ctx->stream>>>(static_cast<const bf16_t*>(hidden), ld_h,
                                                          static_cast<const bf16_t*>(weight), ld_w, rows, dplan, d_model,
                                                          vocab, token_ids, scale, n_vtiles, part_m, part_s, zy, ga);
   return hip_fail(ctx, hipGetLastError());
 }
+
+// Whether W runs two steps ahead: where few token blocks share what the embedding brings, so that its way from HBM is what
+// a step waits for.  Log-prob, us without and with, x 151,936 x 4,096: 64 rows 304 and 241, 300 494 and 387, 390 520 and 462,
+// 520 687 and 568, 1,000 1,014 and 963, 2,000 2,011 and 1,906, 4,096 3,842 and 3,718, 7,168 6,528 and 6,481, 8,192 7,277 and
+// 7,331, 41,643 38.1 and 39.9 ms.  The gradient's chunks are short items, most of them in their first tiles: 4,096 rows x
+// 126,464 x 4,096 10.17 and 9.90 ms, 16,384 x 32,000 x 4,096 10.61 and 10.39, 12,000 x 126,464 x 2,048 16.4 and 16.0, but
+// 3,000 x 50,257 x 1,024 1.23 and 1.25.
+bool lm_deep(bool grad, long long n_rows, int d_model) { return grad ? d_model >= 2048 : n_rows <= 6144; }
 
 int launch_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long ld_h, const void* weight, long long ld_w,
                            long long n_rows, int d_model, int vocab, const int* token_ids,
@@ -800,7 +834,10 @@ int launch_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long ld_h, con
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(ctx, e);
   LmRows rows{valid != nullptr ? row_index : nullptr};
-  const int rc = launch_lm_tile<false>(ctx, max_items, hidden, ld_h, weight, ld_w, rows, dplan, d_model, vocab, token_ids,
+  // (how many rows a mask leaves is known on the device only: half of them is the guess)
+  auto launch = lm_deep(false, valid != nullptr ? n_rows / 2 : n_rows, d_model) ? launch_lm_tile<false, true>
+                                                                                : launch_lm_tile<false, false>;
+  const int rc = launch(ctx, max_items, hidden, ld_h, weight, ld_w, rows, dplan, d_model, vocab, token_ids,
                                        inv_temperature * kLog2e, plan.n_vtiles, part_m, part_s, zy, LmGradArgs{});
   if (rc != AIS_OK) return rc;
   lm_head_merge_kernel<<<(unsigned)((n_rows + kMergeRows - 1) / kMergeRows), kMergeRows * kMergeWays, 0, ctx->stream>>>(
@@ -841,7 +878,8 @@ int launch_lm_head_dlogits_chunk(ais_ctx* ctx, const void* hidden, long long ld_
   const LmDevPlan* dplan = static_cast<const LmDevPlan*>(dev_plan) + which;
   LmRows rows{row_index};
   LmGradArgs ga{lse, logp, coeff, static_cast<bf16_t*>(ds), ds_stride, y_off, row_index != nullptr ? 1 : 0};
-  const int rc = launch_lm_tile<true>(ctx, max_items, hidden, ld_h, weight, ld_w, rows, dplan, d_model, vocab,
+  auto launch = lm_deep(true, n_rows, d_model) ? launch_lm_tile<true, true> : launch_lm_tile<true, false>;
+  const int rc = launch(ctx, max_items, hidden, ld_h, weight, ld_w, rows, dplan, d_model, vocab,
                                         token_ids, inv_temperature * kLog2e, plan.n_vtiles, nullptr, nullptr, nullptr,
                                         ga);
   if (rc != AIS_OK) return rc;

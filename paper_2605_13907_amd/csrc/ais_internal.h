@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "ais.h"
+#include "row_coeff.h"
 
 namespace ais {
 
@@ -144,11 +145,12 @@ int launch_diagnostics(ais_ctx* ctx, const float* logp_train, const float* logp_
                        long long n_rows, const long long* cu_rows, int n_resp, int group_size,
                        const float* rewards, const ais_params& p, int* tile_off, double* partial,
                        bool in_static, float* adv_out, int* count_out, ais_diag* diag_out);
-int launch_row_coeff(ais_ctx* ctx, const float* logp_train, const float* logp_roll, const float* logp_old,
-                     const float* logp_ref, const unsigned char* valid, long long n_rows,
-                     const long long* cu_rows, int n_resp, const float* adv, const int* count,
-                     const ais_diag* diag, const ais_params& p, int* tile_off, double* partial, float* g_out,
+int launch_row_coeff(ais_ctx* ctx, const CoeffInputs& in, long long n_rows, int* tile_off, double* partial, float* g_out,
                      float* wtilde_out, double* loss_out, float g_scale);
+// Coefficients, loss and gradient in one launch, for batches small enough; false where this one is not.
+bool try_loss_dlogits_small(ais_ctx* ctx, const CoeffInputs& in, const void* logits, ais_dtype dtype, long long n_rows,
+                            int vocab, long long row_stride, const int* token_ids, const float* lse, float* wtilde_out,
+                            double* loss_out, void* dlogits);
 int launch_copy(ais_ctx* ctx, void* dst, const void* src, long long bytes);
 int launch_fp8_quantize(ais_ctx* ctx, const void* logits, ais_dtype dtype, long long n_rows, int vocab,
                         long long row_stride, unsigned char* codes, long long codes_stride, float* scale_out);

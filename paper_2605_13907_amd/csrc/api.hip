@@ -367,14 +367,18 @@ int ais_grpo_loss_grad(ais_ctx* ctx, const void* logits, ais_dtype dtype, long l
   const WorkspaceLayout w = workspace_layout(n_rows, n_resp);
   rc = ensure_workspace(ctx, w.total);
   if (rc != AIS_OK) return rc;
+  const CoeffInputs in{logp_train, logp_roll, logp_old, logp_ref, valid, cu_rows, n_resp, adv,
+                       count,      diag,      *params,  std::log((double)params->C)};
+  if (try_loss_dlogits_small(ctx, in, logits, dtype, n_rows, (int)vocab, row_stride, token_ids, lse, wtilde_out, loss_out,
+                             dlogits))
+    return hip_fail(ctx, hipGetLastError());
   char* ws = static_cast<char*>(ctx->ws);
   int* tile_off = reinterpret_cast<int*>(ws + w.tile_off);
   float* g = reinterpret_cast<float*>(ws + w.g);
   rc = plan_for_step(ctx, cu_rows, n_resp, n_rows, tile_off);
   if (rc != AIS_OK) return rc;
-  rc = launch_row_coeff(ctx, logp_train, logp_roll, logp_old, logp_ref, valid, n_rows, cu_rows, n_resp, adv, count,
-                        diag, *params, tile_off, reinterpret_cast<double*>(ws + w.partial), g,
-                        wtilde_out, loss_out, 1.0f);
+  rc = launch_row_coeff(ctx, in, n_rows, tile_off, reinterpret_cast<double*>(ws + w.partial), g, wtilde_out, loss_out,
+                        1.0f);
   if (rc != AIS_OK) return rc;
   return launch_dlogits(ctx, logits, dtype, n_rows, (int)vocab, row_stride, token_ids, g, nullptr, lse, logp_train,
                         params->inv_temperature, dlogits);
@@ -425,9 +429,10 @@ int ais_grpo_row_scale(ais_ctx* ctx, const float* logp_train, const float* logp_
   int* tile_off = reinterpret_cast<int*>(ws + w.tile_off);
   rc = plan_for_step(ctx, cu_rows, n_resp, n_rows, tile_off);
   if (rc != AIS_OK) return rc;
-  return launch_row_coeff(ctx, logp_train, logp_roll, logp_old, logp_ref, valid, n_rows, cu_rows, n_resp, adv, count,
-                          diag, *params, tile_off, reinterpret_cast<double*>(ws + w.partial), g_out,
-                          wtilde_out, loss_out, params->inv_temperature);
+  const CoeffInputs in{logp_train, logp_roll, logp_old, logp_ref, valid, cu_rows, n_resp, adv,
+                       count,      diag,      *params,  std::log((double)params->C)};
+  return launch_row_coeff(ctx, in, n_rows, tile_off, reinterpret_cast<double*>(ws + w.partial), g_out, wtilde_out,
+                          loss_out, params->inv_temperature);
 }
 
 int ais_fp8_quantize_rows(ais_ctx* ctx, const void* logits, ais_dtype dtype, long long n_rows, long long vocab,

@@ -18,6 +18,7 @@
 // 512 19.8, 13.8 -> 14.1, 9.7; 1,200,000 in 1,024 (with stale policy and KL term) 38.0, 29.5 -> 21.8, 17.1; 4,000,000 in 8
 // 50, 43 -> 33.5, 34.
 #include "ais_internal.h"
+#include "row_coeff.h"
 
 #include <algorithm>
 #include <cmath>
@@ -25,6 +26,11 @@
 
 namespace ais {
 namespace {
+
+using dev::CoeffRule;
+using dev::RowTerm;
+using dev::response_weight;
+using dev::row_term;
 
 // What a workgroup of one launch leaves for the workgroup that finishes last goes through device-scope accesses: they
 // reach memory that every XCD sees, so no cache has to be written back or invalidated for them.
@@ -524,10 +530,22 @@ __global__ __launch_bounds__(kThreads, 4) void diag_reduce_kernel(
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int per = (n_tiles + (int)gridDim.x - 1) / (int)gridDim.x;
   const int b0 = blockIdx.x * per, b1 = min(n_tiles, b0 + per);
+  // the advantages, by the wavefronts that have no tile first
+  auto advantages = [&] {
+    const int i = kThreads - 1 - (int)threadIdx.x;
+    if (SELF && i < n_resp) s_adv[i] = advantage(s_rewards, i, group_size, p);
+  };
+  if (b0 >= b1) {                                              // uniform: a workgroup without tiles
+    __syncthreads();
+    advantages();
+  }
   for (int w0 = b0; w0 < b1; w0 += kWaves) {                   // uniform for the workgroup
     tiling.open(w0);
     const int b = w0 + wave;
-    if (b >= b1) continue;
+    if (b >= b1) {
+      if (w0 == b0) advantages();
+      continue;
+    }
     const Tile tile = tiling.tile(b, w0);
     float ltf[kLaneRows], lrf[kLaneRows];
     unsigned char live[kLaneRows] = {1, 1, 1, 1};
@@ -547,6 +565,7 @@ __global__ __launch_bounds__(kThreads, 4) void diag_reduce_kernel(
     double sabs = 0, sd = 0, sdp = 0;
     int nclip = 0;
     if (tile.len > 0) load(0);
+    if (w0 == b0) advantages();                                // while the rows are on their way
     for (int c0 = 0; c0 < tile.len; c0 += kChunkRows) {        // uniform for the wavefront
       double w[kLaneRows] = {}, some = 0;
       bool was[kLaneRows] = {}, any = false;
@@ -604,12 +623,6 @@ __global__ __launch_bounds__(kThreads, 4) void diag_reduce_kernel(
       partials.put(b, {mw.mean, mw.m2, sabs, sd, sdp, __builtin_bit_cast(double, counts)});
     }
   }
-  // the advantages, by the wavefronts that have no tile first
-  if (SELF) {
-    __syncthreads();                                 // (there may have been no window)
-    const int i = kThreads - 1 - (int)threadIdx.x;
-    if (i < n_resp) s_adv[i] = advantage(s_rewards, i, group_size, p);
-  }
   // ---- level 2, in the workgroup that finishes last ----
   if (last_workgroup(tickets))
     diag_final<SELF>(partials, tiling, n_resp, (int)((n_rows + (1LL << rule.shift) - 1) >> rule.shift), group_size,
@@ -619,22 +632,17 @@ __global__ __launch_bounds__(kThreads, 4) void diag_reduce_kernel(
 // ---- per-row coefficient of the gradient, rectification weight, loss ------------------------------------------------
 template <bool SELF>
 __global__ __launch_bounds__(kThreads, 4) void row_coeff_kernel(
-    const float* __restrict__ logp_train, const float* __restrict__ logp_roll, const float* __restrict__ logp_old,
-    const float* __restrict__ logp_ref, const unsigned char* __restrict__ valid, long long n_rows,
-    const long long* __restrict__ cu_rows, int n_resp, const float* __restrict__ adv,
-    const int* __restrict__ count, const ais_diag* __restrict__ diag, ais_params p, double lnC,
-    const int* __restrict__ tile_off, TileRule rule, double* partial, float* __restrict__ g_out,
-    float* __restrict__ wtilde_out, float g_scale, double* __restrict__ loss_out, int* status, Tickets tickets) {
+    CoeffInputs in, long long n_rows, const int* __restrict__ tile_off, TileRule rule, double* partial,
+    float* __restrict__ g_out, float* __restrict__ wtilde_out, float g_scale, double* __restrict__ loss_out, int* status,
+    Tickets tickets) {
   __shared__ double lds[kWaves];
   __shared__ double own_partials[kOwnTiles];
-  const double alpha = diag->alpha;
+  const CoeffRule coeff(in.p, in.diag->alpha, in.lnC, in.logp_old != nullptr, in.logp_ref != nullptr);
   Tiling<SELF> tiling;
-  tiling.init(tile_off, cu_rows, n_resp, n_rows, rule.shift, rule.max_tiles, status);
+  tiling.init(tile_off, in.cu_rows, in.n_resp, n_rows, rule.shift, rule.max_tiles, status);
   const int n_tiles = tiling.tiles();
   const Partials<1> partials{partial, own_partials, rule.max_tiles, rule.max_tiles <= kOwnTiles};
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const double lo_clip = 1.0 - (double)p.clip_eps, hi_clip = 1.0 + (double)p.clip_eps;
-  const bool kl = (logp_ref != nullptr) && (p.beta_kl > 0.f);
   const int per = (n_tiles + (int)gridDim.x - 1) / (int)gridDim.x;
   const int b0 = blockIdx.x * per, b1 = min(n_tiles, b0 + per);
   for (int w0 = b0; w0 < b1; w0 += kWaves) {                   // uniform for the workgroup
@@ -642,8 +650,8 @@ __global__ __launch_bounds__(kThreads, 4) void row_coeff_kernel(
     const int b = w0 + wave;
     if (b >= b1) continue;
     const Tile tile = tiling.tile(b, w0);
-    const float a32 = adv[tile.resp];
-    const int cnt = count[tile.resp];
+    const float a32 = in.adv[tile.resp];
+    const int cnt = in.count[tile.resp];
     float ltf[kLaneRows], rollf[kLaneRows], oldf[kLaneRows], reff[kLaneRows];
     unsigned char live[kLaneRows] = {1, 1, 1, 1};
     auto load = [&](int c0) {                    // the chunk that begins at row c0 of the tile (rows past its end: its last)
@@ -651,25 +659,25 @@ __global__ __launch_bounds__(kThreads, 4) void row_coeff_kernel(
 #pragma unroll
       for (int k = 0; k < kLaneRows; ++k) {
         r[k] = tile.row0 + (unsigned)min(c0 + 64 * k + lane, tile.len - 1);
-        ltf[k] = logp_train[r[k]];
-        rollf[k] = logp_roll[r[k]];
+        ltf[k] = in.logp_train[r[k]];
+        rollf[k] = in.logp_roll[r[k]];
       }
-      if (logp_old != nullptr) {
+      if (coeff.has_old) {
 #pragma unroll
-        for (int k = 0; k < kLaneRows; ++k) oldf[k] = logp_old[r[k]];
+        for (int k = 0; k < kLaneRows; ++k) oldf[k] = in.logp_old[r[k]];
       }
-      if (kl) {
+      if (coeff.kl) {
 #pragma unroll
-        for (int k = 0; k < kLaneRows; ++k) reff[k] = logp_ref[r[k]];
+        for (int k = 0; k < kLaneRows; ++k) reff[k] = in.logp_ref[r[k]];
       }
-      if (valid != nullptr) {
+      if (in.valid != nullptr) {
 #pragma unroll
-        for (int k = 0; k < kLaneRows; ++k) live[k] = valid[r[k]];
+        for (int k = 0; k < kLaneRows; ++k) live[k] = in.valid[r[k]];
       }
     };
     if (tile.len > 0) load(0);
     const double a = (double)a32;
-    const double wgt = cnt > 0 ? 1.0 / ((double)n_resp * (double)cnt) : 0.0;   // 1/G and 1/|o_i| of Eq. 19 over all prompts
+    const double wgt = response_weight(in.n_resp, cnt);
     double acc = 0;
     for (int c0 = 0; c0 < tile.len; c0 += kChunkRows) {        // uniform for the wavefront
       const int n_k = min(kLaneRows, (tile.len - c0 + 63) >> 6);
@@ -679,29 +687,10 @@ __global__ __launch_bounds__(kThreads, 4) void row_coeff_kernel(
         float g = 0.f, wt = 0.f;
         const int r = c0 + 64 * k + lane;
         if (r < tile.len && live[0] != 0) {
-          const double lt = (double)ltf[0];
-          // the sampler-trainer ratio is taken at the checkpoint that generated the rollout (Alg. 1, "Sampler-Trainer
-          // ratio"; Sec. 3.2: the two ratios are orthogonal), the old-new ratio between that checkpoint and theta
-          const double l_old = logp_old != nullptr ? (double)oldf[0] : lt;
-          const double wbar = exp(fmin(l_old - (double)rollf[0], lnC));
-          const double wtilde = 1.0 + alpha * (wbar - 1.0);                       // Eq. 18 / Alg. 1 rectification weight
-          const double rho_on = logp_old != nullptr ? exp(lt - l_old) : 1.0;
-          const double clipped = fmin(fmax(rho_on, lo_clip), hi_clip);
-          // the unclipped branch is the minimum (ties included) iff the ratio has not left the trust
-          // region on the side the advantage pushes towards
-          const bool active = (a >= 0.0) ? (rho_on <= hi_clip) : (rho_on >= lo_clip);
-          const double s = active ? rho_on * a : clipped * a;
-          double obj = wtilde * s;
-          double dobj = active ? wtilde * a * rho_on : 0.0;
-          if (kl) {
-            const double q = (double)reff[0] - lt;
-            const double eq = exp(q);
-            obj -= (double)p.beta_kl * (eq - q - 1.0);
-            dobj -= (double)p.beta_kl * (1.0 - eq);
-          }
-          acc -= wgt * obj;
-          g = (float)(wgt * dobj * (double)g_scale);
-          wt = (float)wtilde;
+          const RowTerm t = row_term(coeff, ltf[0], rollf[0], oldf[0], reff[0], a);
+          acc -= wgt * t.obj;
+          g = (float)(wgt * t.dobj * (double)g_scale);
+          wt = (float)t.wtilde;
         }
         if (r < tile.len) {
           g_out[tile.row0 + (unsigned)r] = g;
@@ -817,16 +806,12 @@ int launch_diagnostics(ais_ctx* ctx, const float* logp_train, const float* logp_
   return hip_fail(ctx, hipGetLastError());
 }
 
-int launch_row_coeff(ais_ctx* ctx, const float* logp_train, const float* logp_roll, const float* logp_old,
-                     const float* logp_ref, const unsigned char* valid, long long n_rows,
-                     const long long* cu_rows, int n_resp, const float* adv, const int* count,
-                     const ais_diag* diag, const ais_params& p, int* tile_off, double* partial, float* g_out,
+int launch_row_coeff(ais_ctx* ctx, const CoeffInputs& in, long long n_rows, int* tile_off, double* partial, float* g_out,
                      float* wtilde_out, double* loss_out, float g_scale) {
-  auto kernel = n_resp <= kSelfPlanResponses ? row_coeff_kernel<true> : row_coeff_kernel<false>;
-  const TileRule rule = tile_rule(n_rows, n_resp);
+  auto kernel = in.n_resp <= kSelfPlanResponses ? row_coeff_kernel<true> : row_coeff_kernel<false>;
+  const TileRule rule = tile_rule(n_rows, in.n_resp);
   kernel<<<reduction_grid(ctx, rule.max_tiles), kThreads, 0, ctx->stream>>>(
-      logp_train, logp_roll, logp_old, logp_ref, valid, n_rows, cu_rows, n_resp, adv, count, diag, p,
-      std::log((double)p.C), tile_off, rule, partial, g_out, wtilde_out, g_scale, loss_out, ctx->status_dev,
+      in, n_rows, tile_off, rule, partial, g_out, wtilde_out, g_scale, loss_out, ctx->status_dev,
       take_tickets(ctx, false));
   return hip_fail(ctx, hipGetLastError());
 }

@@ -182,20 +182,102 @@ __global__ __launch_bounds__(kSweepThreads) void dlogits_elementwise_kernel(
 // are processed in consecutive segments (there is no dependence between segments: lse is an input).
 constexpr int kBurstThreads = 1024;
 
+// Where a row's coefficient comes from: an array that the row-coefficient kernel has written (without one, g == nullptr, it
+// is 1 on evaluated rows: the unscaled direction softmax - onehot) ...
+struct GivenCoeff {
+  static constexpr bool kOwn = false;
+  const float* g;
+  const unsigned char* valid;
+  __device__ __forceinline__ float of_row(long long row) const {
+    return g != nullptr ? g[row] : ((valid == nullptr || valid[row] != 0) ? 1.f : 0.f);
+  }
+  __device__ __forceinline__ float scale(float inv_temperature) const { return g != nullptr ? inv_temperature : 1.f; }
+};
+// ... or the workgroup itself, in small batches, whose coefficient kernel is a launch of 4 us and the gap before it.  One
+// workgroup more, the grid's last, then forms the loss and the rectification weights of all rows.  The step over 512 rows
+// of 1,024 fp32 logits: 24.0 us with the launch, 22.0 without.
+struct OwnCoeff {
+  static constexpr bool kOwn = true;
+  CoeffInputs in;
+  float* wtilde;
+  double* loss;
+  int* status;
+  int n_rows;
+  // Must be called by whole wavefronts.
+  __device__ __forceinline__ float of_row(long long row) const {
+    if (in.valid != nullptr && in.valid[row] == 0) return 0.f;           // uniform
+    const int lane = threadIdx.x & 63;
+    const float lt = in.logp_train[row], roll = in.logp_roll[row];
+    const float old = in.logp_old != nullptr ? in.logp_old[row] : 0.f;
+    const CoeffRule rule(in.p, in.diag->alpha, in.lnC, in.logp_old != nullptr, in.logp_ref != nullptr);
+    const float ref = rule.kl ? in.logp_ref[row] : 0.f;
+    bool here = false;
+    if (lane < in.n_resp) here = in.cu_rows[lane] <= row && row < in.cu_rows[lane + 1];
+    const unsigned long long mask = __ballot(here);
+    if (mask == 0) return 0.f;                                           // no response's row: a faulty cu_rows, reported
+    const int i = __builtin_ctzll(mask);
+    const RowTerm t = row_term(rule, lt, roll, old, ref, (double)in.adv[i]);
+    return (float)(response_weight(in.n_resp, in.count[i]) * t.dobj);
+  }
+  __device__ __forceinline__ float scale(float inv_temperature) const { return inv_temperature; }
+  template <int THREADS>
+  __device__ void loss_of_all() const {
+    __shared__ long long cu[kOwnResponses + 1];
+    __shared__ double sums[THREADS / 64];
+    const int tid = threadIdx.x;
+    if (tid <= in.n_resp) cu[tid] = in.cu_rows[tid];
+    const CoeffRule rule(in.p, in.diag->alpha, in.lnC, in.logp_old != nullptr, in.logp_ref != nullptr);
+    __syncthreads();
+    if (tid < in.n_resp) {
+      const long long lo = cu[tid], hi = cu[tid + 1];
+      if (lo < 0 || hi < lo || hi > n_rows || (tid == 0 && lo != 0) || (tid == in.n_resp - 1 && hi != n_rows))
+        atomicOr(status, AIS_STATUS_BAD_CU);
+    }
+    double acc = 0;
+    for (int r = tid; r < n_rows; r += THREADS) {
+      int i = 0, end = in.n_resp;                // the last response that begins at r or before it
+      while (end - i > 1) {
+        const int mid = (i + end) >> 1;
+        if (cu[mid] <= r) i = mid; else end = mid;
+      }
+      if (r < cu[i] || r >= cu[i + 1]) continue;
+      float wt = 0.f;
+      if (in.valid == nullptr || in.valid[r] != 0) {
+        const RowTerm t = row_term(rule, in.logp_train[r], in.logp_roll[r], in.logp_old != nullptr ? in.logp_old[r] : 0.f,
+                                   rule.kl ? in.logp_ref[r] : 0.f, (double)in.adv[i]);
+        acc -= response_weight(in.n_resp, in.count[i]) * t.obj;
+        wt = (float)t.wtilde;
+      }
+      if (wtilde != nullptr) wtilde[r] = wt;
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) acc += __shfl_xor(acc, off);
+    if ((tid & 63) == 0) sums[tid >> 6] = acc;
+    __syncthreads();
+    if (tid != 0) return;
+    for (int w = 1; w < THREADS / 64; ++w) acc += sums[w];
+    *loss = acc;
+  }
+  static constexpr int kOwnResponses = 64;       // a lane for each
+};
+
 // NSEG > 0 promises that the row fits NSEG segments, which are then unrolled: the loop-free form is ~3 %
 // faster than the same code inside a run-time loop.  NSEG = 0: run-time loop over as many segments as needed.
 // KFULL promises that the row has at least KFULL * 1024 vectors: vectors 0 .. KFULL - 1 of every lane exist and
 // are loaded and stored without a bounds branch (1.5 % faster at 19 vectors per lane).
-template <typename T, bool ALIGNED, int THREADS, int NV, int NSEG, int KFULL>
+template <typename T, bool ALIGNED, int THREADS, int NV, int NSEG, int KFULL, typename Coeff>
 __global__ __launch_bounds__(THREADS) void dlogits_burst_kernel(
-    const T* logits, long long row_stride, int vocab, const int* __restrict__ token_ids,
-    const float* __restrict__ g, const unsigned char* __restrict__ valid, const float* __restrict__ lse,
-    const float* __restrict__ logp, float inv_temperature, T* dlogits, long long n_rows) {
+    const T* logits, long long row_stride, int vocab, const int* __restrict__ token_ids, Coeff coeff,
+    const float* __restrict__ lse, const float* __restrict__ logp, float inv_temperature, T* dlogits, long long n_rows) {
   constexpr int N = Vec<T>::N;
   // Workgroups are dealt to the 8 XCDs round-robin by their index; every XCD walks a contiguous range of rows
   // (grid.x = 8 * ceil(n_rows / 8)).  Against rows dealt round-robin this is neutral on a batch of full rows
   // and 1-3 % faster where zero-filled rows mix with read+write rows.
   const long long rows_per_xcd = gridDim.x >> 3;
+  if (Coeff::kOwn && blockIdx.x == (unsigned)rows_per_xcd * 8) {
+    if constexpr (Coeff::kOwn) coeff.template loss_of_all<THREADS>();
+    return;
+  }
   const long long row = (long long)(blockIdx.x & 7) * rows_per_xcd + (blockIdx.x >> 3);
   if (row >= n_rows) return;
   const int tid = threadIdx.x;
@@ -207,7 +289,7 @@ __global__ __launch_bounds__(THREADS) void dlogits_burst_kernel(
   const int nvec = (vocab - head) / N;
   const int rest = vocab - nvec * N;     // elements outside the vectors, one per thread for the first `rest` threads
   const int v_rest = tid < head ? tid : tid + nvec * N;
-  const float gn = g != nullptr ? g[row] : ((valid == nullptr || valid[row] != 0) ? 1.f : 0.f);
+  const float gn = coeff.of_row(row);
 
   if (gn == 0.f) {
     const u32x4 zero = {0u, 0u, 0u, 0u};
@@ -218,7 +300,7 @@ __global__ __launch_bounds__(THREADS) void dlogits_burst_kernel(
 
   const float scale = inv_temperature * kLog2e;
   const float shift = -lse[row] * kLog2e;
-  const float c = g != nullptr ? gn * inv_temperature : gn;
+  const float c = gn * coeff.scale(inv_temperature);
   int y = token_ids[row];
   if (y < 0 || y >= vocab) y = -1;               // flagged by the first sweep; no one-hot term
   // The sampled token's element is c (p_y - 1) = c expm1(logp): no cancellation when p_y is close to 1.  The
@@ -273,13 +355,14 @@ void launch_dlogits_burst(ais_ctx* ctx, const T* z, long long n_rows, int vocab,
                           const float* logp, float inv_t, T* dz) {
   const int need = (vocab / Vec<T>::N + kBurstThreads - 1) / kBurstThreads;
   dim3 grid((unsigned)(((n_rows + 7) / 8) * 8)), block(kBurstThreads);
+  const GivenCoeff given{g, valid};
   if (!ALIGNED && need <= 1) {
     // A narrow row is no work for 1,024 threads, of which a compute unit holds two sets; of 256 it holds eight.  8,192
     // rows, us with 1,024 threads, element by element and with 256: bf16, 1,001 logits 46.0, 15.0, 17.0; 3,001 47.4, 28.2,
     // 21.2; 8,191 59.8, 67.7, 52.0; fp32, 1,001 34.9, 17.7, 15.7; 4,001 47.2, 43.9, 49.2.  1,000 rows: bf16, 3,001 10.5,
     // 7.5, 7.1; fp32, 4,001 10.8, 12.0, 8.9.
-    dlogits_burst_kernel<T, false, 256, 4, 1, 0><<<grid, dim3(256), 0, ctx->stream>>>(
-        z, row_stride, vocab, token_ids, g, valid, lse, logp, inv_t, dz, n_rows);
+    dlogits_burst_kernel<T, false, 256, 4, 1, 0, GivenCoeff><<<grid, dim3(256), 0, ctx->stream>>>(
+        z, row_stride, vocab, token_ids, given, lse, logp, inv_t, dz, n_rows);
     return;
   }
   // Aligned ones likewise, up to half that width.  41,643 rows, whole call, us with 1,024, 512, 256 and 64 threads: bf16, 1,000
@@ -287,21 +370,21 @@ void launch_dlogits_burst(ais_ctx* ctx, const T* z, long long n_rows, int vocab,
   // 6,000 91.0, 103, 108, 113; fp32, 256 59.6, 33.7, 21.5, 18.2; 2,048 66.9, 60.1, 61.4, 62.2; 3,000 89.9, 102, 105, 111.
   const int nvec = vocab / Vec<T>::N;
   if (ALIGNED && nvec <= 256) {
-    dlogits_burst_kernel<T, true, 256, 1, 1, 0><<<grid, dim3(256), 0, ctx->stream>>>(
-        z, row_stride, vocab, token_ids, g, valid, lse, logp, inv_t, dz, n_rows);
+    dlogits_burst_kernel<T, true, 256, 1, 1, 0, GivenCoeff><<<grid, dim3(256), 0, ctx->stream>>>(
+        z, row_stride, vocab, token_ids, given, lse, logp, inv_t, dz, n_rows);
     return;
   }
   if (ALIGNED && nvec <= 512) {
-    dlogits_burst_kernel<T, true, 512, 1, 1, 0><<<grid, dim3(512), 0, ctx->stream>>>(
-        z, row_stride, vocab, token_ids, g, valid, lse, logp, inv_t, dz, n_rows);
+    dlogits_burst_kernel<T, true, 512, 1, 1, 0, GivenCoeff><<<grid, dim3(512), 0, ctx->stream>>>(
+        z, row_stride, vocab, token_ids, given, lse, logp, inv_t, dz, n_rows);
     return;
   }
   // (vectors that surely exist, vectors per lane and burst, bursts): a row reaches a class only if it is wider than
   // the class before it, which is what the first figure states; an unaligned row may have lost up to 8 vectors to its
   // head, which the next lower figure covers
 #define AIS_BURST_CASE(KFULL, NVAL, NSEG)                                                                      \
-  dlogits_burst_kernel<T, ALIGNED, kBurstThreads, NVAL, NSEG, (ALIGNED || KFULL == 0 ? KFULL : KFULL - 1)>     \
-      <<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, token_ids, g, valid, lse, logp, inv_t, dz, n_rows)
+  dlogits_burst_kernel<T, ALIGNED, kBurstThreads, NVAL, NSEG, (ALIGNED || KFULL == 0 ? KFULL : KFULL - 1), GivenCoeff> \
+      <<<grid, block, 0, ctx->stream>>>(z, row_stride, vocab, token_ids, given, lse, logp, inv_t, dz, n_rows)
   if (need <= 4) AIS_BURST_CASE(0, 4, 1);
   else if (need <= 8) AIS_BURST_CASE(4, 8, 1);
   else if (need <= 12) AIS_BURST_CASE(8, 12, 1);
@@ -419,6 +502,41 @@ int launch_dlogits(ais_ctx* ctx, const void* logits, ais_dtype dtype, long long 
   if (dtype == AIS_BF16) launch(static_cast<const bf16_t*>(logits));
   else launch(static_cast<const float*>(logits));
   return hip_fail(ctx, hipGetLastError());
+}
+
+// Takes batches whose rows all have a workgroup on the chip at once, in up to 64 responses, with no more than two rows for
+// each thread of the one that forms the loss.
+bool try_loss_dlogits_small(ais_ctx* ctx, const CoeffInputs& in, const void* logits, ais_dtype dtype, long long n_rows,
+                            int vocab, long long row_stride, const int* token_ids, const float* lse, float* wtilde_out,
+                            double* loss_out, void* dlogits) {
+  if (n_rows == 0 || n_rows > 1024 || in.n_resp > OwnCoeff::kOwnResponses) return false;
+  auto launch = [&](const auto* z) {
+    typedef std::remove_cv_t<std::remove_pointer_t<decltype(z)>> T;
+    T* dz = static_cast<T*>(dlogits);
+    const bool aligned = vec_ok(z, row_stride, sizeof(T)) && vec_ok(dz, row_stride, sizeof(T));
+    if (!aligned && !(same_lines(z, dz) && vocab * sizeof(T) >= kElementwiseBytes)) return false;
+    const int nvec = vocab / Vec<T>::N;
+    auto run = [&](auto kernel, int threads) {
+      if (n_rows > 2 * threads || n_rows > ctx->n_cus * (2048LL / threads)) return false;
+      ScopedTimer timer(ctx, AIS_K_DLOGITS);
+      kernel<<<dim3((unsigned)(((n_rows + 7) / 8) * 8 + 1)), dim3(threads), 0, ctx->stream>>>(
+          z, row_stride, vocab, token_ids, OwnCoeff{in, wtilde_out, loss_out, ctx->status_dev, (int)n_rows}, lse,
+          in.logp_train, in.p.inv_temperature, dz, n_rows);
+      return true;
+    };
+    if (aligned) {
+      if (nvec <= 256) return run(dlogits_burst_kernel<T, true, 256, 1, 1, 0, OwnCoeff>, 256);
+      if (nvec <= 512) return run(dlogits_burst_kernel<T, true, 512, 1, 1, 0, OwnCoeff>, 512);
+      if (nvec <= 4096) return run(dlogits_burst_kernel<T, true, 1024, 4, 1, 0, OwnCoeff>, 1024);
+      if (nvec <= 8192) return run(dlogits_burst_kernel<T, true, 1024, 8, 1, 0, OwnCoeff>, 1024);
+    } else {
+      if (nvec <= 1024) return run(dlogits_burst_kernel<T, false, 256, 4, 1, 0, OwnCoeff>, 256);
+      if (nvec <= 4096) return run(dlogits_burst_kernel<T, false, 1024, 4, 1, 0, OwnCoeff>, 1024);
+      if (nvec <= 8192) return run(dlogits_burst_kernel<T, false, 1024, 8, 1, 0, OwnCoeff>, 1024);
+    }
+    return false;
+  };
+  return dtype == AIS_BF16 ? launch(static_cast<const bf16_t*>(logits)) : launch(static_cast<const float*>(logits));
 }
 
 int launch_copy(ais_ctx* ctx, void* dst, const void* src, long long bytes) {

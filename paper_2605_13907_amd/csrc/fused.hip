@@ -65,7 +65,7 @@ typedef const __attribute__((address_space(1))) void* glb_ptr;
 template <typename T, bool ALIGNED, int THREADS, int NV, int NL, int KFULL>
 __global__ __launch_bounds__(THREADS) void fused_logprob_softmax_kernel(
     const T* logits, long long row_stride, int vocab, const int* __restrict__ token_ids,
-    const unsigned char* __restrict__ valid, float inv_temperature, float* __restrict__ logp_out,
+    const unsigned char* __restrict__ valid, float inv_temperature, double exact, float* __restrict__ logp_out,
     float* __restrict__ lse_out, T* sgrad, int* __restrict__ status) {
   constexpr int N = Vec<T>::N;
   constexpr int kWaves = THREADS / 64;
@@ -187,7 +187,8 @@ __global__ __launch_bounds__(THREADS) void fused_logprob_softmax_kernel(
     for (int w = 1; w < kWaves; ++w) t = merge(t, lds[w]);
     float lse, logp;
     if (y_ok) {
-      const double l1p = log1p_scaled(t.s, (double)t.m - (double)zy * (double)scale);
+      // (`exact` is what exact_exponent would multiply by: from the host, it takes no vector registers)
+      const double l1p = log1p_scaled(t.s, ((double)t.m - (double)zy * (double)scale) * exact);
       logp = (float)(-l1p);
       lse = (float)((double)zy * (double)inv_temperature + l1p);
     } else {
@@ -259,7 +260,8 @@ int launch_nv(ais_ctx* ctx, const T* z, long long n_rows, int vocab, long long r
       return hip_fail(ctx, hipErrorInvalidValue);
   }
   kernel<<<dim3((unsigned)n_rows), dim3(THREADS), NL * kSlotBytes, ctx->stream>>>(
-      z, row_stride, vocab, token_ids, valid, inv_t, logp, lse, sgrad, ctx->status_dev);
+      z, row_stride, vocab, token_ids, valid, inv_t,
+      (double)inv_t * 1.4426950408889634074 / (double)(inv_t * kLog2e), logp, lse, sgrad, ctx->status_dev);
   return AIS_OK;
 }
 

@@ -95,23 +95,23 @@ def cpu_baseline(batch, params, sample_rows: int):
                                       f"{dt1:.2f} s wall"}}
 
 
-def burst_class(vocab: int, esize: int) -> str:
+def burst_class(vocab: int, esize: int, rows: int = 1 << 30, responses: int = 1 << 30) -> str:
     """Name of the gradient-sweep instantiation that the library's launcher picks for 16-byte aligned rows of this
     width (reporting only; mirrors the table in csrc/sweeps.hip: aligned, threads, vectors per lane and burst, bursts, vectors that
-    surely exist)."""
-    per_vec = 16 // esize
-    need = (vocab // per_vec + 1023) // 1024
-    t = "bf16" if esize == 2 else "float"
-    if need <= 12:
-        nv = 4 * ((max(need, 1) + 3) // 4)
-        return f"dlogits_burst_kernel<{t}, true, 1024, {nv}, 1, {nv - 4}>"
-    if need <= 20:
-        return f"dlogits_burst_kernel<{t}, true, 1024, {need}, 1, {need - 1}>"
-    if need <= 32:
-        return f"dlogits_burst_kernel<{t}, true, 1024, 16, 2, 20>"
-    if need <= 48:
-        return f"dlogits_burst_kernel<{t}, true, 1024, 16, 3, 32>"
-    return f"dlogits_burst_kernel<{t}, true, 1024, 16, 0, 0>"
+    surely exist, where the row's coefficient comes from)."""
+    nvec = vocab // (16 // esize)
+    need = (nvec + 1023) // 1024
+    threads, nv = (256, 1) if nvec <= 256 else (512, 1) if nvec <= 512 else (1024, 4 * ((max(need, 1) + 3) // 4))
+    small = rows <= min(1024, 2 * threads, 256 * (2048 // threads)) and responses <= 64 and need <= 8
+    if small:
+        sizes = f"{threads}, {nv}, 1, 0, OwnCoeff"
+    elif need <= 12:
+        sizes = f"{threads}, {nv}, 1, {nv - 4 if threads == 1024 else 0}, GivenCoeff"
+    elif need <= 20:
+        sizes = f"1024, {need}, 1, {need - 1}, GivenCoeff"
+    else:
+        sizes = f"1024, 16, {'2, 20' if need <= 32 else '3, 32' if need <= 48 else '0, 0'}, GivenCoeff"
+    return f"dlogits_burst_kernel<{'bf16' if esize == 2 else 'float'}, true, {sizes}>"
 
 
 def time_workload(torch, binding, workloads, ctx, k, steps, warmup, mode="ais", stale_old=False, in_place=False):
@@ -200,7 +200,7 @@ def time_workload(torch, binding, workloads, ctx, k, steps, warmup, mode="ais", 
         "group_size": shape.group_size, "logits": shape.logits_dtype, "layout": shape.layout,
         "ms_per_step": ms_step, "tokens_per_s": N / (ms_step * 1e-3), "ms_per_step_hip_graph": ms_graph,
         "path_hbm": {"GB/s": path_gbps, "frac": path_gbps / HBM_PEAK_GBPS, "bytes_per_step": fwd_bytes + bwd_bytes},
-        "dominant_kernel": {"name": burst_class(V, e), "avg_ms": ms_bwd / n_bwd, "bytes_per_launch": bwd_bytes,
+        "dominant_kernel": {"name": burst_class(V, e, R, shape.n_resp), "avg_ms": ms_bwd / n_bwd, "bytes_per_launch": bwd_bytes,
                             "GB/s": bwd_gbps, "frac": bwd_gbps / HBM_PEAK_GBPS,
                             "zero_filled_rows": R - N},
         "token_logprob": {"avg_ms": ms_fwd / n_fwd, "GB/s": fwd_gbps, "frac": fwd_gbps / HBM_PEAK_GBPS},

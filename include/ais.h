@@ -324,8 +324,10 @@ int ais_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long hidden_strid
  *   lse, logp   [n_rows] fp32, outputs of ais_lm_head_logprob for the same operands and temperature
  *   coeff       [n_rows] fp32, as written by ais_grpo_row_scale (its g_out: it carries inv_temperature)
  *   chunk_vocab vocabulary entries per chunk, a multiple of 256.  The context workspace grows to
- *               2 * n_rows * chunk_vocab bytes.  0 selects 8192 and, with up to 3,072 rows to go through, wider chunks;
- *               the workspace is then up to 68 MB whatever the number of those rows.
+ *               2 * n_rows * chunk_vocab bytes.  0 selects 8192 (22 to 31 times 256 for a
+ *               d_model whose embedding gradient then fills the chip better; the workspace stays that of 8192) and,
+ *               with up to 3,072 rows to go through, wider chunks; the workspace is then up to 68 MB whatever the
+ *               number of those rows.
  *   n_live_max  negative, or >= n_rows: every row goes through the recomputation and the GEMMs.  Otherwise a bound
  *               that the caller vouches for on the number of rows with coeff != 0 (for a masked-diffusion batch:
  *               the number of evaluated positions, which its loader knows): those rows are gathered on the device

@@ -74,7 +74,9 @@ struct LmHeadPlan {
 LmHeadPlan lm_head_plan(long long n_rows, int vocab, int n_cus);
 // Workspace of the read-out's two calls (the gradient call's: of a chunk's dlogits) and the gradient call's chunk width.
 size_t lm_head_logprob_bytes(long long n_rows, int vocab, int n_cus);
+constexpr long long kLmGradChunk = 8192;
 long long lm_grad_chunk(long long m_rows, long long vocab, long long asked, int n_cus);
+long long lm_grad_chunk_for(long long chunk, long long vocab, long long d_model, int n_cus);
 size_t lm_grad_dlogits_bytes(long long m_rows, long long vocab, long long asked, int n_cus);
 
 }  // namespace ais

@@ -549,7 +549,10 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   // mask, the list, its inverse, the gathered hidden states and their gradient
   auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
   const size_t ds_bytes = up(lm_grad_dlogits_bytes(m_rows, vocab, chunk_vocab, ctx->n_cus));
+  const bool dw_aligned = reinterpret_cast<uintptr_t>(dweight_out) % 16 == 0;
+  const bool chosen = chunk_vocab == 0;
   chunk_vocab = lm_grad_chunk(m_rows, vocab, chunk_vocab, ctx->n_cus);
+  if (chosen && dw_aligned) chunk_vocab = lm_grad_chunk_for(chunk_vocab, vocab, d_model, ctx->n_cus);
   const size_t plan_bytes = 256;
   const size_t mask_bytes = gather ? up((size_t)n_rows) : 0;
   const size_t list_bytes = gather ? up((size_t)n_rows * 4) : 0;
@@ -581,7 +584,6 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   float* dh_gemm = gather ? dh_gathered : dhidden_out;
   // (the own kernels store 16 bytes at a time; rows of a multiple of 32 floats keep the base's alignment)
   const bool own_dh = lm_dhidden_fits(ctx, d_model, m_rows) && reinterpret_cast<uintptr_t>(dh_gemm) % 16 == 0;
-  const bool dw_aligned = reinterpret_cast<uintptr_t>(dweight_out) % 16 == 0;
   auto own_dw = [&](int width) { return dw_aligned && lm_dweight_fits(ctx, d_model, width); };
   // the list's length, first word of the decomposition on the device: rows past it are nobody's
   const int* n_listed = gather ? static_cast<const int*>(dev_plan) : nullptr;

@@ -256,13 +256,27 @@ int launch_gemm(ais_ctx* ctx, GemmArgs g) {
 // the line of dweight matters little: the whole call over 4,096 rows x 4,096 takes 276 us with its own product at 69 % full
 // and 283 with the library's, at 75 % 287 and 291, at 81 % 301 and 326 (dhidden with it), over 8,192 rows at 62 % 507 and
 // 503.
-static bool rounds_full(const ais_ctx* ctx, long long m, long long n, int percent) {
+static bool rounds_full(int n_cus, long long m, long long n, int percent) {
   const long long tiles = ((m + kTile - 1) / kTile) * ((n + kTile - 1) / kTile);
-  const long long rounds = (tiles + ctx->n_cus - 1) / ctx->n_cus;
-  return tiles > 0 && tiles <= (1 << 28) && 100 * tiles >= percent * rounds * ctx->n_cus;
+  const long long rounds = (tiles + n_cus - 1) / n_cus;
+  return tiles > 0 && tiles <= (1 << 28) && 100 * tiles >= percent * rounds * n_cus;
 }
-bool lm_dweight_fits(const ais_ctx* ctx, long long d, long long n_v) { return rounds_full(ctx, d, n_v, 80); }
-bool lm_dhidden_fits(const ais_ctx* ctx, long long d, long long n_rows) { return rounds_full(ctx, d, n_rows, 95); }
+bool lm_dweight_fits(const ais_ctx* ctx, long long d, long long n_v) { return rounds_full(ctx->n_cus, d, n_v, 80); }
+bool lm_dhidden_fits(const ais_ctx* ctx, long long d, long long n_rows) { return rounds_full(ctx->n_cus, d, n_rows, 95); }
+
+// The library's chunk of 8,192 vocabulary entries (32 tiles), narrowed to the widest of 22 to 31 tiles that fills dweight's
+// rounds where 32 leave them too empty for the own product: d_model 2,304 (28 tiles), 2,560 (25), 2,816 (23), 4,352 (30),
+// 4,608 (28), 4,864 (26), 6,400 (30).  Whole call against chunks of 8,192, in this order, over 3,300 to 12,000 rows and
+// vocabularies of 24,600 to 151,936: 0.79-0.91, 0.82-0.99, 0.79-0.96, 0.83-0.91, 0.96-1.00, 0.92-0.94, 0.91-0.98 (6,144 rows x
+// 50,257 x 2,304: 4,525 -> 3,590 us).  Fewer tiles (21, d_model 3,072: 0.96-1.07) shorten the recomputation's work items too
+// far; vocabularies of two or three chunks are left with too small a last one (0.85-1.02).  Never wider: the chunk fits the
+// workspace of 8,192 entries.
+long long lm_grad_chunk_for(long long chunk, long long vocab, long long d_model, int n_cus) {
+  if (chunk != kLmGradChunk || vocab < 3 * chunk || rounds_full(n_cus, d_model, chunk, 80)) return chunk;
+  for (long long width = chunk - kTile; width >= 22 * kTile; width -= kTile)
+    if (rounds_full(n_cus, d_model, width, 95)) return width;
+  return chunk;
+}
 
 // dweight[n_v, d] = ds^T h over the first k rows (min(k, *k_dev) if k_dev is given); ds rows of pitch ds_stride.
 // Row pitches and bases are 16-byte aligned, d a multiple of 32, ds defined up to a multiple of 256 columns.

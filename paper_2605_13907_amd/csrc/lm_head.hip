@@ -774,7 +774,6 @@ size_t lm_head_logprob_bytes(long long n_rows, int vocab, int n_cus) {
 // 0.74-1.04, 6 0.83-1.09, 7 0.90-1.15, 8 0.84-0.98, 9 0.78-1.03, 10 0.87-1.02, 11 0.82-1.10, 12 0.87-1.07; 13 0.90-1.15, 14
 // 0.91-1.18, 15 0.98-1.15.  (Rounded up to a tile more, which takes a second round or items of three tiles, 6 blocks
 // 0.86-1.16, 7 0.97-1.23, 9 0.81-1.12, 14 1.00-1.22.)
-constexpr long long kLmGradChunk = 8192;
 constexpr long long kLmGradFewBlocks = 12;
 long long lm_grad_chunk(long long m_rows, long long vocab, long long asked, int n_cus) {
   const long long whole = (vocab + kLmTileV - 1) / kLmTileV * kLmTileV;

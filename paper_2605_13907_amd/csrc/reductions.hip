@@ -735,9 +735,12 @@ int reduction_grid(const ais_ctx* ctx, int max_tiles) {
   return (max_tiles + per - 1) / per;
 }
 
-Tickets take_tickets(ais_ctx* ctx, bool in_static) {
+// A launch of one workgroup neither takes a ticket nor clears the other's, so it is not counted as a turn: launches of many
+// workgroups would otherwise, with such ones between them, come to the same ticket every time.
+Tickets take_tickets(ais_ctx* ctx, bool in_static, int grid) {
   int* pair = ctx->status_dev + (in_static ? kStaticTicketWord : kTicketWord);
-  const unsigned turn = (in_static ? ctx->static_turns : ctx->turns)++ & 1u;
+  unsigned& turns = in_static ? ctx->static_turns : ctx->turns;
+  const unsigned turn = (grid > 1 ? turns++ : turns) & 1u;
   return Tickets{pair + turn, pair + (turn ^ 1u)};
 }
 
@@ -800,9 +803,10 @@ int launch_diagnostics(ais_ctx* ctx, const float* logp_train, const float* logp_
                        float* adv_out, int* count_out, ais_diag* diag_out) {
   auto kernel = n_resp <= kSelfPlanResponses ? diag_reduce_kernel<true> : diag_reduce_kernel<false>;
   const TileRule rule = tile_rule(n_rows, n_resp);
-  kernel<<<reduction_grid(ctx, rule.max_tiles), kThreads, 0, ctx->stream>>>(
+  const int grid = reduction_grid(ctx, rule.max_tiles);
+  kernel<<<grid, kThreads, 0, ctx->stream>>>(
       logp_train, logp_roll, valid, n_rows, cu_rows, n_resp, tile_off, rule, partial, group_size, rewards, p,
-      std::log((double)p.C), adv_out, count_out, diag_out, ctx->status_dev, take_tickets(ctx, in_static));
+      std::log((double)p.C), adv_out, count_out, diag_out, ctx->status_dev, take_tickets(ctx, in_static, grid));
   return hip_fail(ctx, hipGetLastError());
 }
 
@@ -810,9 +814,10 @@ int launch_row_coeff(ais_ctx* ctx, const CoeffInputs& in, long long n_rows, int*
                      float* wtilde_out, double* loss_out, float g_scale) {
   auto kernel = in.n_resp <= kSelfPlanResponses ? row_coeff_kernel<true> : row_coeff_kernel<false>;
   const TileRule rule = tile_rule(n_rows, in.n_resp);
-  kernel<<<reduction_grid(ctx, rule.max_tiles), kThreads, 0, ctx->stream>>>(
+  const int grid = reduction_grid(ctx, rule.max_tiles);
+  kernel<<<grid, kThreads, 0, ctx->stream>>>(
       in, n_rows, tile_off, rule, partial, g_out, wtilde_out, g_scale, loss_out, ctx->status_dev,
-      take_tickets(ctx, false));
+      take_tickets(ctx, false, grid));
   return hip_fail(ctx, hipGetLastError());
 }
 

@@ -96,3 +96,27 @@ def test_a_count_that_was_left_behind(static):
         words[word] = 0
     assert bool((words == 0).all()) and ctx.status() == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("static", [False, True])
+def test_a_count_left_behind_with_small_batches_between(static):
+    """A batch of few tiles is reduced by one workgroup, which takes no ticket: it must not use up a turn either, or the
+    large batches between such ones come to the same ticket every time and nobody clears it."""
+    ctx = B.AisContext()
+    large, small = scalars(100_000, 16, 3), scalars(512, 8, 4)
+    diagnostics = lambda args: ctx.diagnostics(*args, static_scratch=static)
+    ref, ref_small = bits(*diagnostics(large)), bits(*diagnostics(small))
+    words = torch.as_tensor(StatusWords(ctx), device="cuda")
+    torch.cuda.synchronize()
+    for word in (48, 49) if static else (32, 33):
+        words[word] = 1 << 20                       # more than there are workgroups: nobody is the last one of a launch
+        for _ in range(3):                          # the results of one of these may be lost
+            diagnostics(large)
+            assert same(bits(*diagnostics(small)), ref_small)
+        for _ in range(3):
+            got = bits(*diagnostics(large))
+            assert same(got, ref), word
+            assert same(bits(*diagnostics(small)), ref_small)
+        assert bool((words == 0).all()), word
+    assert ctx.status() == 0
+    ctx.close()

@@ -107,7 +107,7 @@ template <typename T, int THREADS, bool BITS>
 struct RowCoder {
   RowDivider d;
   float amax;
-  bool special;                            // uniform for the workgroup
+  bool special, large;                     // uniform for the workgroup; large: see accumulate_rounded
   __device__ __forceinline__ RowCoder(const T* zr, int vocab, int head, float* lds) {
     bool nan = false;
     if constexpr (BITS) {
@@ -118,7 +118,8 @@ struct RowCoder {
       amax = row_amax<T, THREADS>(zr, vocab, head, lds);
     }
     d = make_divider(scale_of(amax));
-    special = d.slow || nan || amax > kLargeAmax;
+    special = d.slow || nan;
+    large = amax > kLargeAmax;
   }
   template <bool SPECIAL>
   __device__ __forceinline__ float quotient(float x) const {
@@ -245,8 +246,8 @@ __global__ __launch_bounds__(THREADS) void fp8_rollout_logprob_kernel(
   // the round-tripped logit is s * decode(code): the row scale is folded into the exponent's multiplier (s > 0,
   // so the running maximum can be taken over the decoded values)
   const float scale = s * kLog2e;
-  auto sweep = [&](auto slow) {
-    constexpr bool SLOW = decltype(slow)::value;
+  auto sweep = [&](auto slow, auto rounded) {
+    constexpr bool SLOW = decltype(slow)::value, ROUNDED = decltype(rounded)::value;
     {
       const u32x4* zv = reinterpret_cast<const u32x4*>(zr + head);
       for (int i = tid; i < nvec; i += THREADS) {
@@ -258,17 +259,19 @@ __global__ __launch_bounds__(THREADS) void fp8_rollout_logprob_kernel(
           x[k] = r[0];
           x[k + 1] = r[1];
         }
-        if (SLOW) accumulate_rounded<N>(x, scale, st);
+        if (ROUNDED) accumulate_rounded<N>(x, scale, st);
         else accumulate<N>(x, scale, st);
       }
     }
     for (int e = tid; e < vocab - nvec * N; e += THREADS) {
       float x = from_e4m3x2(coder.template code2<SLOW>(Vec<T>::load1(zr + (e < head ? 0 : nvec * N) + e), 0.f))[0];
-      if (SLOW) accumulate_rounded<1>(&x, scale, st);
+      if (ROUNDED) accumulate_rounded<1>(&x, scale, st);
       else accumulate<1>(&x, scale, st);
     }
   };
-  if (coder.special) sweep(std::true_type{}); else sweep(std::false_type{});
+  if (coder.large) sweep(std::true_type{}, std::true_type{});       // (true division: right for every row)
+  else if (coder.special) sweep(std::true_type{}, std::false_type{});
+  else sweep(std::false_type{}, std::false_type{});
   st = wave_merge(st);
   if ((tid & 63) == 0) lds_ms[tid >> 6] = st;
   __syncthreads();

@@ -71,3 +71,19 @@ def test_any_magnitude(dtype, power):
         tol = 2.0 ** -22 * z.float().abs().amax(dim=1).double() + 1e-5
         assert ((logp - ref).abs() <= tol).all(), (vocab, (logp - ref).abs().max())
     ctx.close()
+
+
+@pytest.mark.parametrize("rows,vocab", [(500, 4096), (2048, 1000)])
+def test_a_nan_does_not_round_the_products(rows, vocab):
+    """A negative NaN in an aligned bf16 row has the code of the row's lowest possible value, so the log-probs are to the bit
+    those of the row that holds this value: the products of its ordinary logits are formed as exactly."""
+    ctx = B.AisContext()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(vocab)
+    z = (torch.randn(rows, vocab, generator=gen, device="cuda") * 3).bfloat16()
+    at = z.float().abs().argmin(dim=1, keepdim=True)             # never the largest magnitude
+    lowest = z.scatter(1, at, -z.float().abs().amax(dim=1, keepdim=True).bfloat16())
+    nan = z.view(torch.int16).scatter(1, at, -64).view(torch.bfloat16)      # 0xffc0
+    y = (at.squeeze(1).int() + 1) % vocab
+    assert torch.equal(ctx.fp8_rollout_logprob(nan, y), ctx.fp8_rollout_logprob(lowest, y))
+    ctx.close()

@@ -9,8 +9,11 @@ there is no fallback: if the shared library is missing, loading raises.
 from __future__ import annotations
 
 import ctypes as C
+import hashlib
 import importlib.util
 import os
+import sysconfig
+import warnings
 from typing import Optional
 
 import torch
@@ -112,21 +115,36 @@ _FAST_ENTRIES = ("ais_set_stream", "ais_token_logprob", "ais_diagnostics", "ais_
                  "ais_fp8_rollout_logprob", "ais_lm_head_logprob", "ais_lm_head_grad")
 
 
+def fast_stamp() -> str:
+    """What a build of the native calls depends on beside their compiler: their source, the library's header (entry points and
+    structures), this torch's object layouts and this interpreter's.  build.py compiles it in."""
+    h = hashlib.sha256(f"{torch.__version__} {torch.version.hip} {sysconfig.get_config_var('SOABI')}".encode())
+    for path in (os.path.join(PKG, "csrc", "fast_binding.cpp"), os.path.join(os.path.dirname(PKG), "include", "ais.h")):
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
+
+
 def _load_fast():
-    """The native form of the calls (csrc/fast_binding.cpp), or None where it has not been built for this torch.  Same checks,
-    outputs and calls of the library without the interpreter: a step over 512 rows takes the 24 us of its kernels instead of
-    the 38-40 that the host needed."""
+    """The native form of the calls (csrc/fast_binding.cpp), or None where there is none, and with a warning where there is one
+    that was not built from these sources for this torch.  Same checks, outputs and calls of the library without the
+    interpreter: a step over 512 rows takes the 24 us of its kernels instead of the 38-40 that the host needed."""
     global _FAST
-    if _FAST is None and os.path.exists(FAST_PATH):
-        try:
-            spec = importlib.util.spec_from_file_location("_ais_fast", FAST_PATH)
-            fast = importlib.util.module_from_spec(spec)
-            spec.loader.exec_module(fast)
-            fast.init(*(C.cast(getattr(_lib(), name), C.c_void_p).value for name in _FAST_ENTRIES))
-            _FAST = fast
-        except ImportError:
-            pass
-    return _FAST
+    if _FAST is None:
+        _FAST = False
+        if os.path.exists(FAST_PATH):
+            try:
+                spec = importlib.util.spec_from_file_location("_ais_fast", FAST_PATH)
+                fast = importlib.util.module_from_spec(spec)
+                spec.loader.exec_module(fast)
+                if getattr(fast, "stamp", None) != fast_stamp():
+                    raise ImportError("it was built from other sources or for another torch")
+                fast.init(*(C.cast(getattr(_lib(), name), C.c_void_p).value for name in _FAST_ENTRIES))
+                _FAST = fast
+            except (ImportError, OSError) as e:
+                warnings.warn(f"{FAST_PATH} is not used ({e}): calls take 4 to 7 us longer on the host.  Build it with "
+                              "`python -m paper_2605_13907_amd.build`", RuntimeWarning, stacklevel=3)
+    return _FAST or None
 
 
 def default_params(**overrides) -> AisParams:

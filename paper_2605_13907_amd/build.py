@@ -28,8 +28,11 @@ LINK_FLAGS = ["-lrocblas"]
 def fast_binding_command():
     """The binding's native calls: host code, against the torch that is installed."""
     from torch.utils import cpp_extension
+
+    from paper_2605_13907_amd.binding import fast_stamp
     dirs = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
-    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", *[f"-I{d}" for d in dirs],
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+            f'-DAIS_FAST_STAMP="{fast_stamp()}"', *[f"-I{d}" for d in dirs],
             os.path.join(CSRC, "fast_binding.cpp"), "-o", FAST, *[f"-L{d}" for d in cpp_extension.library_paths()],
             "-ltorch_python", "-ltorch_cpu", "-lc10"]
 

@@ -438,4 +438,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_ais_fast", nullptr, -1, methods, 
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__ais_fast(void) { return PyModule_Create(&module); }
+// `stamp`: of the sources and the torch that this was compiled from, which the binding compares before it calls anything.
+PyMODINIT_FUNC PyInit__ais_fast(void) {
+  PyObject* m = PyModule_Create(&module);
+  if (m != nullptr && PyModule_AddStringConstant(m, "stamp", AIS_FAST_STAMP) != 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

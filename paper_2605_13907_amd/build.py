@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -26,29 +27,43 @@ LINK_FLAGS = ["-lrocblas"]
 
 
 def fast_binding_command():
-    """The binding's native calls: host code, against the torch that is installed."""
-    from torch.utils import cpp_extension
+    """The binding's native calls: host code, against the torch that is installed.  -> (command, None), or (None, what is
+    missing for them)."""
+    try:
+        from torch.utils import cpp_extension
 
-    from paper_2605_13907_amd.binding import fast_stamp
-    dirs = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
-    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
-            f'-DAIS_FAST_STAMP="{fast_stamp()}"', *[f"-I{d}" for d in dirs],
-            os.path.join(CSRC, "fast_binding.cpp"), "-o", FAST, *[f"-L{d}" for d in cpp_extension.library_paths()],
-            "-ltorch_python", "-ltorch_cpu", "-lc10"]
+        from paper_2605_13907_amd.binding import fast_stamp
+    except ImportError as e:
+        return None, f"torch ({e})"
+    cxx = os.environ.get("CXX", "g++")
+    if shutil.which(cxx) is None:
+        return None, f"a host compiler ({cxx})"
+    python_headers = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(python_headers, "Python.h")):
+        return None, f"Python.h (in {python_headers})"
+    dirs = [*cpp_extension.include_paths(), python_headers, os.path.join(ROOT, "include")]
+    return [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f'-DAIS_FAST_STAMP="{fast_stamp()}"',
+            *[f"-I{d}" for d in dirs], os.path.join(CSRC, "fast_binding.cpp"), "-o", FAST,
+            *[f"-L{d}" for d in cpp_extension.library_paths()], "-ltorch_python", "-ltorch_cpu", "-lc10"], None
 
 
 def build(verbose: bool = True) -> str:
+    """Compiles the library, which needs hipcc alone, and beside it the binding's native calls where there is what they need.
+    Neither is left over from an earlier build if this one fails."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc, *HIPCC_FLAGS, *[os.path.join(CSRC, s) for s in SOURCES], "-o", LIB, *LINK_FLAGS]
-    fast = fast_binding_command()
+    fast, missing = fast_binding_command()
+    for built in (LIB, FAST):
+        if os.path.exists(built):
+            os.remove(built)
     if verbose:
         print(" ".join(cmd), flush=True)
-        print(" ".join(fast), flush=True)
-    beside = subprocess.Popen(fast)
+        print(" ".join(fast) if fast else f"the binding's native calls are not built: no {missing}", flush=True)
+    beside = subprocess.Popen(fast) if fast else None
     try:
         subprocess.run(cmd, check=True)
     finally:
-        rc = beside.wait()
+        rc = beside.wait() if beside else 0
     if rc != 0:
         raise subprocess.CalledProcessError(rc, fast)
     return LIB

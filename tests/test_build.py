@@ -41,7 +41,9 @@ def test_library_alone(place, capsys, lacks):
     if lacks == "compiler":
         monkeypatch.setenv("CXX", "/nowhere/g++")
     elif lacks == "torch":
+        import torch.utils
         monkeypatch.setitem(sys.modules, "torch.utils.cpp_extension", None)
+        monkeypatch.delattr(torch.utils, "cpp_extension", raising=False)
     else:
         monkeypatch.setattr(M.sysconfig, "get_paths", lambda: {"include": "/nowhere"})
     M.build()

@@ -150,15 +150,16 @@ struct Call : Args {
     stream = pointer();
     ok = ok && ctx != nullptr;
   }
-  // Runs `call` on the stream, without the interpreter's lock.
+  // Runs `call` on the stream, without the interpreter's lock, which is taken again however that ends: the address of a
+  // tensor's storage may be refused (a copy-on-write one has to be allocated first) with a C++ exception.
   template <typename F>
   int run(F call) {
-    int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = lib.set_stream(ctx, stream);
-    if (rc == 0) rc = call();
-    Py_END_ALLOW_THREADS
-    return rc;
+    struct Unlocked {
+      PyThreadState* state = PyEval_SaveThread();
+      ~Unlocked() { PyEval_RestoreThread(state); }
+    } unlocked;
+    const int rc = lib.set_stream(ctx, stream);
+    return rc == 0 ? call() : rc;
   }
 };
 

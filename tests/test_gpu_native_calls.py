@@ -144,6 +144,22 @@ def test_same_refusals(both):
     assert outcome(lambda: both[0].token_logprob(z, y)) == outcome(lambda: both[1].token_logprob(z, y))
 
 
+def test_storage_that_refuses_its_address(both):
+    """A C++ exception in the middle of a native call: the method's own way raises it, and the interpreter goes on."""
+    z, y = torch.randn(8, 64, device="cuda"), torch.zeros(8, device="cuda", dtype=torch.int32)
+    h = z.bfloat16()
+    f, codes = torch.zeros(8, device="cuda"), torch.zeros(8, 64, device="cuda", dtype=torch.uint8)
+    for t in (z, h, codes):
+        torch._C._set_throw_on_mutable_data_ptr(t)
+    for call in (lambda c: c.token_logprob(z, y), lambda c: c.token_logprob_softmax_grad(z, y), lambda c: c.fp8_quantize_rows(z),
+                 lambda c: c.fp8_dequantize_rows(codes, f), lambda c: c.fp8_rollout_logprob(z, y),
+                 lambda c: c.lm_head_logprob(h, h, y), lambda c: c.lm_head_grad(h, h, y, f, f, f)):
+        for ctx in both:
+            with pytest.raises(RuntimeError, match="Cannot access data pointer"):
+                call(ctx)
+    torch.cuda.synchronize()
+
+
 def test_outputs_are_new_tensors(both):
     z = torch.randn(64, 1000, device="cuda")
     y = torch.randint(0, 1000, (64,), device="cuda", dtype=torch.int32)

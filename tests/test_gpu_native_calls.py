@@ -144,6 +144,61 @@ def test_same_refusals(both):
     assert outcome(lambda: both[0].token_logprob(z, y)) == outcome(lambda: both[1].token_logprob(z, y))
 
 
+def bad_forms(t):
+    """t on the host, of another type, one element (row) short, and with gaps between its elements."""
+    yield t.cpu()
+    yield t.to(torch.float64)
+    yield t[:-1]
+    yield torch.stack([t, t], dim=-1).flatten(-2)[..., ::2]
+
+
+def test_one_wrong_argument_at_a_time(both):
+    """Every array of every call: refused by both ways, before anything is launched, with the same error."""
+    n, v, d = 8, 64, 32
+    f = torch.zeros(n, device="cuda")
+    z, y, valid = torch.randn(n, v, device="cuda"), torch.zeros(n, device="cuda", dtype=torch.int32), torch.ones(n, device="cuda").byte()
+    cu, r = torch.tensor([0, 3, 5, 8], device="cuda"), torch.ones(3, device="cuda")
+    count, diag = torch.full((3,), 2, device="cuda", dtype=torch.int32), torch.zeros(B.C.sizeof(B.AisDiag), device="cuda", dtype=torch.uint8)
+    h, w, codes = torch.randn(n, d, device="cuda").bfloat16(), torch.randn(v, d, device="cuda").bfloat16(), torch.zeros(n, v, device="cuda").byte()
+    rows = dict(logp_train=f, logp_roll=f, valid=valid, cu_rows=cu)
+    loss = dict(adv=r, count=count, diag=diag, logp_old=f, logp_ref=f)
+    calls = {
+        "token_logprob": dict(logits=z, token_ids=y, valid=valid),
+        "token_logprob_softmax_grad": dict(logits=z, token_ids=y, valid=valid, sgrad=z.clone()),
+        "diagnostics": dict(rows, rewards=r, group_size=3),
+        "grpo_loss_grad": dict(rows, **loss, logits=z, token_ids=y, lse=f, dlogits=z.clone()),
+        "grpo_row_scale": dict(rows, **loss),
+        "fp8_quantize_rows": dict(logits=z),
+        "fp8_dequantize_rows": dict(codes=codes, scale=f),
+        "fp8_rollout_logprob": dict(logits=z, token_ids=y, valid=valid),
+        "lm_head_logprob": dict(hidden=h, weight=w, token_ids=y, valid=valid),
+        "lm_head_grad": dict(hidden=h, weight=w, token_ids=y, lse=f, logp=f, coeff=f),
+    }
+    sized_by_others = {("fp8_quantize_rows", "logits"), ("lm_head_logprob", "weight"), ("lm_head_grad", "weight")}
+    for name, args in calls.items():
+        same(getattr(both[0], name)(**args), getattr(both[1], name)(**args))
+        for arg, t in args.items():
+            if not isinstance(t, torch.Tensor):
+                continue
+            for k, wrong in enumerate(bad_forms(t)):
+                if k == 2 and (name, arg) in sized_by_others:
+                    continue                                   # as many rows as it has
+                errors = []
+                for ctx in both:
+                    with pytest.raises((TypeError, ValueError)) as e:
+                        getattr(ctx, name)(**{**args, arg: wrong})
+                    errors.append((type(e.value), str(e.value)))
+                assert errors[0] == errors[1], (name, arg, k)
+    # what only an output can have wrong: other strides, and the logits' type
+    wide = torch.zeros(n, v + 8, device="cuda")[:, :v]
+    for ctx in both:
+        for out in (wide, z.bfloat16()):
+            with pytest.raises(ValueError):
+                ctx.grpo_loss_grad(**{**calls["grpo_loss_grad"], "dlogits": out})
+            with pytest.raises(ValueError):
+                ctx.token_logprob_softmax_grad(**{**calls["token_logprob_softmax_grad"], "sgrad": out})
+
+
 def test_storage_that_refuses_its_address(both):
     """A C++ exception in the middle of a native call: the method's own way raises it, and the interpreter goes on."""
     z, y = torch.randn(8, 64, device="cuda"), torch.zeros(8, device="cuda", dtype=torch.int32)

@@ -438,16 +438,25 @@ constexpr int kUnrollFwd = 4;
 //   1,500 x 151,936        72.6   74.9    74.6        41,643 x 8,192         101.8   108.2   110.0
 //   1,500 x 248,320 fp32  222.7  228.3   232.1        2,048 x 1,000 fp32       9.1     7.5     7.6
 //   8,192 x 32,003         89.7   80.6    84.8        1,024 x 3,001            8.1     7.5     8.6
-//   8,192 x 32,003 fp32   155.7  156.9   160.3
-//   8,192 x 50,257        128.2  125.5   129.0
+//   8,192 x 32,003 fp32   155.7  156.9   160.3        1,024 x 64               4.5     4.2     4.2
+//   8,192 x 50,257        128.2  125.5   129.0        1,024 x 1,000            4.5     4.2     4.3
 //   41,643 x 32,003       441.7  388.6   404.6
 //   41,643 x 151,936      1,954  1,883   1,860
+// and around the lines between 2,048 and 4,096 vectors (threads 1,024, 512, 256):
+//   256 x 8,192 fp32        4.2    3.9     4.0        300 x 12,288 fp32        5.5     4.9     4.6
+//   64 x 12,288 fp32        4.2    3.9     4.1        700 x 12,288 fp32        8.4     7.6     7.2
+//   256 x 28,000, relative  0.76   0.79    0.96       300 x 20,000, relative   1.02    0.88    0.94
+//   16,384 x 10,001 fp32           96.5   101         30,000 x 20,001                 187     181
+//   16,384 x 24,001               117     121
 int logprob_threads(const ais_ctx* ctx, long long n_rows, long long nvec, bool bf16) {
   const long long cus = ctx->n_cus;
-  if (nvec >= 2048 && n_rows <= cus) return 1024;
+  const bool few = n_rows < 8 * cus;
+  if (nvec >= 2048 && n_rows <= cus) return nvec < 3500 ? 512 : 1024;
   if (nvec >= 8192 && n_rows <= 8 * cus) return n_rows > 2 * cus ? 1024 : bf16 ? 512 : 256;
-  if (nvec >= 2500) return nvec < 8192 ? 512 : 256;
-  if (nvec >= 896 || n_rows < 8 * cus) return 256;
+  if (nvec >= (few == bf16 ? 2500 : few ? 3200 : 3000)) return nvec < 8192 ? 512 : 256;
+  // (256 threads that share a few vectors read some of them more than once)
+  if (few) return nvec <= 64 ? 64 : nvec <= 128 ? 128 : 256;
+  if (nvec >= 896) return 256;
   return nvec >= 512 ? 128 : 64;
 }
 

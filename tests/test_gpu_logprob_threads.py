@@ -37,3 +37,10 @@ def test_log_probs_at_the_edges_of_the_rule(dtype, vectors):
         assert torch.equal(again[0], ctx.token_logprob(base[:7], y[:7])[0])
     assert ctx.status() == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("vectors", [127, 767, 768, 769, 1535, 1537, 2999, 3000, 3199, 3200, 3499, 3501])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_log_probs_at_the_other_edges(dtype, vectors):
+    """The lines that lie elsewhere for few rows and for the two types, and tails of three vectors a thread."""
+    test_log_probs_at_the_edges_of_the_rule(dtype, vectors)

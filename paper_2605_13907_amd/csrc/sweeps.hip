@@ -30,13 +30,14 @@ using namespace dev;
 // instructions.  The three-call step over 12,345 x 50,257 bf16: 1,657 us element-wise, 636 us with vectors; over
 // 4,096 x 32,003 fp32: 415 and 236 us.)  The vectors after the last whole round of UNROLL per thread are loaded together
 // too, those past the end of the row masked, instead of one by one, each waiting for its own: 8,192 x 32,003 bf16 87.9 ->
-// 84.8 us with 256 threads, no difference at 151,936.
+// 84.8 us with 256 threads, no difference at 151,936.  (Three of them as four, one masked: 512 x 6,000 4.55 instead of 4.29
+// us, 1,000 x 6,000 5.75 and 5.40.)
 template <typename T, bool ALIGNED, int THREADS, int UNROLL>
 __global__ __launch_bounds__(THREADS) void token_logprob_kernel(
     const T* __restrict__ logits, long long row_stride, int vocab, const int* __restrict__ token_ids,
     const unsigned char* __restrict__ valid, float inv_temperature, float* __restrict__ logp_out,
     float* __restrict__ lse_out, int* __restrict__ status) {
-  static_assert(UNROLL == 4, "the last vectors of a row are loaded by ones, twos and fours");
+  static_assert(UNROLL == 4, "the last vectors of a row are loaded by one to four a thread");
   constexpr int N = Vec<T>::N;
   const long long row = blockIdx.x;
   const int tid = threadIdx.x;
@@ -94,11 +95,13 @@ __global__ __launch_bounds__(THREADS) void token_logprob_kernel(
     };
     typedef std::integral_constant<int, 1> One;
     typedef std::integral_constant<int, 2> Two;
+    typedef std::integral_constant<int, 3> Three;
     typedef std::integral_constant<int, UNROLL> All;
     int base = 0;
     for (; base + UNROLL * THREADS <= nvec; base += UNROLL * THREADS) batch(base, All{}, std::false_type{});
     const int left = nvec - base;                // uniform
-    if (left > 2 * THREADS) batch(base, All{}, std::true_type{});
+    if (left > 3 * THREADS) batch(base, All{}, std::true_type{});
+    else if (left > 2 * THREADS) batch(base, Three{}, std::true_type{});
     else if (left > THREADS) batch(base, Two{}, std::true_type{});
     else if (left > 0) batch(base, One{}, std::true_type{});
   }

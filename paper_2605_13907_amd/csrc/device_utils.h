@@ -33,14 +33,6 @@ __device__ __forceinline__ double log1p_scaled(float s, double e) {
   return s > 0.f ? log1p((double)s * exp2(e)) : 0.0;   // here e <= 64 + 149: 2^e is finite
 }
 
-// A difference of two logits' exponents as the fp32 `scale` = inv_temperature * log2(e) gives it, with that factor as fp64
-// has it: the fp32 constant alone is 1.3e-8 off, which ten units of difference make 1.3e-7 of a small log-prob (rms relative
-// error of log-probs over 4,096 rows of 32,003 fp32 logits 9.9e-8 without and 5.0e-8 with).
-__device__ __forceinline__ double exact_exponent(double e, float inv_temperature, float scale) {
-  const double off = __builtin_fma((double)inv_temperature, 1.4426950408889634074, -(double)scale);
-  return e * (1.0 + off * __builtin_amdgcn_rcp((double)scale));
-}
-
 __device__ __forceinline__ u32x4 load_stream(const u32x4* p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ void store_stream(u32x4* p, u32x4 v) { __builtin_nontemporal_store(v, p); }
 

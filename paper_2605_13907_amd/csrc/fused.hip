@@ -187,7 +187,6 @@ __global__ __launch_bounds__(THREADS) void fused_logprob_softmax_kernel(
     for (int w = 1; w < kWaves; ++w) t = merge(t, lds[w]);
     float lse, logp;
     if (y_ok) {
-      // (`exact` is what exact_exponent would multiply by: from the host, it takes no vector registers)
       const double l1p = log1p_scaled(t.s, ((double)t.m - (double)zy * (double)scale) * exact);
       logp = (float)(-l1p);
       lse = (float)((double)zy * (double)inv_temperature + l1p);
@@ -260,8 +259,7 @@ int launch_nv(ais_ctx* ctx, const T* z, long long n_rows, int vocab, long long r
       return hip_fail(ctx, hipErrorInvalidValue);
   }
   kernel<<<dim3((unsigned)n_rows), dim3(THREADS), NL * kSlotBytes, ctx->stream>>>(
-      z, row_stride, vocab, token_ids, valid, inv_t,
-      (double)inv_t * 1.4426950408889634074 / (double)(inv_t * kLog2e), logp, lse, sgrad, ctx->status_dev);
+      z, row_stride, vocab, token_ids, valid, inv_t, exact_exponents(inv_t), logp, lse, sgrad, ctx->status_dev);
   return AIS_OK;
 }
 

@@ -35,7 +35,7 @@ using namespace dev;
 template <typename T, bool ALIGNED, int THREADS, int UNROLL>
 __global__ __launch_bounds__(THREADS) void token_logprob_kernel(
     const T* __restrict__ logits, long long row_stride, int vocab, const int* __restrict__ token_ids,
-    const unsigned char* __restrict__ valid, float inv_temperature, float* __restrict__ logp_out,
+    const unsigned char* __restrict__ valid, float inv_temperature, double exact, float* __restrict__ logp_out,
     float* __restrict__ lse_out, int* __restrict__ status) {
   static_assert(UNROLL == 4, "the last vectors of a row are loaded by one to four a thread");
   constexpr int N = Vec<T>::N;
@@ -125,8 +125,7 @@ __global__ __launch_bounds__(THREADS) void token_logprob_kernel(
   if (tid == 0) {
     if (y_ok) {
       // once per row, in fp64: r = S_o / e^{z_y/T};  logp = -log1p(r);  lse = z_y/T + log1p(r)
-      const double l1p =
-          log1p_scaled(t.s, exact_exponent((double)t.m - (double)zy * (double)scale, inv_temperature, scale));
+      const double l1p = log1p_scaled(t.s, ((double)t.m - (double)zy * (double)scale) * exact);
       logp_out[row] = (float)(-l1p);
       lse_out[row] = (float)((double)zy * (double)inv_temperature + l1p);
     } else {
@@ -478,7 +477,8 @@ int launch_token_logprob(ais_ctx* ctx, const void* logits, ais_dtype dtype, long
       auto kernel = vec_ok(z, row_stride, sizeof(T)) ? token_logprob_kernel<T, true, kThreads, kUnrollFwd>
                                                      : token_logprob_kernel<T, false, kThreads, kUnrollFwd>;
       kernel<<<dim3((unsigned)n_rows), dim3(kThreads), 0, ctx->stream>>>(
-          z, row_stride, vocab, token_ids, valid, inv_temperature, logp_out, lse_out, ctx->status_dev);
+          z, row_stride, vocab, token_ids, valid, inv_temperature, exact_exponents(inv_temperature), logp_out, lse_out,
+          ctx->status_dev);
     };
     const int threads = logprob_threads(ctx, n_rows, nvec, std::is_same_v<T, bf16_t>);
     if (threads == 1024) run(std::integral_constant<int, 1024>{});

@@ -30,6 +30,12 @@ constexpr int kTicketWord = 32, kStaticTicketWord = 48;
 // 8,192 44.8 and 97.7, 16,384 82.2 and 104.3, 24,001 120 and 122, 28,001 139 and 122.  41,643 rows of 1,000: 25.6 and 452.4;
 // 31.1 and 467.5.  300 rows of 16,001 13.4 and 14.0, of 20,001 14.8 and 14.3.
 constexpr int kFp8NarrowRow = 16391;
+// ... and where every row has a compute unit to itself and is 16-byte aligned: 256 threads then read the row twice with
+// nothing beside them, which takes longer from about six vectors for each thread on.  us, streaming and table, 1 and 256
+// rows: quantisation, 12,288 logits 4.6 and 5.0, 5.2 and 5.8; 13,312 5.0 and 5.0, 5.7 and 5.8; 16,384 5.5 and 5.0, 6.2 and
+// 5.9; log-prob, 12,288 5.3 and 5.5, 5.9 and 6.2; 13,312 5.7 and 5.6, 6.2 and 6.2; 16,384 6.3 and 5.5, 6.8 and 6.2.  300 rows
+// of 16,384: 6.5 and 8.3, 7.9 and 8.7.
+constexpr int kFp8NarrowLoneRow = 12800;
 constexpr int kMaxDevices = 64;        // device indices a context may be created on
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;

@@ -87,3 +87,32 @@ def test_a_nan_does_not_round_the_products(rows, vocab):
     y = (at.squeeze(1).int() + 1) % vocab
     assert torch.equal(ctx.fp8_rollout_logprob(nan, y), ctx.fp8_rollout_logprob(lowest, y))
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype,vocab", [(torch.bfloat16, v) for v in (12_792, 12_800, 12_801, 12_808, 16_384, 16_391)]
+                         + [(torch.float32, v) for v in (1020, 1024, 1025, 1028, 2052, 4096, 4099, 4100)])
+def test_rows_with_a_compute_unit_each(dtype, vocab):
+    """Up to 256 rows, where kernels that hold a row take narrower ones: both sides of the lines, in rows and in width,
+    with NaNs (the two kinds of kernel agree on their codes)."""
+    ctx = B.AisContext()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(vocab)
+    pitch = -(-vocab // 8) * 8                                # aligned rows, also of odd width
+    for rows in (1, 255, 256, 257):
+        z = (torch.randn(rows, pitch, generator=gen, device="cuda") * 3).to(dtype)[:, :vocab]
+        z[::3, vocab // 3] = float("nan")
+        z[::6, vocab // 3] = -z[::6, vocab // 3]
+        y = torch.randint(0, vocab // 3, (rows,), generator=gen, device="cuda", dtype=torch.int32)
+        # (codes of odd width lie differently from their logits: element by element, where a NaN is -448 in every row)
+        want, s = reference(z, dtype == torch.bfloat16 and pitch == vocab)
+        codes, scale = ctx.fp8_quantize_rows(z)
+        assert torch.equal(scale, s) and torch.equal(codes, want), rows
+        back = reference(z, dtype == torch.bfloat16)[0].view(torch.float8_e4m3fn).double() * s.double().unsqueeze(1)
+        ref = torch.log_softmax(back, dim=1).gather(1, y.long().unsqueeze(1)).squeeze(1)
+        # fp32 log-sum-exp minus an fp32 logit, both of up to 20: a few ulp of 2^-19
+        assert (ctx.fp8_rollout_logprob(z, y).double() - ref).abs().max() < 8e-6, rows
+        flat = reference(torch.nan_to_num(z), False)
+        for out in (torch.float32, torch.bfloat16):
+            assert torch.equal(ctx.fp8_dequantize_rows(flat[0], flat[1], out),
+                               (flat[0].view(torch.float8_e4m3fn).float() * flat[1].unsqueeze(1)).to(out)), rows
+    ctx.close()

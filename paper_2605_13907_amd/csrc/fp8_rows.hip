@@ -251,14 +251,17 @@ bool codes_aligned(const void* z, long long row_stride, int esize, const void* c
 // Vectors per lane of a row that the register-resident kernel takes, otherwise 0: it does not fit, or it is a narrow one
 // that the streaming kernel does better with.  That kernel has eight or more rows in a compute unit at a time (8,192 fp32
 // rows of 1,000 elements: 11.0 us, 25.9 here; of 2,048 15.6 and 28.6; of 4,096 32.3 and 37.0; unaligned, of 5,001 48 and 49, of
-// 6,001 59 and 54).  bf16 rows come here only where they are too wide for the table kernel, which takes all others but the
-// narrow ones.
+// 6,001 59 and 54).  Aligned rows that have a compute unit each are narrow only up to a vector for each thread of that kernel
+// (us, streaming and here, 1 and 256 rows: 1,024 elements 2.4 and 2.4, 2.8 and 3.1; 1,500 2.6 and 2.4, 3.1 and 3.1; 4,096 3.3
+// and 2.6, 3.7 and 3.2; 300 rows of 4,096 3.8 both).  bf16 rows come here only where they are too wide for the table kernel,
+// which takes all others but the narrow ones.
 template <typename T>
-int vectors_per_lane(int vocab) {
+int vectors_per_lane(const ais_ctx* ctx, const T* z, long long n_rows, int vocab, long long row_stride) {
   constexpr int N = Vec<T>::N;
   const int need = (vocab / N + kRowThreads - 1) / kRowThreads;
-  if (sizeof(T) == 2 ? need <= 24 : need <= 1) return 0;
-  return need <= 24 + kLdsSlots ? (need < 1 ? 1 : need) : 0;
+  const bool lone = n_rows <= ctx->n_cus && vocab / N > kSweepThreads && row_aligned(z, row_stride, sizeof(T));
+  if (sizeof(T) == 2 ? need <= 24 : need <= 1 && !lone) return 0;
+  return need <= 24 + kLdsSlots ? need : 0;
 }
 
 template <typename T, bool ALIGNED, int NV, int NL, int KFULL>
@@ -309,16 +312,11 @@ bool dispatch_rows(ais_ctx* ctx, int need, const T* z, long long n_rows, int voc
 bool try_fp8_quantize_rows(ais_ctx* ctx, const void* logits, ais_dtype dtype, long long n_rows, int vocab,
                            long long row_stride, unsigned char* codes, long long codes_stride, float* scale_out) {
   if (!codes_aligned(logits, row_stride, dtype == AIS_BF16 ? 2 : 4, codes, codes_stride)) return false;
-  if (dtype == AIS_BF16) {
-    const int need = vectors_per_lane<bf16_t>(vocab);
-    if (need == 0) return false;
-    return dispatch_rows<bf16_t>(ctx, need, static_cast<const bf16_t*>(logits), n_rows, vocab, row_stride, codes,
-                                 codes_stride, scale_out);
-  }
-  const int need = vectors_per_lane<float>(vocab);
-  if (need == 0) return false;
-  return dispatch_rows<float>(ctx, need, static_cast<const float*>(logits), n_rows, vocab, row_stride, codes,
-                              codes_stride, scale_out);
+  auto launch = [&](const auto* z) {
+    const int need = vectors_per_lane(ctx, z, n_rows, vocab, row_stride);
+    return need != 0 && dispatch_rows(ctx, need, z, n_rows, vocab, row_stride, codes, codes_stride, scale_out);
+  };
+  return dtype == AIS_BF16 ? launch(static_cast<const bf16_t*>(logits)) : launch(static_cast<const float*>(logits));
 }
 
 // Returns true when the burst kernel was launched, false when the rows do not qualify (alignment, or wider than

@@ -333,8 +333,10 @@ bool try_fp8_dequantize_burst(ais_ctx* ctx, const unsigned char* codes, long lon
   const int need = (vocab / n + kRowThreads - 1) / kRowThreads;
   // narrow aligned rows: 256 threads that store each vector as they form it (8,192 rows decoded to bf16, 1,024 elements 7.8
   // us, 22.0 here; 4,096 15.3 and 27.3; 8,192 29.7 and 41.0; to fp32, 1,024 7.2 and 17.1, 4,096 25.0 and 35.7; 41,643 rows of
-  // 8,192 to bf16 170 and 200)
-  if (aligned && need <= 1) return false;
+  // 8,192 to bf16 170 and 200).  Where every row has a compute unit to itself they are narrow up to three vectors for each
+  // of those threads (64 rows to bf16, 4,096 elements 2.32 and 2.45 here, 6,000 2.77 and 2.75, 8,192 2.74 and 2.57; 256 rows
+  // of 4,104 2.93 and 3.13; 64 to fp32, 2,048 2.27 and 2.35, 4,096 2.56 and 2.40)
+  if (aligned && need <= 1 && (n_rows > ctx->n_cus || vocab / n <= 3 * kSweepThreads)) return false;
   dim3 grid((unsigned)n_rows), block(kRowThreads);
   // (vectors that surely exist, vectors per lane and burst, bursts): a row reaches a class only if it is wider than
   // the class before it; an unaligned row may have lost up to 8 vectors to its head

@@ -32,10 +32,10 @@ constexpr int kTicketWord = 32, kStaticTicketWord = 48;
 constexpr int kFp8NarrowRow = 16391;
 // ... and where every row has a compute unit to itself and is 16-byte aligned: 256 threads then read the row twice with
 // nothing beside them, which takes longer from about six vectors for each thread on.  us, streaming and table, 1 and 256
-// rows: quantisation, 12,288 logits 4.6 and 5.0, 5.2 and 5.8; 13,312 5.0 and 5.0, 5.7 and 5.8; 16,384 5.5 and 5.0, 6.2 and
+// rows: quantisation, 12,288 logits 4.6 and 5.0, 5.2 and 5.8; 14,000 5.0 and 5.0, 5.8 and 5.8; 15,000 5.4 and 5.0, 6.2 and
 // 5.9; log-prob, 12,288 5.3 and 5.5, 5.9 and 6.2; 13,312 5.7 and 5.6, 6.2 and 6.2; 16,384 6.3 and 5.5, 6.8 and 6.2.  300 rows
 // of 16,384: 6.5 and 8.3, 7.9 and 8.7.
-constexpr int kFp8NarrowLoneRow = 12800;
+constexpr int kFp8NarrowLoneQuantize = 14336, kFp8NarrowLoneLogprob = 12800;
 constexpr int kMaxDevices = 64;        // device indices a context may be created on
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;

@@ -545,9 +545,11 @@ bool row_aligned(const void* z, long long row_stride) {
 }
 
 // Vectors per lane of a bf16 row, or 0 when the row does not qualify for these kernels: too wide or narrow.
-int table_vectors_per_lane(const ais_ctx* ctx, const void* z, long long n_rows, int vocab, long long row_stride, int most) {
+// lone: widest narrow row where each has a compute unit to itself.
+int table_vectors_per_lane(const ais_ctx* ctx, const void* z, long long n_rows, int vocab, long long row_stride, int lone,
+                           int most) {
   const int need = (vocab / 8 + kRowThreads - 1) / kRowThreads;
-  const int narrow = n_rows <= ctx->n_cus && row_aligned(z, row_stride) ? kFp8NarrowLoneRow : kFp8NarrowRow;
+  const int narrow = n_rows <= ctx->n_cus && row_aligned(z, row_stride) ? lone : kFp8NarrowRow;
   return vocab > narrow && need <= most ? need : 0;
 }
 
@@ -565,7 +567,7 @@ bool try_fp8_quantize_table(ais_ctx* ctx, const void* logits, ais_dtype dtype, l
   if ((reinterpret_cast<uintptr_t>(codes) - reinterpret_cast<uintptr_t>(logits) / 2) % 8 != 0 ||
       (codes_stride - row_stride) % 8 != 0)
     return false;
-  const int need = table_vectors_per_lane(ctx, logits, n_rows, vocab, row_stride, 24);
+  const int need = table_vectors_per_lane(ctx, logits, n_rows, vocab, row_stride, kFp8NarrowLoneQuantize, 24);
   if (need == 0) return false;
   const bf16_t* z = static_cast<const bf16_t*>(logits);
   const long long resident = (long long)ctx->n_cus * quantize_workgroups(need <= 4 ? 4 : 24);
@@ -597,7 +599,7 @@ bool try_fp8_rollout_logprob_table(ais_ctx* ctx, const void* logits, ais_dtype d
                                    float* logp_out) {
   if (dtype != AIS_BF16) return false;
   // 23 vectors per lane in registers, 8 more in LDS slots beside the table
-  const int need = table_vectors_per_lane(ctx, logits, n_rows, vocab, row_stride, 23 + 8);
+  const int need = table_vectors_per_lane(ctx, logits, n_rows, vocab, row_stride, kFp8NarrowLoneLogprob, 23 + 8);
   if (need == 0) return false;
   const bf16_t* z = static_cast<const bf16_t*>(logits);
   const long long resident = (long long)ctx->n_cus * logprob_workgroups(need <= 8 ? 8 : 24);

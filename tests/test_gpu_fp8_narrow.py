@@ -89,7 +89,7 @@ def test_a_nan_does_not_round_the_products(rows, vocab):
     ctx.close()
 
 
-@pytest.mark.parametrize("dtype,vocab", [(torch.bfloat16, v) for v in (6144, 6152, 8192, 12_792, 12_800, 12_801, 12_808, 16_384, 16_391)]
+@pytest.mark.parametrize("dtype,vocab", [(torch.bfloat16, v) for v in (6144, 6152, 8192, 12_792, 12_800, 12_801, 12_808, 14_336, 14_344, 16_384, 16_391)]
                          + [(torch.float32, v) for v in (1020, 1024, 1025, 1028, 3072, 3076, 4096, 4099, 4100)])
 def test_rows_with_a_compute_unit_each(dtype, vocab):
     """Up to 256 rows, where kernels that hold a row take narrower ones: both sides of the lines, in rows and in width,

@@ -371,21 +371,26 @@ __device__ __forceinline__ float advantage(const float* rewards, int i, int grou
 
 // ---- level 2: responses -> batch moments, diagnostics, alpha ---------------------------------------------------------
 // Runs in the last workgroup of diag_reduce_kernel.  A response's tiles are folded by a group of L lanes, L (a power of
-// two up to 64) as large as the responses leave threads for and no larger than their tiles need on average: lane l folds
+// two) as large as the responses leave threads for and no larger than their tiles need on average: lane l folds
 // tiles l, l + L, ... in order, then the lanes are merged in a fixed tree.  With one thread per response a batch of 4
-// responses of 1,000 tiles was a chain of 1,000 dependent reads.
+// responses of 1,000 tiles was a chain of 1,000 dependent reads.  A second wavefront for a response and more come only
+// where each lane has more than five tiles without it: a step of the chain is 0.3 us, a wavefront more at work 0.2 (300,000
+// rows in 1, 2 and 8 responses, 64 lanes each: 20.3, 17.5, 15.9 us; as many as there are threads: 17.6, 17.5, 17.4).
+int fold_lanes(int n_resp, long long most_tiles) {
+  int lanes = 1;
+  while ((lanes < 64 ? 1 : 5) * (long long)lanes * n_resp < most_tiles && 2LL * lanes * n_resp <= kThreads) lanes <<= 1;
+  return lanes;
+}
 // The code runs once per launch, cold: its size is part of its time (a kilobyte of straight code costs 0.3 us of
 // instruction fetches), so what is the same for several quantities is done once, by lanes that hold one each.
 template <bool SELF>
-__device__ void diag_final(const Partials<kDiagWords>& partials, const Tiling<SELF>& tiling, int n_resp, int most_tiles,
+__device__ void diag_final(const Partials<kDiagWords>& partials, const Tiling<SELF>& tiling, int n_resp, int lanes,
                            int group_size, const float* rewards, const float* s_adv, const ais_params& p,
                            float* __restrict__ adv_out, int* __restrict__ count_out, ais_diag* __restrict__ diag_out,
                            const int* status, double* lds) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   Moments m[3] = {};                                  // of w_bar, of A and of A w_bar over the thread's valid rows
   double d[4] = {};                                   // sums: |d|, d, |dp|, rows with rho > C (exact in fp64)
-  int lanes = 1;
-  while (lanes < 64 && lanes * n_resp < most_tiles && 2 * lanes * n_resp <= kThreads) lanes <<= 1;
   const int l = threadIdx.x & (lanes - 1);
   const int per_pass = kThreads / lanes;
   for (int i0 = 0; i0 < n_resp; i0 += per_pass) {     // uniform: the lanes of a wavefront merge across groups below
@@ -410,11 +415,11 @@ __device__ void diag_final(const Partials<kDiagWords>& partials, const Tiling<SE
         t += lanes;
       }
     }
-    for (int off = 1; off < lanes; off <<= 1)          // uniform: every lane of the wavefront takes part
+    for (int off = 1; off < min(lanes, 64); off <<= 1) // uniform: every lane of the wavefront takes part
       r = merge(r, Moments{__shfl_xor(r.n, off), __shfl_xor(r.mean, off), __shfl_xor(r.m2, off)});
-    if (l != 0 || i >= n_resp) continue;               // lane 0 of the group goes on
-    adv_out[i] = (float)a;
-    count_out[i] = (int)r.n;
+    if ((l & 63) != 0 || i >= n_resp) continue;        // lane 0 of the group, or of each of its wavefronts, goes on
+    if (l == 0) adv_out[i] = (float)a;
+    if (lanes <= 64) count_out[i] = (int)r.n;
     // token-level moments of A and A w_bar: A (the stored fp32 value) is constant over the response's rows, so these
     // have mean A mean(w_bar) and squared deviations A^2 m2(w_bar)
     const Moments of[3] = {r, Moments{r.n, a, 0.0}, Moments{r.n, a * r.mean, a * a * r.m2}};
@@ -452,6 +457,11 @@ __device__ void diag_final(const Partials<kDiagWords>& partials, const Tiling<SE
   }
   __syncthreads();
   if (wave != 0) return;
+  if (lanes > 64 && lane < n_resp) {                   // responses of several wavefronts, one pass: their parts' counts
+    double n = 0.0;
+    for (int w = 0; w < lanes >> 6; ++w) n += lds[lane * (lanes >> 6) + w];
+    count_out[lane] = (int)n;
+  }
   // over the workgroup: 16 lanes for each of w_bar, A, A w_bar (and nothing), one for each wavefront; the sums likewise
   static_assert(kWaves == 16, "four groups of 16 lanes");
   const int v = lane & 15, set = lane >> 4, mine = 4 * min(set, 2) * kWaves + v;
@@ -516,7 +526,7 @@ template <bool SELF>
 __global__ __launch_bounds__(kThreads, 4) void diag_reduce_kernel(
     const float* __restrict__ logp_train, const float* __restrict__ logp_roll,
     const unsigned char* __restrict__ valid, long long n_rows, const long long* __restrict__ cu_rows, int n_resp,
-    const int* __restrict__ tile_off, TileRule rule, double* partial, int group_size,
+    const int* __restrict__ tile_off, TileRule rule, double* partial, int lanes, int group_size,
     const float* __restrict__ rewards, ais_params p, double lnC, float* __restrict__ adv_out, int* __restrict__ count_out,
     ais_diag* __restrict__ diag_out, int* status, Tickets tickets) {
   __shared__ double lds[16 * kWaves];                // three sets of moments and four sums per wavefront
@@ -625,8 +635,8 @@ __global__ __launch_bounds__(kThreads, 4) void diag_reduce_kernel(
   }
   // ---- level 2, in the workgroup that finishes last ----
   if (last_workgroup(tickets))
-    diag_final<SELF>(partials, tiling, n_resp, (int)((n_rows + (1LL << rule.shift) - 1) >> rule.shift), group_size,
-                     rewards, s_adv, p, adv_out, count_out, diag_out, status, lds);
+    diag_final<SELF>(partials, tiling, n_resp, lanes, group_size, rewards, s_adv, p, adv_out, count_out, diag_out, status,
+                     lds);
 }
 
 // ---- per-row coefficient of the gradient, rectification weight, loss ------------------------------------------------
@@ -805,7 +815,8 @@ int launch_diagnostics(ais_ctx* ctx, const float* logp_train, const float* logp_
   const TileRule rule = tile_rule(n_rows, n_resp);
   const int grid = reduction_grid(ctx, rule.max_tiles);
   kernel<<<grid, kThreads, 0, ctx->stream>>>(
-      logp_train, logp_roll, valid, n_rows, cu_rows, n_resp, tile_off, rule, partial, group_size, rewards, p,
+      logp_train, logp_roll, valid, n_rows, cu_rows, n_resp, tile_off, rule, partial,
+      fold_lanes(n_resp, (n_rows + (1LL << rule.shift) - 1) >> rule.shift), group_size, rewards, p,
       std::log((double)p.C), adv_out, count_out, diag_out, ctx->status_dev, take_tickets(ctx, in_static, grid));
   return hip_fail(ctx, hipGetLastError());
 }

@@ -17,6 +17,9 @@ CASES = {
     "long_responses": (64, 8, ("lognormal", 9.5, 0.8), 1.0),          # ~13 k rows each, up to ~100 tiles
     "one_huge_response": (1, 1, ("fixed", 2_000_000), 0.6),            # ~2,000 tiles of one response
     "many_short": (20_000, 8, ("uniform", 0, 5), 0.8),                 # empty responses included
+    "two_long": (2, 2, ("fixed", 300_000), 0.6),                       # folded by several wavefronts each
+    "six_long": (6, 3, ("lognormal", 12.4, 0.7), 0.5),
+    "three_skewed": (3, 1, ("lognormal", 10.5, 2.5), 1.0),
     "mixed": (512, 4, ("lognormal", 6.0, 1.5), 0.5),
 }
 

@@ -800,11 +800,12 @@ int launch_lm_tile(ais_ctx* ctx, int grid, const void* hidden, long long ld_h, c
   static std::once_flag once[2][kMaxDevices];                          // per function and device
   static bool ok[2][kMaxDevices];
   const int ragged = d_model % kLmTileK != 0 ? 1 : 0;
-  auto kernel = ragged ? lm_head_tile_kernel<GRAD, true, DEEP> : lm_head_tile_kernel<GRAD, false, DEEP>;
-  if (!allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kernel), lm_lds_bytes(DEEP), once[ragged], ok[ragged]))
+  auto kernel = ragged ? lm_head_tile_kernel<GRAD, true, true> : lm_head_tile_kernel<GRAD, false, DEEP>;
+  const int lds = lm_lds_bytes(DEEP || ragged);                        // (ragged: see lm_deep)
+  if (!allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kernel), lds, once[ragged], ok[ragged]))
     return hip_fail(ctx, hipErrorInvalidValue);
   ScopedTimer timer(ctx, GRAD ? AIS_K_LM_HEAD_GRAD : AIS_K_LM_HEAD);
-  kernel<<<grid, kLmThreads, lm_lds_bytes(DEEP), ctx->stream>>>(static_cast<const bf16_t*>(hidden), ld_h,
+  kernel<<<grid, kLmThreads, lds, ctx->stream>>>(static_cast<const bf16_t*>(hidden), ld_h,
                                                          static_cast<const bf16_t*>(weight), ld_w, rows, dplan, d_model,
                                                          vocab, token_ids, scale, n_vtiles, part_m, part_s, zy, ga);
   return hip_fail(ctx, hipGetLastError());
@@ -816,7 +817,15 @@ int launch_lm_tile(ais_ctx* ctx, int grid, const void* hidden, long long ld_h, c
 // 7,331, 41,643 38.1 and 39.9 ms.  The gradient's chunks are short items, most of them in their first tiles: 4,096 rows x
 // 126,464 x 4,096 10.17 and 9.90 ms, 16,384 x 32,000 x 4,096 10.61 and 10.39, 12,000 x 126,464 x 2,048 16.4 and 16.0, but
 // 3,000 x 50,257 x 1,024 1.23 and 1.25.
-bool lm_deep(bool grad, long long n_rows, int d_model) { return grad ? d_model >= 2048 : n_rows <= 6144; }
+// At any size where the embedding's rows do not begin with a 128-byte line, as with a ragged d_model: a slice's rows then lie
+// across two lines each, and one step is too short for them.  Log-prob, x 151,936, us without and with: 300 rows x 2,056 356
+// and 268, 800 x 4,104 1,343 and 963, 1,600 x 1,032 575 and 462 (without, before blocks had columns of their own: 325, 1,167,
+// 535), 8,192 x 2,056 4,974 and 3,957, 20,000 x 1,032 6,008 and 5,405; gradient, 6,000 x 126,464 x 1,056 6,061 and 5,735,
+// 3,000 x 32,000 x 544 550 and 552.
+bool lm_deep(bool grad, long long n_rows, int d_model, const void* weight, long long ld_w) {
+  if (d_model % kLmTileK != 0 || reinterpret_cast<uintptr_t>(weight) % 128 != 0 || ld_w % 64 != 0) return true;
+  return grad ? d_model >= 2048 : n_rows <= 6144;
+}
 
 int launch_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long ld_h, const void* weight, long long ld_w,
                            long long n_rows, int d_model, int vocab, const int* token_ids,
@@ -834,8 +843,8 @@ int launch_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long ld_h, con
   if (e != hipSuccess) return hip_fail(ctx, e);
   LmRows rows{valid != nullptr ? row_index : nullptr};
   // (how many rows a mask leaves is known on the device only: half of them is the guess)
-  auto launch = lm_deep(false, valid != nullptr ? n_rows / 2 : n_rows, d_model) ? launch_lm_tile<false, true>
-                                                                                : launch_lm_tile<false, false>;
+  auto launch = lm_deep(false, valid != nullptr ? n_rows / 2 : n_rows, d_model, weight, ld_w) ? launch_lm_tile<false, true>
+                                                                                              : launch_lm_tile<false, false>;
   const int rc = launch(ctx, max_items, hidden, ld_h, weight, ld_w, rows, dplan, d_model, vocab, token_ids,
                                        inv_temperature * kLog2e, plan.n_vtiles, part_m, part_s, zy, LmGradArgs{});
   if (rc != AIS_OK) return rc;
@@ -877,7 +886,7 @@ int launch_lm_head_dlogits_chunk(ais_ctx* ctx, const void* hidden, long long ld_
   const LmDevPlan* dplan = static_cast<const LmDevPlan*>(dev_plan) + which;
   LmRows rows{row_index};
   LmGradArgs ga{lse, logp, coeff, static_cast<bf16_t*>(ds), ds_stride, y_off, row_index != nullptr ? 1 : 0};
-  auto launch = lm_deep(true, n_rows, d_model) ? launch_lm_tile<true, true> : launch_lm_tile<true, false>;
+  auto launch = lm_deep(true, n_rows, d_model, weight, ld_w) ? launch_lm_tile<true, true> : launch_lm_tile<true, false>;
   const int rc = launch(ctx, max_items, hidden, ld_h, weight, ld_w, rows, dplan, d_model, vocab,
                                         token_ids, inv_temperature * kLog2e, plan.n_vtiles, nullptr, nullptr, nullptr,
                                         ga);

@@ -59,3 +59,30 @@ def test_either_side_of_the_rule(rows, d):
     check(ctx, rows, 520, d)
     check(ctx, rows, 520, d, grad=False, masked=True)
     ctx.close()
+
+
+@pytest.mark.parametrize("rows,d,pitch", [(6145, 72, 72), (6400, 96, 104), (6160, 128, 136), (300, 64, 72), (6200, 200, 256)])
+def test_embedding_rows_across_lines(rows, d, pitch):
+    """An embedding whose rows do not begin with a 128-byte line is copied two steps ahead at any size: ragged d_model, a pitch
+    that is no multiple of 64 elements, a base in the middle of a line."""
+    ctx = B.AisContext()
+    vocab = 600
+    g, h, w, y = problem(rows, vocab, d, rows + d)
+    for offset in (0, 8):
+        room = torch.zeros(vocab * pitch + offset, device="cuda", dtype=torch.bfloat16)
+        wide = room[offset:].view(vocab, pitch)[:, :d]
+        wide.copy_(w)
+        want = ctx.lm_head_logprob(h, w, y)
+        z = h.double() @ w.double().t()
+        lse = torch.logsumexp(z, dim=1)
+        logp, got_lse = ctx.lm_head_logprob(h, wide, y)
+        # fp32 accumulation of d products and an fp32 log-sum-exp of results of a few units
+        assert (logp.double() - (z.gather(1, y.long().unsqueeze(1)).squeeze(1) - lse)).abs().max() < 1e-5
+        assert torch.equal(logp, want[0]) and torch.equal(got_lse, want[1])
+        if d % 32 == 0:
+            c = torch.randn(rows, generator=g, device="cuda")
+            for a, b in zip(ctx.lm_head_grad(h, wide, y, got_lse, logp, c), ctx.lm_head_grad(h, w, y, got_lse, logp, c)):
+                # the same bf16 dlogits; products by one kernel or another
+                assert (a - b).norm() < 1e-5 * b.norm()
+    assert ctx.status() == 0
+    ctx.close()

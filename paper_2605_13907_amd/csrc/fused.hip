@@ -298,7 +298,13 @@ int launch_typed(ais_ctx* ctx, int need, const void* logits, long long n_rows, i
   // 1,024, 512, 256, 128 and 64 threads: bf16, 1,000 logits 385, 133, 72, 65, 44; 4,096 417, 168, 114, 112, 113; 6,000 440, 196,
   // 177, 189, 191; 12,288 507, 337, 343, 349; 16,384 525, 489, 464, 481; 20,000 592, 615, 627; fp32, 1,000 330, 139, 76, 59,
   // 63; 3,001 272 (in two passes), 184, 161, 165; 8,192 468, 495, 458, 481.
+  // Many rows with a mask, the widest of them: a row of zeros is written without a wait, and fewer threads with more rows at a
+  // time make that slower while the others gain.  us with 1,024, 256 and 512 threads, half of the rows evaluated: 12,345 fp32
+  // rows of 6,000 logits 90, 91, 87, of 8,192 111, 119, 120, 30,000 bf16 rows of 10,000 229, 183, 175, 12,345 of 14,000 109,
+  // 111, 106; a tenth: 30,000 fp32 rows of 4,100 109, 135, 127, bf16 of 10,000 148, 162, 155; all: 12,345 bf16 rows of 14,000
+  // 157, 130, 124, of 8,200 144, 72, 81.
   const int nvec = vocab / Vec<T>::N;
+  const bool many_masked = valid != nullptr && n_rows >= 8LL * ctx->n_cus;
 #define AIS_FUSED_NARROW(MOST, THREADS, NVAL)                                                                    \
   if (nvec <= MOST)                                                                                              \
     return launch_nv<T, ALIGNED, THREADS, NVAL, 0, 0>(ctx, z, n_rows, vocab, row_stride, token_ids, valid, inv_t, \
@@ -308,6 +314,9 @@ int launch_typed(ais_ctx* ctx, int need, const void* logits, long long n_rows, i
   }
   AIS_FUSED_NARROW(512, 128, 4)
   AIS_FUSED_NARROW(1024, 256, 4)
+  if (many_masked) {
+    AIS_FUSED_NARROW(2048, 512, 4)
+  }
   AIS_FUSED_NARROW(2048, 256, 8)
 #undef AIS_FUSED_NARROW
   AIS_FUSED_CASE(0, 4, 4, 0)

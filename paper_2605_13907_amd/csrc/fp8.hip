@@ -80,34 +80,43 @@ __device__ __forceinline__ uint32_t row_top_bits(const bf16_t* zr, int vocab, ui
 }
 
 // Where logits are larger than this, the difference between an exact and a rounded product of logit and log2(e) is no
-// longer small (see accumulate_rounded).
+// longer small (see accumulate_special).
 constexpr float kLargeAmax = 16777216.f;
 
-// As accumulate, but the products are rounded like the maximum's before it is subtracted: the maximum's own term is 1
-// whatever the magnitude, where the fma leaves the rounding of the maximum as its exponent (2^(1e3) at 1e11).  The rounding
-// of the others is an error of 6e-8 of the product in their exponents, which is why this is not the route for ordinary rows.
+// As accumulate; where `rounded` is set (uniform), the products are rounded like the maximum's before it is subtracted: the
+// maximum's own term is 1 whatever the magnitude, where the fma leaves the rounding of the maximum as its exponent (2^(1e3)
+// at 1e11).  The rounding of the others is an error of 6e-8 of the product in their exponents, which is why ordinary rows
+// keep the fma.
 template <int n>
-__device__ __forceinline__ void accumulate_rounded(const float* x, float scale, MaxSum& st) {
-#pragma clang fp contract(off)
+__device__ __forceinline__ void accumulate_special(const float* x, float scale, bool rounded, MaxSum& st) {
   float cm = x[0];
 #pragma unroll
   for (int k = 1; k < n; ++k) cm = fmaxf(cm, x[k]);
   const float mn = fmaxf(st.m, cm * scale);
-  float acc = st.s * exp2_fast(st.m - mn);
+  auto term = [&](float v) {
+#pragma clang fp contract(off)
+    const float product = v * scale;
+    return exp2_fast(rounded ? product - mn : __builtin_fmaf(v, scale, -mn));
+  };
+  float acc0 = st.s * exp2_fast(st.m - mn), acc1 = 0.f;
 #pragma unroll
-  for (int k = 0; k < n; ++k) acc += exp2_fast(x[k] * scale - mn);
+  for (int k = 0; k < n; k += 2) {
+    acc0 += term(x[k]);
+    if (k + 1 < n) acc1 += term(x[k + 1]);
+  }
   st.m = mn;
-  st.s = acc;
+  st.s = acc0 + acc1;
 }
 
 // A row's scale, how its elements are divided by it, and their code as an fp32 value (exact in E4M3).
 // BITS: a 16-byte aligned bf16 row.  There, as in the table kernels that take the wider ones, a NaN has the code of the
-// row's largest magnitude and its own sign, and so has an infinity; elsewhere a NaN's code is that of -448.
+// row's largest magnitude and its own sign; elsewhere a NaN's code is that of -448.  In a row with an infinity, whose scale
+// is infinite, every infinity and every NaN is -448 and everything else a zero of its own sign, aligned or not.
 template <typename T, int THREADS, bool BITS>
 struct RowCoder {
   RowDivider d;
   float amax;
-  bool special, large;                     // uniform for the workgroup; large: see accumulate_rounded
+  bool special, large;                     // uniform for the workgroup; large: see accumulate_special
   __device__ __forceinline__ RowCoder(const T* zr, int vocab, int head, float* lds) {
     bool nan = false;
     if constexpr (BITS) {
@@ -246,8 +255,8 @@ __global__ __launch_bounds__(THREADS) void fp8_rollout_logprob_kernel(
   // the round-tripped logit is s * decode(code): the row scale is folded into the exponent's multiplier (s > 0,
   // so the running maximum can be taken over the decoded values)
   const float scale = s * kLog2e;
-  auto sweep = [&](auto slow, auto rounded) {
-    constexpr bool SLOW = decltype(slow)::value, ROUNDED = decltype(rounded)::value;
+  auto sweep = [&](auto slow) {
+    constexpr bool SLOW = decltype(slow)::value;
     {
       const u32x4* zv = reinterpret_cast<const u32x4*>(zr + head);
       for (int i = tid; i < nvec; i += THREADS) {
@@ -259,19 +268,17 @@ __global__ __launch_bounds__(THREADS) void fp8_rollout_logprob_kernel(
           x[k] = r[0];
           x[k + 1] = r[1];
         }
-        if (ROUNDED) accumulate_rounded<N>(x, scale, st);
+        if (SLOW) accumulate_special<N>(x, scale, coder.large, st);
         else accumulate<N>(x, scale, st);
       }
     }
     for (int e = tid; e < vocab - nvec * N; e += THREADS) {
       float x = from_e4m3x2(coder.template code2<SLOW>(Vec<T>::load1(zr + (e < head ? 0 : nvec * N) + e), 0.f))[0];
-      if (ROUNDED) accumulate_rounded<1>(&x, scale, st);
+      if (SLOW) accumulate_special<1>(&x, scale, coder.large, st);
       else accumulate<1>(&x, scale, st);
     }
   };
-  if (coder.large) sweep(std::true_type{}, std::true_type{});       // (true division: right for every row)
-  else if (coder.special) sweep(std::true_type{}, std::false_type{});
-  else sweep(std::false_type{}, std::false_type{});
+  if (coder.special || coder.large) sweep(std::true_type{}); else sweep(std::false_type{});
   st = wave_merge(st);
   if ((tid & 63) == 0) lds_ms[tid >> 6] = st;
   __syncthreads();

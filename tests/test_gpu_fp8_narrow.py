@@ -1,5 +1,5 @@
 """FP8 kernels on narrow rows: the streaming kernels with 64 and 256 threads a row, at the ends of their ranges, aligned and not,
-with NaNs, infinities and logits of any magnitude."""
+with NaNs, infinities and logits of any magnitude, against the kernels that hold a row where those take over."""
 import pytest
 import torch
 
@@ -115,4 +115,38 @@ def test_rows_with_a_compute_unit_each(dtype, vocab):
         for out in (torch.float32, torch.bfloat16):
             assert torch.equal(ctx.fp8_dequantize_rows(flat[0], flat[1], out),
                                (flat[0].view(torch.float8_e4m3fn).float() * flat[1].unsqueeze(1)).to(out)), rows
+    ctx.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("vocab", [8, 65, 1000, 4096, 12_808, 16_384, 16_385, 16_392])
+def test_rows_with_infinities(dtype, vocab):
+    """An infinite scale: infinities and NaNs are -448, everything else a zero of its own sign, in the kernels that stream a row
+    and in those that hold it; rows without one, beside them, are as ever."""
+    ctx = B.AisContext()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(vocab)
+    for rows in (6, 300):
+        z = (torch.randn(rows, vocab, generator=gen, device="cuda") * 3).to(dtype)
+        plain, _ = reference(z, False)
+        z[0::6, vocab // 2] = float("inf")
+        z[1::6, vocab // 3] = -float("inf")
+        z[2::6, vocab - 1] = float("inf")
+        z[2::6, 0] = -float("inf")
+        z[3::6, vocab // 2] = float("inf")
+        z[3::6, 1] = float("nan")
+        z[4::6] = -float("inf")
+        codes, scale = ctx.fp8_quantize_rows(z)
+        special = z.isnan() | z.isinf()
+        want = torch.where(special, 0xFE, torch.signbit(z).to(torch.uint8) << 7)
+        want[5::6] = plain[5::6]
+        assert torch.equal(codes, want.to(torch.uint8)), rows
+        infinite = torch.arange(rows, device="cuda") % 6 != 5
+        assert torch.equal(scale.isinf(), infinite) and bool((scale > 0).all())
+        y = torch.randint(0, vocab, (rows,), generator=gen, device="cuda", dtype=torch.int32)
+        logp = ctx.fp8_rollout_logprob(z, y)
+        back = plain.view(torch.float8_e4m3fn).double() * scale.double().unsqueeze(1)
+        ref = torch.log_softmax(back, dim=1).gather(1, y.long().unsqueeze(1)).squeeze(1)
+        # fp32 log-sum-exp minus an fp32 logit, both of up to 20: a few ulp of 2^-19
+        assert (logp.double() - ref)[~infinite].abs().max() < 8e-6, rows
     ctx.close()

@@ -293,7 +293,7 @@ int ais_fp8_rollout_logprob(ais_ctx* ctx, const void* logits, ais_dtype dtype, l
  * are never written to memory.
  *   hidden      [n_rows, hidden_stride] device, bf16; the first d_model entries of each row are read;
  *               rows with valid == 0 are neither read nor evaluated (the evaluated rows are gathered
- *               into blocks of 256, so the cost follows their number)
+ *               into equal blocks of up to 256, so the cost follows their number)
  *   weight      [vocab, weight_stride]  device, bf16; row v is the output embedding of token v
  *   token_ids   [n_rows] device; ignored where valid == 0
  *   logp_out, lse_out  [n_rows] device fp32; 0 where valid == 0; a row whose token id is outside

@@ -1,11 +1,12 @@
 // The binding's calls without the interpreter: argument checks, output tensors and the call of the C ABI.
 //
-// A step of the smallest batches is bound by the host: of the 40 us of a step over 512 rows, whose kernels take 24, most
-// went into some twenty argument checks, eight output tensors and three calls through ctypes.  Every function here does
-// what the method of the same name in binding.py does when nothing is wrong with its arguments, and returns None
-// otherwise: the caller then takes the method's own way, which raises what it always raised.  A failing call of the library
-// returns its error code.  us a call, method and here: token_logprob 9.0 and 5.4, diagnostics 11.1 and 7.7 (its kernel's),
-// grpo_loss_grad 17.3 and 10.7, grpo_row_scale 11.9 and 7.1; the step 40 and 24.  Only plain tensors with storage are taken (no subclasses, no wrappers of transforms).
+// A step of the smallest batches was bound by the host: of the 40 us of a step over 512 rows, whose kernels then took 24 (22
+// since the gradient sweep forms the coefficients of such batches itself), most went into some twenty argument checks, eight
+// output tensors and three calls through ctypes.  Every function here does what the method of the same name in binding.py
+// does when nothing is wrong with its arguments, and returns None otherwise: the caller then takes the method's own way,
+// which raises what it always raised.  A failing call of the library returns its error code.  us a call, method and here:
+// token_logprob 9.0 and 5.4, diagnostics 11.1 and 7.7 (its kernel's), grpo_loss_grad 17.3 and 10.7, grpo_row_scale 11.9 and
+// 7.1; the step 40 and 24.  Only plain tensors with storage are taken (no subclasses, no wrappers of transforms).
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/ATen.h>

@@ -12,7 +12,7 @@
 // it, so the running softmax state of a token lives in four lanes' registers and the reduction over the
 // vocabulary needs no cross-lane traffic until the very end.  A 512-thread workgroup (8 wavefronts,
 // 2 along the vocabulary x 4 along the tokens, 128 x 64 outputs each) computes 256 vocabulary entries x
-// 256 tokens per tile.  It owns one block of 256 tokens and a contiguous chunk of vocabulary tiles; per
+// 256 tokens per tile.  It owns one block of up to 256 tokens (all blocks alike) and a contiguous chunk of vocabulary tiles; per
 // token and chunk it emits a partial (max, sum), and a small second kernel merges the partials and
 // subtracts.  Workgroups are numbered so that those resident on one XCD (which share an L2) work on a few
 // token blocks x all vocabulary chunks at the same time, and therefore share both operands.
@@ -26,7 +26,8 @@
 // (the shader clock settles near 1.7 GHz instead of 2.4), so time follows energy.  That is why the products are 16 x 16
 // x 32 and not 32 x 32 x 16, which move twice the accumulators per flop: MFMAs alone on random operands in registers
 // run at 2,090 against 1,845 TFLOP/s, with the fragment reads of this kernel at 1,810 against 1,685.  The whole kernel
-// at 41,643 rows x 151,936 x 4,096 on one device: 44.0 ms with 32 x 32 x 16 products, 39.0 ms (1.33 PFLOP/s) now.
+// at 41,643 rows x 151,936 x 4,096 on one device: 44.0 ms with 32 x 32 x 16 products, 39.0 with these, 38.1 to
+// 38.9 (1.33 to 1.36 PFLOP/s) with the present split over the chip.
 #include "ais_internal.h"
 #include "device_utils.h"
 

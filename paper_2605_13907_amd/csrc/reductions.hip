@@ -759,7 +759,8 @@ Tickets take_tickets(ais_ctx* ctx, bool in_static, int grid) {
 // Tiles of 256 rows, or twice, four times, ... as many where that would be more than kMaxTiles; of kPlanTileRows where
 // the plan kernel lays them out.  With kMaxTiles and 1,024 responses every tile has a wavefront at one workgroup per compute
 // unit.  (8,192: 1,200,000 rows in 1,024 responses 25.7 and 18.4 instead of 21.9 and 17.2 us; 1,536: 25.3 and 23.0.  Tiles of
-// 64 rows while they are few: 41,643 rows in 16 responses 14.1 and 7.9 instead of 13.7 and 7.7.)
+// 64 rows while they are few: 41,643 rows in 16 responses 14.1 and 7.9 instead of 13.7 and 7.7, both with a longer level 2 than
+// the present one, which makes the latter 11.1.)
 constexpr int kMaxTiles = 3072;
 TileRule tile_rule(long long n_rows, int n_resp) {
   int shift = 8;

@@ -383,7 +383,9 @@ int fold_lanes(int n_resp, long long most_tiles) {
 }
 // The code runs once per launch, cold: its size is part of its time (a kilobyte of straight code costs 0.3 us of
 // instruction fetches), so what is the same for several quantities is done once, by lanes that hold one each.
-template <bool SELF>
+// WIDE: more than 64 lanes for a response (in a kernel of its own: in the others the code for it, which they do not run, was
+// 0.2 us of 1,200,000 rows in 1,024 responses).
+template <bool SELF, bool WIDE>
 __device__ void diag_final(const Partials<kDiagWords>& partials, const Tiling<SELF>& tiling, int n_resp, int lanes,
                            int group_size, const float* rewards, const float* s_adv, const ais_params& p,
                            float* __restrict__ adv_out, int* __restrict__ count_out, ais_diag* __restrict__ diag_out,
@@ -415,11 +417,11 @@ __device__ void diag_final(const Partials<kDiagWords>& partials, const Tiling<SE
         t += lanes;
       }
     }
-    for (int off = 1; off < min(lanes, 64); off <<= 1) // uniform: every lane of the wavefront takes part
+    for (int off = 1; off < (WIDE ? 64 : lanes); off <<= 1)   // uniform: every lane of the wavefront takes part
       r = merge(r, Moments{__shfl_xor(r.n, off), __shfl_xor(r.mean, off), __shfl_xor(r.m2, off)});
-    if ((l & 63) != 0 || i >= n_resp) continue;        // lane 0 of the group, or of each of its wavefronts, goes on
-    if (l == 0) adv_out[i] = (float)a;
-    if (lanes <= 64) count_out[i] = (int)r.n;
+    if ((WIDE ? lane : l) != 0 || i >= n_resp) continue;   // lane 0 of the group goes on (WIDE: of each of its wavefronts)
+    if (!WIDE || l == 0) adv_out[i] = (float)a;
+    if (!WIDE) count_out[i] = (int)r.n;
     // token-level moments of A and A w_bar: A (the stored fp32 value) is constant over the response's rows, so these
     // have mean A mean(w_bar) and squared deviations A^2 m2(w_bar)
     const Moments of[3] = {r, Moments{r.n, a, 0.0}, Moments{r.n, a * r.mean, a * a * r.m2}};
@@ -457,7 +459,7 @@ __device__ void diag_final(const Partials<kDiagWords>& partials, const Tiling<SE
   }
   __syncthreads();
   if (wave != 0) return;
-  if (lanes > 64 && lane < n_resp) {                   // responses of several wavefronts, one pass: their parts' counts
+  if (WIDE && lane < n_resp) {                         // responses of several wavefronts, one pass: their parts' counts
     double n = 0.0;
     for (int w = 0; w < lanes >> 6; ++w) n += lds[lane * (lanes >> 6) + w];
     count_out[lane] = (int)n;
@@ -522,7 +524,7 @@ __device__ void diag_final(const Partials<kDiagWords>& partials, const Tiling<SE
 // row's w_bar, gives the mean, the squared deviations from it the spread.  Equal values have spread exactly 0, and each pass
 // is six dependent additions where merging (count, mean, spread) triples lane by lane was six times ten.
 // The four rows of a lane take turns in one copy of the code (three exponentials each): see diag_final for why.
-template <bool SELF>
+template <bool SELF, bool WIDE>
 __global__ __launch_bounds__(kThreads, 4) void diag_reduce_kernel(
     const float* __restrict__ logp_train, const float* __restrict__ logp_roll,
     const unsigned char* __restrict__ valid, long long n_rows, const long long* __restrict__ cu_rows, int n_resp,
@@ -635,7 +637,7 @@ __global__ __launch_bounds__(kThreads, 4) void diag_reduce_kernel(
   }
   // ---- level 2, in the workgroup that finishes last ----
   if (last_workgroup(tickets))
-    diag_final<SELF>(partials, tiling, n_resp, lanes, group_size, rewards, s_adv, p, adv_out, count_out, diag_out, status,
+    diag_final<SELF, WIDE>(partials, tiling, n_resp, lanes, group_size, rewards, s_adv, p, adv_out, count_out, diag_out, status,
                      lds);
 }
 
@@ -812,12 +814,14 @@ int launch_diagnostics(ais_ctx* ctx, const float* logp_train, const float* logp_
                        long long n_rows, const long long* cu_rows, int n_resp, int group_size,
                        const float* rewards, const ais_params& p, int* tile_off, double* partial, bool in_static,
                        float* adv_out, int* count_out, ais_diag* diag_out) {
-  auto kernel = n_resp <= kSelfPlanResponses ? diag_reduce_kernel<true> : diag_reduce_kernel<false>;
   const TileRule rule = tile_rule(n_rows, n_resp);
+  const int lanes = fold_lanes(n_resp, (n_rows + (1LL << rule.shift) - 1) >> rule.shift);
+  auto kernel = n_resp > kSelfPlanResponses ? diag_reduce_kernel<false, false>
+                : lanes > 64                ? diag_reduce_kernel<true, true>
+                                            : diag_reduce_kernel<true, false>;
   const int grid = reduction_grid(ctx, rule.max_tiles);
   kernel<<<grid, kThreads, 0, ctx->stream>>>(
-      logp_train, logp_roll, valid, n_rows, cu_rows, n_resp, tile_off, rule, partial,
-      fold_lanes(n_resp, (n_rows + (1LL << rule.shift) - 1) >> rule.shift), group_size, rewards, p,
+      logp_train, logp_roll, valid, n_rows, cu_rows, n_resp, tile_off, rule, partial, lanes, group_size, rewards, p,
       std::log((double)p.C), adv_out, count_out, diag_out, ctx->status_dev, take_tickets(ctx, in_static, grid));
   return hip_fail(ctx, hipGetLastError());
 }

@@ -450,12 +450,17 @@ constexpr int kUnrollFwd = 4;
 //   256 x 28,000, relative  0.76   0.79    0.96       300 x 20,000, relative   1.02    0.88    0.94
 //   16,384 x 10,001 fp32           96.5   101         30,000 x 20,001                 187     181
 //   16,384 x 24,001               117     121
+//   1,024 x 50,264                21.7    20.6        700 x 16,600 fp32               9.5     9.0
+//   850 x 49,600, relative        1.08    1.01        700 x 50,264, relative          0.96    0.99
 int logprob_threads(const ais_ctx* ctx, long long n_rows, long long nvec, bool bf16) {
   const long long cus = ctx->n_cus;
   const bool few = n_rows < 8 * cus;
   if (nvec >= 2048 && n_rows <= cus) return nvec < 3500 ? 512 : 1024;
   if (nvec >= 8192 && n_rows <= 8 * cus) return n_rows > 2 * cus ? 1024 : bf16 ? 512 : 256;
-  if (nvec >= (few == bf16 ? 2500 : few ? 3200 : 3000)) return nvec < 8192 ? 512 : 256;
+  if (nvec >= (few == bf16 ? 2500 : few ? 3200 : 3000)) {
+    const long long per_cu = (n_rows + cus - 1) / cus;       // 512 threads leave some of these compute units a round more
+    return nvec >= 8192 || (bf16 ? per_cu == 4 || per_cu == 5 : per_cu == 3) ? 256 : 512;
+  }
   // (256 threads that share a few vectors read some of them more than once)
   if (few) return nvec <= 64 ? 64 : nvec <= 128 ? 128 : 256;
   if (nvec >= 896) return 256;

@@ -44,3 +44,22 @@ def test_log_probs_at_the_edges_of_the_rule(dtype, vectors):
 def test_log_probs_at_the_other_edges(dtype, vectors):
     """The lines that lie elsewhere for few rows and for the two types, and tails of three vectors a thread."""
     test_log_probs_at_the_edges_of_the_rule(dtype, vectors)
+
+
+@pytest.mark.parametrize("rows", [769, 1280, 1281])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_rows_per_compute_unit(dtype, rows):
+    """Three to five rows per compute unit (256 of them), where 2,500 to 8,191 vectors have 256 threads instead of 512."""
+    n = 16 // dtype.itemsize
+    ctx = B.AisContext()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows)
+    for vocab in (3300 * n, 6283 * n, 6283 * n + 1):
+        z = (torch.randn(rows, vocab, generator=gen, device="cuda") * 4).to(dtype)
+        y = torch.randint(0, vocab, (rows,), generator=gen, device="cuda", dtype=torch.int32)
+        ref = torch.cat([torch.logsumexp(z[r:r + 256].double(), dim=1) for r in range(0, rows, 256)])
+        ref_y = z.gather(1, y.long().unsqueeze(1)).squeeze(1).double() - ref
+        logp, lse = ctx.token_logprob(z, y)
+        # sums of up to 2^17 fp32 terms in trees of a few hundred: 1e-6 relative, and the rounding of the fp32 results
+        assert (lse.double() - ref).abs().max() < 4e-6 and (logp.double() - ref_y).abs().max() < 6e-6, vocab
+    ctx.close()

@@ -83,6 +83,7 @@ struct LmHeadPlan {
   int max_chunks;        // most chunks the device-side decision can use (sizes the workspace)
   int max_items;         // work items, rounded up to a multiple of 8 (sizes the grid)
   int max_items_masked;  // the same where fewer rows than that may be evaluated
+  int chunks;            // chunks where every row is evaluated
 };
 LmHeadPlan lm_head_plan(long long n_rows, int vocab, int n_cus);
 // Workspace of the read-out's two calls (the gradient call's: of a chunk's dlogits) and the gradient call's chunk width.

@@ -10,8 +10,8 @@
 // Layout of the work.  The product is taken transposed, C^T[v, t] = W H^T, with v_mfma_f32_16x16x32_bf16:
 // a lane of the wavefront then owns one *token* column of every 16x16 tile and 4 vocabulary entries of
 // it, so the running softmax state of a token lives in four lanes' registers and the reduction over the
-// vocabulary needs no cross-lane traffic until the very end.  A 512-thread workgroup (8 wavefronts,
-// 2 along the vocabulary x 4 along the tokens, 128 x 64 outputs each) computes 256 vocabulary entries x
+// vocabulary needs no cross-lane traffic until the very end.  A 256-thread workgroup (4 wavefronts, one to a SIMD,
+// 2 along the vocabulary x 2 along the tokens, 128 x 128 outputs each) computes 256 vocabulary entries x
 // 256 tokens per tile.  It owns one block of up to 256 tokens (all blocks alike) and a contiguous chunk of vocabulary tiles; per
 // token and chunk it emits a partial (max, sum), and a small second kernel merges the partials and
 // subtracts.  Workgroups are numbered so that those resident on one XCD (which share an L2) work on a few
@@ -21,18 +21,20 @@
 // straight into LDS, and copies, LDS reads and MFMAs are interleaved.  The slices lie in LDS with an XOR swizzle of
 // their 16-byte chunks, which makes the fragment reads free of bank conflicts.
 //
-// What bounds it.  With 256 x 256 tiles every 32 K flops need 256 bytes from L2 and, with 128 x 64 outputs per
-// wavefront, 768 bytes of fragments from LDS; under a sustained run with real (toggling) data the part is power-limited
-// (the shader clock settles near 1.7 GHz instead of 2.4), so time follows energy.  That is why the products are 16 x 16
+// What bounds it.  With 256 x 256 tiles every 32 K flops need 256 bytes from L2 and, with 128 x 128 outputs per
+// wavefront, 512 bytes of fragments from LDS; under a sustained run with real (toggling) data the part is power-limited
+// (the shader clock settles near 1.9 GHz instead of 2.4), so time follows energy.  That is why the products are 16 x 16
 // x 32 and not 32 x 32 x 16, which move twice the accumulators per flop: MFMAs alone on random operands in registers
-// run at 2,090 against 1,845 TFLOP/s, with the fragment reads of this kernel at 1,810 against 1,685.  The whole kernel
-// at 41,643 rows x 151,936 x 4,096 on one device: 44.0 ms with 32 x 32 x 16 products, 39.0 with these, 38.1 to
-// 38.9 (1.33 to 1.36 PFLOP/s) with the present split over the chip.
+// run at 2,090 against 1,845 TFLOP/s; and why a wavefront has 128 x 128 outputs, all of its SIMD's accumulation registers:
+// with eight wavefronts of 128 x 64 (768 bytes of fragments) 41,643 rows x 151,936 x 4,096 took 37.8 ms at 0.69 busy matrix
+// pipes, with these 37.0 (1.40 PFLOP/s); 4,096 x 126,464 x 4,096 3,037 -> 2,896 us (0.74 -> 0.76 busy), 64 x 151,936 x 4,096
+// 261 -> 231.
 #include "ais_internal.h"
 #include "device_utils.h"
 
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 namespace ais {
 namespace {
@@ -42,22 +44,23 @@ using namespace dev;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kLmThreads = 512;
+constexpr int kLmThreads = 256;
 constexpr int kLmTileV = 256;      // vocabulary entries per tile
 constexpr int kLmTileT = 256;      // tokens per tile
 constexpr int kLmTileK = 64;       // d_model elements per step
 constexpr int kLmWaveV = 128;      // per wavefront: 8 MFMA tiles along the vocabulary
-constexpr int kLmWaveT = 64;       //                4 along the tokens
+constexpr int kLmWaveT = 128;      //                8 along the tokens
 constexpr int kLmNI = kLmWaveV / 16;
 constexpr int kLmNJ = kLmWaveT / 16;
 constexpr int kLmOperandBytes = kLmTileV * kLmTileK * 2;            // 32 KiB: one operand slice
 // Operand slices in LDS: two of W (DEEP: three), then two of H.
 constexpr int lm_lds_bytes(bool deep) { return (deep ? 5 : 4) * kLmOperandBytes; }
 
-// Byte offset of 16-byte chunk `c` (0..7) of row `row` inside one operand slice.  A row is 128 bytes; the
-// chunk index is XORed with bits 1..3 of the row so that 16 consecutive rows read at the same logical
-// chunk touch 16 different 16-byte bank groups.
-__device__ __forceinline__ int lds_chunk_offset(int row, int c) { return row * 128 + ((c ^ ((row >> 1) & 7)) << 4); }
+// A row of an operand slice is 128 bytes, eight 16-byte chunks; chunk c lies at position c ^ swizzle(row), so that the 16 rows
+// that a fragment read touches at the same logical chunk lie in 16 different 16-byte bank groups (two rows fill the banks
+// once).  The 16 rows of a fragment are consecutive ones of H; of W they are four fours, eight rows apart (see lm_entry).
+__device__ __forceinline__ int lds_swizzle_h(int row) { return (row >> 1) & 7; }
+__device__ __forceinline__ int lds_swizzle_w(int row) { return (row >> 1 & 1) | (row >> 2 & 6); }
 // Token blocks that walk the vocabulary chunks together (see LmItem::init).  1 = token block major: the workgroups
 // resident on an XCD share a few hidden-state blocks and sit on all chunks of the vocabulary.  Measured at 41,643
 // rows x 151,936 x 4,096: 43.9 ms; groups of 2 / 4 / 8 / 16 / 32 token blocks on the same chunk (more sharing of the
@@ -65,18 +68,26 @@ __device__ __forceinline__ int lds_chunk_offset(int row, int c) { return row * 1
 // 44.3 / 47.4 / 47.5 / 50.1 / 52.9 ms.  Where there are fewer than 8 token blocks every one of them fits the L2 beside
 // the tiles, and sharing the tiles is what counts: 390 rows 618 us alone, 601 us in twos; 1,500 rows 1,734 us alone,
 // 1,670 us in fours; from 2,000 rows on no difference beyond the noise.
-__device__ __forceinline__ int lm_token_block_group(int n_tblocks) { return n_tblocks < 8 ? min(n_tblocks, 4) : 1; }
+__host__ __device__ inline int lm_token_block_group(int n_tblocks) { return n_tblocks < 8 ? (n_tblocks < 4 ? n_tblocks : 4) : 1; }
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 q) { return __builtin_bit_cast(bf16x8, q); }
 
 
 // ---- pieces of the tile kernel ---------------------------------------------------------------------
 
-// Decomposition of the evaluated rows into work items, decided on the device once their number is known
-// (lm_head_setup_kernel): n_tblocks blocks of block_rows (a multiple of 16, at most 256) evaluated rows x n_chunks chunks of tiles_per_chunk
+// Decomposition of the evaluated rows into work items, decided on the device where a mask makes their number known only
+// there (lm_head_setup_kernel), by lm_head_plan otherwise: n_tblocks blocks of block_rows (a multiple of 16, at most 256) evaluated rows x n_chunks chunks of tiles_per_chunk
 // vocabulary tiles, per_xcd work items for each of the 8 XCDs.
 struct LmDevPlan {
   int n_eval, n_tblocks, n_chunks, tiles_per_chunk, per_xcd, n_items, tb_group, block_rows;
+};
+
+// The decomposition as a kernel gets it: in memory, or (at == nullptr) with its arguments, which saves the launch that would
+// put it there: us of 266 rows x 1,216 x 832 25.0 -> 21, of 390 x 151,936 x 4,096 452 -> 447.
+struct LmPlanArg {
+  const LmDevPlan* at;
+  LmDevPlan given;
+  __device__ __forceinline__ LmDevPlan get() const { return at != nullptr ? *at : given; }
 };
 
 // Cost of splitting n_vtiles vocabulary tiles into `chunks` equal chunks, or -1 where that gives more than max_items work
@@ -111,6 +122,20 @@ __host__ __device__ inline int lm_chunk_limit(int n_tblocks, int n_vtiles, int n
   return n_vtiles < limit ? n_vtiles : limit;
 }
 
+// What `chunks` chunks make of `total` evaluated rows.
+__host__ __device__ inline LmDevPlan lm_decomposition(int total, int chunks, int n_vtiles, int n_cus, long long max_items) {
+  LmDevPlan d;
+  d.n_eval = total;
+  d.n_tblocks = (total + kLmTileT - 1) / kLmTileT;
+  lm_chunks_cost(chunks, d.n_tblocks, n_vtiles, n_cus, max_items, &d.n_chunks, &d.tiles_per_chunk);
+  d.n_items = d.n_tblocks * d.n_chunks;
+  d.per_xcd = (d.n_items + 7) / 8;
+  d.tb_group = d.n_tblocks > 0 ? lm_token_block_group(d.n_tblocks) : 1;
+  // as many rows in every block: a block's time goes with its columns of 16 (see LmItem)
+  d.block_rows = d.n_tblocks > 0 ? ((total + d.n_tblocks - 1) / d.n_tblocks + 15) / 16 * 16 : kLmTileT;
+  return d;
+}
+
 // The rows to evaluate.  With a mask, `index` lists the evaluated rows in order (built by
 // lm_head_setup_kernel); without one, every row is evaluated.
 struct LmRows {
@@ -124,38 +149,38 @@ struct LmRows {
 
 // Which part of the problem this workgroup owns, and where the thread sits in its tile.
 struct LmItem {
-  int tb, ch, vt0, vt1, t0, n_eval, n_chunks;
+  int tb, ch, vt0, vt1, t0, t_end, n_eval, n_chunks;
   int lane, wave, wv, wt, quarter, col;
-  int col0, n_cols;      // first of the wavefront's columns of 16 tokens inside the block, and their number, 0 to 4
-  __device__ __forceinline__ bool init(const LmDevPlan* __restrict__ plan, int n_vtiles) {
+  int col0, n_cols;      // first of the wavefront's columns of 16 tokens inside the block, and their number, 0 to 8
+  __device__ __forceinline__ bool init(const LmDevPlan& plan, int n_vtiles) {
     // Workgroups are dealt to the 8 XCDs round-robin; every XCD takes a contiguous, equally long range of work
     // items (token block major): its resident workgroups then share a few token blocks' hidden-state slices and
     // each other's vocabulary tiles through the L2.
     const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-    const int item = xcd * plan->per_xcd + local;
-    if (local >= plan->per_xcd || item >= plan->n_items) return false;   // uniform for the workgroup
-    n_eval = plan->n_eval;
-    n_chunks = plan->n_chunks;
-    const int tiles_per_chunk = plan->tiles_per_chunk;
+    const int item = xcd * plan.per_xcd + local;
+    if (local >= plan.per_xcd || item >= plan.n_items) return false;   // uniform for the workgroup
+    n_eval = plan.n_eval;
+    n_chunks = plan.n_chunks;
+    const int tiles_per_chunk = plan.tiles_per_chunk;
     // items are ordered group by group of tb_group token blocks, chunk by chunk inside a group, token block by
     // token block inside a chunk: the workgroups resident on an XCD then sit on tb_group token blocks x a few chunks
-    const int group = plan->tb_group, per_group = group * n_chunks;
+    const int group = plan.tb_group, per_group = group * n_chunks;
     const int g = item / per_group, j = item - g * per_group;
-    const int gsize = min(group, plan->n_tblocks - g * group);     // the last group may be smaller
+    const int gsize = min(group, plan.n_tblocks - g * group);     // the last group may be smaller
     ch = j / gsize;
     tb = g * group + (j - ch * gsize);
     vt0 = ch * tiles_per_chunk;
     vt1 = min(n_vtiles, vt0 + tiles_per_chunk);
-    t0 = tb * plan->block_rows;
+    t0 = tb * plan.block_rows;
+    t_end = min(t0 + plan.block_rows, n_eval);
     lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     wv = wave & 1;                                               // position of the wavefront in the tile
     wt = wave >> 1;
-    // the block's columns are dealt evenly to the four wavefronts along the tokens: those of 195 rows (two blocks of a
-    // batch of 390) are 4, 3, 3 and 3 instead of 4, 4, 4 and a part of 4
-    const int cols = __builtin_amdgcn_readfirstlane((min(plan->block_rows, n_eval - t0) + 15) >> 4);
-    n_cols = (cols + 3 - wt) >> 2;
-    col0 = wt * (cols >> 2) + min(wt, cols & 3);
+    // the block's columns are dealt evenly to the two wavefronts along the tokens
+    const int cols = __builtin_amdgcn_readfirstlane((min(plan.block_rows, n_eval - t0) + 15) >> 4);
+    n_cols = (cols + 1 - wt) >> 1;
+    col0 = wt * ((cols + 1) >> 1);
     quarter = lane >> 4;
     col = lane & 15;
     return true;
@@ -164,15 +189,63 @@ struct LmItem {
 
 typedef f32x4 LmAcc[kLmNI][kLmNJ];
 
-template <int NJ>
-__device__ __forceinline__ void lm_clear(LmAcc& acc) {
-#pragma unroll
-  for (int i = 0; i < kLmNI; ++i)
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+// First of the four vocabulary entries, inside the wavefront's 128, that MFMA tile i leaves in a lane of this quarter: two
+// tiles are 32 entries, eight consecutive ones to a lane.
+__device__ __forceinline__ int lm_entry(int i, int quarter) { return 32 * (i >> 1) + 8 * quarter + 4 * (i & 1); }
+
+// The products are written as instructions because the accumulators take all of the accumulation registers: the compiler's own
+// form of a product may have its result elsewhere than its addend, and without a register to spare it moved fragments and
+// accumulators about in the loop.  It does not know what such a statement is, so what it would wait for is waited for here:
+//   fragments come straight from LDS reads, whose arrival it does wait for (an operand that an ordinary instruction has just
+//   written would need two wait states; there is none in the loop);
+//   lm_settle() stands between the last product and the first look at an accumulator.
+__device__ __forceinline__ void lm_product(f32x4& c, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void lm_settle() { asm volatile("s_nop 15\n\ts_nop 3"); }
+// c = 0, by the matrix pipe, which has nothing else to do between two tiles: beside the soft-max arithmetic of the finished
+// one.  Where the accumulators have not held anything before, `first` makes them do so.
+struct LmClear {
+  u32x4 zero;
+  __device__ __forceinline__ LmClear() {
+    zero = u32x4{0u, 0u, 0u, 0u};
+    asm volatile("s_nop 3" : "+v"(zero));
+  }
+  __device__ __forceinline__ void operator()(f32x4& c) const {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %1, 0" : "+a"(c) : "v"(zero));
+  }
+  __device__ __forceinline__ void first(f32x4& c) const {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %1, 0" : "=a"(c) : "v"(zero));
+  }
+};
+
+// f(0), f(1), ... f(N - 1) with the index a constant in each.
+template <typename F, int... I>
+__device__ __forceinline__ void unrolled_over(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unrolled(F&& f) {
+  unrolled_over(f, std::make_integer_sequence<int, N>{});
 }
 
-// Per-lane soft-max state of the lane's four token columns, in the base-2 domain (logit * scale).
+// Copies the accumulators of MFMA tiles I .. I + N - 1 of column J out, to z[0 ..] if I = 0 and N = 2, to their places in a
+// column otherwise, before whatever follows.
+template <int J, int I, int N>
+__device__ __forceinline__ void lm_take(LmAcc& acc, float* z) {
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = I; i < I + N; ++i) asm volatile("" : "+a"(acc[i][J]));      // where the products left them until here
+#pragma unroll
+  for (int k = 0; k < 4 * N; ++k) {
+    float v = acc[I + (k >> 2)][J][k & 3];
+    asm volatile("" : "+v"(v));
+    z[N == 2 ? k : 4 * I + k] = v;
+  }
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Per-lane soft-max state of the lane's token columns, up to eight, in the base-2 domain (logit * scale).
 struct LmSoftmax {
   float run_m[kLmNJ], run_s[kLmNJ];
   int tok0, y[kLmNJ];
@@ -191,50 +264,45 @@ struct LmSoftmax {
       }
     }
   }
-  // Folds the finished tile `vt` into the running state.  Accumulator element v of MFMA tile i holds
-  // vocabulary entry  vbase + 16 i + 4 quarter + v  of token column j.
-  template <int NJ>
+  // Folds column j of the finished tile `vt` into the running state.  Accumulator element v of MFMA tile i holds vocabulary
+  // entry  vbase + lm_entry(i, quarter) + v.  Leaves the column at zero.
+  template <int J>
   __device__ __forceinline__ void fold(LmAcc& acc, const LmItem& it, int vt, int vocab, float scale,
-                                       float* __restrict__ zy_out) {
+                                       float* __restrict__ zy_out, const LmClear& clear) {
     const int vbase = vt * kLmTileV + it.wv * kLmWaveV;
+    float z[4 * kLmNI];
+    lm_take<J, 0, kLmNI>(acc, z);
     if (vt * kLmTileV + kLmTileV > vocab) {                      // uniform: only the last tile of the vocabulary
       // entries past the end of the vocabulary become -inf: they never win the max (which starts from a
       // finite value) and add exp2(-inf) = 0 to the sum
+      int left = vocab - vbase - 8 * it.quarter;
+      asm volatile("" : "+v"(left));             // keeps the comparisons below in this branch
 #pragma unroll
-      for (int i = 0; i < kLmNI; ++i)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const bool in = vbase + 16 * i + 4 * it.quarter + v < vocab;
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) acc[i][j][v] = in ? acc[i][j][v] : -__builtin_inff();
-        }
+      for (int k = 0; k < 4 * kLmNI; ++k) z[k] = lm_entry(k >> 2, 0) + (k & 3) < left ? z[k] : -__builtin_inff();
     }
+    float tmax = kNegHuge;
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      float tmax = kNegHuge;
+    for (int k = 0; k < 4 * kLmNI; ++k) tmax = fmaxf(tmax, z[k]);
+    const float m_new = fmaxf(run_m[J], tmax * scale);           // finite: run_m is, and -inf never wins
+    float sum = 0.f;
+    unrolled<4>([&](auto part) __attribute__((always_inline)) {
 #pragma unroll
-      for (int i = 0; i < kLmNI; ++i)
+      for (int k = 8 * part.value; k < 8 * part.value + 8; ++k) sum += exp2_fast(fmaf(z[k], scale, -m_new));
+      asm volatile("" : "+v"(sum));                              // summed here, not with all other columns at the end
+      clear(acc[2 * part.value][J]);
+      clear(acc[2 * part.value + 1][J]);
+    });
+    run_s[J] = fmaf(run_s[J], exp2_fast(run_m[J] - m_new), sum);
+    run_m[J] = m_new;
+    // the sampled token's own logit: held by exactly one lane of one wavefront of one workgroup
+    const int rel = y[J] - vbase;
+    if ((unsigned)rel < (unsigned)kLmWaveV && ((rel >> 3) & 3) == it.quarter) {
+      int idx = (rel >> 5) * 8 + (rel & 7), tok = tok0 + 16 * J;
+      asm volatile("" : "+v"(idx), "+v"(tok));                   // keeps what is formed from them in this branch
+      float zy = 0.f;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) tmax = fmaxf(tmax, acc[i][j][v]);
-      const float m_new = fmaxf(run_m[j], tmax * scale);         // finite: run_m is, and -inf never wins
-      float sum = 0.f;
-#pragma unroll
-      for (int i = 0; i < kLmNI; ++i)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) sum += exp2_fast(fmaf(acc[i][j][v], scale, -m_new));
-      run_s[j] = fmaf(run_s[j], exp2_fast(run_m[j] - m_new), sum);
-      run_m[j] = m_new;
-      // the sampled token's own logit: held by exactly one lane of one wavefront of one workgroup
-      const int rel = y[j] - vbase;
-      if ((unsigned)rel < (unsigned)kLmWaveV && ((rel >> 2) & 3) == it.quarter) {
-        const int idx = (rel >> 4) * 4 + (rel & 3);
-        float zy = 0.f;
-#pragma unroll
-        for (int i = 0; i < kLmNI; ++i)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) zy = (i * 4 + v == idx) ? acc[i][j][v] : zy;
-        zy_out[tok0 + 16 * j] = zy;
-      }
+      for (int k = 0; k < 4 * kLmNI; ++k) zy = k == idx ? z[k] : zy;
+      zy_out[tok] = zy;
     }
   }
   // Merges the four lane quarters, then the two wavefronts along the vocabulary (through `xch`, 2 KiB of LDS that
@@ -251,20 +319,20 @@ struct LmSoftmax {
         run_m[j] = m;
       }
     __syncthreads();                                            // everyone is done with the staging buffers
-    float* xm = xch;                                            // [4 token groups][64 tokens] max, then sum
+    float* xm = xch;                                            // [2 token groups][128 tokens] max, then sum
     float* xs = xch + 256;
     if (it.wv == 1 && it.quarter == 0) {
 #pragma unroll
       for (int j = 0; j < kLmNJ; ++j) {
-        xm[it.wt * 64 + j * 16 + it.col] = run_m[j];
-        xs[it.wt * 64 + j * 16 + it.col] = run_s[j];
+        xm[it.wt * 128 + j * 16 + it.col] = run_m[j];
+        xs[it.wt * 128 + j * 16 + it.col] = run_s[j];
       }
     }
     __syncthreads();
     if (it.wv == 0 && it.quarter == 0) {
 #pragma unroll
       for (int j = 0; j < kLmNJ; ++j) {
-        const float om = xm[it.wt * 64 + j * 16 + it.col], os = xs[it.wt * 64 + j * 16 + it.col];
+        const float om = xm[it.wt * 128 + j * 16 + it.col], os = xs[it.wt * 128 + j * 16 + it.col];
         const float m = fmaxf(run_m[j], om);
         const float s = run_s[j] * exp2_fast(run_m[j] - m) + os * exp2_fast(om - m);
         const int tok = tok0 + 16 * j;
@@ -289,7 +357,7 @@ struct LmGradArgs {
   int compact;             // != 0: row p of ds belongs to the p-th listed row (LmRows::index), not to source row p
 };
 
-// Per-lane state of the gradient variant: for each of the lane's four token columns the row it writes to, the
+// Per-lane state of the gradient variant: for each of the lane's token columns the row it writes to, the
 // sampled token's position inside the chunk, -lse in the base-2 domain, the coefficient and the sampled token's
 // own element coeff (p_y - 1) = coeff expm1(logp), which would cancel if it were formed from p_y.
 struct LmGrad {
@@ -318,32 +386,38 @@ struct LmGrad {
       }
     }
   }
-  // Writes the finished tile `vt`, zeros past the end of the chunk (a row of ds holds whole tiles, and the products that
-  // read it take whole steps).  Accumulator element v of MFMA tile i holds vocabulary entry
-  // vbase + 16 i + 4 quarter + v of token column j: four consecutive entries, 8 bytes, per tile.
-  template <int NJ>
-  __device__ __forceinline__ void emit(const LmAcc& acc, const LmItem& it, int vt, int vocab, float scale,
-                                       const LmGradArgs& ga) {
+  // Writes column j of the finished tile `vt`, zeros past the end of the chunk (a row of ds holds whole tiles, and the
+  // products that read it take whole steps).  Two MFMA tiles hold eight consecutive entries of the column's row: 16 bytes.
+  // Leaves the column at zero.
+  template <int J>
+  __device__ __forceinline__ void emit(LmAcc& acc, const LmItem& it, int vt, int vocab, float scale, const LmGradArgs& ga,
+                                       const LmClear& clear) {
     const int vbase = vt * kLmTileV + it.wv * kLmWaveV;
+    bf16_t* out = ga.ds + (long long)row[J] * ga.ds_stride;
+    unrolled<kLmNI / 2>([&](auto pair) __attribute__((always_inline)) {
+      constexpr int i = 2 * pair.value;
+      const int v0 = vbase + lm_entry(i, it.quarter);
+      float z[8], x[8];
+      lm_take<J, i, 2>(acc, z);
+      clear(acc[i][J]);
+      clear(acc[i + 1][J]);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      if (row[j] < 0) continue;
-      bf16_t* out = ga.ds + (long long)row[j] * ga.ds_stride;
+      for (int e = 0; e < 8; ++e) x[e] = c[J] != 0.f ? c[J] * exp2_fast(fmaf(z[e], scale, shift[J])) : 0.f;
+      if (vt * kLmTileV + kLmTileV > vocab) {                    // uniform: only the last tile of the chunk
+        int left = vocab - v0;
+        asm volatile("" : "+v"(left));           // keeps the comparisons below in this branch
 #pragma unroll
-      for (int i = 0; i < kLmNI; ++i) {
-        const int v0 = vbase + 16 * i + 4 * it.quarter;
-        float x[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          x[e] = c[j] != 0.f && v0 + e < vocab ? c[j] * exp2_fast(fmaf(acc[i][j][e], scale, shift[j])) : 0.f;
-          if (v0 + e == y[j]) x[e] = dy[j];
-        }
-        f32x2 lo = {x[0], x[1]}, hi = {x[2], x[3]};
-        uint2 w = {__builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2)),
-                   __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, bf16x2))};
-        *reinterpret_cast<uint2*>(out + v0) = w;
+        for (int e = 0; e < 8; ++e) x[e] = e < left ? x[e] : 0.f;
       }
-    }
+      int at = y[J] - v0;
+      if ((unsigned)at < 8u) {                                   // one lane of one wavefront in the whole row
+        asm volatile("" : "+v"(at));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = e == at ? dy[J] : x[e];
+      }
+      u32x4 q = Vec<bf16_t>::pack(x);
+      if (row[J] >= 0) *reinterpret_cast<u32x4*>(out + v0) = q;
+    });
   }
 };
 
@@ -355,20 +429,19 @@ typedef const __attribute__((address_space(1))) void* glb_ptr;
 // one of two LDS buffers (DEEP: of three for W; global_load_lds_dwordx4: lane i of a wavefront deposits its 16 bytes at base + 16 i, so the
 // swizzle is applied by choosing which chunk each lane fetches).  A row of a slice is a whole 128-byte line, so a copy
 // instruction of a wavefront asks L2 for 8 full lines.
-// A step is 16 groups of four MFMAs: group g multiplies fragment a(g) (16 vocabulary entries x 32 elements) by the
-// four token fragments of its half of the step.  The a fragments pass through a ring of four registers sets, read
-// three groups ahead, the b fragments of a half step are read during the half before.  The instruction order is
-// pinned: LDS reads and copies sit in the shadow of the MFMAs.
-// One barrier per step, after group 12: every wavefront has then received all it reads of the step's buffer (the last
-// read is two groups old, so the wait costs nothing) and its own copies of the next step, so the barrier publishes the
-// next step and frees the buffer; the copies of the step after next go into it at once, one after each of the eight
-// groups that follow (three in this step, five in the next), half a step or more before they are awaited.  Measured at
-// 41,643 rows x 151,936 x 4,096 (39.0 ms): two copies after each of groups 13 and 14, then one after each of four
-// groups, 39.2; one after each from group 12 on 40.2; two after each of three groups 40.2; none before the next step
-// 41.4; all W copies before all H copies 40.3.
+// A step is two half steps of 32 elements: with eight columns of tokens 64 MFMAs each, every one of the half's eight
+// fragments of W with every one of its token fragments.  All fragments of a half step are in registers before it begins: they
+// are read during the half before, one after every second or third MFMA.  The instruction order is pinned: a wavefront has its
+// SIMD to itself, so what it issues between two MFMAs has to fit beside one (16 cycles).  Reads and copies in groups after
+// every eighth MFMA left the matrix pipe busy 0.59 of the cycles, spread out 0.76.
+// One barrier per step, after three quarters of its first half: every wavefront has then received all it reads of the step's
+// slices and its own copies of the next step, so the barrier publishes the next step and frees the slices; the copies of the
+// step after next go into them at once, spread over a half step's worth of MFMAs, and are awaited a step later.  Reads over
+// 4 to 6 eighths of a half step, the barrier at 5 to 7, copies over 6 to 9: no difference beyond the noise, but for copies
+// over 6 eighths (1-2 % slower).  Folding a tile beside the next one's first products: nothing at d_model 4,096 or 960.
 // DEEP: W has a third slice in LDS (160 KiB in all) and is copied two steps ahead instead of one, H first in every set of
-// copies so that the wait can leave W's last four in flight.  See lm_deep for where that pays.
-// A wavefront multiplies as many columns of 16 tokens as its block gives it, 0 to 4, in a loop of its own for each number.
+// copies so that the wait can leave W's last eight in flight.  See lm_deep for where that pays.
+// A wavefront multiplies as many columns of 16 tokens as its block gives it, 0 to 8, in a loop of its own for each number.
 // RAGGED: d_model is not a multiple of 64; lanes whose chunk of a tile's last step lies past the end of d_model fetch
 // zeros (both operands, so that an infinity in one does not meet the zeros of the other).
 // GRAD = false: every finished tile is folded into the running soft-max state (log-prob call).  GRAD = true: every
@@ -376,51 +449,52 @@ typedef const __attribute__((address_space(1))) void* glb_ptr;
 __device__ __align__(16) const bf16_t kLmZeros[8] = {};
 
 template <bool GRAD, bool RAGGED, bool DEEP>
-__global__ __launch_bounds__(kLmThreads) void lm_head_tile_kernel(
+__global__ __launch_bounds__(kLmThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void lm_head_tile_kernel(
     const bf16_t* __restrict__ hidden, long long ld_h, const bf16_t* __restrict__ weight, long long ld_w,
-    LmRows rows, const LmDevPlan* __restrict__ plan, int d_model, int vocab, const int* __restrict__ token_ids,
+    LmRows rows, LmPlanArg plan, int d_model, int vocab, const int* __restrict__ token_ids,
     float scale, int n_vtiles, float* __restrict__ part_m, float* __restrict__ part_s,
     float* __restrict__ zy_out, LmGradArgs ga) {
   extern __shared__ __align__(16) unsigned char lds[];
   LmItem it;
-  if (!it.init(plan, n_vtiles)) return;
+  if (!it.init(plan.get(), n_vtiles)) return;
   const int lane = it.lane, wave = it.wave;
 
-  // ---- copies: wavefront w moves rows 8 w .. 8 w + 7 (+ 64 j, j = 0..3) of each slice; a lane sits at chunk
-  // position lane & 7 of row lane >> 3 and therefore fetches logical chunk (lane & 7) ^ ((row >> 1) & 7), which is
-  // the same for the four rows 64 apart
+  // ---- copies: wavefront w moves rows 8 w .. 8 w + 7 (+ 32 j, j = 0..7) of each slice; a lane sits at chunk
+  // position lane & 7 of row lane >> 3 and therefore fetches logical chunk (lane & 7) ^ swizzle(row), which is
+  // the same for the eight rows 32 apart
   const int crow = 8 * wave + (lane >> 3);
-  const int cchunk = (lane & 7) ^ ((crow >> 1) & 7);
-  const bf16_t* hp[4];
-  const bf16_t* wp[4];
+  const int hchunk = (lane & 7) ^ lds_swizzle_h(crow), wchunk = (lane & 7) ^ lds_swizzle_w(crow);
+  const bf16_t* hp[8];
+  const bf16_t* wp[8];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int trow = rows.row(it.t0 + crow + 64 * j, it.n_eval);
-    hp[j] = hidden + (long long)trow * ld_h + cchunk * 8;
+  for (int j = 0; j < 8; ++j) {
+    // (rows past the block's are one row again and again: a line of L2 instead of eight for what nobody multiplies)
+    const int trow = rows.row(min(it.t0 + crow + 32 * j, it.t_end - 1), it.n_eval);
+    hp[j] = hidden + (long long)trow * ld_h + hchunk * 8;
   }
   auto point_w = [&](int vt) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int vrow = min(vt * kLmTileV + crow + 64 * j, vocab - 1);
-      wp[j] = weight + (long long)vrow * ld_w + cchunk * 8;
+    for (int j = 0; j < 8; ++j) {
+      const int vrow = min(vt * kLmTileV + crow + 32 * j, vocab - 1);
+      wp[j] = weight + (long long)vrow * ld_w + wchunk * 8;
     }
   };
   const int n_ksteps = (d_model + kLmTileK - 1) / kLmTileK;
   const int n_steps = (it.vt1 - it.vt0) * n_ksteps;
-  // One of the four copy instructions (rows, then the same 64, 128 and 192 rows further) that bring a step's slice of W into
-  // the slice at byte `at`, or of H; the fourth advances the cursor.  Once the cursor of W has reached the last step it stays
+  // One of the eight copy instructions (rows, then those 32, 64, ... rows further) that bring a step's slice of W into the
+  // slice at byte `at`, or of H; the eighth advances the cursor.  Once the cursor of W has reached the last step it stays
   // there: the copies issued after that re-fetch the last step into a slice nobody reads any more, which keeps the loop free
   // of branches.  (H has the same rows for every tile: its cursor goes round.)
   int w_step = 0, w_kt = 0, w_vt = it.vt0, h_kt = 0;
   point_w(w_vt);
-  auto copy = [&](const bf16_t* row, int k0, int at, int q) {
+  auto copy = [&](const bf16_t* row, int k0, int chunk, int at, int q) {
     const bf16_t* src = row + k0;
-    if (RAGGED) src = k0 + cchunk * 8 < d_model ? src : kLmZeros;
-    __builtin_amdgcn_global_load_lds((glb_ptr)src, (lds_ptr)(lds + at + (8 * wave + 64 * q) * 128), 16, 0, 0);
+    if (RAGGED) src = k0 + chunk * 8 < d_model ? src : kLmZeros;
+    __builtin_amdgcn_global_load_lds((glb_ptr)src, (lds_ptr)(lds + at + (8 * wave + 32 * q) * 128), 16, 0, 0);
   };
   auto copy_w = [&](int at, int q) {
-    copy(wp[q], w_kt * kLmTileK, at, q);
-    if (q == 3 && w_step + 1 < n_steps) {
+    copy(wp[q], w_kt * kLmTileK, wchunk, at, q);
+    if (q == 7 && w_step + 1 < n_steps) {
       ++w_step;
       if (++w_kt == n_ksteps) {
         w_kt = 0;
@@ -430,25 +504,27 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_tile_kernel(
     }
   };
   auto copy_h = [&](int at, int q) {
-    copy(hp[q], h_kt * kLmTileK, at, q);
-    if (q == 3) h_kt = h_kt + 1 == n_ksteps ? 0 : h_kt + 1;
+    copy(hp[q], h_kt * kLmTileK, hchunk, at, q);
+    if (q == 7) h_kt = h_kt + 1 == n_ksteps ? 0 : h_kt + 1;
   };
-  // The eight copies of a set, in order: those of H first where W runs a step further ahead, in turns otherwise.
+  // The sixteen copies of a set, in order: those of H first where W runs a step further ahead, in turns otherwise.
   auto copy_part = [&](int w_at, int h_at, int p) {
-    if (DEEP ? p < 4 : (p & 1) != 0) copy_h(h_at, DEEP ? p : p >> 1);
-    else copy_w(w_at, DEEP ? p - 4 : p >> 1);
+    if (DEEP ? p < 8 : (p & 1) != 0) copy_h(h_at, DEEP ? p : p >> 1);
+    else copy_w(w_at, DEEP ? p - 8 : p >> 1);
   };
 
-  // ---- fragments: lane reads row (16-row tile base + col), chunk 4 kk + quarter of a 128-byte row
-  const int frag_off[2] = {lds_chunk_offset(it.col, it.quarter), lds_chunk_offset(it.col, 4 + it.quarter)};
-  const int a_base = it.wv * kLmWaveV * 128;
-  const int b_base = it.col0 * 16 * 128;
-  bf16x8 a[4], b[2][kLmNJ];
-  auto read_a = [&](int at, int g) {                   // the fragment of group g (0..15) into its place in the ring
-    a[g & 3] = as_bf16x8(*reinterpret_cast<const u32x4*>(lds + at + a_base + (g & 7) * 2048 + frag_off[g >> 3]));
+  // ---- fragments of a half step (32 elements): lane reads chunk 4 kk + quarter of a 128-byte row
+  const int arow = 8 * (it.col >> 2) + (it.col & 3);           // tile i: rows 32 (i >> 1) + 4 (i & 1) + arow, see lm_entry
+  const int a_off[2] = {arow * 128 + ((it.quarter ^ lds_swizzle_w(arow)) << 4) + it.wv * kLmWaveV * 128,
+                        arow * 128 + (((4 + it.quarter) ^ lds_swizzle_w(arow)) << 4) + it.wv * kLmWaveV * 128};
+  const int b_off[2] = {it.col * 128 + ((it.quarter ^ lds_swizzle_h(it.col)) << 4) + it.col0 * 16 * 128,
+                        it.col * 128 + (((4 + it.quarter) ^ lds_swizzle_h(it.col)) << 4) + it.col0 * 16 * 128};
+  bf16x8 a[2][kLmNI], b[2][kLmNJ];
+  auto read_a = [&](int at, int kk, int i) {
+    a[kk][i] = as_bf16x8(*reinterpret_cast<const u32x4*>(lds + at + a_off[kk] + (i >> 1) * 4096 + (i & 1) * 512));
   };
   auto read_b = [&](int at, int kk, int j) {
-    b[kk][j] = as_bf16x8(*reinterpret_cast<const u32x4*>(lds + at + b_base + j * 2048 + frag_off[kk]));
+    b[kk][j] = as_bf16x8(*reinterpret_cast<const u32x4*>(lds + at + b_off[kk] + j * 2048));
   };
 
   LmSoftmax sm;
@@ -462,81 +538,106 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_tile_kernel(
   auto walk = [&](auto columns) {
     constexpr int NJ = decltype(columns)::value;
     LmAcc acc;
-    lm_clear<NJ>(acc);
-    int vt = it.vt0, kt = 0;
     // slices of the step at hand, of the next one and (DEEP: of W) of the one after that
     constexpr int kH = (DEEP ? 3 : 2) * kLmOperandBytes;
     int w0 = 0, w1 = kLmOperandBytes, w2 = DEEP ? 2 * kLmOperandBytes : 0, h0 = kH, h1 = kH + kLmOperandBytes;
-    // ---- prologue: step 0 and the first copies that follow it in flight, step 0 published
+    // ---- prologue: step 0 published, those after it in flight
 #pragma unroll
-    for (int p = 0; p < 8; ++p) copy_part(w0, h0, p);
+    for (int p = 0; p < 16; ++p) copy_part(w0, h0, p);
     if (DEEP) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) copy_w(w1, q);
+      for (int q = 0; q < 8; ++q) copy_w(w1, q);
     }
 #pragma unroll
-    for (int p = 0; p < 3; ++p) copy_part(DEEP ? w2 : w1, h1, p);
-    // copies complete in order: all but the last three (DEEP: seven) are step 0's
-    if (DEEP) asm volatile("s_waitcnt vmcnt(7)\n\ts_barrier" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(3)\n\ts_barrier" ::: "memory");
+    for (int p = 0; p < 16; ++p) copy_part(DEEP ? w2 : w1, h1, p);
+    // copies complete in order: all but the last 16 (DEEP: 24) are step 0's
+    if (DEEP) asm volatile("s_waitcnt vmcnt(24)\n\ts_barrier" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(16)\n\ts_barrier" ::: "memory");
+    // the reads of a half step in the order in which its products need them
+    auto read_part = [&](int w_at, int h_at, int kk, int p) {
+      if (p == 0) read_a(w_at, kk, 0);
+      else if (p <= NJ) read_b(h_at, kk, p - 1);
+      else if (p < NJ + kLmNI) read_a(w_at, kk, p - NJ);
+    };
+    if (NJ > 0) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) read_b(h0, 0, j);
+      for (int p = 0; p < NJ + kLmNI; ++p) read_part(w0, h0, 0, p);
+    }
+    // slices change places after a step
+    auto turn = [&] {
+      const int w = w0, h = h0;
+      w0 = w1;
+      w1 = DEEP ? w2 : w;
+      w2 = w;
+      h0 = h1;
+      h1 = h;
+    };
+    // every copy in flight is of step s + 1 (DEEP: or one of the last eight, W of step s + 2)
+    auto meet = [&] {
+      if (DEEP) asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      AIS_PIN;
+    };
+    if constexpr (NJ == 0) {                             // copies and barriers only
+      for (int s = 0; s < n_steps; ++s) {
+        meet();
 #pragma unroll
-    for (int g = 0; g < 3; ++g)
-      if (NJ > 0) read_a(w0, g);
-    for (int s = 0; s < n_steps; ++s) {
-#pragma unroll
-      for (int g = 0; g < 16; ++g) {
-        const int kk = g >> 3, i = g & 7;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[g & 3], b[kk][j], acc[i][j], 0, 0, 0);
+        for (int p = 0; p < 16; ++p) copy_part(w0, h0, p);
+        turn();
+      }
+    } else {
+      // Products of a half step, its reads, and where in the step (counted in products) reads end, the barrier comes and
+      // copies end.  The p-th of n things that are spread over a span of products comes after product p * span / n.
+      constexpr int kHalf = kLmNI * NJ, kReads = kLmNI + NJ;
+      constexpr int kReadSpan = kHalf * 5 / 8, kBarrierAt = kHalf * 6 / 8, kCopySpan = kHalf;
+      auto half_step = [&](auto which) __attribute__((always_inline)) {
+        constexpr int kk = decltype(which)::value;
         AIS_PIN;
-        // reads three groups ahead; the last two of the buffer together, so that all have arrived at the barrier
-        if (NJ > 0 && g <= 10) read_a(w0, g + 3);
-        if (NJ > 0 && g == 11) {
-          read_a(w0, 14);
-          read_a(w0, 15);                             // takes the place that group 11 has just used
-        }
-        if (g >= 2 && g - 2 < NJ) read_b(h0, 1, g - 2);
-        if (g < 5) copy_part(DEEP ? w2 : w1, h1, g + 3);
-        AIS_PIN;
-        if (g == 12) {
-          // every copy in flight is of step s + 1 (DEEP: or one of the last four, W of step s + 2)
-          if (DEEP) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-          else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        unrolled<kHalf>([&](auto product) __attribute__((always_inline)) {
+          constexpr int in = decltype(product)::value, m = kk * kHalf + in, i = in / NJ, j = in % NJ;
+          lm_product(acc[i][j], a[kk][i], b[kk][j]);
           AIS_PIN;
-          if (NJ > 0) read_a(w1, 0);
-          if (NJ > 0) read_b(h1, 0, 0);
-          if (NJ > 1) read_b(h1, 0, 1);
-        }
-        if (g == 13) {
-          if (NJ > 2) read_b(h1, 0, 2);
-          if (NJ > 3) read_b(h1, 0, 3);
-          if (NJ > 0) read_a(w1, 1);
-        }
-        if (NJ > 0 && g == 14) read_a(w1, 2);
-        if (g >= 13) copy_part(w0, h0, g - 13);        // the slices that the barrier has freed
-        AIS_PIN;
-      }
+          constexpr int r0 = (in * kReads + kReadSpan - 1) / kReadSpan, r1 = ((in + 1) * kReads + kReadSpan - 1) / kReadSpan;
+#pragma unroll
+          for (int p = r0; p < r1; ++p) {
+            if (kk == 0) read_part(w0, h0, 1, p);
+            else read_part(w1, h1, 0, p);
+          }
+          if constexpr (m == kBarrierAt) meet();
+          if constexpr (m >= kBarrierAt) {               // into the slices that the barrier has freed
+            constexpr int after = m - kBarrierAt;
+            constexpr int c0 = (after * 16 + kCopySpan - 1) / kCopySpan, c1 = ((after + 1) * 16 + kCopySpan - 1) / kCopySpan;
+#pragma unroll
+            for (int p = c0; p < (c1 < 16 ? c1 : 16); ++p) copy_part(w0, h0, p);
+          }
+          AIS_PIN;
+        });
+      };
       {
-        const int w = w0, h = h0;
-        w0 = w1;
-        w1 = DEEP ? w2 : w;
-        w2 = w;
-        h0 = h1;
-        h1 = h;
+        const LmClear clear;
+        unrolled<kHalf>([&](auto k) __attribute__((always_inline)) { clear.first(acc[k.value / NJ][k.value % NJ]); });
       }
-      if (++kt == n_ksteps) {
-        if (GRAD) gr.template emit<NJ>(acc, it, vt, vocab, scale, ga);
-        else sm.template fold<NJ>(acc, it, vt, vocab, scale, zy_out);
-        lm_clear<NJ>(acc);
-        kt = 0;
-        ++vt;
+      for (int vt = it.vt0; vt < it.vt1; ++vt) {
+        for (int kt = 0; kt < n_ksteps; ++kt) {
+          half_step(std::integral_constant<int, 0>{});
+          half_step(std::integral_constant<int, 1>{});
+          turn();
+        }
+        lm_settle();
+        const LmClear clear;
+        unrolled<NJ>([&](auto column) __attribute__((always_inline)) {
+          constexpr int j = decltype(column)::value;
+          if constexpr (GRAD) gr.template emit<j>(acc, it, vt, vocab, scale, ga, clear);
+          else sm.template fold<j>(acc, it, vt, vocab, scale, zy_out, clear);
+        });
       }
     }
   };
-  if (it.n_cols == 4) walk(std::integral_constant<int, 4>{});
+  if (it.n_cols == 8) walk(std::integral_constant<int, 8>{});
+  else if (it.n_cols == 7) walk(std::integral_constant<int, 7>{});
+  else if (it.n_cols == 6) walk(std::integral_constant<int, 6>{});
+  else if (it.n_cols == 5) walk(std::integral_constant<int, 5>{});
+  else if (it.n_cols == 4) walk(std::integral_constant<int, 4>{});
   else if (it.n_cols == 3) walk(std::integral_constant<int, 3>{});
   else if (it.n_cols == 2) walk(std::integral_constant<int, 2>{});
   else if (it.n_cols == 1) walk(std::integral_constant<int, 1>{});
@@ -627,17 +728,7 @@ __global__ __launch_bounds__(1024) void lm_head_setup_kernel(const unsigned char
   if (tid < 2) {
     const LmSetupGoal goal = tid == 0 ? goal0 : goal1;
     if (goal.n_vtiles == 0) return;
-    LmDevPlan d;
-    d.n_eval = total;
-    d.n_tblocks = n_tblocks;
-    lm_chunks_cost((int)(best[tid] & 0xffffu), n_tblocks, goal.n_vtiles, n_cus, goal.max_items, &d.n_chunks,
-                   &d.tiles_per_chunk);
-    d.n_items = d.n_tblocks * d.n_chunks;
-    d.per_xcd = (d.n_items + 7) / 8;
-    d.tb_group = max(1, lm_token_block_group(n_tblocks));
-    // as many rows in every block: a block's time goes with its columns of 16 (see LmItem)
-    d.block_rows = n_tblocks > 0 ? ((total + n_tblocks - 1) / n_tblocks + 15) / 16 * 16 : kLmTileT;
-    plan[tid] = d;
+    plan[tid] = lm_decomposition(total, (int)(best[tid] & 0xffffu), goal.n_vtiles, n_cus, goal.max_items);
   }
 }
 
@@ -648,14 +739,15 @@ constexpr int kMergeRows = 16;
 constexpr int kMergeWays = 16;
 __global__ __launch_bounds__(kMergeRows * kMergeWays) void lm_head_merge_kernel(
     const float* __restrict__ part_m, const float* __restrict__ part_s, const float* __restrict__ zy, int n_rows,
-    const LmDevPlan* __restrict__ plan, int vocab, const int* __restrict__ token_ids, const int* __restrict__ pos,
+    LmPlanArg plan, int vocab, const int* __restrict__ token_ids, const int* __restrict__ pos,
     float inv_temperature, float* __restrict__ logp_out, float* __restrict__ lse_out, int* __restrict__ status) {
   __shared__ float way_m[kMergeWays][kMergeRows];
   __shared__ double way_s[kMergeWays][kMergeRows];
   const int r = threadIdx.x % kMergeRows, way = threadIdx.x / kMergeRows;
   const long long n = (long long)blockIdx.x * kMergeRows + r;
-  const int n_chunks = plan->n_chunks;
-  const long long stride = plan->n_eval;
+  const LmDevPlan decomposition = plan.get();
+  const int n_chunks = decomposition.n_chunks;
+  const long long stride = decomposition.n_eval;
   const int p = n >= n_rows ? -1 : (pos != nullptr ? pos[n] : (int)n);
   float m = kNegHuge;
   if (p >= 0)
@@ -738,12 +830,14 @@ LmHeadPlan lm_head_plan(long long n_rows, int vocab, int n_cus) {
   p.n_vtiles = (vocab + kLmTileV - 1) / kLmTileV;
   p.max_chunks = lm_chunk_limit(n_tblocks, p.n_vtiles, n_cus);
   long long best = -1, items = 1;
+  p.chunks = 1;
   for (int c = 1; c <= p.max_chunks; ++c) {
     int real, tpc;
     const long long cost = lm_chunks_cost(c, n_tblocks, p.n_vtiles, n_cus, 1LL << 40, &real, &tpc);
     if (best < 0 || cost < best) {
       best = cost;
       items = (long long)n_tblocks * real;
+      p.chunks = c;
     }
   }
   p.max_items = (int)((items + 7) / 8 * 8);
@@ -796,7 +890,7 @@ size_t lm_grad_dlogits_bytes(long long m_rows, long long vocab, long long asked,
 
 template <bool GRAD, bool DEEP>
 int launch_lm_tile(ais_ctx* ctx, int grid, const void* hidden, long long ld_h, const void* weight, long long ld_w,
-                     LmRows rows, const LmDevPlan* dplan, int d_model, int vocab, const int* token_ids, float scale,
+                     LmRows rows, const LmPlanArg& decomposition, int d_model, int vocab, const int* token_ids, float scale,
                      int n_vtiles, float* part_m, float* part_s, float* zy, const LmGradArgs& ga) {
   static std::once_flag once[2][kMaxDevices];                          // per function and device
   static bool ok[2][kMaxDevices];
@@ -807,25 +901,26 @@ int launch_lm_tile(ais_ctx* ctx, int grid, const void* hidden, long long ld_h, c
     return hip_fail(ctx, hipErrorInvalidValue);
   ScopedTimer timer(ctx, GRAD ? AIS_K_LM_HEAD_GRAD : AIS_K_LM_HEAD);
   kernel<<<grid, kLmThreads, lds, ctx->stream>>>(static_cast<const bf16_t*>(hidden), ld_h,
-                                                         static_cast<const bf16_t*>(weight), ld_w, rows, dplan, d_model,
+                                                         static_cast<const bf16_t*>(weight), ld_w, rows, decomposition, d_model,
                                                          vocab, token_ids, scale, n_vtiles, part_m, part_s, zy, ga);
   return hip_fail(ctx, hipGetLastError());
 }
 
-// Whether W runs two steps ahead: where few token blocks share what the embedding brings, so that its way from HBM is what
-// a step waits for.  Log-prob, us without and with, x 151,936 x 4,096: 64 rows 304 and 241, 300 494 and 387, 390 520 and 462,
-// 520 687 and 568, 1,000 1,014 and 963, 2,000 2,011 and 1,906, 4,096 3,842 and 3,718, 7,168 6,528 and 6,481, 8,192 7,277 and
-// 7,331, 41,643 38.1 and 39.9 ms.  The gradient's chunks are short items, most of them in their first tiles: 4,096 rows x
-// 126,464 x 4,096 10.17 and 9.90 ms, 16,384 x 32,000 x 4,096 10.61 and 10.39, 12,000 x 126,464 x 2,048 16.4 and 16.0, but
-// 3,000 x 50,257 x 1,024 1.23 and 1.25.
+// Whether the log-prob call's W runs two steps ahead: where few token blocks share what the embedding brings and it is more than the Infinity
+// Cache's 256 MB, so that its way from HBM is what a step waits for.  Log-prob, us without and with: 64 rows x 151,936 x 4,096
+// 306 and 228, x 1,024 85 and 71, 390 x 4,096 503 and 447, x 1,024 138 and 120, 1,000 x 4,096 983 and 918, 2,000 1,920 and
+// 1,839, 4,096 x 126,464 x 4,096 3,022 and 2,896; but 5,000 x 128,256 x 4,096 3,797 and 3,849, 6,500 4,935 and 5,042, 30,000 x
+// 151,936 27.1 and 29.1 ms (between, 8,192 to 20,000 rows of 4,096, it would gain 1 to 3 %, at 25,000 lose 2).  Embeddings that
+// the cache holds: 1,800 rows x 46,336 x 960 143 and 153, 390 x 50,257 x 1,024 51.5 and 52.6, 1,000 95.2 and 96.7, 390 x
+// 151,936 x 576 74.9 and 76.7, 2,000 x 50,257 x 2,048 327 and 325.  The gradient's chunks are short items, most of them in
+// their first tiles: 4,052 rows x 126,464 x 4,096 10.23 and 9.97 ms, 3,000 x 50,257 x 1,024 1.148 and 1.117, 8,192 x 126,464 x
+// 576 4.81 and 4.66, 600 x 50,257 x 1,024 464 and 438 us, but 2,500 x 32,000 x 512 501 and 504: always two steps ahead.
 // At any size where the embedding's rows do not begin with a 128-byte line, as with a ragged d_model: a slice's rows then lie
-// across two lines each, and one step is too short for them.  Log-prob, x 151,936, us without and with: 300 rows x 2,056 356
-// and 268, 800 x 4,104 1,343 and 963, 1,600 x 1,032 575 and 462 (without, before blocks had columns of their own: 325, 1,167,
-// 535), 8,192 x 2,056 4,974 and 3,957, 20,000 x 1,032 6,008 and 5,405; gradient, 6,000 x 126,464 x 1,056 6,061 and 5,735,
-// 3,000 x 32,000 x 544 550 and 552.
-bool lm_deep(bool grad, long long n_rows, int d_model, const void* weight, long long ld_w) {
+// across two lines each, and one step is too short for them (with eight wavefronts to a workgroup 300 rows x 151,936 x 2,056
+// 356 without and 268 with, 8,192 rows 4,974 and 3,957).
+bool lm_deep(long long n_rows, int d_model, long long vocab, const void* weight, long long ld_w) {
   if (d_model % kLmTileK != 0 || reinterpret_cast<uintptr_t>(weight) % 128 != 0 || ld_w % 64 != 0) return true;
-  return grad ? d_model >= 2048 : n_rows <= 6144;
+  return n_rows <= 4608 && vocab * d_model >= 128LL << 20;
 }
 
 int launch_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long ld_h, const void* weight, long long ld_w,
@@ -837,20 +932,24 @@ int launch_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long ld_h, con
   // more, shorter chunks, but never more items than that, and the workgroups left over leave at once.
   const int max_items = valid != nullptr ? plan.max_items_masked : plan.max_items;
   LmDevPlan* dplan = static_cast<LmDevPlan*>(dev_plan);
-  lm_head_setup_kernel<<<1, 1024, 0, ctx->stream>>>(
-      valid, (int)n_rows, LmSetupGoal{plan.n_vtiles, max_items, (long long)plan.max_chunks * n_rows}, LmSetupGoal{},
-      ctx->n_cus, row_index, row_pos, dplan, -1, nullptr);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail(ctx, e);
+  LmPlanArg decomposition{nullptr, lm_decomposition((int)n_rows, plan.chunks, plan.n_vtiles, ctx->n_cus, max_items)};
+  if (valid != nullptr) {
+    lm_head_setup_kernel<<<1, 1024, 0, ctx->stream>>>(
+        valid, (int)n_rows, LmSetupGoal{plan.n_vtiles, max_items, (long long)plan.max_chunks * n_rows}, LmSetupGoal{},
+        ctx->n_cus, row_index, row_pos, dplan, -1, nullptr);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(ctx, e);
+    decomposition.at = dplan;
+  }
   LmRows rows{valid != nullptr ? row_index : nullptr};
   // (how many rows a mask leaves is known on the device only: half of them is the guess)
-  auto launch = lm_deep(false, valid != nullptr ? n_rows / 2 : n_rows, d_model, weight, ld_w) ? launch_lm_tile<false, true>
+  auto launch = lm_deep(valid != nullptr ? n_rows / 2 : n_rows, d_model, vocab, weight, ld_w) ? launch_lm_tile<false, true>
                                                                                               : launch_lm_tile<false, false>;
-  const int rc = launch(ctx, max_items, hidden, ld_h, weight, ld_w, rows, dplan, d_model, vocab, token_ids,
+  const int rc = launch(ctx, max_items, hidden, ld_h, weight, ld_w, rows, decomposition, d_model, vocab, token_ids,
                                        inv_temperature * kLog2e, plan.n_vtiles, part_m, part_s, zy, LmGradArgs{});
   if (rc != AIS_OK) return rc;
   lm_head_merge_kernel<<<(unsigned)((n_rows + kMergeRows - 1) / kMergeRows), kMergeRows * kMergeWays, 0, ctx->stream>>>(
-      part_m, part_s, zy, (int)n_rows, dplan, vocab, token_ids, valid != nullptr ? row_pos : nullptr,
+      part_m, part_s, zy, (int)n_rows, decomposition, vocab, token_ids, valid != nullptr ? row_pos : nullptr,
       inv_temperature, logp_out, lse_out, ctx->status_dev);
   return hip_fail(ctx, hipGetLastError());
 }
@@ -859,15 +958,15 @@ int launch_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long ld_h, con
 // call's chunks: plan 0 for chunks of `width` vocabulary entries, plan 1 for a last chunk of width_last (0: none).
 int launch_lm_head_grad_setup(ais_ctx* ctx, const unsigned char* live_mask, long long n_rows, int n_cap, int width,
                               int width_last, int* row_index, int* row_pos, void* dev_plan) {
-  const int m_rows = live_mask != nullptr ? n_cap : (int)n_rows;
+  if (live_mask == nullptr) return AIS_OK;         // every row: the decompositions go with the launches
   auto goal = [&](int w) {
     if (w == 0) return LmSetupGoal{};
-    const LmHeadPlan plan = lm_head_plan(m_rows, w, ctx->n_cus);
-    return LmSetupGoal{plan.n_vtiles, live_mask != nullptr ? plan.max_items_masked : plan.max_items, 1LL << 62};
+    const LmHeadPlan plan = lm_head_plan(n_cap, w, ctx->n_cus);
+    return LmSetupGoal{plan.n_vtiles, plan.max_items_masked, 1LL << 62};
   };
   lm_head_setup_kernel<<<1, 1024, 0, ctx->stream>>>(live_mask, (int)n_rows, goal(width), goal(width_last), ctx->n_cus,
-                                                    row_index, row_pos, static_cast<LmDevPlan*>(dev_plan),
-                                                    live_mask != nullptr ? n_cap : -1, ctx->status_dev);
+                                                    row_index, row_pos, static_cast<LmDevPlan*>(dev_plan), n_cap,
+                                                    ctx->status_dev);
   return hip_fail(ctx, hipGetLastError());
 }
 
@@ -885,10 +984,11 @@ int launch_lm_head_dlogits_chunk(ais_ctx* ctx, const void* hidden, long long ld_
   const LmHeadPlan plan = lm_head_plan(row_index != nullptr ? n_cap : n_rows, vocab, ctx->n_cus);
   const int max_items = row_index != nullptr ? plan.max_items_masked : plan.max_items;
   const LmDevPlan* dplan = static_cast<const LmDevPlan*>(dev_plan) + which;
+  const LmPlanArg decomposition{row_index != nullptr ? dplan : nullptr,
+                                lm_decomposition((int)n_rows, plan.chunks, plan.n_vtiles, ctx->n_cus, max_items)};
   LmRows rows{row_index};
   LmGradArgs ga{lse, logp, coeff, static_cast<bf16_t*>(ds), ds_stride, y_off, row_index != nullptr ? 1 : 0};
-  auto launch = lm_deep(true, n_rows, d_model, weight, ld_w) ? launch_lm_tile<true, true> : launch_lm_tile<true, false>;
-  const int rc = launch(ctx, max_items, hidden, ld_h, weight, ld_w, rows, dplan, d_model, vocab,
+  const int rc = launch_lm_tile<true, true>(ctx, max_items, hidden, ld_h, weight, ld_w, rows, decomposition, d_model, vocab,
                                         token_ids, inv_temperature * kLog2e, plan.n_vtiles, nullptr, nullptr, nullptr,
                                         ga);
   if (rc != AIS_OK) return rc;

@@ -317,17 +317,16 @@ int ais_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long hidden_strid
  *   dhidden[n, :]  = sum_v dlogits[n, v] weight[v, :]
  *   dweight[v, :]  = sum_n dlogits[n, v] hidden[n, :]
  * The vocabulary is walked in chunks: the logits of a chunk are recomputed on the matrix cores from the operands,
- * turned into dlogits (bf16) with the row's lse, and consumed at once by two products (fp32 accumulation and output;
- * the library's own kernels where their tiles fill the GPU, rocBLAS otherwise); only [n_rows, chunk_vocab] dlogits exist
- * at any time.
+ * turned into dlogits (bf16) with the row's lse, and consumed at once by two products (fp32 accumulation and output);
+ * only [n_rows, chunk_vocab] dlogits exist at any time.
  *   hidden, weight, token_ids, dtype, strides   as for ais_lm_head_logprob; d_model a multiple of 32
  *   lse, logp   [n_rows] fp32, outputs of ais_lm_head_logprob for the same operands and temperature
  *   coeff       [n_rows] fp32, as written by ais_grpo_row_scale (its g_out: it carries inv_temperature)
- *   chunk_vocab vocabulary entries per chunk, a multiple of 256.  The context workspace grows to
- *               2 * n_rows * chunk_vocab bytes.  0 selects 8192 (22 to 31 times 256 for a
- *               d_model whose embedding gradient then fills the chip better; the workspace stays that of 8192) and,
- *               with up to 3,072 rows to go through, wider chunks; the workspace is then up to 68 MB whatever the
- *               number of those rows.
+ *   chunk_vocab vocabulary entries per chunk, a multiple of 256.  The context workspace grows to 2 * n_rows * chunk_vocab
+ *               bytes, and up to 256 MiB in which parts of the two sums are kept where a product alone would not fill the GPU.
+ *               0: the library's choice, chunks of up to 65536 (with few rows 131072) entries, all alike, whose workspace is
+ *               at most 1 GiB, and 8192 entries where that would take more.  Where the device has no room for it, 8192 (up to
+ *               68 MB with up to 3,072 rows) and sums in one part.
  *   n_live_max  negative, or >= n_rows: every row goes through the recomputation and the GEMMs.  Otherwise a bound
  *               that the caller vouches for on the number of rows with coeff != 0 (for a masked-diffusion batch:
  *               the number of evaluated positions, which its loader knows): those rows are gathered on the device
@@ -335,11 +334,11 @@ int ais_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long hidden_strid
  *               a gradient.  If there are more such rows than n_live_max, the surplus rows are left out (their
  *               dhidden is 0 and they do not enter dweight) and AIS_STATUS_LIVE_OVERFLOW is set; nothing is read
  *               or written out of range.  The workspace then holds 2 n_live_max (chunk_vocab + 3 d_model) bytes
- *               and 9 bytes per row.
+ *               and 9 bytes per row, and the parts above.
  *   dhidden_out [n_rows, d_model] fp32, contiguous; dweight_out [vocab, d_model] fp32, contiguous; both are
  *               overwritten.
  * Errors: as ais_lm_head_logprob; d_model not a multiple of 32 or chunk_vocab not a multiple of 256
- * (AIS_ERR_SIZE); a failing library call (AIS_ERR_HIP). */
+ * (AIS_ERR_SIZE). */
 int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, const void* weight,
                      long long weight_stride, ais_dtype dtype, long long n_rows, long long d_model,
                      long long vocab, const int* token_ids, const float* lse, const float* logp,

@@ -22,8 +22,6 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
-# the hidden-state gradient call's products at sizes that its own kernels leave are the library's
-LINK_FLAGS = ["-lrocblas"]
 
 
 def fast_binding_command():
@@ -51,7 +49,7 @@ def build(verbose: bool = True) -> str:
     """Compiles the library, which needs hipcc alone, and beside it the binding's native calls where there is what they need.
     Neither is left over from an earlier build if this one fails."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc, *HIPCC_FLAGS, *[os.path.join(CSRC, s) for s in SOURCES], "-o", LIB, *LINK_FLAGS]
+    cmd = [hipcc, *HIPCC_FLAGS, *[os.path.join(CSRC, s) for s in SOURCES], "-o", LIB]
     fast, missing = fast_binding_command()
     for built in (LIB, FAST):
         if os.path.exists(built):

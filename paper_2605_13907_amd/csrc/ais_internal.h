@@ -90,7 +90,18 @@ LmHeadPlan lm_head_plan(long long n_rows, int vocab, int n_cus);
 size_t lm_head_logprob_bytes(long long n_rows, int vocab, int n_cus);
 constexpr long long kLmGradChunk = 8192;
 long long lm_grad_chunk(long long m_rows, long long vocab, long long asked, int n_cus);
+long long lm_grad_even_chunk(long long chunk, long long m_rows, long long vocab);
+size_t lm_grad_wide_bytes(long long m_rows, long long vocab);
 long long lm_grad_chunk_for(long long chunk, long long vocab, long long d_model, int n_cus);
+// Parts that the sums of the gradient's two products over a chunk are split into, at most so many and so many bytes of each.
+struct LmParts {
+  int w, h;                  // of dweight and of dhidden
+};
+constexpr int kLmMaxParts = 32, kLmMaxWeightParts = 8;
+constexpr long long kLmPartsBytes = 128LL << 20;
+LmParts lm_grad_parts(int n_cus, long long n_rows, long long d, long long n_v);
+size_t lm_dhidden_parts_bytes(long long n_rows, long long d);
+size_t lm_dweight_parts_bytes(long long vocab, long long d, int n_cus);
 size_t lm_grad_dlogits_bytes(long long m_rows, long long vocab, long long asked, int n_cus);
 
 }  // namespace ais
@@ -119,7 +130,6 @@ struct ais_ctx {
     bool valid = false;
   } plan;
   void* static_scratch = nullptr;   // address, on this context's device, of the library's static scratch array
-  void* blas = nullptr;             // rocblas_handle of ais_lm_head_grad's products at sizes its own kernels leave, created by its first call
 };
 
 namespace ais {
@@ -191,18 +201,15 @@ int launch_lm_head_dlogits_chunk(ais_ctx* ctx, const void* hidden, long long ld_
                                  long long ld_w, long long n_rows, int d_model, int vocab, int y_off,
                                  const int* token_ids, const float* lse, const float* logp, const float* coeff,
                                  float inv_temperature, const void* dev_plan, int which, void* ds, long long ds_stride,
-                                 const int* row_index, int n_cap, bool zero_tail);
-bool lm_dweight_fits(const ais_ctx* ctx, long long d, long long n_v);
-bool lm_dhidden_fits(const ais_ctx* ctx, long long d, long long n_rows);
-int launch_lm_dweight(ais_ctx* ctx, const void* ds, long long ds_stride, const void* h, long long ld_h, int k,
-                      const int* k_dev, int n_v, int d, float* dweight);
-int launch_lm_dhidden(ais_ctx* ctx, const void* ds, long long ds_stride, const void* w, long long ld_w, int n_v,
-                      int n_rows, int d, bool accumulate, float* dhidden);
+                                 const int* row_index, int n_cap);
+int launch_lm_grad_products(ais_ctx* ctx, const void* ds, long long ds_stride, const void* h, long long ld_h, const void* w,
+                            long long ld_w, int n_rows, const int* n_rows_dev, int n_v, int d, float* dweight,
+                            float* dhidden, LmParts parts, long long w_stride, long long h_stride, bool accumulate);
+int launch_lm_add_parts(ais_ctx* ctx, const float* part, long long part_stride, int parts, const int* row_pos,
+                           long long n_rows, int d, float* out);
 int launch_lm_live_mask(ais_ctx* ctx, const float* coeff, long long n_rows, unsigned char* mask);
 int launch_lm_gather_rows(ais_ctx* ctx, const void* hidden, long long ld_h, int d_model, const int* row_index,
                           const void* dev_plan, int n_cap, void* gathered);
-int launch_lm_scatter_rows(ais_ctx* ctx, const float* gathered, const int* row_pos, long long n_rows, int d_model,
-                           float* out);
 int launch_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long ld_h, const void* weight, long long ld_w,
                            long long n_rows, int d_model, int vocab, const int* token_ids,
                            const unsigned char* valid, float inv_temperature, const LmHeadPlan& plan,

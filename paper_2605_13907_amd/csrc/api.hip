@@ -5,7 +5,6 @@
 #include <mutex>
 #include <new>
 
-#include <rocblas/rocblas.h>
 
 #include "ais_internal.h"
 
@@ -252,7 +251,6 @@ int ais_destroy(ais_ctx* ctx) {
     (void)hipEventDestroy(t.stop);
   }
   for (auto& e : ctx->pool) (void)hipEventDestroy(e);
-  if (ctx->blas != nullptr) (void)rocblas_destroy_handle(static_cast<rocblas_handle>(ctx->blas));
   if (ctx->ws != nullptr) (void)hipFree(ctx->ws);
   if (ctx->status_dev != nullptr) (void)hipFree(ctx->status_dev);
   delete ctx;
@@ -545,20 +543,37 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
                        ctx->stream>>>(dhidden_out, (size_t)n_rows * (size_t)d_model);
     return hip_fail(ctx, hipGetLastError());
   }
-  // workspace: the chunk's dlogits, the device-side decomposition of the recompute kernel and, with a row list, the
-  // mask, the list, its inverse, the gathered hidden states and their gradient
+  // workspace: the chunk's dlogits, the device-side decomposition of the recompute kernel, with a row list the mask, the
+  // list, its inverse, the gathered hidden states and their gradient, and the parts of the products' sums.  Where there is no
+  // room for wide chunks and parts: the narrow chunks, and sums in one part.
   auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
-  const size_t ds_bytes = up(lm_grad_dlogits_bytes(m_rows, vocab, chunk_vocab, ctx->n_cus));
-  const bool dw_aligned = reinterpret_cast<uintptr_t>(dweight_out) % 16 == 0;
-  const bool chosen = chunk_vocab == 0;
-  chunk_vocab = lm_grad_chunk(m_rows, vocab, chunk_vocab, ctx->n_cus);
-  if (chosen && dw_aligned) chunk_vocab = lm_grad_chunk_for(chunk_vocab, vocab, d_model, ctx->n_cus);
+  const long long asked = chunk_vocab;
   const size_t plan_bytes = 256;
   const size_t mask_bytes = gather ? up((size_t)n_rows) : 0;
   const size_t list_bytes = gather ? up((size_t)n_rows * 4) : 0;
   const size_t hg_bytes = gather ? up((size_t)m_rows * (size_t)d_model * 2) : 0;
-  const size_t dhg_bytes = gather ? up((size_t)m_rows * (size_t)d_model * 4) : 0;
-  int rc = ensure_workspace(ctx, ds_bytes + plan_bytes + mask_bytes + 2 * list_bytes + hg_bytes + dhg_bytes);
+  size_t ds_bytes = 0, dhg_bytes = 0;
+  LmParts parts{1, 1};
+  int rc = AIS_OK;
+  for (const bool roomy : {true, false}) {
+    ds_bytes = up(lm_grad_dlogits_bytes(m_rows, vocab, asked, ctx->n_cus));
+    chunk_vocab = lm_grad_chunk(m_rows, vocab, asked, ctx->n_cus);
+    if (asked == 0) {
+      const long long even = roomy ? lm_grad_even_chunk(chunk_vocab, m_rows, vocab) : chunk_vocab;
+      chunk_vocab = even != chunk_vocab ? even : lm_grad_chunk_for(chunk_vocab, vocab, d_model, ctx->n_cus);
+      if (roomy) ds_bytes = std::max(ds_bytes, up(lm_grad_wide_bytes(m_rows, vocab)));
+    }
+    dhg_bytes = gather ? up((size_t)m_rows * (size_t)d_model * 4) : 0;
+    parts = LmParts{1, 1};
+    size_t dwp_bytes = 0;
+    if (roomy) {
+      parts = lm_grad_parts(ctx->n_cus, m_rows, d_model, std::min(chunk_vocab, vocab));
+      dhg_bytes = std::max(dhg_bytes, up(lm_dhidden_parts_bytes(m_rows, d_model)));
+      dwp_bytes = up(lm_dweight_parts_bytes(vocab, d_model, ctx->n_cus));
+    }
+    rc = ensure_workspace(ctx, ds_bytes + plan_bytes + mask_bytes + 2 * list_bytes + hg_bytes + dhg_bytes + dwp_bytes);
+    if (rc != AIS_ERR_NOMEM) break;
+  }
   if (rc != AIS_OK) return rc;
   ctx->plan.valid = false;             // the chunk's dlogits overwrite whatever tiling the workspace held
   char* ds = static_cast<char*>(ctx->ws);
@@ -578,68 +593,33 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   if (rc == AIS_OK && gather)
     rc = launch_lm_gather_rows(ctx, hidden, hidden_stride, (int)d_model, row_index, dev_plan, (int)m_rows, h_gathered);
   if (rc != AIS_OK) return rc;
-  // operands of the two GEMMs: the hidden states they read and the gradient they write, with their pitches
+  // operands of the two products: the hidden states they read and the gradient they write
   const void* h_gemm = gather ? static_cast<const void*>(h_gathered) : hidden;
   const long long h_gemm_stride = gather ? d_model : hidden_stride;
-  float* dh_gemm = gather ? dh_gathered : dhidden_out;
-  // (the own kernels store 16 bytes at a time; rows of a multiple of 32 floats keep the base's alignment)
-  const bool own_dh = lm_dhidden_fits(ctx, d_model, m_rows) && reinterpret_cast<uintptr_t>(dh_gemm) % 16 == 0;
-  auto own_dw = [&](int width) { return dw_aligned && lm_dweight_fits(ctx, d_model, width); };
+  const bool elsewhere = gather || parts.h > 1;
+  float* dw_parts = reinterpret_cast<float*>(h_gathered + hg_bytes + dhg_bytes);
+  float* dh_gemm = elsewhere ? dh_gathered : dhidden_out;
+  const long long h_stride = m_rows * d_model, w_stride = std::min(chunk_vocab, vocab) * d_model;
   // the list's length, first word of the decomposition on the device: rows past it are nobody's
   const int* n_listed = gather ? static_cast<const int*>(dev_plan) : nullptr;
-  // created by the first call, whichever kernels that call takes: later ones may be recorded into a graph, where nothing
-  // can be allocated
-  if (ctx->blas == nullptr) {
-    rocblas_handle h = nullptr;
-    if (rocblas_create_handle(&h) != rocblas_status_success) return AIS_ERR_HIP;
-    ctx->blas = h;
-  }
-  rocblas_handle blas = static_cast<rocblas_handle>(ctx->blas);
-  if (!own_dh || !own_dw((int)std::min<long long>(chunk_vocab, vocab)) || (width_last != 0 && !own_dw(width_last))) {
-    if (rocblas_set_stream(blas, ctx->stream) != rocblas_status_success) return AIS_ERR_HIP;
-    if (rocblas_set_pointer_mode(blas, rocblas_pointer_mode_host) != rocblas_status_success) return AIS_ERR_HIP;
-  }
-  const float one = 1.f, zero = 0.f;
   const char* w_base = static_cast<const char*>(weight);
   for (long long v0 = 0; v0 < vocab; v0 += chunk_vocab) {
     const int width = (int)std::min<long long>(chunk_vocab, vocab - v0);
     const void* w_chunk = w_base + (size_t)v0 * (size_t)weight_stride * 2;
     rc = launch_lm_head_dlogits_chunk(ctx, hidden, hidden_stride, w_chunk, weight_stride, n_rows, (int)d_model, width,
                                       (int)v0, token_ids, lse, logp, coeff, inv_temperature, dev_plan,
-                                      width == width_last ? 1 : 0, ds, chunk_vocab, row_index, (int)m_rows,
-                                      !own_dw(width));
-    if (rc != AIS_OK) return rc;
-    // The library is column-major; a row-major [r, c] matrix with pitch p is its column-major [c, r] transpose
-    // with leading dimension p.
-    // dhidden[m_rows, D] (+)= ds[m_rows, width] weight_chunk[width, D]:   C^T[D, m_rows] = W_c^T[D, width] ds^T[width, m_rows]
-    if (own_dh) {
-      rc = launch_lm_dhidden(ctx, ds, chunk_vocab, w_chunk, weight_stride, width, (int)m_rows, (int)d_model, v0 != 0,
-                             dh_gemm);
-      if (rc != AIS_OK) return rc;
-    } else if (rocblas_gemm_ex(blas, rocblas_operation_none, rocblas_operation_none, (rocblas_int)d_model,
-                               (rocblas_int)m_rows, width, &one, w_chunk, rocblas_datatype_bf16_r,
-                               (rocblas_int)weight_stride, ds, rocblas_datatype_bf16_r, (rocblas_int)chunk_vocab,
-                               v0 == 0 ? &zero : &one, dh_gemm, rocblas_datatype_f32_r, (rocblas_int)d_model, dh_gemm,
-                               rocblas_datatype_f32_r, (rocblas_int)d_model, rocblas_datatype_f32_r,
-                               rocblas_gemm_algo_standard, 0, 0) != rocblas_status_success) {
-      return AIS_ERR_HIP;
-    }
-    // dweight_chunk[width, D] = ds^T[width, m_rows] hidden[m_rows, D]:   C^T[D, width] = H^T[D, m_rows] ds[m_rows, width]
+                                      width == width_last ? 1 : 0, ds, chunk_vocab, row_index, (int)m_rows);
     float* dw_chunk = dweight_out + (size_t)v0 * (size_t)d_model;
-    if (own_dw(width)) {
-      rc = launch_lm_dweight(ctx, ds, chunk_vocab, h_gemm, h_gemm_stride, (int)m_rows, n_listed, width, (int)d_model,
-                             dw_chunk);
-      if (rc != AIS_OK) return rc;
-    } else if (rocblas_gemm_ex(blas, rocblas_operation_none, rocblas_operation_transpose, (rocblas_int)d_model, width,
-                               (rocblas_int)m_rows, &one, h_gemm, rocblas_datatype_bf16_r, (rocblas_int)h_gemm_stride,
-                               ds, rocblas_datatype_bf16_r, (rocblas_int)chunk_vocab, &zero, dw_chunk,
-                               rocblas_datatype_f32_r, (rocblas_int)d_model, dw_chunk, rocblas_datatype_f32_r,
-                               (rocblas_int)d_model, rocblas_datatype_f32_r, rocblas_gemm_algo_standard, 0,
-                               0) != rocblas_status_success) {
-      return AIS_ERR_HIP;
-    }
+    if (rc == AIS_OK)
+      rc = launch_lm_grad_products(ctx, ds, chunk_vocab, h_gemm, h_gemm_stride, w_chunk, weight_stride, (int)m_rows, n_listed,
+                                   width, (int)d_model, parts.w > 1 ? dw_parts : dw_chunk, dh_gemm, parts, w_stride, h_stride,
+                                   v0 != 0);
+    if (rc == AIS_OK && parts.w > 1)
+      rc = launch_lm_add_parts(ctx, dw_parts, w_stride, parts.w, nullptr, width, (int)d_model, dw_chunk);
+    if (rc != AIS_OK) return rc;
   }
-  if (gather) return launch_lm_scatter_rows(ctx, dh_gathered, row_pos, n_rows, (int)d_model, dhidden_out);
+  if (elsewhere)
+    return launch_lm_add_parts(ctx, dh_gathered, h_stride, parts.h, row_pos, n_rows, (int)d_model, dhidden_out);
   return AIS_OK;
 }
 

@@ -3,274 +3,377 @@
 //   dweight[v, d] = sum_n ds[n, v] H[n, d]          both operands lie with the summed index along their rows
 //   dhidden[n, d] (+)= sum_v ds[n, v] W[v, d]       ds lies with the summed index along its columns
 //
-// on the matrix cores, bf16 operands, fp32 accumulation and output.  Written as C[b, a] = sum_k A[k, a] B(k, b): A is H
-// or W (a = d), B is ds.  A 512-thread workgroup (8 wavefronts, 128 a x 64 b each) computes 256 x 256 outputs, K in
-// steps of 64; the schedule is that of the tile kernel in lm_head.hip: operand slices go straight from global memory into
-// one of two LDS buffers, fragments pass through a ring of registers, one barrier per step.
+// on the matrix cores, bf16 operands, fp32 accumulation and output, in one launch: the tiles of both fill the rounds of the
+// chip together.  Written as C[b, a] = sum_k A[k, a] B(k, b): A is H or W (a = d), B is ds.  A 256-thread workgroup (4
+// wavefronts, one to a SIMD, 128 a x 128 b each) computes 256 x 256 outputs, K in steps of 64; the schedule is that of the
+// tile kernel in lm_head.hip: operand slices go straight from global memory into one of two LDS buffers, the fragments of a
+// half step are read during the half step before, one barrier per step.
+//
+// dhidden has few tiles where there are few rows, each of them a sum over the whole chunk: its sum is then split, every part
+// accumulates over the chunks in an array of its own, and the arrays are added at the end, in order.  So is dweight's where
+// d_model or the vocabulary is small (its arrays are added chunk by chunk).
 //
 // An operand whose rows run along the summed index needs the transpose of what its rows are: its fragments come from LDS
 // by ds_read_b64_tr_b16, which hands lane i of 16 the column i of a 4 x 16 block (checked on the device).  The 16 rows
 // that such a read touches are 512 bytes apart; an XOR of the 32-byte column blocks with bits 0, 1 and 3 of the row
 // spreads them over all banks.
 //
-// Power-limited like that kernel.  Against the library's products for the same layouts, which these replace where their
-// tiles fill the chip: 4,052 rows x 8,192 entries x 4,096, dweight 271-304 -> 225 us (1.21 PFLOP/s), dhidden 223-230 ->
-// 214 us (1.27).
+// What bounds it: power nearly (the shader clock is 2.0 GHz, the matrix pipe busy 0.63 of the cycles), the outputs that leave at
+// the end of a tile, and what a wavefront, alone on its SIMD, can issue beside its products.  4,052 rows x 8,192 entries x
+// 4,096, both products: two launches of eight wavefronts of 128 x 64 outputs 458 us; one launch, copies with a select per lane
+// for rows past the end and a 64-bit product per address 462; those once per item instead 424 (1.28 PFLOP/s).  The whole
+// call against separate launches, in one part, of the library's product (rocBLAS) where tiles left the rounds too empty:
+// 367 rows x 51,492 x 4,608 1,014 -> 792 us, 832 x 85,480 x 2,688 1,633 -> 1,288, 300 x 32,000 x 1,024 189 -> 115, 5,952 x
+// 2,048 x 1,216 153 -> 108, 13,922 x 5,696 x 1,792 944 -> 762, 9,070 x 74,356 x 3,712 13.7 -> 12.7 ms, 20,000 x 32,000 x 512
+// 2,607 -> 2,152 us, 41,643 x 16,384 x 4,096 14.0 -> 13.8 ms.
 #include "ais_internal.h"
 #include "device_utils.h"
+#include "lm_tile.h"
+
+#include <algorithm>
 
 namespace ais {
 namespace {
 
 using namespace dev;
+using namespace tile;
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void* lds_ptr;
 typedef __attribute__((address_space(3))) bf16x4* lds_bf16x4;
 
-constexpr int kThreads = 512;
+constexpr int kThreads = 256;
 constexpr int kTile = 256;                       // outputs along either index
 constexpr int kStep = 64;                        // summed elements per step
 constexpr int kSliceBytes = kTile * kStep * 2;   // 32 KiB
-constexpr int kBufferBytes = 2 * kSliceBytes;    // A slice, then B slice
-constexpr int kLdsBytes = 2 * kBufferBytes;
-constexpr int kNI = 8, kNJ = 4;                  // 16 x 16 products per wavefront along a and b
+constexpr int kLdsBytes = 4 * kSliceBytes;       // two slices of A, then two of B
+constexpr int kNI = 8, kNJ = 8;                  // 16 x 16 products per wavefront along a and b
 
 __device__ __align__(16) const bf16_t kZeros[8] = {};
 
-// Copies 16 bytes per lane from `src` (per lane) to LDS at `base` + 16 * lane.  Written as an instruction because the
-// compiler, which does not see through the transposing reads, would wait for every copy in flight before each of them;
-// the waits below are written out.  (It has no result register; a wait that the compiler places for loads of its own
-// counts these copies too, which makes it wait longer, never shorter.)
+// Copies 16 bytes per lane from `src` + `ahead` elements (src per lane) to LDS at `base` + `at` + 16 * lane.  Written as
+// instructions because the compiler, which does not see through the transposing reads, would wait for every copy in flight
+// before each of them; the waits below are written out.  (It has no result but the address; a wait that the compiler places
+// for loads of its own counts these copies too, which makes it wait longer, never shorter.)  The address is formed where m0,
+// just written, may not be used yet.
 // (m0 is said to be written although the compiler warns that it is a register of its own: it orders its own uses of m0
 // by that.)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void copy_to_lds(const bf16_t* src, const unsigned char* base) {
-  const uint32_t at = (uint32_t)(uintptr_t)(lds_ptr)base;               // uniform
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(at), "v"(src) : "m0", "memory");
+template <int AT>
+__device__ __forceinline__ void copy_to_lds(const bf16_t* src, long long ahead, uint32_t base) {
+  const bf16_t* from;
+  asm volatile("s_add_i32 m0, %1, %4\n\tv_lshl_add_u64 %0, %3, 1, %2\n\tglobal_load_lds_dwordx4 %0, off"
+               : "=&v"(from) : "s"(base), "v"(src), "s"(ahead), "n"(AT) : "m0", "scc", "memory");
 }
 #pragma clang diagnostic pop
 
+// One product.
 struct GemmArgs {
   const bf16_t* a;          // [k][ld_a]
   long long ld_a;
-  const bf16_t* b;          // [k][ld_b], or [b][ld_b] (KC)
+  const bf16_t* b;          // [k][ld_b], or [b][ld_b] (dhidden)
   long long ld_b;
-  float* out;               // [b][ld_out]
-  long long ld_out;
-  int m, n, k;              // outputs along a (a multiple of 4) and b; summed elements
+  float* out;               // [b][m]; one such array for each part of the sum, part_stride elements apart
+  long long part_stride;
+  int m, n, k;              // outputs along a (a multiple of 32) and b; summed elements
   const int* k_dev;         // if not null: the number of summed elements is min(k, *k_dev)
-  int accumulate;
-  int a_tiles, b_tiles, per_xcd;
+  int accumulate, aligned;  // onto what is there; rows of out begin with 16 aligned bytes
+  int a_tiles, b_tiles, parts, part_k, per_xcd;   // part_k: summed elements of a part, a multiple of 64
 };
 
 // Byte offset of the 16-byte chunk `pos` of row `row` in a slice with 512-byte rows, and the chunk that lies there.
 __device__ __forceinline__ int row_swizzle(int row) { return (row & 3) | ((row >> 3) & 1) << 2; }
 
+// Work item `item` of a product.  KC: B lies with the summed index along its rows' elements (dhidden).
 template <bool KC>
-__global__ __launch_bounds__(kThreads) void lm_grad_gemm_kernel(GemmArgs g) {
-  extern __shared__ __align__(16) unsigned char lds[];
-  // every XCD takes a contiguous range of tiles, four b tiles under each a tile: the 32 resident workgroups of an XCD
-  // then share 8 slices of A and 4 of B through its L2
-  const int item = (blockIdx.x & 7) * g.per_xcd + (blockIdx.x >> 3);
-  if ((int)(blockIdx.x >> 3) >= g.per_xcd || item >= g.a_tiles * g.b_tiles) return;     // uniform for the workgroup
-  const int group = item / (4 * g.a_tiles), in = item - group * 4 * g.a_tiles;
+__device__ __forceinline__ void gemm_item(const GemmArgs& g, int item, unsigned char* lds) {
+  const int tiles = g.a_tiles * g.b_tiles;
+  const int part = item / tiles, tile = item - part * tiles;
+  const int group = tile / (4 * g.a_tiles), in = tile - group * 4 * g.a_tiles;
   const int rows_in = min(4, g.b_tiles - 4 * group);
   const int at = in / rows_in, bt = 4 * group + in - at * rows_in;
   const int a0 = at * kTile, b0 = bt * kTile;
-  const int k_len = g.k_dev != nullptr ? min(g.k, *g.k_dev) : g.k;
-  const int n_steps = (k_len + kStep - 1) / kStep;
+  const int k_first = part * g.part_k;
+  const int k_len = min((g.k_dev != nullptr ? min(g.k, *g.k_dev) : g.k) - k_first, g.part_k);
+  const int n_steps = (max(k_len, 0) + kStep - 1) / kStep;
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wa = wave & 1, wb = wave >> 1, quarter = lane >> 4, col = lane & 15;
 
-  // ---- copies.  Rows along k: wavefront w moves rows 8 w + 2 q + (lane >> 5), q = 0..3, of a slice; the lane sits at
-  // chunk lane & 31 of the row and fetches the chunk that belongs there.
-  const int krow = 8 * wave + (lane >> 5);
-  const int chunk0 = (lane & 31) ^ (row_swizzle(krow) << 1);             // q even; q odd: bit 1 of the row flips
-  const bf16_t* ap = g.a + (long long)krow * g.ld_a + a0;
-  const bool a_in0 = a0 + chunk0 * 8 < g.m, a_in1 = a0 + (chunk0 ^ 4) * 8 < g.m;
-  const bf16_t* bp[4];
-  bool b_in0 = true, b_in1 = true;
-  if (KC) {                                        // rows along b: 128-byte rows, eight to an instruction
-    const int crow = 8 * wave + (lane >> 3);
+  // ---- copies.  Rows along k: wavefront w moves rows 16 w + 2 q + (lane >> 5), q = 0..7, of a slice; the lane sits at
+  // chunk lane & 31 of the row and fetches the chunk that belongs there.  (Columns of A past its end are columns of C
+  // that nobody stores: any chunk of the row does.  ds holds whole tiles.)
+  const int krow = 16 * wave + (lane >> 5);
+  const bf16_t* ap[8];
+  const bf16_t* bp[8];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      bp[q] = g.b + (long long)min(b0 + crow + 64 * q, g.n - 1) * g.ld_b + ((lane & 7) ^ ((crow >> 1) & 7)) * 8;
-  } else {
-    bp[0] = g.b + (long long)krow * g.ld_b + b0;
-    b_in0 = b0 + chunk0 * 8 < g.n;
-    b_in1 = b0 + (chunk0 ^ 4) * 8 < g.n;
-  }
-  uint32_t zeros_lo = (uint32_t)reinterpret_cast<uintptr_t>(kZeros);
-  uint32_t zeros_hi = (uint32_t)(reinterpret_cast<uintptr_t>(kZeros) >> 32);
-  asm volatile("" : "+v"(zeros_lo), "+v"(zeros_hi));
-  auto either = [&](bool in, const bf16_t* src) {   // src or the zeros: two selects, no branch
-    const uint64_t p = reinterpret_cast<uint64_t>(src);
-    const uint32_t lo = in ? (uint32_t)p : zeros_lo, hi = in ? (uint32_t)(p >> 32) : zeros_hi;
-    return reinterpret_cast<const bf16_t*>((uint64_t)hi << 32 | lo);
-  };
-  int c_step = 0;                                  // step being copied; stays at the last one
-  auto copy_part = [&](int buf, int p) {           // p = 0..7: the four parts of A and B in turn
-    const int q = p >> 1, k0 = c_step * kStep;
-    unsigned char* base = lds + buf * kBufferBytes;
-    const int chunk = (q & 1) ? chunk0 ^ 4 : chunk0;
-    const bool k_in = k0 + krow + 2 * q < k_len;
-    if ((p & 1) == 0) {
-      const bf16_t* src = ap + (long long)(k0 + 2 * q) * g.ld_a + chunk * 8;
-      copy_to_lds(either(k_in & ((q & 1) ? a_in1 : a_in0), src), base + (8 * wave + 2 * q) * 512);
-    } else if (KC) {
-      copy_to_lds(bp[q] + k0, base + kSliceBytes + (8 * wave + 64 * q) * 128);
+  for (int q = 0; q < 8; ++q) {
+    const int chunk = (lane & 31) ^ (row_swizzle(krow + 2 * q) << 1);
+    ap[q] = g.a + (long long)(k_first + krow + 2 * q) * g.ld_a + min(a0 + chunk * 8, g.m - 8);
+    if (KC) {                                      // rows along b: 128-byte rows, eight to an instruction
+      const int crow = 8 * wave + (lane >> 3);
+      bp[q] = g.b + (long long)min(b0 + crow + 32 * q, g.n - 1) * g.ld_b + k_first + ((lane & 7) ^ ((crow >> 1) & 7)) * 8;
     } else {
-      const bf16_t* src = bp[0] + (long long)(k0 + 2 * q) * g.ld_b + chunk * 8;
-      copy_to_lds(either(k_in & ((q & 1) ? b_in1 : b_in0), src), base + kSliceBytes + (8 * wave + 2 * q) * 512);
+      bp[q] = g.b + (long long)(k_first + krow + 2 * q) * g.ld_b + b0 + chunk * 8;
     }
-    if (p == 7 && c_step + 1 < n_steps) ++c_step;
+  }
+  int c_step = 0;                                  // step being copied; stays at the last one
+  long long a_ahead = 0, b_ahead = 0;              // elements from ap, bp to it
+  const long long a_step = kStep * g.ld_a, b_step = KC ? kStep : kStep * g.ld_b;
+  // Once the cursor is at the last step: rows past the end of the sum are zeros (of both operands, so that an infinity in one
+  // does not meet the zeros of the other).
+  auto end_rows = [&] {
+    const int left = k_len - c_step * kStep;
+    if (c_step + 1 != n_steps || left >= kStep) return;                        // uniform
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      if (krow + 2 * q >= left) {
+        ap[q] = kZeros - a_ahead;
+        if (!KC) bp[q] = kZeros - b_ahead;
+      }
+    }
+  };
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr)lds;
+  const uint32_t a_base = lds0 + wave * (16 * 512), b_base = lds0 + 2 * kSliceBytes + wave * (KC ? 8 * 128 : 16 * 512);
+  auto copy_part = [&](int buf, auto part_number) __attribute__((always_inline)) {   // 0..15: the eight parts of A and B in turn
+    constexpr int p = decltype(part_number)::value, q = p >> 1;
+    if constexpr ((p & 1) == 0) copy_to_lds<2 * q * 512>(ap[q], a_ahead, a_base + buf);
+    else copy_to_lds<KC ? 32 * q * 128 : 2 * q * 512>(bp[q], b_ahead, b_base + buf);
+    if constexpr (p == 15) {
+      if (c_step + 1 < n_steps) {
+        ++c_step;
+        a_ahead += a_step;
+        b_ahead += b_step;
+        end_rows();
+      }
+    }
   };
 
   // ---- fragments.  Transposed: the lane addresses row 8 quarter + 4 h + (col >> 2) of a 32-row half slice and 4 of the
-  // 16 columns; the read gives it rows 8 quarter + 4 h .. + 3 of its own column.
+  // 16 columns; the read gives it rows 8 quarter + 4 h .. + 3 of its own column.  16-column blocks: bits 5..8 of the offset.
   const int tr_row = 8 * quarter + (col >> 2);
   const int tr_off = tr_row * 512 + (row_swizzle(tr_row) << 5) + (col & 3) * 8;
-  const int a_off = tr_off ^ (wa << 8);            // 16-column blocks 8 wa + i: bits 5..8 of the offset
-  const int bt_off = kSliceBytes + (tr_off ^ (wb << 7));      // 16-column blocks 4 wb + j
-  const int bk_off[2] = {kSliceBytes + wb * 64 * 128 + col * 128 + ((quarter ^ ((col >> 1) & 7)) << 4),
-                         kSliceBytes + wb * 64 * 128 + col * 128 + (((4 + quarter) ^ ((col >> 1) & 7)) << 4)};
-  bf16x4 a[4][2], b[2][kNJ][2];
-  auto read_tr = [&](int offset) { return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4)(lds + offset)); };
-  auto read_a = [&](int buf, int gr) {             // fragment of group gr (0..15): block gr & 7, half gr >> 3
-    const int at_block = buf * kBufferBytes + (a_off ^ ((gr & 7) << 5)) + (gr >> 3) * 32 * 512;
-    a[gr & 3][0] = read_tr(at_block);
-    a[gr & 3][1] = read_tr(at_block + 4 * 512);
+  const int a_off = tr_off ^ (wa << 8);
+  const int bt_off = 2 * kSliceBytes + (tr_off ^ (wb << 8));
+  const int bk_row = 2 * kSliceBytes + wb * 128 * 128 + col * 128;
+  const int bk_off[2] = {bk_row + ((quarter ^ ((col >> 1) & 7)) << 4), bk_row + (((4 + quarter) ^ ((col >> 1) & 7)) << 4)};
+  bf16x8 a[2][kNI], b[2][kNJ];
+  auto read_tr = [&](int offset) {
+    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4)(lds + offset));
+    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4)(lds + offset + 4 * 512));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   };
-  auto read_b = [&](int buf, int kk, int j) {
-    if (KC) {
-      const bf16x8 v = *reinterpret_cast<const bf16x8*>(lds + buf * kBufferBytes + bk_off[kk] + j * 2048);
-      b[kk][j][0] = __builtin_shufflevector(v, v, 0, 1, 2, 3);
-      b[kk][j][1] = __builtin_shufflevector(v, v, 4, 5, 6, 7);
+  // the fragments of half step kk in the order in which its products need them: A's first, B's, the others of A
+  auto read_part = [&](int buf, int kk, int p) {
+    if (p == 0 || p > kNJ) {
+      const int i = p == 0 ? 0 : p - kNJ;
+      a[kk][i] = read_tr(buf + (a_off ^ (i << 5)) + kk * 32 * 512);
     } else {
-      const int at_block = buf * kBufferBytes + (bt_off ^ (j << 5)) + kk * 32 * 512;
-      b[kk][j][0] = read_tr(at_block);
-      b[kk][j][1] = read_tr(at_block + 4 * 512);
+      const int j = p - 1;
+      if (KC) b[kk][j] = *reinterpret_cast<const bf16x8*>(lds + buf + bk_off[kk] + j * 2048);
+      else b[kk][j] = read_tr(buf + (bt_off ^ (j << 5)) + kk * 32 * 512);
     }
   };
-  auto whole = [](const bf16x4 (&v)[2]) -> bf16x8 { return __builtin_shufflevector(v[0], v[1], 0, 1, 2, 3, 4, 5, 6, 7); };
 
   f32x4 acc[kNI][kNJ];
-#pragma unroll
-  for (int i = 0; i < kNI; ++i)
-#pragma unroll
-    for (int j = 0; j < kNJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
+  {
+    const Clear clear;
+    unrolled<kNI * kNJ>([&](auto k) __attribute__((always_inline)) { clear.first(acc[k.value / kNJ][k.value % kNJ]); });
+  }
   if (n_steps > 0) {                               // uniform
+    int now = 0, next = kSliceBytes;
+    end_rows();
+    unrolled<16>([&](auto p) __attribute__((always_inline)) { copy_part(now, p); });
+    unrolled<16>([&](auto p) __attribute__((always_inline)) { copy_part(next, p); });
+    // copies complete in order: all but the last sixteen are step 0's
+    asm volatile("s_waitcnt vmcnt(16)\n\ts_barrier" ::: "memory");
 #pragma unroll
-    for (int p = 0; p < 8; ++p) copy_part(0, p);
-#pragma unroll
-    for (int p = 0; p < 3; ++p) copy_part(1, p);
-    // copies complete in order: all but the last three are step 0's
-    asm volatile("s_waitcnt vmcnt(3)\n\ts_barrier" ::: "memory");
-#pragma unroll
-    for (int j = 0; j < kNJ; ++j) read_b(0, 0, j);
-#pragma unroll
-    for (int gr = 0; gr < 3; ++gr) read_a(0, gr);
-  }
+    for (int p = 0; p < kNI + kNJ; ++p) read_part(now, 0, p);
 #define AIS_PIN __builtin_amdgcn_sched_barrier(0)
-  for (int s = 0; s < n_steps; ++s) {
-    const int buf = s & 1;
-#pragma unroll
-    for (int gr = 0; gr < 16; ++gr) {
-      const int kk = gr >> 3, i = gr & 7;
-#pragma unroll
-      for (int j = 0; j < kNJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(whole(a[gr & 3]), whole(b[kk][j]), acc[i][j], 0, 0, 0);
+    // (see the tile kernel in lm_head.hip for why the reads, the barrier and the copies are where they are)
+    // A fragment of two transposing reads and their address is what fits beside one product, and so is a copy: reads after
+    // every third product, copies after every third from the barrier on, never both after the same one.
+    constexpr int kHalf = kNI * kNJ, kBarrierAt = 54, kCopiesFrom = 56;
+    for (int s = 0; s < n_steps; ++s) {
       AIS_PIN;
-      // (see the tile kernel in lm_head.hip for why the reads and copies are where they are)
-      if (gr <= 10) read_a(buf, gr + 3);
-      if (gr == 11) {
-        read_a(buf, 14);
-        read_a(buf, 15);
-      }
-      if (gr >= 2 && gr < 6) read_b(buf, 1, gr - 2);
-      if (gr < 5) copy_part(buf ^ 1, gr + 3);
-      AIS_PIN;
-      if (gr == 12) {
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      unrolled<2 * kHalf>([&](auto product) __attribute__((always_inline)) {
+        constexpr int m = decltype(product)::value, kk = m / kHalf, at = m % kHalf, i = at / kNJ, j = at % kNJ;
+        multiply(acc[i][j], a[kk][i], b[kk][j]);
         AIS_PIN;
-        read_a(buf ^ 1, 0);
-        read_b(buf ^ 1, 0, 0);
-        read_b(buf ^ 1, 0, 1);
-      }
-      if (gr == 13) {
-        read_b(buf ^ 1, 0, 2);
-        read_b(buf ^ 1, 0, 3);
-        read_a(buf ^ 1, 1);
-      }
-      if (gr == 14) read_a(buf ^ 1, 2);
-      if (gr >= 13) copy_part(buf, gr - 13);
-      AIS_PIN;
+        if constexpr (at % 3 == 0 && at / 3 < kNI + kNJ) read_part(kk == 0 ? now : next, kk ^ 1, at / 3);
+        if constexpr (m == kBarrierAt) {
+          asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+          AIS_PIN;
+        }
+        if constexpr (m >= kCopiesFrom && (m - kCopiesFrom) % 3 == 0 && (m - kCopiesFrom) / 3 < 16)
+          copy_part(now, std::integral_constant<int, (m - kCopiesFrom) / 3>{});
+        AIS_PIN;
+      });
+      const int n = now;
+      now = next;
+      next = n;
     }
-  }
 #undef AIS_PIN
-  // copies re-fetched after the last step are still on their way into LDS
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // copies re-fetched after the last step are still on their way into LDS
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
+  settle();
 
   // ---- outputs: element v of product (i, j) is C[b = 16 j + col][a = 16 i + 4 quarter + v]
-#pragma unroll
-  for (int j = 0; j < kNJ; ++j) {
-    const int bi = b0 + wb * 64 + 16 * j + col;
-    if (bi >= g.n) continue;
-    float* row = g.out + (long long)bi * g.ld_out;
+  float* out = g.out + part * g.part_stride + a0 + wa * 128 + 4 * quarter;
+  const int a_left = g.m - (a0 + wa * 128 + 4 * quarter);       // outputs of the lane's row from here on
+  unrolled<kNJ>([&](auto column) __attribute__((always_inline)) {
+    constexpr int j = decltype(column)::value;
+    f32x4 c[kNI];
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < kNI; ++i) {
-      const int ai = a0 + wa * 128 + 16 * i + 4 * quarter;
-      if (ai >= g.m) continue;
-      f32x4* p = reinterpret_cast<f32x4*>(row + ai);
-      *p = g.accumulate ? *p + acc[i][j] : acc[i][j];
+      asm volatile("" : "+a"(acc[i][j]));
+      c[i] = acc[i][j];
+    }
+    const int bi = b0 + wb * 128 + 16 * j + col;
+    if (bi < g.n) {
+      float* row = out + (long long)bi * g.m;
+      if (g.aligned) {
+        f32x4 old[kNI];
+        if (g.accumulate) {
+#pragma unroll
+          for (int i = 0; i < kNI; ++i) old[i] = 16 * i < a_left ? *reinterpret_cast<const f32x4*>(row + 16 * i) : c[i];
+#pragma unroll
+          for (int i = 0; i < kNI; ++i) c[i] += old[i];
+        }
+#pragma unroll
+        for (int i = 0; i < kNI; ++i)
+          if (16 * i < a_left) *reinterpret_cast<f32x4*>(row + 16 * i) = c[i];
+      } else {
+#pragma unroll
+        for (int i = 0; i < kNI; ++i)
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            if (16 * i < a_left) row[16 * i + v] = g.accumulate ? row[16 * i + v] + c[i][v] : c[i][v];
+      }
+    }
+  });
+}
+
+// Every XCD takes a contiguous range of the work items of either product, four b tiles under each a tile: the 32 resident
+// workgroups of an XCD then share 8 slices of A and 4 of B through its L2.  The product with the longer items goes first.
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void lm_grad_products_kernel(
+    GemmArgs dweight, GemmArgs dhidden, int dhidden_first) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const int xcd = blockIdx.x & 7;
+  int local = blockIdx.x >> 3;
+  const int first = dhidden_first ? dhidden.per_xcd : dweight.per_xcd;
+  const bool hidden = (local < first) == (dhidden_first != 0);                 // uniform for the workgroup, as all of this
+  if (local >= first) local -= first;
+  const int per_xcd = hidden ? dhidden.per_xcd : dweight.per_xcd;
+  const int item = xcd * per_xcd + local;
+  const int items = hidden ? dhidden.a_tiles * dhidden.b_tiles * dhidden.parts
+                           : dweight.a_tiles * dweight.b_tiles * dweight.parts;
+  if (local >= per_xcd || item >= items) return;
+  if (hidden) gemm_item<true>(dhidden, item, lds);
+  else gemm_item<false>(dweight, item, lds);
+}
+
+// out[n, :] = sum over the parts of part[p][row, :], in order, row = n or pos[n] (zeros where that is negative).  One
+// workgroup per row.
+__global__ __launch_bounds__(256) void lm_add_parts_kernel(const float* __restrict__ part, long long part_stride,
+                                                              int parts, const int* __restrict__ pos, int d_model,
+                                                              float* __restrict__ out, int aligned) {
+  const int n = blockIdx.x;
+  const int row = pos != nullptr ? pos[n] : n;
+  const float* src = part + (long long)(row < 0 ? 0 : row) * d_model;
+  float* dst = out + (long long)n * d_model;
+  for (int c = threadIdx.x * 4; c < d_model; c += 1024) {
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    if (row >= 0) {
+      sum = *reinterpret_cast<const f32x4*>(src + c);
+#pragma unroll 4
+      for (int p = 1; p < parts; ++p) sum += *reinterpret_cast<const f32x4*>(src + p * part_stride + c);
+    }
+    if (aligned) {
+      *reinterpret_cast<f32x4*>(dst + c) = sum;
+    } else {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) dst[c + v] = sum[v];
     }
   }
 }
 
-template <bool KC>
-int launch_gemm(ais_ctx* ctx, GemmArgs g) {
-  static std::once_flag once[kMaxDevices];
-  static bool ok[kMaxDevices];
-  if (!allow_dynamic_lds(ctx, reinterpret_cast<const void*>(lm_grad_gemm_kernel<KC>), kLdsBytes, once, ok))
-    return hip_fail(ctx, hipErrorInvalidValue);
-  g.a_tiles = (g.m + kTile - 1) / kTile;
-  g.b_tiles = (g.n + kTile - 1) / kTile;
-  g.per_xcd = (g.a_tiles * g.b_tiles + 7) / 8;
-  lm_grad_gemm_kernel<KC><<<8 * g.per_xcd, kThreads, kLdsBytes, ctx->stream>>>(g);
-  return hip_fail(ctx, hipGetLastError());
+// Time of a launch whose `n0` items of length l0 come before `n1` of length l1 <= l0, in units of a step: whoever is done
+// first takes the next item.
+long long launch_time(int n_cus, long long n0, long long l0, long long n1, long long l1) {
+  const long long full = n0 / n_cus, rest = n0 % n_cus;          // `rest` compute units have one more
+  long long t = full * l0 + (rest != 0 ? l0 : 0);
+  if (n1 == 0) return t;
+  auto room = [&](long long until) {
+    const long long early = std::max<long long>(until - full * l0, 0), late = std::max<long long>(until - (full + 1) * l0, 0);
+    return (n_cus - rest) * (early / l1) + rest * (late / l1);
+  };
+  long long lo = t, hi = t + (n1 / n_cus + 2) * l1;              // smallest time that has room for the n1
+  while (lo < hi) {
+    const long long mid = (lo + hi) / 2;
+    if (room(mid) >= n1) hi = mid;
+    else lo = mid + 1;
+  }
+  return lo;
 }
+
+// Length of an item in steps: its sum, and what its start and its outputs take besides.
+constexpr int kItemSteps = 8;
 
 }  // namespace
 
-// Whether the 256 x 256 tiles of an [n, m] product keep enough of the compute units busy over all rounds to beat the
-// library's product, which has smaller tiles and can split the sum.  With full rounds dweight takes 0.78-0.82 of the
-// library's time and dhidden 0.93-0.96, so that is about how full the rounds have to be: dhidden of 14,000 rows x 1,024
-// (86 % full) takes 216 against 194 us, of 6,000 rows x 2,048 (75 %) 175 against 165, of 2,600 rows x 5,120 (86 %) the
-// same; dweight of 8,192 entries x 5,120 (83 %) 210 against 262, of 8,192 x 1,024 (50 %) 314 against 233.  Between those
-// the line of dweight matters little: the whole call over 4,096 rows x 4,096 takes 276 us with its own product at 69 % full
-// and 283 with the library's, at 75 % 287 and 291, at 81 % 301 and 326 (dhidden with it), over 8,192 rows at 62 % 507 and
-// 503.
+// Parts of either sum: those that make the launch of both products shortest, and fewer arrays to add up unless it is so by
+// 2 %.  dweight's is a sum over all rows: few tiles, each of them long, where d_model or the vocabulary is small.
+LmParts lm_grad_parts(int n_cus, long long n_rows, long long d, long long n_v) {
+  const long long a_tiles = (d + kTile - 1) / kTile;
+  const long long h_tiles = a_tiles * ((n_rows + kTile - 1) / kTile), w_tiles = a_tiles * ((n_v + kTile - 1) / kTile);
+  const long long h_steps = (n_v + kStep - 1) / kStep, w_steps = (n_rows + kStep - 1) / kStep;
+  const bool split_w = 2 * w_tiles < n_cus && n_v <= kLmGradChunk;
+  LmParts best{1, 1};
+  long long best_time = -1;
+  for (int w = 1; w <= (split_w ? kLmMaxWeightParts : 1) && w <= w_steps; ++w) {
+    if (w > 1 && w * n_v * d * 4 > kLmPartsBytes) break;
+    const long long w_len = (w_steps + w - 1) / w + kItemSteps + (w > 1 ? 4 : 0);
+    for (int h = 1; h <= kLmMaxParts && h <= h_steps; ++h) {
+      if (h > 1 && h * n_rows * d * 4 > kLmPartsBytes) break;
+      const long long h_len = (h_steps + h - 1) / h + kItemSteps + (h > 1 ? 2 : 0);
+      const long long time = h_len >= w_len ? launch_time(n_cus, h_tiles * h, h_len, w_tiles * w, w_len)
+                                            : launch_time(n_cus, w_tiles * w, w_len, h_tiles * h, h_len);
+      if (best_time < 0 || 50 * time < 49 * best_time) {
+        best = LmParts{w, h};
+        best_time = time;
+      }
+    }
+  }
+  return best;
+}
+
+// Bytes of the parts' arrays: dhidden's as many as any smaller number of rows may take, too, dweight's the same for all, so
+// that a call never needs more than one over more rows before it.
+size_t lm_dhidden_parts_bytes(long long n_rows, long long d) {
+  return (size_t)std::min<long long>(kLmPartsBytes, kLmMaxParts * n_rows * d * 4);
+}
+size_t lm_dweight_parts_bytes(long long vocab, long long d, int n_cus) {
+  const long long n_v = std::min(vocab, kLmGradChunk);
+  if (2 * ((d + kTile - 1) / kTile) * ((n_v + kTile - 1) / kTile) >= n_cus) return 0;
+  return (size_t)std::min<long long>(kLmPartsBytes, kLmMaxWeightParts * n_v * d * 4);
+}
+
+// Whether the 256 x 256 tiles of an [n, m] product keep `percent` of the compute units busy over all rounds.
 static bool rounds_full(int n_cus, long long m, long long n, int percent) {
   const long long tiles = ((m + kTile - 1) / kTile) * ((n + kTile - 1) / kTile);
   const long long rounds = (tiles + n_cus - 1) / n_cus;
   return tiles > 0 && tiles <= (1 << 28) && 100 * tiles >= percent * rounds * n_cus;
 }
-bool lm_dweight_fits(const ais_ctx* ctx, long long d, long long n_v) { return rounds_full(ctx->n_cus, d, n_v, 80); }
-bool lm_dhidden_fits(const ais_ctx* ctx, long long d, long long n_rows) { return rounds_full(ctx->n_cus, d, n_rows, 95); }
 
-// The library's chunk of 8,192 vocabulary entries (32 tiles), narrowed to the widest of 22 to 31 tiles that fills dweight's
-// rounds where 32 leave them too empty for the own product: d_model 2,304 (28 tiles), 2,560 (25), 2,816 (23), 4,352 (30),
-// 4,608 (28), 4,864 (26), 6,400 (30).  Whole call against chunks of 8,192, in this order, over 3,300 to 12,000 rows and
-// vocabularies of 24,600 to 151,936: 0.79-0.91, 0.82-0.99, 0.79-0.96, 0.83-0.91, 0.96-1.00, 0.92-0.94, 0.91-0.98 (6,144 rows x
-// 50,257 x 2,304: 4,525 -> 3,590 us).  Fewer tiles (21, d_model 3,072: 0.96-1.07) shorten the recomputation's work items too
-// far; vocabularies of two or three chunks are left with too small a last one (0.85-1.02).  Never wider: the chunk fits the
-// workspace of 8,192 entries.
+// Chunks of 8,192 vocabulary entries (32 tiles; lm_grad_even_chunk keeps them beyond 65,536 rows, and where there is no room for
+// wider ones), narrowed to the widest of 22 to 31 tiles that fills dweight's rounds where 32 do not: d_model 2,304 (28 tiles),
+// 2,560 (25), 2,816 (23), 4,352 (30), 4,608 (28), 4,864 (26), 6,400 (30).  With both products in one launch the two are within
+// a per cent of each other (70,000 rows x 30,000 x 2,560 26.8 ms and 27.0 with 8,192, x 40,000 x 2,304 32.3 and 32.0).  Never
+// wider: the chunk fits the workspace of 8,192 entries.
 long long lm_grad_chunk_for(long long chunk, long long vocab, long long d_model, int n_cus) {
   if (chunk != kLmGradChunk || vocab < 3 * chunk || rounds_full(n_cus, d_model, chunk, 80)) return chunk;
   for (long long width = chunk - kTile; width >= 22 * kTile; width -= kTile)
@@ -278,21 +381,40 @@ long long lm_grad_chunk_for(long long chunk, long long vocab, long long d_model,
   return chunk;
 }
 
-// dweight[n_v, d] = ds^T h over the first k rows (min(k, *k_dev) if k_dev is given); ds rows of pitch ds_stride.
-// Row pitches and bases are 16-byte aligned, d a multiple of 32, ds defined up to a multiple of 256 columns.
-int launch_lm_dweight(ais_ctx* ctx, const void* ds, long long ds_stride, const void* h, long long ld_h, int k,
-                      const int* k_dev, int n_v, int d, float* dweight) {
-  GemmArgs g{static_cast<const bf16_t*>(h), ld_h, static_cast<const bf16_t*>(ds), ds_stride, dweight, d, d, n_v, k, k_dev,
-             0, 0, 0, 0};
-  return launch_gemm<false>(ctx, g);
+// dweight[n_v, d] = ds^T h over the first k rows (min(k, *k_dev) if k_dev is given), and dhidden[n_rows, d] (+)= ds w over the
+// n_v entries of the chunk (ds is zero from there to the next multiple of 256 columns); where there are several parts of a
+// sum, the part p of it, that many elements of the stride further.  ds rows of pitch ds_stride; pitches of ds, h, w and
+// their bases are 16-byte aligned, d a multiple of 32, the outputs' rows contiguous.
+int launch_lm_grad_products(ais_ctx* ctx, const void* ds, long long ds_stride, const void* h, long long ld_h, const void* w,
+                            long long ld_w, int n_rows, const int* n_rows_dev, int n_v, int d, float* dweight,
+                            float* dhidden, LmParts parts, long long w_stride, long long h_stride, bool accumulate) {
+  static std::once_flag once[kMaxDevices];
+  static bool ok[kMaxDevices];
+  if (!allow_dynamic_lds(ctx, reinterpret_cast<const void*>(lm_grad_products_kernel), kLdsBytes, once, ok))
+    return hip_fail(ctx, hipErrorInvalidValue);
+  const bf16_t* p = static_cast<const bf16_t*>(ds);
+  const int a_tiles = (d + kTile - 1) / kTile;
+  GemmArgs gw{static_cast<const bf16_t*>(h), ld_h, p, ds_stride, dweight, w_stride, d, n_v, n_rows, n_rows_dev, 0, 0,
+              a_tiles, (n_v + kTile - 1) / kTile, parts.w, 0, 0};
+  GemmArgs gh{static_cast<const bf16_t*>(w), ld_w, p, ds_stride, dhidden, h_stride, d, n_rows, n_v, nullptr,
+              accumulate ? 1 : 0, 0, a_tiles, (n_rows + kTile - 1) / kTile, parts.h, 0, 0};
+  for (GemmArgs* g : {&gw, &gh}) {
+    g->aligned = reinterpret_cast<uintptr_t>(g->out) % 16 == 0;
+    g->part_k = ((g->k + g->parts - 1) / g->parts + kStep - 1) / kStep * kStep;
+    g->per_xcd = (int)(((long long)g->a_tiles * g->b_tiles * g->parts + 7) / 8);
+  }
+  const long long grid = 8LL * (gw.per_xcd + (long long)gh.per_xcd);
+  if (grid > 0x7fffffff) return AIS_ERR_SIZE;
+  lm_grad_products_kernel<<<(unsigned)grid, kThreads, kLdsBytes, ctx->stream>>>(gw, gh, gh.part_k >= gw.part_k ? 1 : 0);
+  return hip_fail(ctx, hipGetLastError());
 }
 
-// dhidden[n_rows, d] (+)= ds w over n_v vocabulary entries (ds is zero from there to the next multiple of 64 columns).
-int launch_lm_dhidden(ais_ctx* ctx, const void* ds, long long ds_stride, const void* w, long long ld_w, int n_v,
-                      int n_rows, int d, bool accumulate, float* dhidden) {
-  GemmArgs g{static_cast<const bf16_t*>(w), ld_w, static_cast<const bf16_t*>(ds), ds_stride, dhidden, d, d, n_rows, n_v,
-             nullptr, accumulate ? 1 : 0, 0, 0, 0};
-  return launch_gemm<true>(ctx, g);
+// The sums of the parts, their rows in the order of the list where there is one.
+int launch_lm_add_parts(ais_ctx* ctx, const float* part, long long part_stride, int parts, const int* row_pos,
+                           long long n_rows, int d, float* out) {
+  lm_add_parts_kernel<<<(unsigned)n_rows, 256, 0, ctx->stream>>>(part, part_stride, parts, row_pos, d, out,
+                                                                    reinterpret_cast<uintptr_t>(out) % 16 == 0 ? 1 : 0);
+  return hip_fail(ctx, hipGetLastError());
 }
 
 }  // namespace ais

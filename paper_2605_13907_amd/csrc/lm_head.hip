@@ -31,18 +31,15 @@
 // 261 -> 231.
 #include "ais_internal.h"
 #include "device_utils.h"
+#include "lm_tile.h"
 
 #include <algorithm>
-#include <type_traits>
-#include <utility>
 
 namespace ais {
 namespace {
 
 using namespace dev;
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+using namespace tile;
 
 constexpr int kLmThreads = 256;
 constexpr int kLmTileV = 256;      // vocabulary entries per tile
@@ -193,42 +190,6 @@ typedef f32x4 LmAcc[kLmNI][kLmNJ];
 // tiles are 32 entries, eight consecutive ones to a lane.
 __device__ __forceinline__ int lm_entry(int i, int quarter) { return 32 * (i >> 1) + 8 * quarter + 4 * (i & 1); }
 
-// The products are written as instructions because the accumulators take all of the accumulation registers: the compiler's own
-// form of a product may have its result elsewhere than its addend, and without a register to spare it moved fragments and
-// accumulators about in the loop.  It does not know what such a statement is, so what it would wait for is waited for here:
-//   fragments come straight from LDS reads, whose arrival it does wait for (an operand that an ordinary instruction has just
-//   written would need two wait states; there is none in the loop);
-//   lm_settle() stands between the last product and the first look at an accumulator.
-__device__ __forceinline__ void lm_product(f32x4& c, bf16x8 a, bf16x8 b) {
-  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
-}
-__device__ __forceinline__ void lm_settle() { asm volatile("s_nop 15\n\ts_nop 3"); }
-// c = 0, by the matrix pipe, which has nothing else to do between two tiles: beside the soft-max arithmetic of the finished
-// one.  Where the accumulators have not held anything before, `first` makes them do so.
-struct LmClear {
-  u32x4 zero;
-  __device__ __forceinline__ LmClear() {
-    zero = u32x4{0u, 0u, 0u, 0u};
-    asm volatile("s_nop 3" : "+v"(zero));
-  }
-  __device__ __forceinline__ void operator()(f32x4& c) const {
-    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %1, 0" : "+a"(c) : "v"(zero));
-  }
-  __device__ __forceinline__ void first(f32x4& c) const {
-    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %1, 0" : "=a"(c) : "v"(zero));
-  }
-};
-
-// f(0), f(1), ... f(N - 1) with the index a constant in each.
-template <typename F, int... I>
-__device__ __forceinline__ void unrolled_over(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void unrolled(F&& f) {
-  unrolled_over(f, std::make_integer_sequence<int, N>{});
-}
-
 // Copies the accumulators of MFMA tiles I .. I + N - 1 of column J out, to z[0 ..] if I = 0 and N = 2, to their places in a
 // column otherwise, before whatever follows.
 template <int J, int I, int N>
@@ -268,7 +229,7 @@ struct LmSoftmax {
   // entry  vbase + lm_entry(i, quarter) + v.  Leaves the column at zero.
   template <int J>
   __device__ __forceinline__ void fold(LmAcc& acc, const LmItem& it, int vt, int vocab, float scale,
-                                       float* __restrict__ zy_out, const LmClear& clear) {
+                                       float* __restrict__ zy_out, const Clear& clear) {
     const int vbase = vt * kLmTileV + it.wv * kLmWaveV;
     float z[4 * kLmNI];
     lm_take<J, 0, kLmNI>(acc, z);
@@ -391,7 +352,7 @@ struct LmGrad {
   // Leaves the column at zero.
   template <int J>
   __device__ __forceinline__ void emit(LmAcc& acc, const LmItem& it, int vt, int vocab, float scale, const LmGradArgs& ga,
-                                       const LmClear& clear) {
+                                       const Clear& clear) {
     const int vbase = vt * kLmTileV + it.wv * kLmWaveV;
     bf16_t* out = ga.ds + (long long)row[J] * ga.ds_stride;
     unrolled<kLmNI / 2>([&](auto pair) __attribute__((always_inline)) {
@@ -595,7 +556,7 @@ __global__ __launch_bounds__(kLmThreads) __attribute__((amdgpu_waves_per_eu(1, 1
         AIS_PIN;
         unrolled<kHalf>([&](auto product) __attribute__((always_inline)) {
           constexpr int in = decltype(product)::value, m = kk * kHalf + in, i = in / NJ, j = in % NJ;
-          lm_product(acc[i][j], a[kk][i], b[kk][j]);
+          multiply(acc[i][j], a[kk][i], b[kk][j]);
           AIS_PIN;
           constexpr int r0 = (in * kReads + kReadSpan - 1) / kReadSpan, r1 = ((in + 1) * kReads + kReadSpan - 1) / kReadSpan;
 #pragma unroll
@@ -614,7 +575,7 @@ __global__ __launch_bounds__(kLmThreads) __attribute__((amdgpu_waves_per_eu(1, 1
         });
       };
       {
-        const LmClear clear;
+        const Clear clear;
         unrolled<kHalf>([&](auto k) __attribute__((always_inline)) { clear.first(acc[k.value / NJ][k.value % NJ]); });
       }
       for (int vt = it.vt0; vt < it.vt1; ++vt) {
@@ -623,8 +584,8 @@ __global__ __launch_bounds__(kLmThreads) __attribute__((amdgpu_waves_per_eu(1, 1
           half_step(std::integral_constant<int, 1>{});
           turn();
         }
-        lm_settle();
-        const LmClear clear;
+        settle();
+        const Clear clear;
         unrolled<NJ>([&](auto column) __attribute__((always_inline)) {
           constexpr int j = decltype(column)::value;
           if constexpr (GRAD) gr.template emit<j>(acc, it, vt, vocab, scale, ga, clear);
@@ -801,26 +762,6 @@ __global__ __launch_bounds__(256) void lm_gather_rows_kernel(const bf16_t* __res
   for (int c = threadIdx.x; c < d_model / 8; c += 256) dst[c] = live ? src[c] : zero;
 }
 
-// Rows [n_eval, n_cap) of a chunk of dlogits are nobody's: zeros, so that the two GEMMs can run over n_cap rows.
-__global__ __launch_bounds__(256) void lm_zero_tail_rows_kernel(bf16_t* __restrict__ ds, long long ds_stride,
-                                                                int width, const LmDevPlan* __restrict__ plan) {
-  const int p = plan->n_eval + blockIdx.x;                      // the grid covers n_cap rows; only the tail works
-  if (p >= (int)gridDim.x) return;
-  bf16_t* row = ds + (long long)p * ds_stride;
-  for (int v = threadIdx.x; v < width; v += 256) row[v] = 0;
-}
-
-// dhidden[n, :] = gathered[pos[n], :] for the listed rows, zeros for the others.  One workgroup per row.
-__global__ __launch_bounds__(256) void lm_scatter_rows_kernel(const float* __restrict__ gathered,
-                                                              const int* __restrict__ pos, int d_model,
-                                                              float* __restrict__ out) {
-  const int n = blockIdx.x;
-  const int p = pos[n];
-  const float4* src = reinterpret_cast<const float4*>(gathered + (long long)(p < 0 ? 0 : p) * d_model);
-  float4* dst = reinterpret_cast<float4*>(out + (long long)n * d_model);
-  for (int c = threadIdx.x; c < d_model / 4; c += 256) dst[c] = p < 0 ? make_float4(0.f, 0.f, 0.f, 0.f) : src[c];
-}
-
 }  // namespace
 
 // Worst case of the decomposition (every row evaluated): sizes the grid and the workspace.
@@ -886,6 +827,29 @@ size_t lm_grad_dlogits_bytes(long long m_rows, long long vocab, long long asked,
   const long long whole = (vocab + kLmTileV - 1) / kLmTileV * kLmTileV;
   const long long tiles = std::max<long long>(2 * n_cus, kLmGradFewBlocks * (kLmGradChunk / kLmTileV));
   return std::max(own, 2 * (size_t)std::min(kLmTileT * kLmTileV * tiles, kLmGradFewBlocks * kLmTileT * whole));
+}
+
+// The width that the call takes where the choice is the library's: chunks alike, as few as kLmWideBytes of dlogits allow, of
+// a multiple of 16 or 8 tiles (so that the token blocks' items of whole tiles fill the rounds), or `chunk`, the narrower choice
+// above, where it is no narrower.  Wide chunks are longer sums and fewer of them: dhidden is read and written once per chunk.
+// Whole call, 8,192 entries and this: 3,300 rows x 100,000 x 2,560 4,935 and 4,264 us, 4,000 x 128,256 x 2,304 6,402 and
+// 5,716, 5,128 x 40,360 x 1,152 1,485 and 1,339, 6,000 x 151,936 x 1,024 5,373 and 4,950, 33,000 x 50,257 x 2,560 22.8 and 21.4
+// ms, 16,576 x 20,800 x 1,920 3,666 and 3,440 us; at d_model 4,096 within a per cent; 20,000 x 32,000 x 1,024 3,559 and 3,662.
+constexpr long long kLmWideBytes = 1LL << 30, kLmWideChunk = 65536;
+long long lm_grad_even_chunk(long long chunk, long long m_rows, long long vocab) {
+  const long long tiles = (vocab + kLmTileV - 1) / kLmTileV;
+  const long long wide = std::min(kLmWideChunk, kLmWideBytes / (2 * std::max<long long>(m_rows, 1)));
+  if (wide <= chunk) return chunk;
+  const long long most = wide / kLmTileV, n = (tiles + most - 1) / most, even = (tiles + n - 1) / n;
+  for (long long of : {16, 8}) {
+    const long long up = (even + of - 1) / of * of;
+    if (up <= most && up < tiles) return up * kLmTileV;
+  }
+  return even * kLmTileV;
+}
+size_t lm_grad_wide_bytes(long long m_rows, long long vocab) {
+  const long long whole = (vocab + kLmTileV - 1) / kLmTileV * kLmTileV;
+  return (size_t)std::min(kLmWideBytes, 2 * m_rows * std::min(whole, kLmWideChunk));
 }
 
 template <bool GRAD, bool DEEP>
@@ -975,12 +939,12 @@ int launch_lm_head_grad_setup(ais_ctx* ctx, const unsigned char* live_mask, long
 // first vocabulary entry, `which` the plan for its width.  Every row is processed (rows whose coefficient is 0 come out
 // as zeros).
 // With a list (row_index != nullptr: the rows with a gradient, at most n_cap of them) row p of ds belongs to the p-th
-// listed row; with `zero_tail` the rows from the end of the list up to n_cap - 1 become zeros.
+// listed row; rows past the end of the list are left as they are.
 int launch_lm_head_dlogits_chunk(ais_ctx* ctx, const void* hidden, long long ld_h, const void* weight,
                                  long long ld_w, long long n_rows, int d_model, int vocab, int y_off,
                                  const int* token_ids, const float* lse, const float* logp, const float* coeff,
                                  float inv_temperature, const void* dev_plan, int which, void* ds, long long ds_stride,
-                                 const int* row_index, int n_cap, bool zero_tail) {
+                                 const int* row_index, int n_cap) {
   const LmHeadPlan plan = lm_head_plan(row_index != nullptr ? n_cap : n_rows, vocab, ctx->n_cus);
   const int max_items = row_index != nullptr ? plan.max_items_masked : plan.max_items;
   const LmDevPlan* dplan = static_cast<const LmDevPlan*>(dev_plan) + which;
@@ -988,14 +952,9 @@ int launch_lm_head_dlogits_chunk(ais_ctx* ctx, const void* hidden, long long ld_
                                 lm_decomposition((int)n_rows, plan.chunks, plan.n_vtiles, ctx->n_cus, max_items)};
   LmRows rows{row_index};
   LmGradArgs ga{lse, logp, coeff, static_cast<bf16_t*>(ds), ds_stride, y_off, row_index != nullptr ? 1 : 0};
-  const int rc = launch_lm_tile<true, true>(ctx, max_items, hidden, ld_h, weight, ld_w, rows, decomposition, d_model, vocab,
+  return launch_lm_tile<true, true>(ctx, max_items, hidden, ld_h, weight, ld_w, rows, decomposition, d_model, vocab,
                                         token_ids, inv_temperature * kLog2e, plan.n_vtiles, nullptr, nullptr, nullptr,
                                         ga);
-  if (rc != AIS_OK) return rc;
-  if (row_index != nullptr && zero_tail && n_cap > 0)
-    lm_zero_tail_rows_kernel<<<(unsigned)n_cap, 256, 0, ctx->stream>>>(static_cast<bf16_t*>(ds), ds_stride, vocab,
-                                                                       dplan);
-  return hip_fail(ctx, hipGetLastError());
 }
 
 int launch_lm_live_mask(ais_ctx* ctx, const float* coeff, long long n_rows, unsigned char* mask) {
@@ -1009,12 +968,6 @@ int launch_lm_gather_rows(ais_ctx* ctx, const void* hidden, long long ld_h, int 
   lm_gather_rows_kernel<<<(unsigned)n_cap, 256, 0, ctx->stream>>>(
       static_cast<const bf16_t*>(hidden), ld_h, row_index, static_cast<const LmDevPlan*>(dev_plan), d_model,
       static_cast<bf16_t*>(gathered));
-  return hip_fail(ctx, hipGetLastError());
-}
-
-int launch_lm_scatter_rows(ais_ctx* ctx, const float* gathered, const int* row_pos, long long n_rows, int d_model,
-                           float* out) {
-  lm_scatter_rows_kernel<<<(unsigned)n_rows, 256, 0, ctx->stream>>>(gathered, row_pos, d_model, out);
   return hip_fail(ctx, hipGetLastError());
 }
 

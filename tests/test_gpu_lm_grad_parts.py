@@ -1,0 +1,85 @@
+"""The hidden-state gradient's products where their sums are split into parts: few rows (the hidden gradient), a narrow model or
+a small vocabulary (the embedding gradient), both, with a row list, over several chunks, and with outputs whose rows are not
+16-byte aligned.  Every element against float64 on the dlogits' own rounding."""
+import ctypes as C
+
+import pytest
+import torch
+
+from paper_2605_13907_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+class Parts(C.Structure):
+    _fields_ = [("w", C.c_int), ("h", C.c_int)]
+
+
+# rows, d, vocab, rows with a gradient (None: all), chunk (0: the library's choice), sums that are split
+CASES = [
+    (300, 4096, 20_000, None, 0, "h"),           # two blocks of rows, one chunk
+    (65, 96, 3000, None, 1024, "h"),             # one tile, three chunks, the last one of 952 entries
+    (257, 64, 70_001, 130, 0, "h"),              # two chunks, a row list
+    (6001, 512, 2048, None, 0, "wh"),            # a long sum over rows, a last step of 49
+    (5000, 64, 700, None, 256, "w"),             # three chunks, the last one narrower
+    (9000, 128, 1500, 4097, 0, "wh"),            # a row list shorter than its bound would be
+    (64, 32, 64, None, 0, ""),                   # one step each
+]
+
+
+def operands(rows, d, vocab, live, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    w = (torch.randn(vocab, d, generator=g, device="cuda") / d ** 0.5).bfloat16()
+    h = (torch.randn(rows, d, generator=g, device="cuda") * 2.0).bfloat16()
+    y = torch.randint(0, vocab, (rows,), generator=g, device="cuda").to(torch.int32)
+    c = torch.randn(rows, generator=g, device="cuda")
+    if live is not None:
+        c[torch.randperm(rows, generator=torch.Generator().manual_seed(seed))[live:].cuda()] = 0.0
+    return h, w, y, c
+
+
+def check(h, w, y, c, dh, dw):
+    z = h.double() @ w.double().t()
+    ds = torch.softmax(z, dim=1)
+    ds.scatter_add_(1, y.long().unsqueeze(1), torch.full((h.shape[0], 1), -1.0, dtype=torch.float64, device="cuda"))
+    ds *= c.double().unsqueeze(1)
+    # a dlogit is rounded to bf16 once: up to 2^-8 of itself (eight significant bits), and the product's error is at most
+    # that of all its terms; the fp32 lse and exponential and the fp32 sums add about 1e-5 of the same
+    for got, a, b in ((dh, ds, w.double()), (dw, ds.t(), h.double())):
+        a, b = a.contiguous(), b.contiguous()
+        tol = (2.0 ** -8 + 1e-4) * (a.abs() @ b.abs()) + 1e-9
+        err = (got.double() - a @ b).abs()
+        assert bool((err <= tol).all()), float((err / tol).max())
+
+
+@pytest.mark.parametrize("k", range(len(CASES)))
+def test_parts(k):
+    rows, d, vocab, live, chunk, split = CASES[k]
+    print("rows", rows, "d", d, "vocab", vocab, "live", live, "chunk", chunk, flush=True)
+    ctx = B.AisContext()
+    choose = B._lib()["_ZN3ais13lm_grad_partsEixxx"]              # lm_grad_parts(compute units, rows, d_model, chunk)
+    choose.argtypes, choose.restype = [C.c_int] + [C.c_longlong] * 3, Parts
+    parts = choose(torch.cuda.get_device_properties(0).multi_processor_count, rows if live is None else live, d,
+                   min(vocab, chunk or 65_536))
+    assert (parts.w > 1, parts.h > 1) == ("w" in split, "h" in split), (parts.w, parts.h)
+    h, w, y, c = operands(rows, d, vocab, live, 31 + k)
+    logp, lse = ctx.lm_head_logprob(h, w, y)
+    bound = -1 if live is None else live
+    dh, dw = ctx.lm_head_grad(h, w, y, lse, logp, c, chunk_vocab=chunk, n_live_max=bound)
+    check(h, w, y, c, dh, dw)
+    if live is not None:
+        assert bool((dh[c == 0] == 0).all())
+    again = ctx.lm_head_grad(h, w, y, lse, logp, c, chunk_vocab=chunk, n_live_max=bound)
+    assert torch.equal(dh, again[0]) and torch.equal(dw, again[1])
+    # outputs that begin four bytes after a 16-byte boundary: the same bits, and nothing beside them is touched
+    at = {n: torch.full((t.numel() + 8,), 7.0, device="cuda") for n, t in (("h", dh), ("w", dw))}
+    rc = B._lib().ais_lm_head_grad(ctx._h, h.data_ptr(), d, w.data_ptr(), d, B.AIS_BF16, rows, d, vocab, y.data_ptr(),
+                                   lse.data_ptr(), logp.data_ptr(), c.data_ptr(), 1.0, chunk, bound,
+                                   at["h"].data_ptr() + 4, at["w"].data_ptr() + 4)
+    torch.cuda.synchronize()
+    assert rc == 0
+    for n, t in (("h", dh), ("w", dw)):
+        assert torch.equal(at[n][1:-7].view_as(t), t) and bool((at[n][:1] == 7).all()) and bool((at[n][-7:] == 7).all())
+    assert ctx.status() == 0
+    ctx.close()

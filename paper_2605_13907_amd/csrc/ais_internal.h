@@ -60,9 +60,9 @@ enum DiagWord {
   kDiagWords
 };
 
-// How a batch of (n_rows, n_resp) is cut into tiles: 2^shift rows each, at most max_tiles of them.
+// How a batch of more than kSelfPlanResponses responses is cut into tiles of kPlanTileRows: at most max_tiles of them.
 struct TileRule {
-  int shift, max_tiles;
+  int max_tiles;
 };
 TileRule tile_rule(long long n_rows, int n_resp);
 

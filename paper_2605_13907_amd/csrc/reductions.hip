@@ -1,22 +1,23 @@
 // Per-row scalar work and the batch-wide reductions of the path.
 //
-// The batch is a set of variable-length segments (responses) of rows, some rows masked out.  Every response is cut into
-// tiles of 256 rows or a power of two times that (each workgroup works the tiling out for itself, for up to
-// kSelfPlanResponses responses; beyond that a small plan kernel does it once); level 1 reduces a tile per wavefront to a
-// partial, without a barrier; level 2, run by whichever workgroup of the same launch finishes last, folds the partials of
-// each response in order, forms the group-relative advantages (Eq. 3) and the batch moments, and evaluates the three
-// diagnostics and the mixing coefficient (Eq. 12-17).  Everything is accumulated in fp64 in a fixed order (no floating
-// point atomics), so results are bit-reproducible from run to run; spreads are carried as (count, mean, squared
-// deviations) triples, never as differences of power sums.
+// The batch is a set of variable-length segments (responses) of rows, some rows masked out.  Up to kSelfPlanResponses responses
+// the rows are dealt out evenly to at most one workgroup per compute unit, whatever responses they belong to: a row finds its
+// response by its number, and everything that depends on the response alone is in LDS.  Beyond that a small plan kernel cuts
+// every response into tiles of 1,024 rows and a wavefront takes a tile.  Level 1 reduces a workgroup's rows (or a tile) to a
+// partial; level 2, run by whichever workgroup of the same launch finishes last, merges the partials in order and evaluates the
+// three diagnostics and the mixing coefficient (Eq. 12-17).  Everything is accumulated in fp64 in a fixed order (no floating
+// point atomics), so results are bit-reproducible from run to run; spreads are carried as sums of differences from a value of
+// the set, or as (count, mean, squared deviations), never as differences of power sums.
 //
-// These kernels move a few bytes per row (about a megabyte per batch) and are bound by the length of their dependent
-// chains and, small as they are, by the instruction fetches of code that runs once.  Hence a tile per wavefront without
-// barriers, 16 wavefronts to a workgroup that share one look at cu_rows, level 2 by 1,024 threads in one pass, partials as
-// arrays of words (12,000 separate reads of 1,700 structures by one compute unit before), and code that is not unrolled.
-// Diagnostics and row coefficients, us, a 256-thread workgroup per tile of 1,024 rows before and now: 512 rows in 8
-// responses 12.9 and 7.1 -> 7.3 and 4.2; 8,192 in 16 12.8, 7.7 -> 9.6, 7.4; 41,643 in 16 13.3, 8.9 -> 11.1, 7.7; 200,000 in
-// 512 19.8, 13.8 -> 14.1, 9.7; 1,200,000 in 1,024 (with stale policy and KL term) 38.0, 29.5 -> 21.8, 17.1; 4,000,000 in 8
-// 50, 43 -> 33.5, 34.
+// These kernels move a few bytes per row (about a megabyte per batch) and are bound by the length of their dependent chains, by
+// the instruction fetches of code that runs once, and from some 500,000 rows on by fp64 instructions: 150 of them a row, 840
+// cycles for 64 rows before and 550 now.  Hence rows asked for before anything else, one copy of the code for all rows of a
+// thread, exponentials of 20 instructions (row_coeff.h) and two of them where there were three, sums over the workgroup through
+// LDS (see MergeRoom).  Diagnostics and row coefficients, us a call, tiles of responses dealt to wavefronts before and rows
+// dealt out evenly now: 512 rows in 8 responses 7.8 and 6.7 (the host's time) -> 6.7 and 6.7; 2,048 in 8 9.4 -> 7.6; 41,643 in
+// 16 10.9 and 6.9 -> 9.2 and 6.8; 108,495 in 104 12.8 and 7.7 -> 10.0 and 6.9; 731,967 in 164 20.2 and 10.9 -> 13.7 and 11.1;
+// 1,200,000 in 1,024 (with stale policy and KL term) 21.6 and 16.8 -> 16.1 and 16.8; 4,000,000 in 8 32.5 and 25.2 -> 26.0 and
+// 23.5.
 #include "ais_internal.h"
 #include "row_coeff.h"
 
@@ -29,6 +30,8 @@ namespace {
 
 using dev::CoeffRule;
 using dev::RowTerm;
+using dev::exp64;
+using dev::exp64_finite;
 using dev::response_weight;
 using dev::row_term;
 
@@ -105,46 +108,25 @@ __device__ __forceinline__ int find_response(const int* __restrict__ tile_off, i
   return lo;
 }
 
-// Sum over each row of 16 lanes.
-__device__ __forceinline__ int row_sum(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true);
-  return v + __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, true);
-}
-
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
 constexpr int kLaneRows = 4;                     // rows of a lane whose inputs are loaded together
 constexpr int kChunkRows = 64 * kLaneRows;       // rows of a wavefront that are
+constexpr int kAtOnce = 8;                       // the same, where rows are dealt out evenly
 
 // Rows [row0, row0 + len) of response `resp`, the work of one wavefront.
 struct Tile {
   int resp, row0, len;
 };
 
-// The tiling of the batch as a workgroup sees it: from the plan kernel's array in memory, or worked out by the workgroup
-// itself into LDS, a thread per response.  The latter costs one read of cu_rows (8 KiB at most) and a scan where the
-// former costs a launch and a chain of log2(n_resp) dependent reads in every wavefront.
-// Both are used the same way: init, then open() for every window of kWaves tiles, whose tiles the wavefronts take in turn.
-template <bool SELF>
-struct Tiling;
-
-template <>
-struct Tiling<false> {
+// The tiling of a batch of more than kSelfPlanResponses responses, from the plan kernel's array in memory.
+struct Tiling {
   const int* tile_off;
   const long long* cu_rows;
   int n_resp, n_rows;
-  __device__ __forceinline__ void init(const int* off, const long long* cu, int resp, long long rows, int, int, int*) {
-    tile_off = off;
-    cu_rows = cu;
-    n_resp = resp;
-    n_rows = (int)rows;
-  }
   __device__ __forceinline__ int tiles() const { return tile_off[n_resp]; }
   __device__ __forceinline__ int first(int i) const { return tile_off[i]; }
-  __device__ __forceinline__ void open(int) const {}
-  __device__ __forceinline__ Tile tile(int b, int) const {
+  __device__ __forceinline__ Tile tile(int b) const {
     const int i = find_response(tile_off, n_resp, b);
     long long lo, hi;
     response_rows(cu_rows, i, n_rows, lo, hi);
@@ -155,71 +137,83 @@ struct Tiling<false> {
   }
 };
 
-template <>
-struct Tiling<true> {
-  struct Shared {
-    int off[kSelfPlanResponses + 1];
-    int wave_tiles[kWaves];
-    Tile window[kWaves];
-  };
-  __device__ static Shared& shared() {
-    __shared__ Shared sh;
-    return sh;
-  }
-  static_assert(kSelfPlanResponses <= kThreads, "a thread per response");
-  int shift, n_tiles;
-  int lo, hi, tile0, tile1;          // of the thread's response: its rows and its tiles
-  // Must be called by all threads of the workgroup.  Workgroup 0 reports a cu_rows that is no partition of the rows.
-  __device__ __forceinline__ void init(const int*, const long long* __restrict__ cu, int n_resp, long long n_rows,
-                                       int tile_shift, int max_tiles, int* status) {
-    Shared& sh = shared();
-    shift = tile_shift;
-    const int i = threadIdx.x, lane = i & 63, wave = i >> 6;
-    bool bad = false;
-    lo = hi = 0;
+// The responses of a batch of up to kSelfPlanResponses, a thread each: their rows, forced into [0, n_rows], in LDS, so that a row
+// finds its own whatever way the rows are dealt out.
+struct Responses {
+  int lo[kSelfPlanResponses], hi[kSelfPlanResponses];
+  // Must be called by all threads of the workgroup, and a barrier before search().  Workgroup 0 reports a cu_rows that is no
+  // partition of the rows.
+  __device__ __forceinline__ void init(const long long* __restrict__ cu, int n_resp, long long n_rows, int* status) {
+    static_assert(kSelfPlanResponses <= kThreads, "a thread per response");
+    const int i = threadIdx.x;
+    int l = 0x7fffffff, h = 0;
     if (i < n_resp) {
       const long long c0 = cu[i], c1 = cu[i + 1];
-      const long long l = clampll(c0, 0, n_rows), h = clampll(c1, l, n_rows);
-      bad = c0 != l || c1 != h || (i == 0 && c0 != 0) || (i == n_resp - 1 && c1 != n_rows);
-      lo = (int)l;
-      hi = (int)h;
+      l = (int)clampll(c0, 0, n_rows);
+      h = (int)clampll(c1, l, n_rows);
+      const bool bad = c0 != l || c1 != h || (i == 0 && c0 != 0) || (i == n_resp - 1 && c1 != n_rows);
+      if (bad && blockIdx.x == 0) atomicOr(status, AIS_STATUS_BAD_CU);
     }
-    const int mine = (int)(((long long)(hi - lo) + (1 << shift) - 1) >> shift);
-    int incl = mine;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int o = __shfl_up(incl, off);
-      incl += lane >= off ? o : 0;
+    if (i < kSelfPlanResponses) {
+      lo[i] = l;
+      hi[i] = h;
     }
-    if (lane == 63) sh.wave_tiles[wave] = incl;
-    __syncthreads();
-    static_assert(kWaves == 16, "a row of lanes");
-    const int t = sh.wave_tiles[lane & 15];
-    const int before = incl - mine + row_sum((lane & 15) < wave ? t : 0), total = row_sum(t);
-    bad |= total > max_tiles;                    // cannot happen when cu_rows is a partition of the rows
-    n_tiles = min(total, max_tiles);
-    tile0 = min(before, max_tiles);
-    tile1 = min(before + mine, max_tiles);
-    if (i < n_resp) sh.off[i] = tile0;
-    if (i == 0) sh.off[n_resp] = n_tiles;
-    if (bad && blockIdx.x == 0) atomicOr(status, AIS_STATUS_BAD_CU);
   }
-  __device__ __forceinline__ int tiles() const { return n_tiles; }
-  __device__ __forceinline__ int first(int i) const { return shared().off[i]; }
-  // Publishes tiles w0 .. w0 + kWaves - 1.  Must be called by all threads of the workgroup.
-  __device__ __forceinline__ void open(int w0) const {
-    Shared& sh = shared();
-    __syncthreads();                             // the window before has been read
-    for (int b = max(tile0, w0); b < min(tile1, w0 + kWaves); ++b) {
-      const int r0 = lo + ((b - tile0) << shift);
-      sh.window[b - w0] = Tile{(int)threadIdx.x, r0, min(hi - r0, 1 << shift)};
-    }
-    __syncthreads();
+  // The last response that begins at row `first` or before it, where row `last` has the same one (both uniform), or -1: 32 lanes
+  // look for either, 32 responses at a step.
+  __device__ __forceinline__ int of_both(int first, int last) const {
+    const int lane = threadIdx.x & 63, in = lane & 31, row = lane < 32 ? first : last;
+    auto count = [](unsigned long long below, int& f, int& l) {
+      f = max(__popc((unsigned)below) - 1, 0);
+      l = max(__popc((unsigned)(below >> 32)) - 1, 0);
+    };
+    int f, l, f2, l2;
+    static_assert(kSelfPlanResponses == 32 * 32, "two steps");
+    count(__ballot(lo[32 * in] <= row), f, l);
+    count(__ballot(lo[32 * (lane < 32 ? f : l) + in] <= row), f2, l2);
+    return f == l && f2 == l2 ? 32 * f + f2 : -1;
   }
-  __device__ __forceinline__ Tile tile(int b, int w0) const {
-    const Tile t = shared().window[b - w0];
-    return Tile{__builtin_amdgcn_readfirstlane(t.resp), __builtin_amdgcn_readfirstlane(t.row0),
-                __builtin_amdgcn_readfirstlane(t.len)};
+  // The same for a row of each lane.
+  __device__ __forceinline__ int search(int row, int n_resp) const {
+    int i = 0;
+    for (int step = n_resp > 1 ? 1 << (31 - __builtin_clz(n_resp - 1)) : 0; step > 0; step >>= 1)        // uniform
+      if (lo[i + step] <= row) i += step;            // (beyond n_resp lo is larger than any row)
+    return i;
+  }
+  // Whether response i, which has been found for the row, holds it: it does unless cu_rows is no partition.
+  __device__ __forceinline__ bool holds(int i, int row) const { return lo[i] <= row && row < hi[i]; }
+};
+
+// The rows of a wavefront, one run of them, 64 at a time: while they stay inside a response it is looked for once.
+struct WaveRows {
+  int first, end;                                    // uniform, as all of this
+  int i = 0, lo = 1, hi = 0;                         // the response that held the last 64, if one did
+  __device__ __forceinline__ WaveRows(int r0, int r1, int rows_each) {
+    const int run = ((rows_each + kWaves - 1) / kWaves + 63) / 64 * 64;
+    const int at = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * run;
+    first = at < r1 - r0 ? r0 + at : r1;
+    end = run < r1 - first ? first + run : r1;
+  }
+  __device__ __forceinline__ int turns() const { return (end - first + 63) >> 6; }
+  // Row of this lane in turn k (past the end: the last).
+  __device__ __forceinline__ int row(int k) const {
+    return (int)min((unsigned)first + 64 * k + (threadIdx.x & 63), (unsigned)(end - 1));
+  }
+  __device__ __forceinline__ bool in(int k) const { return (unsigned)first + 64 * k + (threadIdx.x & 63) < (unsigned)end; }
+  // Whether the rows of turn k have a response in common, which is i then.
+  __device__ __forceinline__ bool common(const Responses& resp, int k) {
+    const int a = first + 64 * k, b = min(63, end - 1 - a) + a;
+    if (lo <= a && b < hi) return true;
+    const int j = resp.of_both(a, b);
+    if (j >= 0) {
+      i = j;
+      lo = __builtin_amdgcn_readfirstlane(resp.lo[j]);
+      hi = __builtin_amdgcn_readfirstlane(resp.hi[j]);
+      if (lo <= a && b < hi) return true;
+    }
+    lo = 1;
+    hi = 0;
+    return false;
   }
 };
 
@@ -317,35 +311,23 @@ __device__ __forceinline__ bool last_workgroup(Tickets t) {
   return s_last != 0;
 }
 
-// The partials of the tiles, NW words each: in memory, or in LDS where one workgroup does it all.
-constexpr int kOwnTiles = kWaves;                // most tiles that a single workgroup takes on
+// The partials of the tiles or workgroups, NW words each, as arrays of words: lanes that read consecutive ones read consecutive
+// words.
 template <int NW>
 struct Partials {
   double* global;
-  double* local;                                 // [word][kOwnTiles]
   int stride;
-  bool own;                                      // uniform for the launch
   struct Words { double v[NW]; };
   __device__ __forceinline__ void put(int tile, const Words& q) const {
-    if (own) {
+    double* to = global + tile;
 #pragma unroll
-      for (int k = 0; k < NW; ++k) local[k * kOwnTiles + tile] = q.v[k];
-    } else {
-      double* to = global + tile;
-#pragma unroll
-      for (int k = 0; k < NW; ++k) put_device(to + (size_t)k * stride, q.v[k]);
-    }
+    for (int k = 0; k < NW; ++k) put_device(to + (size_t)k * stride, q.v[k]);
   }
   __device__ __forceinline__ Words get(int tile) const {
     Words q;
-    if (own) {
+    const double* from = global + tile;
 #pragma unroll
-      for (int k = 0; k < NW; ++k) q.v[k] = local[k * kOwnTiles + tile];
-    } else {
-      const double* from = global + tile;
-#pragma unroll
-      for (int k = 0; k < NW; ++k) q.v[k] = get_device(from + (size_t)k * stride);
-    }
+    for (int k = 0; k < NW; ++k) q.v[k] = get_device(from + (size_t)k * stride);
     return q;
   }
 };
@@ -369,115 +351,102 @@ __device__ __forceinline__ float advantage(const float* rewards, int i, int grou
   return (float)a;
 }
 
-// ---- level 2: responses -> batch moments, diagnostics, alpha ---------------------------------------------------------
-// Runs in the last workgroup of diag_reduce_kernel.  A response's tiles are folded by a group of L lanes, L (a power of
-// two) as large as the responses leave threads for and no larger than their tiles need on average: lane l folds
-// tiles l, l + L, ... in order, then the lanes are merged in a fixed tree.  With one thread per response a batch of 4
-// responses of 1,000 tiles was a chain of 1,000 dependent reads.  A second wavefront for a response and more come only
-// where each lane has more than five tiles without it: a step of the chain is 0.3 us, a wavefront more at work 0.2 (300,000
-// rows in 1, 2 and 8 responses, 64 lanes each: 20.3, 17.5, 15.9 us; as many as there are threads: 17.6, 17.5, 17.4).
-int fold_lanes(int n_resp, long long most_tiles) {
-  int lanes = 1;
-  while ((lanes < 64 ? 1 : 5) * (long long)lanes * n_resp < most_tiles && 2LL * lanes * n_resp <= kThreads) lanes <<= 1;
-  return lanes;
+// What a row brings to the diagnostics: d = log rho (Alg. 1, sampler-trainer ratio), w_bar = min(rho, C) (Eq. 10) and
+// |pi_train - pi_roll|.  Two exponentials for three quantities: e^-|d|, whose reciprocal the ratio is where it exceeds 1, and
+// the larger probability, of which 1 - e^-|d| is the part that the smaller one lacks.
+struct RowRatio {
+  double d, w, dp;
+};
+__device__ __forceinline__ RowRatio row_ratio(float train, float roll, double lnC, double C) {
+  const double t = (double)train, l = (double)roll;
+  RowRatio r;
+  r.d = t - l;
+  // (of a NaN only its sums tell: the ratio counts as truncated)
+  const double less = exp64_finite(fmax(-fabs(r.d), -800.0)), most = exp64(fmax(t, l));
+  const double rho = r.d <= 0.0 ? less : reciprocal(less);
+  r.w = r.d <= lnC ? fmin(rho, C) : C;
+  r.dp = most > 0.0 ? most * (1.0 - less) : 0.0;
+  return r;
 }
-// The code runs once per launch, cold: its size is part of its time (a kilobyte of straight code costs 0.3 us of
-// instruction fetches), so what is the same for several quantities is done once, by lanes that hold one each.
-// WIDE: more than 64 lanes for a response (in a kernel of its own: in the others the code for it, which they do not run, was
-// 0.2 us of 1,200,000 rows in 1,024 responses).
-template <bool SELF, bool WIDE>
-__device__ void diag_final(const Partials<kDiagWords>& partials, const Tiling<SELF>& tiling, int n_resp, int lanes,
-                           int group_size, const float* rewards, const float* s_adv, const ais_params& p,
-                           float* __restrict__ adv_out, int* __restrict__ count_out, ais_diag* __restrict__ diag_out,
-                           const int* status, double* lds) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  Moments m[3] = {};                                  // of w_bar, of A and of A w_bar over the thread's valid rows
-  double d[4] = {};                                   // sums: |d|, d, |dp|, rows with rho > C (exact in fp64)
-  const int l = threadIdx.x & (lanes - 1);
-  const int per_pass = kThreads / lanes;
-  for (int i0 = 0; i0 < n_resp; i0 += per_pass) {     // uniform: the lanes of a wavefront merge across groups below
-    const int i = i0 + threadIdx.x / lanes;
-    Moments r{0, 0, 0};
-    double a = 0.0;
-    if (i < n_resp) {
-      const int t1 = tiling.first(i + 1);
-      int t = tiling.first(i) + l;
-      Partials<kDiagWords>::Words q{};
-      if (t < t1) q = partials.get(t);
-      a = SELF ? (double)s_adv[i] : (double)advantage(rewards, i, group_size, p);
-      while (t < t1) {
-        const auto next = partials.get(min(t + lanes, t1 - 1));    // in flight while this one is folded
-        const unsigned long long counts = __builtin_bit_cast(unsigned long long, q.v[kCounts]);
-        r = merge(r, Moments{(double)(unsigned)counts, q.v[kMeanW], q.v[kM2W]});
-        d[0] += q.v[kSumAbs];
-        d[1] += q.v[kSumD];
-        d[2] += q.v[kSumDp];
-        d[3] += (double)(unsigned)(counts >> 32);
-        q = next;
-        t += lanes;
-      }
-    }
-    for (int off = 1; off < (WIDE ? 64 : lanes); off <<= 1)   // uniform: every lane of the wavefront takes part
-      r = merge(r, Moments{__shfl_xor(r.n, off), __shfl_xor(r.mean, off), __shfl_xor(r.m2, off)});
-    if ((WIDE ? lane : l) != 0 || i >= n_resp) continue;   // lane 0 of the group goes on (WIDE: of each of its wavefronts)
-    if (!WIDE || l == 0) adv_out[i] = (float)a;
-    if (!WIDE) count_out[i] = (int)r.n;
-    // token-level moments of A and A w_bar: A (the stored fp32 value) is constant over the response's rows, so these
-    // have mean A mean(w_bar) and squared deviations A^2 m2(w_bar)
-    const Moments of[3] = {r, Moments{r.n, a, 0.0}, Moments{r.n, a * r.mean, a * a * r.m2}};
-    if (r.n == 0.0) continue;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) m[k] = m[0].n == 0.0 || n_resp <= per_pass ? of[k] : merge(m[k], of[k]);
+
+// Sums of a set of values as differences from x0, one of them: sum (x - x0), sum (x - x0)^2.  Values that are all equal have both
+// exactly 0, whatever parts they were summed in; else the error is that of fp64 sums of differences of the values' own range.
+struct Shifted {
+  double x0, s1, s2;
+  __device__ __forceinline__ void add(double x) {
+    const double e = x - x0;
+    s1 += e;
+    s2 = fma(e, e, s2);
   }
-  // over the wavefront, in two passes as in level 1: the mean as a difference from one lane's, then the deviations from it
-  const unsigned long long some = __ballot(m[0].n != 0.0);
-  if (some != 0) {                                     // uniform
-    const int src = __builtin_ctzll(some);
-    const double n = wave_sum(m[0].n), inv = reciprocal(n);
+  __device__ __forceinline__ void rebase(double n, double to) {      // of n values; of none: stays 0
+    const double e = x0 - to, ne = n * e;
+    s2 = fma(e, s1 + s1 + ne, s2);
+    s1 += ne;
+    x0 = to;
+  }
+};
+
+// The rows of a thread, a wavefront or a workgroup as the diagnostics see them: their number, w_bar, A and A w_bar over them, and
+// the sums of |d|, d, |dp| and of rows with rho > C.
+struct RowSums {
+  double n;
+  Shifted x[3];
+  double d[4];
+};
+constexpr int kRowSums = 11, kRowWords = kRowSums + 3;      // n, s1 of the three sets, their s2, the four sums; and the three x0
+template <typename F>
+__device__ __forceinline__ void each_sum(RowSums& r, F&& f) {
+  f(0, r.n);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const double x0 = lane_value(m[k].mean, src);
-      const double mean = x0 + wave_sum(m[k].n * (m[k].mean - x0)) * inv;
-      const double e = m[k].mean - mean;
-      m[k].m2 = wave_sum(m[k].m2 + m[k].n * (e * e));
-      m[k].mean = mean;
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) m[k].n = n;
+  for (int k = 0; k < 3; ++k) {
+    f(1 + k, r.x[k].s1);
+    f(4 + k, r.x[k].s2);
   }
 #pragma unroll
-  for (int k = 0; k < 4; ++k) d[k] = wave_sum(d[k]);
-  if (lane == 0) {
+  for (int k = 0; k < 4; ++k) f(7 + k, r.d[k]);
+}
+// Over the workgroup, in all threads' words[]: a thread with rows gives its x0 to all, and the sums, eleven for each of 1,024
+// threads, are added by a wavefront each from LDS, lane by lane over the wavefronts and then over the lanes.  (Six exchanges
+// across the lanes of all sixteen wavefronts for every sum, and four more in one of them, were 4 us of 10 twice over.)
+struct MergeRoom {
+  double sum[kRowSums * kThreads], words[kRowWords];
+  int first;
+};
+__device__ __forceinline__ void merge_workgroup(RowSums& r, MergeRoom& room) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (tid == 0) room.first = kThreads;
+  __syncthreads();
+  const unsigned long long some = __ballot(r.n != 0.0);
+  if (some != 0 && lane == 0) atomicMin(&room.first, (tid & ~63) + __builtin_ctzll(some));
+  if (tid < 3) room.words[kRowSums + tid] = 0.0;
+  __syncthreads();
+  if (tid == room.first) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      lds[(4 * k + 0) * kWaves + wave] = m[k].n;
-      lds[(4 * k + 1) * kWaves + wave] = m[k].mean;
-      lds[(4 * k + 2) * kWaves + wave] = m[k].m2;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) lds[(4 * k + 3) * kWaves + wave] = d[k];
+    for (int k = 0; k < 3; ++k) room.words[kRowSums + k] = r.x[k].x0;
   }
   __syncthreads();
-  if (wave != 0) return;
-  if (WIDE && lane < n_resp) {                         // responses of several wavefronts, one pass: their parts' counts
-    double n = 0.0;
-    for (int w = 0; w < lanes >> 6; ++w) n += lds[lane * (lanes >> 6) + w];
-    count_out[lane] = (int)n;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) r.x[k].rebase(r.n, room.words[kRowSums + k]);
+  each_sum(r, [&](int k, double& v) { room.sum[k * kThreads + tid] = v; });
+  __syncthreads();
+  if (wave < kRowSums) {
+    double v = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) v += room.sum[wave * kThreads + 64 * w + lane];
+    v = wave_sum(v);
+    if (lane == 0) room.words[wave] = v;
   }
-  // over the workgroup: 16 lanes for each of w_bar, A, A w_bar (and nothing), one for each wavefront; the sums likewise
-  static_assert(kWaves == 16, "four groups of 16 lanes");
-  const int v = lane & 15, set = lane >> 4, mine = 4 * min(set, 2) * kWaves + v;
-  Moments b{lds[mine], lds[mine + kWaves], lds[mine + 2 * kWaves]};
-  double sum = lds[(4 * set + 3) * kWaves + v];
-  b = merge_level<0>(b);
-  b = merge_level<1>(b);
-  b = merge_level<2>(b);
-  b = merge_level<3>(b);
-  sum += butterfly<0>(sum);
-  sum += butterfly<1>(sum);
-  sum += butterfly<2>(sum);
-  sum += butterfly<3>(sum);
+  __syncthreads();
+}
 
+// ---- level 2: batch moments, diagnostics, alpha -----------------------------------------------------------------------
+// The code runs once per launch, cold: its size is part of its time (a kilobyte of straight code costs 0.3 us of
+// instruction fetches), so what is the same for several quantities is done once, by lanes that hold one each.  By wavefront 0:
+// lanes 16 s .. 16 s + 15 hold the moments of w_bar, A and A w_bar (s = 0 .. 2) in `b` and the sums of |d|, d, |dp| and of rows
+// with rho > C (0 .. 3) in `sum`.
+__device__ __forceinline__ void diag_formulas(const Moments& b, double sum, const ais_params& p,
+                                              ais_diag* __restrict__ diag_out, const int* status) {
+  const int lane = threadIdx.x & 63;
   ais_diag out;
   const double N = b.n;
   out.n_valid = (long long)N;
@@ -519,46 +488,163 @@ __device__ void diag_final(const Partials<kDiagWords>& partials, const Tiling<SE
   if (lane == 0) *diag_out = out;
 }
 
-// ---- level 1: a tile of one response per wavefront; level 2 in the last workgroup ------------------------------------
+// ---- diagnostics of up to kSelfPlanResponses responses -----------------------------------------------------------------
+// Every workgroup takes rows_each rows, a run for each of its wavefronts, whatever responses they belong to: a row's advantage is known as soon
+// as the rewards are, so a thread sums w_bar, A and A w_bar over its rows (see Shifted), and threads, wavefronts and workgroups
+// are merged by plain sums of differences from one value.  What is loaded for the rows is asked for before anything else.
+// Where there is a mask, a workgroup's number of valid rows of response i goes to word i + blockIdx of `counts`: the pairs of a
+// response and a workgroup that share rows, in order, have words of their own.
+__global__ __launch_bounds__(kThreads, 4) void diag_rows_kernel(
+    const float* __restrict__ logp_train, const float* __restrict__ logp_roll, const unsigned char* __restrict__ valid,
+    int n_rows, int rows_each, const long long* __restrict__ cu_rows, int n_resp, double* partial, int* counts,
+    int group_size, const float* __restrict__ rewards, ais_params p, double lnC, float* __restrict__ adv_out,
+    int* __restrict__ count_out, ais_diag* __restrict__ diag_out, int* status, Tickets tickets) {
+  __shared__ Responses resp;
+  __shared__ float s_rewards[kSelfPlanResponses], s_adv[kSelfPlanResponses];
+  __shared__ int s_count[kSelfPlanResponses];
+  __shared__ MergeRoom room;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int r0 = blockIdx.x * rows_each, r1 = n_rows - r0 < rows_each ? n_rows : r0 + rows_each;
+  float lt[kAtOnce], lr[kAtOnce];
+  unsigned char live[kAtOnce] = {1, 1, 1, 1, 1, 1, 1, 1};
+  WaveRows wave_rows(r0, r1, rows_each);
+  const int turns = wave_rows.turns();
+  auto load = [&](int k0) {                          // those of turns k0 .. k0 + 7 (rows past the end: the last)
+    auto four = [&](auto from) __attribute__((always_inline)) {
+#pragma unroll
+      for (int k = from.value; k < from.value + 4; ++k) {
+        const int r = wave_rows.row(k0 + k);
+        lt[k] = logp_train[r];
+        lr[k] = logp_roll[r];
+        if (valid != nullptr) live[k] = valid[r];
+      }
+    };
+    four(std::integral_constant<int, 0>{});
+    if (turns - k0 > 4) four(std::integral_constant<int, 4>{});
+  };
+  if (turns > 0) load(0);                            // uniform
+  if (tid < n_resp) s_rewards[tid] = rewards[tid];
+  resp.init(cu_rows, n_resp, n_rows, status);
+  s_count[tid] = 0;
+  __syncthreads();
+  if (tid < n_resp) {
+    const float a = advantage(s_rewards, tid, group_size, p);
+    s_adv[tid] = a;
+    if (blockIdx.x == 0) adv_out[tid] = a;
+    if (valid == nullptr && blockIdx.x == 0) count_out[tid] = resp.hi[tid] - resp.lo[tid];
+  }
+  __syncthreads();
+  RowSums sums = {};
+  int n = 0;
+  for (int k0 = 0; k0 < turns; k0 += kAtOnce) {                          // uniform
+    // the rows take turns in one copy of the code
+    const int k1 = min(turns, k0 + kAtOnce);
+#pragma unroll 1
+    for (int k = k0; k < k1; ++k) {
+      const bool one = wave_rows.common(resp, k);                        // uniform
+      const int i = one ? wave_rows.i : resp.search(wave_rows.row(k), n_resp);
+      const bool on = wave_rows.in(k) && live[0] != 0 && (one || resp.holds(i, wave_rows.row(k)));
+      if (valid != nullptr) {
+        const unsigned long long mask = __ballot(on);
+        if (one) {
+          if (lane == 0) atomicAdd(&s_count[i], (int)__popcll(mask));
+        } else if (on) {
+          atomicAdd(&s_count[i], 1);
+        }
+      }
+      const RowRatio q = row_ratio(lt[0], lr[0], lnC, (double)p.C);
+      const double a = (double)s_adv[i];
+      const double x[3] = {q.w, a, a * q.w};
+      if (on) {
+        if (n++ == 0) {
+#pragma unroll
+          for (int s = 0; s < 3; ++s) sums.x[s].x0 = x[s];
+        }
+#pragma unroll
+        for (int s = 0; s < 3; ++s) sums.x[s].add(x[s]);
+        sums.d[0] += fabs(q.d);
+        sums.d[1] += q.d;
+        sums.d[2] += q.dp;
+        sums.d[3] += q.d > lnC ? 1.0 : 0.0;
+      }
+#pragma unroll
+      for (int j = 0; j < kAtOnce - 1; ++j) {                  // the thread's next row
+        lt[j] = lt[j + 1];
+        lr[j] = lr[j + 1];
+        live[j] = live[j + 1];
+      }
+    }
+    if (k1 < turns) load(k1);
+  }
+  sums.n = (double)n;
+  const int n_wg = gridDim.x;
+  // once over the workgroup's rows, and in the workgroup that finishes last once over the workgroups'
+  for (bool all = n_wg == 1;; all = true) {                              // uniform
+    merge_workgroup(sums, room);
+    if (all) break;
+    if (tid < kRowWords) put_device(partial + (size_t)tid * n_wg + blockIdx.x, room.words[tid]);
+    if (valid != nullptr && tid < n_resp && resp.lo[tid] < r1 && resp.hi[tid] > r0)
+      put_device(counts + tid + (int)blockIdx.x, s_count[tid]);
+    if (!last_workgroup(tickets)) return;
+    sums = RowSums{};
+    if (tid < n_wg) {
+      each_sum(sums, [&](int k, double& v) { v = get_device(partial + (size_t)k * n_wg + tid); });
+#pragma unroll
+      for (int k = 0; k < 3; ++k) sums.x[k].x0 = get_device(partial + (size_t)(kRowSums + k) * n_wg + tid);
+    }
+    if (valid != nullptr) {
+      // the parts of a response's count: by its thread, those of responses with many by its wavefront
+      int b0 = 0, parts = 0, sum = 0;
+      if (tid < n_resp && resp.hi[tid] > resp.lo[tid]) {
+        b0 = resp.lo[tid] / rows_each;
+        parts = (resp.hi[tid] - 1) / rows_each - b0 + 1;
+      }
+      const int* mine = counts + tid + b0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (k < parts && parts <= 4) sum += get_device(mine + k);
+      for (unsigned long long many = __ballot(parts > 4); many != 0; many &= many - 1) {         // uniform
+        const int src = __builtin_ctzll(many);
+        const int first = __builtin_amdgcn_readlane(b0, src) + (tid & ~63) + src, len = __builtin_amdgcn_readlane(parts, src);
+        int part = 0;
+        for (int k = lane; k < len; k += 64) part += get_device(counts + first + k);
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) part += __shfl_xor(part, off);
+        if (lane == src) sum = part;
+      }
+      if (tid < n_resp) count_out[tid] = sum;
+    }
+  }
+  if (valid != nullptr && n_wg == 1 && tid < n_resp) count_out[tid] = s_count[tid];
+  if (tid >= 64) return;
+  // lanes 16 s .. 16 s + 15 go on with the set s and the sum s
+  const int set = min(lane >> 4, 2);
+  const double n_rows_in = room.words[0], s1 = room.words[1 + set], s2 = room.words[4 + set];
+  const double share = reciprocal(fmax(n_rows_in, 1.0));
+  const Moments b{n_rows_in, fma(s1, share, room.words[kRowSums + set]), fmax(fma(-s1, s1 * share, s2), 0.0)};
+  diag_formulas(b, room.words[7 + (lane >> 4)], p, diag_out, status);
+}
+
+// ---- diagnostics of more responses: a tile of one response per wavefront; level 2 in the last workgroup ---------------------
 // A chunk of 256 rows (four per lane) is reduced in two passes over its registers: the sum of w_bar - x0, x0 being some
 // row's w_bar, gives the mean, the squared deviations from it the spread.  Equal values have spread exactly 0, and each pass
 // is six dependent additions where merging (count, mean, spread) triples lane by lane was six times ten.
 // The four rows of a lane take turns in one copy of the code (three exponentials each): see diag_final for why.
-template <bool SELF, bool WIDE>
 __global__ __launch_bounds__(kThreads, 4) void diag_reduce_kernel(
     const float* __restrict__ logp_train, const float* __restrict__ logp_roll,
     const unsigned char* __restrict__ valid, long long n_rows, const long long* __restrict__ cu_rows, int n_resp,
-    const int* __restrict__ tile_off, TileRule rule, double* partial, int lanes, int group_size,
+    const int* __restrict__ tile_off, TileRule rule, double* partial, int group_size,
     const float* __restrict__ rewards, ais_params p, double lnC, float* __restrict__ adv_out, int* __restrict__ count_out,
     ais_diag* __restrict__ diag_out, int* status, Tickets tickets) {
   __shared__ double lds[16 * kWaves];                // three sets of moments and four sums per wavefront
-  __shared__ double own_partials[kDiagWords * kOwnTiles];
-  __shared__ float s_rewards[SELF ? kSelfPlanResponses : 1], s_adv[SELF ? kSelfPlanResponses : 1];
-  if (SELF && (int)threadIdx.x < n_resp) s_rewards[threadIdx.x] = rewards[threadIdx.x];
-  Tiling<SELF> tiling;
-  tiling.init(tile_off, cu_rows, n_resp, n_rows, rule.shift, rule.max_tiles, status);
+  const Tiling tiling{tile_off, cu_rows, n_resp, (int)n_rows};
   const int n_tiles = tiling.tiles();
-  const Partials<kDiagWords> partials{partial, own_partials, rule.max_tiles, rule.max_tiles <= kOwnTiles};
+  const Partials<kDiagWords> partials{partial, rule.max_tiles};
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int per = (n_tiles + (int)gridDim.x - 1) / (int)gridDim.x;
   const int b0 = blockIdx.x * per, b1 = min(n_tiles, b0 + per);
-  // the advantages, by the wavefronts that have no tile first
-  auto advantages = [&] {
-    const int i = kThreads - 1 - (int)threadIdx.x;
-    if (SELF && i < n_resp) s_adv[i] = advantage(s_rewards, i, group_size, p);
-  };
-  if (b0 >= b1) {                                              // uniform: a workgroup without tiles
-    __syncthreads();
-    advantages();
-  }
-  for (int w0 = b0; w0 < b1; w0 += kWaves) {                   // uniform for the workgroup
-    tiling.open(w0);
-    const int b = w0 + wave;
-    if (b >= b1) {
-      if (w0 == b0) advantages();
-      continue;
-    }
-    const Tile tile = tiling.tile(b, w0);
+  for (int b = b0 + wave; b < b1; b += kWaves) {               // uniform for the wavefront
+    const Tile tile = tiling.tile(b);
     float ltf[kLaneRows], lrf[kLaneRows];
     unsigned char live[kLaneRows] = {1, 1, 1, 1};
     auto load = [&](int c0) {                    // the chunk that begins at row c0 of the tile (rows past its end: its last)
@@ -577,7 +663,6 @@ __global__ __launch_bounds__(kThreads, 4) void diag_reduce_kernel(
     double sabs = 0, sd = 0, sdp = 0;
     int nclip = 0;
     if (tile.len > 0) load(0);
-    if (w0 == b0) advantages();                                // while the rows are on their way
     for (int c0 = 0; c0 < tile.len; c0 += kChunkRows) {        // uniform for the wavefront
       double w[kLaneRows] = {}, some = 0;
       bool was[kLaneRows] = {}, any = false;
@@ -585,17 +670,14 @@ __global__ __launch_bounds__(kThreads, 4) void diag_reduce_kernel(
       const int n_k = min(kLaneRows, (tile.len - c0 + 63) >> 6);
 #pragma unroll 1
       for (int k = 0; k < n_k; ++k) {
-        const double lt = (double)ltf[0], lr = (double)lrf[0];
-        const double d = lt - lr;                              // log rho (Alg. 1, sampler-trainer ratio)
-        const double wk = exp(fmin(d, lnC));                   // w_bar = min(rho, C) (Eq. 10)
-        const double dp = fabs(exp(lt) - exp(lr));
+        const RowRatio q = row_ratio(ltf[0], lrf[0], lnC, (double)p.C);
         const bool o = c0 + 64 * k + lane < tile.len && live[0] != 0;
         cnt += (int)__popcll(__ballot(o));
-        sabs += o ? fabs(d) : 0.0;
-        sd += o ? d : 0.0;
-        sdp += o ? dp : 0.0;
-        nclip += (int)__popcll(__ballot(o && d > lnC));
-        some = o && !any ? wk : some;
+        sabs += o ? fabs(q.d) : 0.0;
+        sd += o ? q.d : 0.0;
+        sdp += o ? q.dp : 0.0;
+        nclip += (int)__popcll(__ballot(o && q.d > lnC));
+        some = o && !any ? q.w : some;
         any |= o;
 #pragma unroll
         for (int j = 0; j < kLaneRows - 1; ++j) {              // the lane's next row, and room for the one after this
@@ -605,7 +687,7 @@ __global__ __launch_bounds__(kThreads, 4) void diag_reduce_kernel(
           w[kLaneRows - 1 - j] = w[kLaneRows - 2 - j];
           was[kLaneRows - 1 - j] = was[kLaneRows - 2 - j];
         }
-        w[0] = wk;
+        w[0] = q.w;
         was[0] = o;
       }
       if (c0 + kChunkRows < tile.len) load(c0 + kChunkRows);   // on its way while this chunk is folded
@@ -635,97 +717,133 @@ __global__ __launch_bounds__(kThreads, 4) void diag_reduce_kernel(
       partials.put(b, {mw.mean, mw.m2, sabs, sd, sdp, __builtin_bit_cast(double, counts)});
     }
   }
-  // ---- level 2, in the workgroup that finishes last ----
-  if (last_workgroup(tickets))
-    diag_final<SELF, WIDE>(partials, tiling, n_resp, lanes, group_size, rewards, s_adv, p, adv_out, count_out, diag_out, status,
-                     lds);
+  if (!last_workgroup(tickets)) return;
+  // ---- level 2: a thread folds the tiles of a response in order, and takes the next 1,024 responses after these
+  Moments m[3] = {};                                           // of w_bar, of A and of A w_bar over the thread's valid rows
+  double d[4] = {};
+  for (int i = threadIdx.x; i < n_resp; i += kThreads) {
+    Moments r{0, 0, 0};
+    const int t1 = tiling.first(i + 1);
+    int t = tiling.first(i);
+    Partials<kDiagWords>::Words q{};
+    if (t < t1) q = partials.get(t);
+    const double a = (double)advantage(rewards, i, group_size, p);
+    while (t < t1) {
+      const auto next = partials.get(min(t + 1, t1 - 1));      // in flight while this one is folded
+      const unsigned long long counts = __builtin_bit_cast(unsigned long long, q.v[kCounts]);
+      r = merge(r, Moments{(double)(unsigned)counts, q.v[kMeanW], q.v[kM2W]});
+      d[0] += q.v[kSumAbs];
+      d[1] += q.v[kSumD];
+      d[2] += q.v[kSumDp];
+      d[3] += (double)(unsigned)(counts >> 32);
+      q = next;
+      ++t;
+    }
+    adv_out[i] = (float)a;
+    count_out[i] = (int)r.n;
+    // token-level moments of A and A w_bar: A (the stored fp32 value) is constant over the response's rows, so these
+    // have mean A mean(w_bar) and squared deviations A^2 m2(w_bar)
+    if (r.n == 0.0) continue;
+    const Moments of[3] = {r, Moments{r.n, a, 0.0}, Moments{r.n, a * r.mean, a * a * r.m2}};
+    const bool none = m[0].n == 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) m[k] = none ? of[k] : merge(m[k], of[k]);
+  }
+  // over the wavefront in two passes: the mean as a difference from one lane's, then the deviations from it
+  const unsigned long long some = __ballot(m[0].n != 0.0);
+  if (some != 0) {                                     // uniform
+    const int src = __builtin_ctzll(some);
+    const double n = wave_sum(m[0].n), inv = reciprocal(n);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const double x0 = lane_value(m[k].mean, src);
+      const double mean = x0 + wave_sum(m[k].n * (m[k].mean - x0)) * inv;
+      const double e = m[k].mean - mean;
+      m[k].m2 = wave_sum(m[k].m2 + m[k].n * (e * e));
+      m[k].mean = mean;
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) m[k].n = n;
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) d[k] = wave_sum(d[k]);
+  if (lane == 0) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      lds[(4 * k + 0) * kWaves + wave] = m[k].n;
+      lds[(4 * k + 1) * kWaves + wave] = m[k].mean;
+      lds[(4 * k + 2) * kWaves + wave] = m[k].m2;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) lds[(4 * k + 3) * kWaves + wave] = d[k];
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  // over the workgroup: 16 lanes for each of w_bar, A, A w_bar (and nothing), one for each wavefront; the sums likewise
+  static_assert(kWaves == 16, "four groups of 16 lanes");
+  const int v = lane & 15, set = lane >> 4, mine = 4 * min(set, 2) * kWaves + v;
+  Moments b{lds[mine], lds[mine + kWaves], lds[mine + 2 * kWaves]};
+  b = merge_level<0>(b);
+  b = merge_level<1>(b);
+  b = merge_level<2>(b);
+  b = merge_level<3>(b);
+  double sum = lds[(4 * set + 3) * kWaves + v];
+  sum += butterfly<0>(sum);
+  sum += butterfly<1>(sum);
+  sum += butterfly<2>(sum);
+  sum += butterfly<3>(sum);
+  diag_formulas(b, sum, p, diag_out, status);
 }
 
 // ---- per-row coefficient of the gradient, rectification weight, loss ------------------------------------------------
-template <bool SELF>
-__global__ __launch_bounds__(kThreads, 4) void row_coeff_kernel(
-    CoeffInputs in, long long n_rows, const int* __restrict__ tile_off, TileRule rule, double* partial,
-    float* __restrict__ g_out, float* __restrict__ wtilde_out, float g_scale, double* __restrict__ loss_out, int* status,
-    Tickets tickets) {
-  __shared__ double lds[kWaves];
-  __shared__ double own_partials[kOwnTiles];
-  const CoeffRule coeff(in.p, in.diag->alpha, in.lnC, in.logp_old != nullptr, in.logp_ref != nullptr);
-  Tiling<SELF> tiling;
-  tiling.init(tile_off, in.cu_rows, in.n_resp, n_rows, rule.shift, rule.max_tiles, status);
-  const int n_tiles = tiling.tiles();
-  const Partials<1> partials{partial, own_partials, rule.max_tiles, rule.max_tiles <= kOwnTiles};
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int per = (n_tiles + (int)gridDim.x - 1) / (int)gridDim.x;
-  const int b0 = blockIdx.x * per, b1 = min(n_tiles, b0 + per);
-  for (int w0 = b0; w0 < b1; w0 += kWaves) {                   // uniform for the workgroup
-    tiling.open(w0);
-    const int b = w0 + wave;
-    if (b >= b1) continue;
-    const Tile tile = tiling.tile(b, w0);
-    const float a32 = in.adv[tile.resp];
-    const int cnt = in.count[tile.resp];
-    float ltf[kLaneRows], rollf[kLaneRows], oldf[kLaneRows], reff[kLaneRows];
-    unsigned char live[kLaneRows] = {1, 1, 1, 1};
-    auto load = [&](int c0) {                    // the chunk that begins at row c0 of the tile (rows past its end: its last)
-      unsigned r[kLaneRows];
+// The inputs of N rows of a thread.
+template <int N>
+struct CoeffRows {
+  float lt[N], roll[N], old[N], ref[N];
+  unsigned char live[N];
+  // FROM .. FROM + 3
+  template <int FROM, typename F>
+  __device__ __forceinline__ void load(const CoeffInputs& in, const CoeffRule& rule, F&& row) {
+    int r[4];
 #pragma unroll
-      for (int k = 0; k < kLaneRows; ++k) {
-        r[k] = tile.row0 + (unsigned)min(c0 + 64 * k + lane, tile.len - 1);
-        ltf[k] = in.logp_train[r[k]];
-        rollf[k] = in.logp_roll[r[k]];
-      }
-      if (coeff.has_old) {
-#pragma unroll
-        for (int k = 0; k < kLaneRows; ++k) oldf[k] = in.logp_old[r[k]];
-      }
-      if (coeff.kl) {
-#pragma unroll
-        for (int k = 0; k < kLaneRows; ++k) reff[k] = in.logp_ref[r[k]];
-      }
-      if (in.valid != nullptr) {
-#pragma unroll
-        for (int k = 0; k < kLaneRows; ++k) live[k] = in.valid[r[k]];
-      }
-    };
-    if (tile.len > 0) load(0);
-    const double a = (double)a32;
-    const double wgt = response_weight(in.n_resp, cnt);
-    double acc = 0;
-    for (int c0 = 0; c0 < tile.len; c0 += kChunkRows) {        // uniform for the wavefront
-      const int n_k = min(kLaneRows, (tile.len - c0 + 63) >> 6);
-      // the four rows of a lane take turns in one copy of the code
-#pragma unroll 1
-      for (int k = 0; k < n_k; ++k) {
-        float g = 0.f, wt = 0.f;
-        const int r = c0 + 64 * k + lane;
-        if (r < tile.len && live[0] != 0) {
-          const RowTerm t = row_term(coeff, ltf[0], rollf[0], oldf[0], reff[0], a);
-          acc -= wgt * t.obj;
-          g = (float)(wgt * t.dobj * (double)g_scale);
-          wt = (float)t.wtilde;
-        }
-        if (r < tile.len) {
-          g_out[tile.row0 + (unsigned)r] = g;
-          if (wtilde_out != nullptr) wtilde_out[tile.row0 + (unsigned)r] = wt;
-        }
-#pragma unroll
-        for (int j = 0; j < kLaneRows - 1; ++j) {
-          ltf[j] = ltf[j + 1];
-          rollf[j] = rollf[j + 1];
-          oldf[j] = oldf[j + 1];
-          reff[j] = reff[j + 1];
-          live[j] = live[j + 1];
-        }
-      }
-      if (c0 + kChunkRows < tile.len) load(c0 + kChunkRows);
+    for (int k = 0; k < 4; ++k) {
+      r[k] = row(FROM + k);
+      lt[FROM + k] = in.logp_train[r[k]];
+      roll[FROM + k] = in.logp_roll[r[k]];
+      old[FROM + k] = ref[FROM + k] = 0.f;
+      live[FROM + k] = 1;
     }
-    acc = wave_sum(acc);
-    if (lane == 0) partials.put(b, {acc});
+    if (rule.has_old) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) old[FROM + k] = in.logp_old[r[k]];
+    }
+    if (rule.kl) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) ref[FROM + k] = in.logp_ref[r[k]];
+    }
+    if (in.valid != nullptr) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) live[FROM + k] = in.valid[r[k]];
+    }
   }
-  if (!last_workgroup(tickets)) return;
+  __device__ __forceinline__ void next() {           // the rows take turns in one copy of the code
+#pragma unroll
+    for (int j = 0; j < N - 1; ++j) {
+      lt[j] = lt[j + 1];
+      roll[j] = roll[j + 1];
+      old[j] = old[j + 1];
+      ref[j] = ref[j + 1];
+      live[j] = live[j + 1];
+    }
+  }
+};
+
+// The loss from every workgroup's partials, `words` of them in all, in the workgroup that finishes last.
+__device__ __forceinline__ void loss_final(const Partials<1>& partials, int words, double* lds, double* loss_out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   double acc = 0;
 #pragma unroll 4
-  for (int t = threadIdx.x; t < n_tiles; t += kThreads) acc += partials.get(t).v[0];
+  for (int t = threadIdx.x; t < words; t += kThreads) acc += partials.get(t).v[0];
   acc = wave_sum(acc);
   if (lane == 0) lds[wave] = acc;
   __syncthreads();
@@ -738,13 +856,134 @@ __global__ __launch_bounds__(kThreads, 4) void row_coeff_kernel(
   if (threadIdx.x == 0) *loss_out = acc;
 }
 
-// Workgroups of a reduction: a tile per wavefront, four or more wavefronts at work in each, on as many compute units as
-// that gives; one workgroup alone where it has a wavefront for every tile: its partials stay in LDS and it takes no ticket,
-// 2 to 3 us less.  (Alone up to 64 tiles, four rounds: 4,096 rows in 16 responses 11.4 and 8.0 us instead of 10.5 and 7.2.)
+// Up to kSelfPlanResponses responses: every workgroup takes rows_each rows (see diag_rows_kernel).
+__global__ __launch_bounds__(kThreads, 4) void coeff_rows_kernel(
+    CoeffInputs in, int n_rows, int rows_each, double* partial, float* __restrict__ g_out, float* __restrict__ wtilde_out,
+    float g_scale, double* __restrict__ loss_out, int* status, Tickets tickets) {
+  __shared__ Responses resp;
+  __shared__ float s_adv[kSelfPlanResponses];
+  __shared__ double s_weight[kSelfPlanResponses], lds[kWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r0 = blockIdx.x * rows_each, r1 = n_rows - r0 < rows_each ? n_rows : r0 + rows_each;
+  const CoeffRule rule(in.p, in.diag->alpha, in.lnC, in.logp_old != nullptr, in.logp_ref != nullptr);
+  CoeffRows<kAtOnce> rows;
+  WaveRows wave_rows(r0, r1, rows_each);
+  const int turns = wave_rows.turns();
+  auto load = [&](int k0) {                          // those of turns k0 .. k0 + 7 (rows past the end: the last)
+    rows.load<0>(in, rule, [&](int k) { return wave_rows.row(k0 + k); });
+    if (turns - k0 > 4) rows.load<4>(in, rule, [&](int k) { return wave_rows.row(k0 + k); });        // uniform
+  };
+  if (turns > 0) load(0);                            // uniform
+  if (tid < in.n_resp) {
+    s_adv[tid] = in.adv[tid];
+    s_weight[tid] = response_weight(in.n_resp, in.count[tid]);
+  }
+  resp.init(in.cu_rows, in.n_resp, n_rows, status);
+  __syncthreads();
+  double acc = 0;
+  for (int k0 = 0; k0 < turns; k0 += kAtOnce) {                          // uniform
+    const int k1 = min(turns, k0 + kAtOnce);
+#pragma unroll 1
+    for (int k = k0; k < k1; ++k) {
+      const bool one = wave_rows.common(resp, k);                        // uniform
+      const int r = wave_rows.row(k), i = one ? wave_rows.i : resp.search(r, in.n_resp);
+      if (wave_rows.in(k)) {
+        float g = 0.f, wt = 0.f;
+        if (rows.live[0] != 0 && (one || resp.holds(i, r))) {
+          const RowTerm t = row_term(rule, rows.lt[0], rows.roll[0], rows.old[0], rows.ref[0], (double)s_adv[i]);
+          const double wgt = s_weight[i];
+          acc -= wgt * t.obj;
+          g = (float)(wgt * t.dobj * (double)g_scale);
+          wt = (float)t.wtilde;
+        }
+        g_out[r] = g;
+        if (wtilde_out != nullptr) wtilde_out[r] = wt;
+      }
+      rows.next();
+    }
+    if (k1 < turns) load(k1);
+  }
+  acc = wave_sum(acc);
+  const Partials<1> partials{partial, 0};
+  if (gridDim.x > 1) {                               // uniform
+    if (lane == 0) partials.put(blockIdx.x * kWaves + wave, {acc});
+    if (last_workgroup(tickets)) loss_final(partials, gridDim.x * kWaves, lds, loss_out);
+    return;
+  }
+  if (lane == 0) lds[wave] = acc;
+  __syncthreads();
+  if (wave != 0) return;
+  acc = lds[lane & (kWaves - 1)];
+  acc += butterfly<0>(acc);
+  acc += butterfly<1>(acc);
+  acc += butterfly<2>(acc);
+  acc += butterfly<3>(acc);
+  if (tid == 0) *loss_out = acc;
+}
+
+// More responses: a tile of one response per wavefront.
+__global__ __launch_bounds__(kThreads, 4) void row_coeff_kernel(
+    CoeffInputs in, long long n_rows, const int* __restrict__ tile_off, TileRule rule, double* partial,
+    float* __restrict__ g_out, float* __restrict__ wtilde_out, float g_scale, double* __restrict__ loss_out,
+    Tickets tickets) {
+  __shared__ double lds[kWaves];
+  const CoeffRule coeff(in.p, in.diag->alpha, in.lnC, in.logp_old != nullptr, in.logp_ref != nullptr);
+  const Tiling tiling{tile_off, in.cu_rows, in.n_resp, (int)n_rows};
+  const int n_tiles = tiling.tiles();
+  const Partials<1> partials{partial, 0};
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int per = (n_tiles + (int)gridDim.x - 1) / (int)gridDim.x;
+  const int b0 = blockIdx.x * per, b1 = min(n_tiles, b0 + per);
+  for (int b = b0 + wave; b < b1; b += kWaves) {               // uniform for the wavefront
+    const Tile tile = tiling.tile(b);
+    const double a = (double)in.adv[tile.resp], wgt = response_weight(in.n_resp, in.count[tile.resp]);
+    CoeffRows<kLaneRows> rows;
+    auto load = [&](int c0) {                        // (rows past the tile's end: its last)
+      rows.load<0>(in, coeff, [&](int k) { return tile.row0 + min(c0 + 64 * k + lane, tile.len - 1); });
+    };
+    if (tile.len > 0) load(0);
+    double acc = 0;
+    for (int c0 = 0; c0 < tile.len; c0 += kChunkRows) {        // uniform for the wavefront
+      const int n_k = min(kLaneRows, (tile.len - c0 + 63) >> 6);
+#pragma unroll 1
+      for (int k = 0; k < n_k; ++k) {
+        float g = 0.f, wt = 0.f;
+        const int r = c0 + 64 * k + lane;
+        if (r < tile.len && rows.live[0] != 0) {
+          const RowTerm t = row_term(coeff, rows.lt[0], rows.roll[0], rows.old[0], rows.ref[0], a);
+          acc -= wgt * t.obj;
+          g = (float)(wgt * t.dobj * (double)g_scale);
+          wt = (float)t.wtilde;
+        }
+        if (r < tile.len) {
+          g_out[tile.row0 + (unsigned)r] = g;
+          if (wtilde_out != nullptr) wtilde_out[tile.row0 + (unsigned)r] = wt;
+        }
+        rows.next();
+      }
+      if (c0 + kChunkRows < tile.len) load(c0 + kChunkRows);
+    }
+    acc = wave_sum(acc);
+    if (lane == 0) partials.put(b, {acc});
+  }
+  if (last_workgroup(tickets)) loss_final(partials, n_tiles, lds, loss_out);
+}
+
+// Workgroups that share the tiles of more than kSelfPlanResponses responses: four or more tiles each, on as many compute units
+// as that gives.
 int reduction_grid(const ais_ctx* ctx, int max_tiles) {
-  if (max_tiles <= kOwnTiles) return 1;
   const int per = std::max(4, (max_tiles + ctx->n_cus - 1) / ctx->n_cus);
   return (max_tiles + per - 1) / per;
+}
+
+// Rows of a workgroup where the rows are dealt out evenly: 1,024 on as many compute units as that gives, all alone where a
+// workgroup has no more than kAloneRows: it takes no ticket and nothing goes through memory.  Diagnostics, us, alone up to 1,024,
+// 2,048 and 4,096 rows: 1,500 rows in 8 responses 8.6, 7.0, 7.0; 2,048 9.3, 7.6, 7.6; 3,000 8.9, 8.8, 8.8; 4,096 9.5, 9.4, 9.9.
+constexpr int kAloneRows = 2048;
+int rows_each(const ais_ctx* ctx, long long n_rows) {
+  if (n_rows <= kAloneRows) return (int)std::max<long long>(n_rows, 1);
+  const long long wgs = std::min<long long>(ctx->n_cus, (n_rows + kThreads - 1) / kThreads);
+  return (int)(((n_rows + wgs - 1) / wgs + 63) / 64 * 64);
 }
 
 // A launch of one workgroup neither takes a ticket nor clears the other's, so it is not counted as a turn: launches of many
@@ -758,28 +997,17 @@ Tickets take_tickets(ais_ctx* ctx, bool in_static, int grid) {
 
 }  // namespace
 
-// Tiles of 256 rows, or twice, four times, ... as many where that would be more than kMaxTiles; of kPlanTileRows where
-// the plan kernel lays them out.  With kMaxTiles and 1,024 responses every tile has a wavefront at one workgroup per compute
-// unit.  (8,192: 1,200,000 rows in 1,024 responses 25.7 and 18.4 instead of 21.9 and 17.2 us; 1,536: 25.3 and 23.0.  Tiles of
-// 64 rows while they are few: 41,643 rows in 16 responses 14.1 and 7.9 instead of 13.7 and 7.7, both with a longer level 2 than
-// the present one, which makes the latter 11.1.)
-constexpr int kMaxTiles = 3072;
+// The tiling of batches of more than kSelfPlanResponses responses.
 TileRule tile_rule(long long n_rows, int n_resp) {
-  int shift = 8;
-  if (n_resp > kSelfPlanResponses) {
-    static_assert(kPlanTileRows == 1 << 10, "shift below");
-    shift = 10;
-  } else {
-    while (((n_rows + (1LL << shift) - 1) >> shift) > kMaxTiles) ++shift;
-  }
-  return TileRule{shift, (int)((n_rows + (1LL << shift) - 1) >> shift) + n_resp};
+  return TileRule{(int)((n_rows + kPlanTileRows - 1) / kPlanTileRows) + n_resp};
 }
 
 // Monotone in both arguments, so that a call at the largest batch sizes the workspace for all others: the partials have
-// room for kMaxTiles tiles of whole responses as soon as there are that many rows, whatever rule cuts them.
+// room for the tiles of a planned batch and for the workgroups' of any other.
+constexpr int kMostTiles = 3072;
 WorkspaceLayout workspace_layout(long long n_rows, int n_resp) {
   auto up = [](size_t v) { return (v + 255) & ~size_t(255); };
-  const long long fine = std::min<long long>((n_rows + kChunkRows - 1) / kChunkRows, kMaxTiles);
+  const long long fine = std::min<long long>((n_rows + kChunkRows - 1) / kChunkRows, kMostTiles);
   const long long planned = (n_rows + kPlanTileRows - 1) / kPlanTileRows;
   const size_t tiles = (size_t)(std::max(fine, planned) + n_resp);
   WorkspaceLayout w;
@@ -796,7 +1024,7 @@ size_t static_scratch_bytes(long long n_rows, int n_resp) {
   auto up = [](size_t v) { return (v + 255) & ~size_t(255); };
   static_assert(sizeof(double) * kDiagWords <= 56, "partials of planned tiles fit what is documented");
   static_assert(sizeof(int) * (kSelfPlanResponses + 2) + 256 +
-                        sizeof(double) * kDiagWords * (kMaxTiles + kSelfPlanResponses) <= AIS_STATIC_SCRATCH_BYTES,
+                        sizeof(double) * kDiagWords * (kMostTiles + kSelfPlanResponses) <= AIS_STATIC_SCRATCH_BYTES,
                 "those of other batches always fit");
   return up(up(sizeof(int) * (size_t)(n_resp + 2)) +
             56 * ((size_t)((n_rows + kPlanTileRows - 1) / kPlanTileRows) + (size_t)n_resp));
@@ -814,26 +1042,35 @@ int launch_diagnostics(ais_ctx* ctx, const float* logp_train, const float* logp_
                        long long n_rows, const long long* cu_rows, int n_resp, int group_size,
                        const float* rewards, const ais_params& p, int* tile_off, double* partial, bool in_static,
                        float* adv_out, int* count_out, ais_diag* diag_out) {
+  const double lnC = std::log((double)p.C);
+  if (n_resp <= kSelfPlanResponses) {
+    const int each = rows_each(ctx, n_rows), grid = (int)std::max<long long>((n_rows + each - 1) / each, 1);
+    int* counts = reinterpret_cast<int*>(partial + (size_t)kRowWords * grid);
+    diag_rows_kernel<<<grid, kThreads, 0, ctx->stream>>>(
+        logp_train, logp_roll, valid, (int)n_rows, each, cu_rows, n_resp, partial, counts, group_size, rewards, p, lnC, adv_out,
+        count_out, diag_out, ctx->status_dev, take_tickets(ctx, in_static, grid));
+    return hip_fail(ctx, hipGetLastError());
+  }
   const TileRule rule = tile_rule(n_rows, n_resp);
-  const int lanes = fold_lanes(n_resp, (n_rows + (1LL << rule.shift) - 1) >> rule.shift);
-  auto kernel = n_resp > kSelfPlanResponses ? diag_reduce_kernel<false, false>
-                : lanes > 64                ? diag_reduce_kernel<true, true>
-                                            : diag_reduce_kernel<true, false>;
   const int grid = reduction_grid(ctx, rule.max_tiles);
-  kernel<<<grid, kThreads, 0, ctx->stream>>>(
-      logp_train, logp_roll, valid, n_rows, cu_rows, n_resp, tile_off, rule, partial, lanes, group_size, rewards, p,
-      std::log((double)p.C), adv_out, count_out, diag_out, ctx->status_dev, take_tickets(ctx, in_static, grid));
+  diag_reduce_kernel<<<grid, kThreads, 0, ctx->stream>>>(
+      logp_train, logp_roll, valid, n_rows, cu_rows, n_resp, tile_off, rule, partial, group_size, rewards, p, lnC, adv_out,
+      count_out, diag_out, ctx->status_dev, take_tickets(ctx, in_static, grid));
   return hip_fail(ctx, hipGetLastError());
 }
 
 int launch_row_coeff(ais_ctx* ctx, const CoeffInputs& in, long long n_rows, int* tile_off, double* partial, float* g_out,
                      float* wtilde_out, double* loss_out, float g_scale) {
-  auto kernel = in.n_resp <= kSelfPlanResponses ? row_coeff_kernel<true> : row_coeff_kernel<false>;
+  if (in.n_resp <= kSelfPlanResponses) {
+    const int each = rows_each(ctx, n_rows), grid = (int)std::max<long long>((n_rows + each - 1) / each, 1);
+    coeff_rows_kernel<<<grid, kThreads, 0, ctx->stream>>>(in, (int)n_rows, each, partial, g_out, wtilde_out, g_scale, loss_out,
+                                                          ctx->status_dev, take_tickets(ctx, false, grid));
+    return hip_fail(ctx, hipGetLastError());
+  }
   const TileRule rule = tile_rule(n_rows, in.n_resp);
   const int grid = reduction_grid(ctx, rule.max_tiles);
-  kernel<<<grid, kThreads, 0, ctx->stream>>>(
-      in, n_rows, tile_off, rule, partial, g_out, wtilde_out, g_scale, loss_out, ctx->status_dev,
-      take_tickets(ctx, false, grid));
+  row_coeff_kernel<<<grid, kThreads, 0, ctx->stream>>>(in, n_rows, tile_off, rule, partial, g_out, wtilde_out, g_scale,
+                                                       loss_out, take_tickets(ctx, false, grid));
   return hip_fail(ctx, hipGetLastError());
 }
 

@@ -5,7 +5,6 @@
 #include <mutex>
 #include <new>
 
-
 #include "ais_internal.h"
 
 // Scratch memory of ais_diagnostics_static: every GPU the library runs on holds its own copy of this array, at its
@@ -552,28 +551,48 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   const size_t mask_bytes = gather ? up((size_t)n_rows) : 0;
   const size_t list_bytes = gather ? up((size_t)n_rows * 4) : 0;
   const size_t hg_bytes = gather ? up((size_t)m_rows * (size_t)d_model * 2) : 0;
-  size_t ds_bytes = 0, dhg_bytes = 0;
-  LmParts parts{1, 1};
-  int rc = AIS_OK;
-  for (const bool roomy : {true, false}) {
-    ds_bytes = up(lm_grad_dlogits_bytes(m_rows, vocab, asked, ctx->n_cus));
-    chunk_vocab = lm_grad_chunk(m_rows, vocab, asked, ctx->n_cus);
+  struct Room {
+    long long chunk;
+    size_t ds, dhg, all;
+    LmParts parts;
+  };
+  auto room = [&](bool roomy) {
+    Room r{lm_grad_chunk(m_rows, vocab, asked, ctx->n_cus), up(lm_grad_dlogits_bytes(m_rows, vocab, asked, ctx->n_cus)),
+           gather ? up((size_t)m_rows * (size_t)d_model * 4) : 0, 0, LmParts{1, 1}};
     if (asked == 0) {
-      const long long even = roomy ? lm_grad_even_chunk(chunk_vocab, m_rows, vocab) : chunk_vocab;
-      chunk_vocab = even != chunk_vocab ? even : lm_grad_chunk_for(chunk_vocab, vocab, d_model, ctx->n_cus);
-      if (roomy) ds_bytes = std::max(ds_bytes, up(lm_grad_wide_bytes(m_rows, vocab)));
+      const long long even = roomy ? lm_grad_even_chunk(r.chunk, m_rows, vocab) : r.chunk;
+      r.chunk = even != r.chunk ? even : lm_grad_chunk_for(r.chunk, vocab, d_model, ctx->n_cus);
+      if (roomy) r.ds = std::max(r.ds, up(lm_grad_wide_bytes(m_rows, vocab)));
     }
-    dhg_bytes = gather ? up((size_t)m_rows * (size_t)d_model * 4) : 0;
-    parts = LmParts{1, 1};
-    size_t dwp_bytes = 0;
+    size_t dwp = 0;
     if (roomy) {
-      parts = lm_grad_parts(ctx->n_cus, m_rows, d_model, std::min(chunk_vocab, vocab));
-      dhg_bytes = std::max(dhg_bytes, up(lm_dhidden_parts_bytes(m_rows, d_model)));
-      dwp_bytes = up(lm_dweight_parts_bytes(vocab, d_model, ctx->n_cus));
+      r.parts = lm_grad_parts(ctx->n_cus, m_rows, d_model, std::min(r.chunk, vocab));
+      r.dhg = std::max(r.dhg, up(lm_dhidden_parts_bytes(m_rows, d_model)));
+      dwp = up(lm_dweight_parts_bytes(vocab, d_model, ctx->n_cus));
     }
-    rc = ensure_workspace(ctx, ds_bytes + plan_bytes + mask_bytes + 2 * list_bytes + hg_bytes + dhg_bytes + dwp_bytes);
-    if (rc != AIS_ERR_NOMEM) break;
+    r.all = r.ds + plan_bytes + mask_bytes + 2 * list_bytes + hg_bytes + r.dhg + dwp;
+    return r;
+  };
+  Room use = room(true);
+  if (use.all > ctx->ws_bytes) {
+    // What is there already may hold the narrow chunks.  It stays where the larger block was refused before (asking again
+    // would give the one in hand back, on every call), and where the stream is being recorded, when nothing can be allocated.
+    const Room narrow = room(false);
+    hipStreamCaptureStatus recording = hipStreamCaptureStatusNone;
+    if (narrow.all <= ctx->ws_bytes &&
+        (use.all >= ctx->ws_refused ||
+         (hipStreamIsCapturing(ctx->stream, &recording) == hipSuccess && recording != hipStreamCaptureStatusNone)))
+      use = narrow;
   }
+  int rc = ensure_workspace(ctx, use.all);
+  if (rc == AIS_ERR_NOMEM) {
+    ctx->ws_refused = use.all;
+    use = room(false);
+    rc = ensure_workspace(ctx, use.all);
+  }
+  chunk_vocab = use.chunk;
+  const size_t ds_bytes = use.ds, dhg_bytes = use.dhg;
+  const LmParts parts = use.parts;
   if (rc != AIS_OK) return rc;
   ctx->plan.valid = false;             // the chunk's dlogits overwrite whatever tiling the workspace held
   char* ds = static_cast<char*>(ctx->ws);

@@ -83,3 +83,35 @@ def test_parts(k):
         assert torch.equal(at[n][1:-7].view_as(t), t) and bool((at[n][:1] == 7).all()) and bool((at[n][-7:] == 7).all())
     assert ctx.status() == 0
     ctx.close()
+
+
+def test_recorded_in_a_workspace_without_room_for_parts():
+    """A call that is being recorded can allocate nothing: with a workspace that holds the narrow chunks and no more it
+    takes those, and its replays are right."""
+    ctx = B.AisContext()
+    h, w, y, c = operands(8192, 32, 8192, None, 77)          # sizes the workspace: 2 * 8192 * 8192 bytes and 42 MB, and a quarter
+    logp, lse = ctx.lm_head_logprob(h, w, y)
+    ctx.lm_head_grad(h, w, y, lse, logp, c, chunk_vocab=8192)
+    small = operands(64, 256, 64, None, 78)
+    logp, lse = ctx.lm_head_logprob(*small[:3])
+    ctx.lm_head_grad(*small[:3], lse, logp, small[3])
+    # 67 MB of dlogits in chunks of 8,192; 166 MB in one chunk and 134 + 67 MB of parts
+    h, w, y, c = operands(4096, 256, 20_000, None, 79)
+    logp, lse = ctx.lm_head_logprob(h, w, y)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            dh, dw = ctx.lm_head_grad(h, w, y, lse, logp, c)
+    torch.cuda.synchronize()
+    for scale in (1.0, -0.5):
+        c.mul_(scale)
+        dh.fill_(7.0)
+        dw.fill_(7.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        check(h, w, y, c, dh, dw)
+    assert ctx.status() == 0
+    ctx.close()

@@ -629,7 +629,7 @@ __global__ __launch_bounds__(kThreads, 4) void diag_rows_kernel(
 // A chunk of 256 rows (four per lane) is reduced in two passes over its registers: the sum of w_bar - x0, x0 being some
 // row's w_bar, gives the mean, the squared deviations from it the spread.  Equal values have spread exactly 0, and each pass
 // is six dependent additions where merging (count, mean, spread) triples lane by lane was six times ten.
-// The four rows of a lane take turns in one copy of the code (three exponentials each): see diag_final for why.
+// The four rows of a lane take turns in one copy of the code (two exponentials each): see diag_formulas for why.
 __global__ __launch_bounds__(kThreads, 4) void diag_reduce_kernel(
     const float* __restrict__ logp_train, const float* __restrict__ logp_roll,
     const unsigned char* __restrict__ valid, long long n_rows, const long long* __restrict__ cu_rows, int n_resp,

@@ -202,9 +202,8 @@ def test_static_diagnostics_replays(ctx):
 
 @pytest.mark.parametrize("rows,live", [(4096, -1), (3000, -1), (4096, 2000)])
 def test_lm_head_grad_replays(rows, live):
-    """The gradient of the hidden-state read-out, recorded after calls at the largest size whose products run on the
-    library's own kernels: 3,000 rows and a list of 2,000 take rocBLAS for the hidden gradient, for the first time on this
-    context and inside the capture."""
+    """The gradient of the hidden-state read-out, recorded after calls at the largest size: 3,000 rows and a list of
+    2,000 take other splits of the products' sums, for the first time on this context and inside the capture."""
     ctx = B.AisContext()
     d, vocab = 4096, 8192
     gen = torch.Generator(device="cuda")

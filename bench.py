@@ -407,7 +407,7 @@ def main():
             "avg_ms": ms_grad, "avg_ms_with_row_bound": ms_bound, "rows_with_gradient": n_live,
             "recompute_kernel_ms": ms_rec / 3, "chunks": n_rec // 3, "flops": 3 * flops,
             "TFLOP/s": 3 * flops / (ms_grad * 1e-3) / 1e12, "frac_of_mfma_peak": 3 * flops / (ms_grad * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS,
-            "dlogits_bytes_held": 2 * R * 8192, "logits_bytes_of_materialised_route": 2 * R * V,
+            "dlogits_bytes_held": 2 * R * (-(-V // (256 * max(n_rec // 3, 1))) * 256), "logits_bytes_of_materialised_route": 2 * R * V,
             "materialised_route": {"ms": ms_gemm + k_fwd + k_bwd + ms_two, "logits_gemm_ms": ms_gemm,
                                    "two_sweeps_ms": k_fwd + k_bwd, "two_gradient_gemms_ms": ms_two,
                                    "note": "library GEMMs with bf16 outputs; the sweeps are this library's"}}

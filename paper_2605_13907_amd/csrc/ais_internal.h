@@ -101,8 +101,22 @@ constexpr int kLmMaxParts = 32, kLmMaxWeightParts = 8;
 constexpr long long kLmPartsBytes = 128LL << 20;
 LmParts lm_grad_parts(int n_cus, long long n_rows, long long d, long long n_v);
 size_t lm_dhidden_parts_bytes(long long n_rows, long long d);
-size_t lm_dweight_parts_bytes(long long vocab, long long d, int n_cus);
+size_t lm_dweight_parts_bytes(long long n_v, long long d, int n_cus);
 size_t lm_grad_dlogits_bytes(long long m_rows, long long vocab, long long asked, int n_cus);
+// The gradient call's chunk, the parts of its sums and where its arrays lie in the workspace, which begins with the chunk's
+// dlogits (byte offsets).
+struct LmGradRoom {
+  long long chunk;
+  LmParts parts;
+  size_t plan;                 // decompositions of the recompute kernel
+  size_t mask, index, pos;     // with a row list: rows with a gradient, their list, its inverse,
+  size_t hidden, dhidden;      // the listed rows' hidden states and their gradient; the parts of dhidden
+  size_t dweight;              // the parts of dweight
+  size_t end;                  // end of the last of them
+  size_t all;                  // what is asked for: no less, and no less than any call over fewer rows asks for
+};
+LmGradRoom lm_grad_room(long long n_rows, long long m_rows, long long d, long long vocab, long long asked, int n_cus,
+                        int roomy);
 
 }  // namespace ais
 

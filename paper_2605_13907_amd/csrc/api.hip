@@ -542,42 +542,13 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
                        ctx->stream>>>(dhidden_out, (size_t)n_rows * (size_t)d_model);
     return hip_fail(ctx, hipGetLastError());
   }
-  // workspace: the chunk's dlogits, the device-side decomposition of the recompute kernel, with a row list the mask, the
-  // list, its inverse, the gathered hidden states and their gradient, and the parts of the products' sums.  Where there is no
-  // room for wide chunks and parts: the narrow chunks, and sums in one part.
-  auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
-  const long long asked = chunk_vocab;
-  const size_t plan_bytes = 256;
-  const size_t mask_bytes = gather ? up((size_t)n_rows) : 0;
-  const size_t list_bytes = gather ? up((size_t)n_rows * 4) : 0;
-  const size_t hg_bytes = gather ? up((size_t)m_rows * (size_t)d_model * 2) : 0;
-  struct Room {
-    long long chunk;
-    size_t ds, dhg, all;
-    LmParts parts;
-  };
-  auto room = [&](bool roomy) {
-    Room r{lm_grad_chunk(m_rows, vocab, asked, ctx->n_cus), up(lm_grad_dlogits_bytes(m_rows, vocab, asked, ctx->n_cus)),
-           gather ? up((size_t)m_rows * (size_t)d_model * 4) : 0, 0, LmParts{1, 1}};
-    if (asked == 0) {
-      const long long even = roomy ? lm_grad_even_chunk(r.chunk, m_rows, vocab) : r.chunk;
-      r.chunk = even != r.chunk ? even : lm_grad_chunk_for(r.chunk, vocab, d_model, ctx->n_cus);
-      if (roomy) r.ds = std::max(r.ds, up(lm_grad_wide_bytes(m_rows, vocab)));
-    }
-    size_t dwp = 0;
-    if (roomy) {
-      r.parts = lm_grad_parts(ctx->n_cus, m_rows, d_model, std::min(r.chunk, vocab));
-      r.dhg = std::max(r.dhg, up(lm_dhidden_parts_bytes(m_rows, d_model)));
-      dwp = up(lm_dweight_parts_bytes(vocab, d_model, ctx->n_cus));
-    }
-    r.all = r.ds + plan_bytes + mask_bytes + 2 * list_bytes + hg_bytes + r.dhg + dwp;
-    return r;
-  };
-  Room use = room(true);
+  // Where there is no room for wide chunks and parts: the narrow chunks, and sums in one part.
+  auto room = [&](int roomy) { return lm_grad_room(n_rows, m_rows, d_model, vocab, chunk_vocab, ctx->n_cus, roomy); };
+  LmGradRoom use = room(1);
   if (use.all > ctx->ws_bytes) {
     // What is there already may hold the narrow chunks.  It stays where the larger block was refused before (asking again
     // would give the one in hand back, on every call), and where the stream is being recorded, when nothing can be allocated.
-    const Room narrow = room(false);
+    const LmGradRoom narrow = room(0);
     hipStreamCaptureStatus recording = hipStreamCaptureStatusNone;
     if (narrow.all <= ctx->ws_bytes &&
         (use.all >= ctx->ws_refused ||
@@ -587,28 +558,26 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   int rc = ensure_workspace(ctx, use.all);
   if (rc == AIS_ERR_NOMEM) {
     ctx->ws_refused = use.all;
-    use = room(false);
+    use = room(0);
     rc = ensure_workspace(ctx, use.all);
   }
-  chunk_vocab = use.chunk;
-  const size_t ds_bytes = use.ds, dhg_bytes = use.dhg;
-  const LmParts parts = use.parts;
   if (rc != AIS_OK) return rc;
+  const long long chunk = use.chunk;
+  const LmParts parts = use.parts;
   ctx->plan.valid = false;             // the chunk's dlogits overwrite whatever tiling the workspace held
   char* ds = static_cast<char*>(ctx->ws);
-  void* dev_plan = ds + ds_bytes;
-  unsigned char* live_mask = gather ? reinterpret_cast<unsigned char*>(ds + ds_bytes + plan_bytes) : nullptr;
-  int* row_index = gather ? reinterpret_cast<int*>(ds + ds_bytes + plan_bytes + mask_bytes) : nullptr;
-  int* row_pos = gather ? reinterpret_cast<int*>(ds + ds_bytes + plan_bytes + mask_bytes + list_bytes) : nullptr;
-  char* h_gathered = ds + ds_bytes + plan_bytes + mask_bytes + 2 * list_bytes;
-  float* dh_gathered = reinterpret_cast<float*>(h_gathered + hg_bytes);
+  void* dev_plan = ds + use.plan;
+  unsigned char* live_mask = gather ? reinterpret_cast<unsigned char*>(ds + use.mask) : nullptr;
+  int* row_index = gather ? reinterpret_cast<int*>(ds + use.index) : nullptr;
+  int* row_pos = gather ? reinterpret_cast<int*>(ds + use.pos) : nullptr;
+  char* h_gathered = ds + use.hidden;
+  float* dh_gathered = reinterpret_cast<float*>(ds + use.dhidden);
   if (gather) {
     rc = launch_lm_live_mask(ctx, coeff, n_rows, live_mask);
     if (rc != AIS_OK) return rc;
   }
-  const int width_last = (int)(vocab % chunk_vocab);
-  rc = launch_lm_head_grad_setup(ctx, live_mask, n_rows, (int)m_rows, (int)chunk_vocab, width_last, row_index, row_pos,
-                                 dev_plan);
+  const int width_last = (int)(vocab % chunk);
+  rc = launch_lm_head_grad_setup(ctx, live_mask, n_rows, (int)m_rows, (int)chunk, width_last, row_index, row_pos, dev_plan);
   if (rc == AIS_OK && gather)
     rc = launch_lm_gather_rows(ctx, hidden, hidden_stride, (int)d_model, row_index, dev_plan, (int)m_rows, h_gathered);
   if (rc != AIS_OK) return rc;
@@ -616,21 +585,21 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   const void* h_gemm = gather ? static_cast<const void*>(h_gathered) : hidden;
   const long long h_gemm_stride = gather ? d_model : hidden_stride;
   const bool elsewhere = gather || parts.h > 1;
-  float* dw_parts = reinterpret_cast<float*>(h_gathered + hg_bytes + dhg_bytes);
+  float* dw_parts = reinterpret_cast<float*>(ds + use.dweight);
   float* dh_gemm = elsewhere ? dh_gathered : dhidden_out;
-  const long long h_stride = m_rows * d_model, w_stride = std::min(chunk_vocab, vocab) * d_model;
+  const long long h_stride = m_rows * d_model, w_stride = std::min(chunk, vocab) * d_model;
   // the list's length, first word of the decomposition on the device: rows past it are nobody's
   const int* n_listed = gather ? static_cast<const int*>(dev_plan) : nullptr;
   const char* w_base = static_cast<const char*>(weight);
-  for (long long v0 = 0; v0 < vocab; v0 += chunk_vocab) {
-    const int width = (int)std::min<long long>(chunk_vocab, vocab - v0);
+  for (long long v0 = 0; v0 < vocab; v0 += chunk) {
+    const int width = (int)std::min<long long>(chunk, vocab - v0);
     const void* w_chunk = w_base + (size_t)v0 * (size_t)weight_stride * 2;
     rc = launch_lm_head_dlogits_chunk(ctx, hidden, hidden_stride, w_chunk, weight_stride, n_rows, (int)d_model, width,
                                       (int)v0, token_ids, lse, logp, coeff, inv_temperature, dev_plan,
-                                      width == width_last ? 1 : 0, ds, chunk_vocab, row_index, (int)m_rows);
+                                      width == width_last ? 1 : 0, ds, chunk, row_index, (int)m_rows);
     float* dw_chunk = dweight_out + (size_t)v0 * (size_t)d_model;
     if (rc == AIS_OK)
-      rc = launch_lm_grad_products(ctx, ds, chunk_vocab, h_gemm, h_gemm_stride, w_chunk, weight_stride, (int)m_rows, n_listed,
+      rc = launch_lm_grad_products(ctx, ds, chunk, h_gemm, h_gemm_stride, w_chunk, weight_stride, (int)m_rows, n_listed,
                                    width, (int)d_model, parts.w > 1 ? dw_parts : dw_chunk, dh_gemm, parts, w_stride, h_stride,
                                    v0 != 0);
     if (rc == AIS_OK && parts.w > 1)

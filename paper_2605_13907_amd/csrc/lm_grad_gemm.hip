@@ -351,14 +351,13 @@ LmParts lm_grad_parts(int n_cus, long long n_rows, long long d, long long n_v) {
   return best;
 }
 
-// Bytes of the parts' arrays: dhidden's as many as any smaller number of rows may take, too, dweight's the same for all, so
-// that a call never needs more than one over more rows before it.
+// Most bytes that the parts' arrays take: dhidden's over that many rows or fewer, dweight's of chunks of n_v entries (the same
+// whatever the rows).
 size_t lm_dhidden_parts_bytes(long long n_rows, long long d) {
   return (size_t)std::min<long long>(kLmPartsBytes, kLmMaxParts * n_rows * d * 4);
 }
-size_t lm_dweight_parts_bytes(long long vocab, long long d, int n_cus) {
-  const long long n_v = std::min(vocab, kLmGradChunk);
-  if (2 * ((d + kTile - 1) / kTile) * ((n_v + kTile - 1) / kTile) >= n_cus) return 0;
+size_t lm_dweight_parts_bytes(long long n_v, long long d, int n_cus) {
+  if (n_v > kLmGradChunk || 2 * ((d + kTile - 1) / kTile) * ((n_v + kTile - 1) / kTile) >= n_cus) return 0;
   return (size_t)std::min<long long>(kLmPartsBytes, kLmMaxWeightParts * n_v * d * 4);
 }
 
@@ -379,6 +378,42 @@ long long lm_grad_chunk_for(long long chunk, long long vocab, long long d_model,
   for (long long width = chunk - kTile; width >= 22 * kTile; width -= kTile)
     if (rounds_full(n_cus, d_model, width, 95)) return width;
   return chunk;
+}
+
+// Room for a call over n_rows rows of which m_rows are gone through (fewer: by a list).  roomy: wide chunks and parts; 0: the
+// narrow chunks, and sums in one part, for where there is no room for those.  Every array's place follows from the chunk and
+// the parts that the launches take; what is asked for beyond the last one's end is for calls over fewer rows, whose chunks may
+// be wider and whose sums may have more parts.
+LmGradRoom lm_grad_room(long long n_rows, long long m_rows, long long d, long long vocab, long long asked, int n_cus,
+                        int roomy) {
+  auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
+  const bool list = m_rows < n_rows;
+  LmGradRoom r{};
+  r.chunk = lm_grad_chunk(m_rows, vocab, asked, n_cus);
+  if (asked == 0) {
+    const long long even = roomy ? lm_grad_even_chunk(r.chunk, m_rows, vocab) : r.chunk;
+    r.chunk = even != r.chunk ? even : lm_grad_chunk_for(r.chunk, vocab, d, n_cus);
+  }
+  const long long n_v = std::min(r.chunk, vocab);                // entries of the widest chunk
+  r.parts = roomy ? lm_grad_parts(n_cus, m_rows, d, n_v) : LmParts{1, 1};
+  const size_t dh_row = (size_t)m_rows * (size_t)d * 4, dw_part = (size_t)n_v * (size_t)d * 4;
+  const size_t dh_bytes = list || r.parts.h > 1 ? up(dh_row * r.parts.h) : 0, dw_bytes = r.parts.w > 1 ? up(dw_part * r.parts.w) : 0;
+  r.plan = up(2 * (size_t)m_rows * (size_t)r.chunk);
+  r.mask = r.plan + 256;
+  r.index = r.mask + (list ? up((size_t)n_rows) : 0);
+  r.pos = r.index + (list ? up((size_t)n_rows * 4) : 0);
+  r.hidden = r.pos + (list ? up((size_t)n_rows * 4) : 0);
+  r.dhidden = r.hidden + (list ? up((size_t)m_rows * (size_t)d * 2) : 0);
+  r.dweight = r.dhidden + dh_bytes;
+  r.end = r.dweight + dw_bytes;
+  size_t ds_most = up(lm_grad_dlogits_bytes(m_rows, vocab, asked, n_cus)), dh_most = list ? up(dh_row) : 0, dw_most = 0;
+  if (roomy) {
+    if (asked == 0) ds_most = std::max(ds_most, up(lm_grad_wide_bytes(m_rows, vocab)));
+    dh_most = std::max(dh_most, up(lm_dhidden_parts_bytes(m_rows, d)));
+    dw_most = up(lm_dweight_parts_bytes(std::min(asked != 0 ? asked : kLmGradChunk, vocab), d, n_cus));
+  }
+  r.all = std::max(r.end, r.end - r.plan - dh_bytes - dw_bytes + ds_most + dh_most + dw_most);
+  return r;
 }
 
 // dweight[n_v, d] = ds^T h over the first k rows (min(k, *k_dev) if k_dev is given), and dhidden[n_rows, d] (+)= ds w over the

@@ -18,6 +18,17 @@ def sizes():
     return logprob, dlogits, chunk
 
 
+class Room(C.Structure):
+    _fields_ = [("chunk", C.c_longlong), ("w", C.c_int), ("h", C.c_int)] + [(n, C.c_size_t) for n in (
+        "plan", "mask", "index", "pos", "hidden", "dhidden", "dweight", "end", "all")]
+
+
+def room():
+    f = B._lib()["_ZN3ais12lm_grad_roomExxxxxii"]        # lm_grad_room(rows, rows gone through, d_model, vocab, asked chunk, units, roomy)
+    f.argtypes, f.restype = [C.c_longlong] * 5 + [C.c_int] * 2, Room
+    return f
+
+
 def chunks(rows, vocab, n_cus):
     """Most chunks that a batch of so many rows is split into: at least 64, two work items per compute unit."""
     blocks = (rows + 255) // 256
@@ -57,3 +68,45 @@ def test_wide_chunks_fill_one_round(n_cus):
     for rows in range(1, 5000, 61):
         tiles, blocks = chunk(rows, 1 << 20, 0, n_cus) // 256, (rows + 255) // 256
         assert tiles == 32 or (blocks <= 12 and blocks * ((tiles + 1) // 2) <= n_cus), (rows, tiles)
+
+
+@pytest.mark.parametrize("n_cus", [256, 64, 304])
+@pytest.mark.parametrize("asked", [0, 256, 1024, 1536, 1792, 4096, 8192, 65_536])
+def test_gradient_arrays_lie_inside_what_is_asked_for(asked, n_cus):
+    """Every array of the gradient call begins where the one before it ends or later and ends inside the workspace, the
+    parts of both sums among them, over many rows, widths, vocabularies and chunks, with and without a row list."""
+    f = room()
+    split = 0
+    for rows in (1, 64, 300, 2000, 3000, 4096, 5000, 12_000, 16_384, 41_643):
+        for d in (32, 64, 512, 1024, 1056, 2048, 3584, 4096, 8192):
+            for vocab in (1, 700, 2048, 8192, 8193, 32_000, 50_257, 151_936):
+                for m in (rows, max(1, rows // 3)):
+                    for roomy in (1, 0):
+                        r = f(rows, m, d, vocab, asked, n_cus, roomy)
+                        width = min(r.chunk, vocab)
+                        listed = m < rows
+                        assert r.chunk % 256 == 0 and 0 < r.chunk < vocab + 256 and r.w >= 1 and r.h >= 1
+                        assert roomy or (r.w, r.h) == (1, 1)
+                        ends = [(0, 2 * m * r.chunk), (r.plan, 2 * 32), (r.mask, rows * listed), (r.index, 4 * rows * listed),
+                                (r.pos, 4 * rows * listed), (r.hidden, 2 * m * d * listed),
+                                (r.dhidden, 4 * r.h * m * d if listed or r.h > 1 else 0),
+                                (r.dweight, 4 * r.w * width * d if r.w > 1 else 0), (r.end, 0)]
+                        case = (rows, m, d, vocab, roomy, r.chunk, r.w, r.h)
+                        assert all(a + n <= b for (a, n), (b, _) in zip(ends, ends[1:])), case
+                        assert all(a % 256 == 0 for a, _ in ends) and r.end <= r.all, case
+                        split += r.w > 1 and vocab > 8192 and d >= 1024
+    if 0 < asked < 8192 and n_cus == 256:
+        assert split > 0                # sizes where it is the chunk that has dweight split, not the vocabulary or the model
+
+
+@pytest.mark.parametrize("n_cus", [256, 64])
+@pytest.mark.parametrize("asked", [0, 1024, 8192])
+@pytest.mark.parametrize("d,vocab", [(64, 700), (512, 2048), (1024, 50_257), (2304, 128_256), (4096, 20_000), (4096, 151_936)])
+def test_more_rows_never_need_less_for_the_gradient(d, vocab, asked, n_cus):
+    f = room()
+    for roomy in (1, 0):
+        last = [0, 0]
+        for n in list(range(1, 5200, 97)) + [6000, 8191, 8192, 8193, 12_000, 16_384, 30_000, 41_643, 65_537, 1 << 20]:
+            now = [f(n, n, d, vocab, asked, n_cus, roomy).all, f(1 << 21, n, d, vocab, asked, n_cus, roomy).all]
+            assert now[0] >= last[0] and now[1] >= last[1], (n, roomy, last, now)
+            last = now

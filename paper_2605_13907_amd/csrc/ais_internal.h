@@ -125,6 +125,7 @@ struct ais_ctx {
   hipStream_t stream = nullptr;
   void* ws = nullptr;
   size_t ws_bytes = 0;
+  bool ws_recorded = false;      // a call that was recorded into a graph uses the block: replaced only for a call it cannot hold
   int* status_dev = nullptr;     // 256 bytes: the status word and the tickets, which are 0 between launches
   unsigned turns = 0, static_turns = 0;   // reductions launched with either pair of tickets
   int n_cus = 256;               // compute units of the device

@@ -20,8 +20,20 @@ int hip_fail(ais_ctx* ctx, hipError_t e) {
   return AIS_ERR_HIP;
 }
 
+// Whether the context's stream is being recorded into a graph (the default stream cannot be).
+static bool being_recorded(ais_ctx* ctx) {
+  if (ctx->stream == nullptr) return false;
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(ctx->stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return false;
+}
+
 int ensure_workspace(ais_ctx* ctx, size_t bytes) {
-  if (bytes <= ctx->ws_bytes) return AIS_OK;
+  if (bytes <= ctx->ws_bytes) {
+    ctx->ws_recorded = ctx->ws_recorded || being_recorded(ctx);
+    return AIS_OK;
+  }
   ctx->plan.valid = false;             // the tiling lived in the block that is about to be replaced
   // growing is rare (first call at a new size); it waits for queued work that may still use the old block
   hipError_t e = hipStreamSynchronize(ctx->stream);
@@ -30,6 +42,7 @@ int ensure_workspace(ais_ctx* ctx, size_t bytes) {
     (void)hipFree(ctx->ws);
     ctx->ws = nullptr;
     ctx->ws_bytes = 0;
+    ctx->ws_recorded = false;
   }
   const size_t want = bytes + bytes / 4;
   e = hipMalloc(&ctx->ws, want);
@@ -547,13 +560,10 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   LmGradRoom use = room(1);
   if (use.all > ctx->ws_bytes) {
     // What is there already may hold the narrow chunks.  It stays where the larger block was refused before (asking again
-    // would give the one in hand back, on every call), and where the stream is being recorded, when nothing can be allocated.
+    // would give the one in hand back, on every call), where the stream is being recorded, when nothing can be allocated, and
+    // where a call that was recorded used it: a graph still writes there.
     const LmGradRoom narrow = room(0);
-    hipStreamCaptureStatus recording = hipStreamCaptureStatusNone;
-    if (narrow.all <= ctx->ws_bytes &&
-        (use.all >= ctx->ws_refused ||
-         (hipStreamIsCapturing(ctx->stream, &recording) == hipSuccess && recording != hipStreamCaptureStatusNone)))
-      use = narrow;
+    if (narrow.all <= ctx->ws_bytes && (use.all >= ctx->ws_refused || ctx->ws_recorded || being_recorded(ctx))) use = narrow;
   }
   int rc = ensure_workspace(ctx, use.all);
   if (rc == AIS_ERR_NOMEM) {

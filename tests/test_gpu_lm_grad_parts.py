@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from paper_2605_13907_amd import binding as B
+from tests.test_workspace import room
 
 pytestmark = pytest.mark.gpu
 
@@ -114,5 +115,55 @@ def test_recorded_in_a_workspace_without_room_for_parts():
         graph.replay()
         torch.cuda.synchronize()
         check(h, w, y, c, dh, dw)
+    assert ctx.status() == 0
+    ctx.close()
+
+
+@pytest.mark.parametrize("first", ["gradient", "diagnostics"])
+def test_a_recorded_workspace_stays(first):
+    """After a call has been recorded, an eager gradient call that the workspace holds in narrow chunks and one part leaves it
+    where it is, although it would like a larger one: the graph still writes there.  Nothing is allocated, and replays before and
+    after it are right."""
+    ctx = B.AisContext()
+    big = operands(8192, 32, 8192, None, 81)                 # sizes the workspace
+    logp, lse = ctx.lm_head_logprob(*big[:3])
+    ctx.lm_head_grad(*big[:3], lse, logp, big[3], chunk_vocab=8192)
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    held = room()(8192, 8192, 32, 8192, 8192, units, 1).all * 1.25
+    assert room()(4096, 4096, 256, 40_000, 0, units, 0).all < held < room()(4096, 4096, 256, 40_000, 0, units, 1).all
+    h, w, y, c = operands(4096, 256, 40_000, None, 82)
+    logp, lse = ctx.lm_head_logprob(h, w, y)
+    ctx.lm_head_grad(*operands(64, 256, 64, None, 83)[:3], lse[:64], logp[:64], c[:64])        # (kernel attributes)
+    small = torch.rand(4096, device="cuda") - 2.0
+    cu, rewards, params = torch.tensor([0, 4096], device="cuda"), torch.ones(1, device="cuda"), B.default_params()
+    ctx.diagnostics(small, small, None, cu, rewards, 1, params)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        if first == "gradient":
+            dh, dw = ctx.lm_head_grad(h, w, y, lse, logp, c)
+        else:
+            adv, count, diag = ctx.diagnostics(small, small * 0.5, None, cu, rewards, 1, params)
+    eager = [torch.empty(4096, 256, device="cuda"), torch.empty(40_000, 256, device="cuda")]
+    torch.cuda.synchronize()
+    for scale in (1.0, -0.5, 3.0):
+        c.mul_(scale)
+        small.sub_(0.125)
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        ctx._sync_stream()
+        rc = B._lib().ais_lm_head_grad(ctx._h, h.data_ptr(), 256, w.data_ptr(), 256, B.AIS_BF16, 4096, 256, 40_000, y.data_ptr(),
+                                       lse.data_ptr(), logp.data_ptr(), c.data_ptr(), 1.0, 0, -1, eager[0].data_ptr(),
+                                       eager[1].data_ptr())
+        torch.cuda.synchronize()
+        assert rc == 0 and torch.cuda.mem_get_info()[0] == free
+        check(h, w, y, c, *eager)
+        graph.replay()
+        torch.cuda.synchronize()
+        if first == "gradient":
+            assert torch.equal(dh, eager[0]) and torch.equal(dw, eager[1])
+        else:
+            ref = ctx.diagnostics(small, small * 0.5, None, cu, rewards, 1, params)
+            assert all(torch.equal(a, b) for a, b in zip((adv, count, diag), ref))
     assert ctx.status() == 0
     ctx.close()

@@ -145,7 +145,6 @@ struct ais_ctx {
     bool valid = false;
   } plan;
   void* static_scratch = nullptr;   // address, on this context's device, of the library's static scratch array
-  size_t ws_refused = ~size_t(0);   // workspace of a read-out gradient with wide chunks and parts that the device last had no room for
 };
 
 namespace ais {

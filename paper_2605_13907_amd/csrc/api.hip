@@ -55,6 +55,29 @@ int ensure_workspace(ais_ctx* ctx, size_t bytes) {
   return AIS_OK;
 }
 
+// A larger block where the one in hand would do: the one in hand goes only when the other is there.  The device is asked for its
+// room first: where there is none, that is all a call pays.
+static void grow_workspace(ais_ctx* ctx, size_t bytes) {
+  const size_t want = bytes + bytes / 4;
+  size_t free_bytes = 0, total = 0;
+  void* block = nullptr;
+  if (hipMemGetInfo(&free_bytes, &total) != hipSuccess || free_bytes < want || hipMalloc(&block, want) != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  // queued work may still use the old block
+  if (hipStreamSynchronize(ctx->stream) != hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipFree(block);
+    return;
+  }
+  if (ctx->ws != nullptr) (void)hipFree(ctx->ws);
+  ctx->plan.valid = false;             // the tiling lived in that block
+  ctx->ws = block;
+  ctx->ws_bytes = want;
+  ctx->ws_recorded = false;
+}
+
 ScopedTimer::ScopedTimer(ais_ctx* c, int which) : ctx(c) {
   if (!ctx->profiling) return;
   ais_ctx::Timed t;
@@ -559,15 +582,16 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   auto room = [&](int roomy) { return lm_grad_room(n_rows, m_rows, d_model, vocab, chunk_vocab, ctx->n_cus, roomy); };
   LmGradRoom use = room(1);
   if (use.all > ctx->ws_bytes) {
-    // What is there already may hold the narrow chunks.  It stays where the larger block was refused before (asking again
-    // would give the one in hand back, on every call), where the stream is being recorded, when nothing can be allocated, and
-    // where a call that was recorded used it: a graph still writes there.
+    // What is there already may hold the narrow chunks.  It stays where the stream is being recorded, when nothing can be
+    // allocated, where a call that was recorded used it (a graph still writes there), and where the device has no room for more.
     const LmGradRoom narrow = room(0);
-    if (narrow.all <= ctx->ws_bytes && (use.all >= ctx->ws_refused || ctx->ws_recorded || being_recorded(ctx))) use = narrow;
+    if (narrow.all <= ctx->ws_bytes) {
+      if (!ctx->ws_recorded && !being_recorded(ctx)) grow_workspace(ctx, use.all);
+      if (use.all > ctx->ws_bytes) use = narrow;
+    }
   }
   int rc = ensure_workspace(ctx, use.all);
   if (rc == AIS_ERR_NOMEM) {
-    ctx->ws_refused = use.all;
     use = room(0);
     rc = ensure_workspace(ctx, use.all);
   }

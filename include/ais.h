@@ -322,11 +322,12 @@ int ais_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long hidden_strid
  *   hidden, weight, token_ids, dtype, strides   as for ais_lm_head_logprob; d_model a multiple of 32
  *   lse, logp   [n_rows] fp32, outputs of ais_lm_head_logprob for the same operands and temperature
  *   coeff       [n_rows] fp32, as written by ais_grpo_row_scale (its g_out: it carries inv_temperature)
- *   chunk_vocab vocabulary entries per chunk, a multiple of 256.  The context workspace grows to 2 * n_rows * chunk_vocab
- *               bytes, and up to 256 MiB in which parts of the two sums are kept where a product alone would not fill the GPU.
- *               0: the library's choice, chunks of up to 65536 (with few rows 131072) entries, all alike, whose workspace is
- *               at most 1 GiB, and 8192 entries where that would take more.  Where the device has no room for it, 8192 (up to
- *               68 MB with up to 3,072 rows) and sums in one part.
+ *   chunk_vocab vocabulary entries per chunk, a multiple of 256.  The context workspace holds 2 * n_rows * chunk_vocab bytes,
+ *               and up to 96 MiB in which parts of the two sums are kept where a product alone would not fill the GPU.
+ *               0: the library's choice, chunks of up to 65536 (with few rows 131072) entries, all alike, whose dlogits take at
+ *               most 1 GiB, and 8192 entries where those would take more, with up to 256 MiB of parts.  Where the device has
+ *               no room for it, 8192 (up to 68 MB with up to 3,072 rows) and sums in one part.  (As everywhere, a workspace
+ *               that grows is allocated a quarter larger than the call asks for.)
  *   n_live_max  negative, or >= n_rows: every row goes through the recomputation and the GEMMs.  Otherwise a bound
  *               that the caller vouches for on the number of rows with coeff != 0 (for a masked-diffusion batch:
  *               the number of evaluated positions, which its loader knows): those rows are gathered on the device

@@ -93,15 +93,18 @@ long long lm_grad_chunk(long long m_rows, long long vocab, long long asked, int 
 long long lm_grad_even_chunk(long long chunk, long long m_rows, long long vocab);
 size_t lm_grad_wide_bytes(long long m_rows, long long vocab);
 long long lm_grad_chunk_for(long long chunk, long long vocab, long long d_model, int n_cus);
-// Parts that the sums of the gradient's two products over a chunk are split into, at most so many and so many bytes of each.
+// Parts that the sums of the gradient's two products over a chunk are split into, at most so many and so many bytes of each:
+// fewer where the caller chose the chunk, which is how it bounds the workspace: 96 MiB and a quarter is less than the 150 MiB
+// beside the workspace that a handle of the library's products held, which ran at these sizes before.  us a call with those,
+// with up to 128 and with up to 48 MiB of each sum, chunks of 8,192: 300 rows x 50,257 x 4,096 1,228, 1,000, 1,021; 2,000 x
+// 50,257 x 1,024 994, 708, 744; 20,000 x 32,000 x 512 2,489, 2,047, 2,237; chunks of 4,096: 5,000 x 32,000 x 512 976, 750, 777.
 struct LmParts {
   int w, h;                  // of dweight and of dhidden
 };
 constexpr int kLmMaxParts = 32, kLmMaxWeightParts = 8;
-constexpr long long kLmPartsBytes = 128LL << 20;
+constexpr long long kLmPartsBytes = 128LL << 20, kLmAskedPartsBytes = 48LL << 20;
 LmParts lm_grad_parts(int n_cus, long long n_rows, long long d, long long n_v);
-size_t lm_dhidden_parts_bytes(long long n_rows, long long d);
-size_t lm_dweight_parts_bytes(long long n_v, long long d, int n_cus);
+LmParts lm_grad_parts(int n_cus, long long n_rows, long long d, long long n_v, long long bytes_each);
 size_t lm_grad_dlogits_bytes(long long m_rows, long long vocab, long long asked, int n_cus);
 // The gradient call's chunk, the parts of its sums and where its arrays lie in the workspace, which begins with the chunk's
 // dlogits (byte offsets).

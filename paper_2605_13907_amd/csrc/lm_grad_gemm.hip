@@ -328,6 +328,9 @@ constexpr int kItemSteps = 8;
 // Parts of either sum: those that make the launch of both products shortest, and fewer arrays to add up unless it is so by
 // 2 %.  dweight's is a sum over all rows: few tiles, each of them long, where d_model or the vocabulary is small.
 LmParts lm_grad_parts(int n_cus, long long n_rows, long long d, long long n_v) {
+  return lm_grad_parts(n_cus, n_rows, d, n_v, kLmPartsBytes);
+}
+LmParts lm_grad_parts(int n_cus, long long n_rows, long long d, long long n_v, long long bytes_each) {
   const long long a_tiles = (d + kTile - 1) / kTile;
   const long long h_tiles = a_tiles * ((n_rows + kTile - 1) / kTile), w_tiles = a_tiles * ((n_v + kTile - 1) / kTile);
   const long long h_steps = (n_v + kStep - 1) / kStep, w_steps = (n_rows + kStep - 1) / kStep;
@@ -335,10 +338,10 @@ LmParts lm_grad_parts(int n_cus, long long n_rows, long long d, long long n_v) {
   LmParts best{1, 1};
   long long best_time = -1;
   for (int w = 1; w <= (split_w ? kLmMaxWeightParts : 1) && w <= w_steps; ++w) {
-    if (w > 1 && w * n_v * d * 4 > kLmPartsBytes) break;
+    if (w > 1 && w * n_v * d * 4 > bytes_each) break;
     const long long w_len = (w_steps + w - 1) / w + kItemSteps + (w > 1 ? 4 : 0);
     for (int h = 1; h <= kLmMaxParts && h <= h_steps; ++h) {
-      if (h > 1 && h * n_rows * d * 4 > kLmPartsBytes) break;
+      if (h > 1 && h * n_rows * d * 4 > bytes_each) break;
       const long long h_len = (h_steps + h - 1) / h + kItemSteps + (h > 1 ? 2 : 0);
       const long long time = h_len >= w_len ? launch_time(n_cus, h_tiles * h, h_len, w_tiles * w, w_len)
                                             : launch_time(n_cus, w_tiles * w, w_len, h_tiles * h, h_len);
@@ -351,14 +354,10 @@ LmParts lm_grad_parts(int n_cus, long long n_rows, long long d, long long n_v) {
   return best;
 }
 
-// Most bytes that the parts' arrays take: dhidden's over that many rows or fewer, dweight's of chunks of n_v entries (the same
-// whatever the rows).
-size_t lm_dhidden_parts_bytes(long long n_rows, long long d) {
-  return (size_t)std::min<long long>(kLmPartsBytes, kLmMaxParts * n_rows * d * 4);
-}
-size_t lm_dweight_parts_bytes(long long n_v, long long d, int n_cus) {
+// Most bytes that the parts of dweight take, in chunks of n_v entries, whatever the rows.
+static size_t dweight_parts_bytes(long long n_v, long long d, int n_cus, long long bytes_each) {
   if (n_v > kLmGradChunk || 2 * ((d + kTile - 1) / kTile) * ((n_v + kTile - 1) / kTile) >= n_cus) return 0;
-  return (size_t)std::min<long long>(kLmPartsBytes, kLmMaxWeightParts * n_v * d * 4);
+  return (size_t)std::min<long long>(bytes_each, kLmMaxWeightParts * n_v * d * 4);
 }
 
 // Whether the 256 x 256 tiles of an [n, m] product keep `percent` of the compute units busy over all rounds.
@@ -383,11 +382,13 @@ long long lm_grad_chunk_for(long long chunk, long long vocab, long long d_model,
 // Room for a call over n_rows rows of which m_rows are gone through (fewer: by a list).  roomy: wide chunks and parts; 0: the
 // narrow chunks, and sums in one part, for where there is no room for those.  Every array's place follows from the chunk and
 // the parts that the launches take; what is asked for beyond the last one's end is for calls over fewer rows, whose chunks may
-// be wider and whose sums may have more parts.
+// be wider and whose sums may have more parts (dhidden's only with so few rows that two of them fit: their dlogits and parts
+// often lie where the dlogits of many rows do).
 LmGradRoom lm_grad_room(long long n_rows, long long m_rows, long long d, long long vocab, long long asked, int n_cus,
                         int roomy) {
   auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
   const bool list = m_rows < n_rows;
+  const long long bytes_each = asked == 0 ? kLmPartsBytes : kLmAskedPartsBytes;
   LmGradRoom r{};
   r.chunk = lm_grad_chunk(m_rows, vocab, asked, n_cus);
   if (asked == 0) {
@@ -395,24 +396,29 @@ LmGradRoom lm_grad_room(long long n_rows, long long m_rows, long long d, long lo
     r.chunk = even != r.chunk ? even : lm_grad_chunk_for(r.chunk, vocab, d, n_cus);
   }
   const long long n_v = std::min(r.chunk, vocab);                // entries of the widest chunk
-  r.parts = roomy ? lm_grad_parts(n_cus, m_rows, d, n_v) : LmParts{1, 1};
-  const size_t dh_row = (size_t)m_rows * (size_t)d * 4, dw_part = (size_t)n_v * (size_t)d * 4;
-  const size_t dh_bytes = list || r.parts.h > 1 ? up(dh_row * r.parts.h) : 0, dw_bytes = r.parts.w > 1 ? up(dw_part * r.parts.w) : 0;
+  r.parts = roomy ? lm_grad_parts(n_cus, m_rows, d, n_v, bytes_each) : LmParts{1, 1};
+  auto dh_bytes = [&](long long rows, int parts) { return list || parts > 1 ? up((size_t)rows * (size_t)d * 4 * parts) : 0; };
+  const size_t dh = dh_bytes(m_rows, r.parts.h), dw = r.parts.w > 1 ? up((size_t)n_v * (size_t)d * 4 * r.parts.w) : 0;
   r.plan = up(2 * (size_t)m_rows * (size_t)r.chunk);
   r.mask = r.plan + 256;
   r.index = r.mask + (list ? up((size_t)n_rows) : 0);
   r.pos = r.index + (list ? up((size_t)n_rows * 4) : 0);
   r.hidden = r.pos + (list ? up((size_t)n_rows * 4) : 0);
   r.dhidden = r.hidden + (list ? up((size_t)m_rows * (size_t)d * 2) : 0);
-  r.dweight = r.dhidden + dh_bytes;
-  r.end = r.dweight + dw_bytes;
-  size_t ds_most = up(lm_grad_dlogits_bytes(m_rows, vocab, asked, n_cus)), dh_most = list ? up(dh_row) : 0, dw_most = 0;
+  r.dweight = r.dhidden + dh;
+  r.end = r.dweight + dw;
+  // dlogits and dhidden's parts, no fewer bytes than over any smaller number of rows
+  auto ds_most = [&](long long rows) {
+    const size_t own = lm_grad_dlogits_bytes(rows, vocab, asked, n_cus);
+    return up(roomy && asked == 0 ? std::max(own, lm_grad_wide_bytes(rows, vocab)) : own);
+  };
+  size_t most = ds_most(m_rows) + dh_bytes(m_rows, 1), dw_most = 0;
   if (roomy) {
-    if (asked == 0) ds_most = std::max(ds_most, up(lm_grad_wide_bytes(m_rows, vocab)));
-    dh_most = std::max(dh_most, up(lm_dhidden_parts_bytes(m_rows, d)));
-    dw_most = up(lm_dweight_parts_bytes(std::min(asked != 0 ? asked : kLmGradChunk, vocab), d, n_cus));
+    const long long few = std::min(m_rows, bytes_each / (8 * d));                 // most rows whose dhidden has parts
+    most = std::max(most, ds_most(few) + up((size_t)std::min<long long>(bytes_each, kLmMaxParts * few * d * 4)));
+    dw_most = up(dweight_parts_bytes(std::min(asked != 0 ? asked : kLmGradChunk, vocab), d, n_cus, bytes_each));
   }
-  r.all = std::max(r.end, r.end - r.plan - dh_bytes - dw_bytes + ds_most + dh_most + dw_most);
+  r.all = std::max(r.end, r.end - r.plan - dh - dw + most + dw_most);
   return r;
 }
 

@@ -110,3 +110,20 @@ def test_more_rows_never_need_less_for_the_gradient(d, vocab, asked, n_cus):
             now = [f(n, n, d, vocab, asked, n_cus, roomy).all, f(1 << 21, n, d, vocab, asked, n_cus, roomy).all]
             assert now[0] >= last[0] and now[1] >= last[1], (n, roomy, last, now)
             last = now
+
+
+def test_bytes_asked_for_by_the_gradient():
+    """What the header says of the call's workspace: the chunk's dlogits, with an explicit chunk at most 96 MiB of parts beside
+    them; with the library's choice at most 1 GiB of dlogits (or those of 8,192 entries) and 256 MiB of parts, and parts only
+    where some number of rows up to this one has them."""
+    f, mib = room(), 1 << 20
+    for rows in (1, 300, 2000, 4096, 12_000, 41_643, 100_000):
+        for d in (64, 512, 1024, 4096):
+            for vocab in (700, 8192, 50_257, 151_936):
+                for asked in (256, 1024, 8192):
+                    r = f(rows, rows, d, vocab, asked, 256, 1)
+                    assert r.all <= 2 * rows * r.chunk + 96 * mib + 4096
+                r = f(rows, rows, d, vocab, 0, 256, 1)
+                assert r.all <= max(1024 * mib, 2 * rows * min(vocab + 255, 8192)) + 256 * mib + 4096
+    # two parts of dhidden fit 128 MiB up to 4,096 rows of 4,096: these and their dlogits need less than 41,643 rows' dlogits
+    assert f(41_643, 41_643, 4096, 151_936, 0, 256, 1).all == 1024 * mib + 256

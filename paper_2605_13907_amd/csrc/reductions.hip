@@ -361,11 +361,12 @@ __device__ __forceinline__ RowRatio row_ratio(float train, float roll, double ln
   const double t = (double)train, l = (double)roll;
   RowRatio r;
   r.d = t - l;
-  // (of a NaN only its sums tell: the ratio counts as truncated)
+  // (of a NaN the sums tell: the ratio counts as truncated)
   const double less = exp64_finite(fmax(-fabs(r.d), -800.0)), most = exp64(fmax(t, l));
   const double rho = r.d <= 0.0 ? less : reciprocal(less);
   r.w = r.d <= lnC ? fmin(rho, C) : C;
   r.dp = most > 0.0 ? most * (1.0 - less) : 0.0;
+  if (r.d != r.d) r.dp = most == 0.0 && t == l ? 0.0 : r.d;      // two probabilities of 0 are equal
   return r;
 }
 
@@ -624,7 +625,8 @@ __global__ __launch_bounds__(kThreads, 4) void diag_rows_kernel(
   const int set = min(lane >> 4, 2);
   const double n_rows_in = room.words[0], s1 = room.words[1 + set], s2 = room.words[4 + set];
   const double share = reciprocal(fmax(n_rows_in, 1.0));
-  const Moments b{n_rows_in, fma(s1, share, room.words[kRowSums + set]), fmax(fma(-s1, s1 * share, s2), 0.0)};
+  const double spread = fma(-s1, s1 * share, s2);                // (below 0 by rounding: 0; a NaN stays one)
+  const Moments b{n_rows_in, fma(s1, share, room.words[kRowSums + set]), spread < 0.0 ? 0.0 : spread};
   diag_formulas(b, room.words[7 + (lane >> 4)], p, diag_out, status);
 }
 

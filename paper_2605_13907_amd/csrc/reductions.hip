@@ -152,7 +152,10 @@ struct Responses {
       l = (int)clampll(c0, 0, n_rows);
       h = (int)clampll(c1, l, n_rows);
       const bool bad = c0 != l || c1 != h || (i == 0 && c0 != 0) || (i == n_resp - 1 && c1 != n_rows);
-      if (bad && blockIdx.x == 0) atomicOr(status, AIS_STATUS_BAD_CU);
+      if (bad && blockIdx.x == 0) {
+        atomicOr(status, AIS_STATUS_BAD_CU);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // a workgroup alone reads the word after no more than barriers
+      }
     }
     if (i < kSelfPlanResponses) {
       lo[i] = l;

@@ -29,7 +29,7 @@ def test_edges_of_the_tile_rule(monkeypatch, n_resp, length):
     S.test_scalars_at_scale("edge", True)
 
 
-@pytest.mark.parametrize("n_resp", [2, 1024, 1025])
+@pytest.mark.parametrize("n_resp", [2, 512, 1024, 1025])       # 512: one workgroup, the offsets in eight wavefronts
 @pytest.mark.parametrize("fault", ["first", "last", "order", "range"])
 def test_row_offsets_that_are_no_partition(n_resp, fault):
     """Reported, and nothing is read out of range: the offsets are clamped wherever they point."""

@@ -365,11 +365,11 @@ __device__ __forceinline__ RowRatio row_ratio(float train, float roll, double ln
   RowRatio r;
   r.d = t - l;
   // (of a NaN the sums tell: the ratio counts as truncated)
-  const double less = exp64_finite(fmax(-fabs(r.d), -800.0)), most = exp64(fmax(t, l));
+  const double less = exp64_finite(fmax(-fabs(r.d), -800.0));
+  const double most = exp64(__builtin_isunordered(train, roll) ? __builtin_nan("") : fmax(t, l));
   const double rho = r.d <= 0.0 ? less : reciprocal(less);
   r.w = r.d <= lnC ? fmin(rho, C) : C;
-  r.dp = most > 0.0 ? most * (1.0 - less) : 0.0;
-  if (r.d != r.d) r.dp = most == 0.0 && t == l ? 0.0 : r.d;      // two probabilities of 0 are equal
+  r.dp = most * (1.0 - less);
   return r;
 }
 

@@ -128,7 +128,6 @@ struct ais_ctx {
   hipStream_t stream = nullptr;
   void* ws = nullptr;
   size_t ws_bytes = 0;
-  bool ws_recorded = false;      // a call that was recorded into a graph uses the block: replaced only for a call it cannot hold
   int* status_dev = nullptr;     // 256 bytes: the status word and the tickets, which are 0 between launches
   unsigned turns = 0, static_turns = 0;   // reductions launched with either pair of tickets
   int n_cus = 256;               // compute units of the device
@@ -147,6 +146,7 @@ struct ais_ctx {
     hipStream_t stream = nullptr;
     bool valid = false;
   } plan;
+  bool ws_recorded = false;         // a call that was recorded into a graph uses ws: replaced only for a call that it cannot hold
   void* static_scratch = nullptr;   // address, on this context's device, of the library's static scratch array
 };
 

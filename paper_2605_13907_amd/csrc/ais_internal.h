@@ -69,7 +69,8 @@ TileRule tile_rule(long long n_rows, int n_resp);
 // Byte offsets of the regions of the context workspace for a call with (n_rows, n_resp).
 struct WorkspaceLayout {
   size_t tile_off;   // int [n_resp + 2]   first tile of each response, and the total (n_resp > kSelfPlanResponses)
-  size_t partial;    // double [kDiagWords][max_tiles]  (reused as double [max_tiles] by the loss)
+  size_t partial;    // of tiles: double [kDiagWords][max_tiles] (the loss: [max_tiles]); where rows are dealt out evenly: double
+                     // [14][workgroups], then int [n_resp + workgroups] (the loss: double [16 workgroups])
   size_t g;          // float [n_rows]     per-row gradient coefficient
   size_t total;
 };

@@ -15,11 +15,11 @@
 // the instruction fetches of code that runs once, and from some 500,000 rows on by fp64 instructions: 150 of them a row, 840
 // cycles for 64 rows before and 550 now.  Hence rows asked for before anything else, one copy of the code for all rows of a
 // thread, exponentials of 20 instructions (row_coeff.h) and two of them where there were three, sums over the workgroup through
-// LDS (see MergeRoom).  Diagnostics and row coefficients, us a call, tiles of responses dealt to wavefronts before and rows
-// dealt out evenly now: 512 rows in 8 responses 7.8 and 6.7 (the host's time) -> 6.7 and 6.7; 2,048 in 8 9.4 -> 7.6; 41,643 in
-// 16 10.9 and 6.9 -> 9.2 and 6.8; 108,495 in 104 12.8 and 7.7 -> 10.0 and 6.9; 731,967 in 164 20.2 and 10.9 -> 13.7 and 11.1;
-// 1,200,000 in 1,024 (with stale policy and KL term) 21.6 and 16.8 -> 16.1 and 16.8; 4,000,000 in 8 32.5 and 25.2 -> 26.0 and
-// 23.5.
+// LDS (see MergeRoom).  Diagnostics and row coefficients, us a call in a graph of forty, tiles of responses dealt to wavefronts
+// before and rows dealt out evenly now: 512 rows in 8 responses 7.8 and 4.4 -> 5.7 and 3.5; 2,048 in 8 9.5 and 5.5 -> 7.4 and 5.0;
+// 2,432 masked in 128 8.5 and 5.4 -> 8.0 and 4.9; 19,968 masked in 128 9.6 and 6.5 -> 8.4 and 5.3; 41,643 in 16 10.8 and 6.7 -> 8.1
+// and 5.6; 108,495 in 104 13.1 and 7.6 -> 9.1 and 6.6; 299,000 masked in 1,024 16.9 and 9.4 -> 12.8 and 9.8; 1,200,000 in 1,024 26.0
+// and 13.5 -> 15.3 and 13.6; 4,000,000 in 8 33.6 and 26.2 -> 24.6 and 23.8.
 #include "ais_internal.h"
 #include "row_coeff.h"
 
@@ -475,6 +475,65 @@ __device__ __forceinline__ void merge_workgroup(const RowSums& r, MergeRoom& roo
   add(7);                                              // (the first, the number of rows, is what it was)
 }
 
+// Over the workgroups, in words[] of the one that finishes last (a barrier before they are read): a set or a sum to each of seven
+// wavefronts, four workgroups to a lane, nothing but the result through LDS.  (As merge_workgroup does it, over as many threads as
+// there are workgroups, 1,024 rows to a workgroup: 2,432 masked rows 9.9 us and 8.6 so, 19,968 10.3 and 8.9, 1,200,000 16.3 and 15.3.)
+constexpr int kMostWorkgroups = 256;
+__device__ __forceinline__ void merge_workgroups(const double* partial, int n_wg, MergeRoom& room) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (wave >= 7) return;
+  const bool set = wave < 3;                           // w_bar, A, A w_bar; the four sums are s1 of sets of no rows
+  constexpr int kEach = kMostWorkgroups / 64;
+  double n[kEach], s1[kEach], s2[kEach], x0[kEach];
+#pragma unroll
+  for (int k = 0; k < kEach; ++k) {
+    const int b = lane + 64 * k;
+    n[k] = s1[k] = s2[k] = x0[k] = 0.0;
+    if (b < n_wg) {
+      s1[k] = get_device(partial + (size_t)(set ? 1 + wave : 4 + wave) * n_wg + b);
+      if (set) {
+        n[k] = get_device(partial + b);
+        s2[k] = get_device(partial + (size_t)(4 + wave) * n_wg + b);
+        x0[k] = get_device(partial + (size_t)(kRowSums + wave) * n_wg + b);
+      }
+    }
+  }
+  double to = 0.0, rows = 0.0, t1, t2;
+#pragma unroll
+  for (int k = 0; k < kEach; ++k) {
+    const unsigned long long some = __ballot(n[k] != 0.0);
+    if (some != 0 && rows == 0.0) to = lane_value(x0[k], __builtin_ctzll(some));
+    rows = some != 0 ? 1.0 : rows;
+  }
+  auto about = [&](double at) {
+    rows = t1 = t2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < kEach; ++k) {
+      Shifted x{x0[k], s1[k], s2[k]};
+      x.rebase(n[k], at);
+      rows += n[k];
+      t1 += x.s1;
+      t2 += x.s2;
+    }
+    rows = wave_sum(rows);
+    t1 = wave_sum(t1);
+    t2 = wave_sum(t2);
+  };
+  about(to);
+  if (kFarSpread * t1 * t1 > (kFarSpread - 1.0) * rows * t2 && set) {            // uniform; see merge_workgroup
+    to = fma(t1, reciprocal(rows), to);
+    about(to);
+  }
+  if (lane == 0) {
+    if (wave == 0) room.words[0] = rows;
+    room.words[set ? 1 + wave : 4 + wave] = t1;
+    if (set) {
+      room.words[4 + wave] = t2;
+      room.words[kRowSums + wave] = to;
+    }
+  }
+}
+
 // ---- level 2: batch moments, diagnostics, alpha -----------------------------------------------------------------------
 // The code runs once per launch, cold: its size is part of its time (a kilobyte of straight code costs 0.3 us of
 // instruction fetches), so what is the same for several quantities is done once, by lanes that hold one each.  By wavefront 0:
@@ -614,20 +673,13 @@ __global__ __launch_bounds__(kThreads, 4) void diag_rows_kernel(
   }
   sums.n = (double)n;
   const int n_wg = gridDim.x;
-  // once over the workgroup's rows, and in the workgroup that finishes last once over the workgroups'
-  for (bool all = n_wg == 1;; all = true) {                              // uniform
-    merge_workgroup(sums, room);
-    if (all) break;
+  merge_workgroup(sums, room);
+  if (n_wg > 1) {                                                        // uniform
     if (tid < kRowWords) put_device(partial + (size_t)tid * n_wg + blockIdx.x, room.words[tid]);
     if (valid != nullptr && tid < n_resp && resp.lo[tid] < r1 && resp.hi[tid] > r0)
       put_device(counts + tid + (int)blockIdx.x, s_count[tid]);
     if (!last_workgroup(tickets)) return;
-    sums = RowSums{};
-    if (tid < n_wg) {
-      each_sum(sums, [&](int k, double& v) { v = get_device(partial + (size_t)k * n_wg + tid); });
-#pragma unroll
-      for (int k = 0; k < 3; ++k) sums.x[k].x0 = get_device(partial + (size_t)(kRowSums + k) * n_wg + tid);
-    }
+    merge_workgroups(partial, n_wg, room);
     if (valid != nullptr) {
       // the parts of a response's count: by its thread, those of responses with many by its wavefront, to which neighbours are
       // not dealt: it takes one after the other.  (60,000 masked rows in 16 responses, all of them in one wavefront 13.7 us, now
@@ -653,8 +705,10 @@ __global__ __launch_bounds__(kThreads, 4) void diag_rows_kernel(
       }
       if (r < n_resp) count_out[r] = sum;
     }
+    __syncthreads();
+  } else if (valid != nullptr && tid < n_resp) {
+    count_out[tid] = s_count[tid];
   }
-  if (valid != nullptr && n_wg == 1 && tid < n_resp) count_out[tid] = s_count[tid];
   if (tid >= 64) return;
   // lanes 16 s .. 16 s + 15 go on with the set s and the sum s
   const int set = min(lane >> 4, 2);
@@ -1016,13 +1070,21 @@ int reduction_grid(const ais_ctx* ctx, int max_tiles) {
   return (max_tiles + per - 1) / per;
 }
 
-// Rows of a workgroup where the rows are dealt out evenly: 1,024 on as many compute units as that gives, all alone where a
-// workgroup has no more than kAloneRows: it takes no ticket and nothing goes through memory.  Diagnostics, us, alone up to 1,024,
-// 2,048 and 4,096 rows: 1,500 rows in 8 responses 8.6, 7.0, 7.0; 2,048 9.3, 7.6, 7.6; 3,000 8.9, 8.8, 8.8; 4,096 9.5, 9.4, 9.9.
-constexpr int kAloneRows = 2048;
+// Workgroups that the rows are dealt out to.  Up to kAloneRows one, all alone: it takes no ticket and nothing goes through memory.
+// Beyond, 256 rows each (a wavefront on every SIMD: with more they wait for each other's fp64 instructions) on up to
+// kFewWorkgroups, since every ticket is a turn at one word; then 1,024 rows each.  Diagnostics and row coefficients, us, 256, 512
+// and 1,024 rows each: 2,432 rows 8.1, 8.3, 8.6 and 4.9, 5.1, 5.3; 4,096 7.8, 8.0, 8.6 and 4.7, 4.8, 5.3; 8,192 8.2, 8.1, 8.6 and
+// 4.8, 4.8, 5.3; 19,968 8.7, 8.4, 8.9 and 5.6, 5.2, 5.5; 41,643 9.0, 8.2, 8.1 and 6.7, 5.7, 5.6; 108,495 10.3, 10.0, 9.1 and 8.5, 7.8,
+// 6.6.  Alone and with 256 each: 1,500 rows 6.9 and 7.2, 4.6 and 4.6; 2,048 7.4 and 7.3, 5.0 and 4.6.
+constexpr int kAloneRows = 2048, kFewRows = 256, kFewWorkgroups = 32;
+long long dealt_workgroups(long long n_rows, int n_cus) {
+  if (n_rows <= kAloneRows) return 1;
+  const long long few = std::min<long long>((n_rows + kFewRows - 1) / kFewRows, kFewWorkgroups);
+  return std::min<long long>(std::max(few, (n_rows + kThreads - 1) / kThreads), std::min(n_cus, kMostWorkgroups));
+}
 int rows_each(const ais_ctx* ctx, long long n_rows) {
-  if (n_rows <= kAloneRows) return (int)std::max<long long>(n_rows, 1);
-  const long long wgs = std::min<long long>(ctx->n_cus, (n_rows + kThreads - 1) / kThreads);
+  const long long wgs = dealt_workgroups(n_rows, ctx->n_cus);
+  if (wgs == 1) return (int)std::max<long long>(n_rows, 1);
   return (int)(((n_rows + wgs - 1) / wgs + 63) / 64 * 64);
 }
 
@@ -1043,28 +1105,28 @@ TileRule tile_rule(long long n_rows, int n_resp) {
 }
 
 // Monotone in both arguments, so that a call at the largest batch sizes the workspace for all others: the partials have
-// room for the tiles of a planned batch and for the workgroups' of any other.
-constexpr int kMostTiles = 3072;
+// room for the tiles of a planned batch and for the workgroups' of any other (the sums over a workgroup's rows and a word of the
+// counts, and one beside it per response; or its wavefronts' parts of the loss).
+constexpr size_t kWorkgroupBytes = 128;
+static_assert(sizeof(double) * kRowWords + sizeof(int) <= kWorkgroupBytes && sizeof(double) * kWaves <= kWorkgroupBytes, "");
 WorkspaceLayout workspace_layout(long long n_rows, int n_resp) {
   auto up = [](size_t v) { return (v + 255) & ~size_t(255); };
-  const long long fine = std::min<long long>((n_rows + kChunkRows - 1) / kChunkRows, kMostTiles);
-  const long long planned = (n_rows + kPlanTileRows - 1) / kPlanTileRows;
-  const size_t tiles = (size_t)(std::max(fine, planned) + n_resp);
+  const size_t workgroups = (size_t)dealt_workgroups(n_rows, kMostWorkgroups);
+  const size_t planned = (size_t)((n_rows + kPlanTileRows - 1) / kPlanTileRows) + (size_t)n_resp;
   WorkspaceLayout w;
   w.tile_off = 0;
   w.partial = up(w.tile_off + sizeof(int) * (size_t)(n_resp + 2));
-  w.g = up(w.partial + sizeof(double) * kDiagWords * tiles);
+  w.g = up(w.partial + std::max(kWorkgroupBytes * workgroups + sizeof(int) * (size_t)n_resp, sizeof(double) * kDiagWords * planned));
   w.total = up(w.g + sizeof(float) * (size_t)n_rows);
   return w;
 }
 
 // The documented limit of ais_diagnostics_static, 56 bytes for each of the tiles of 1,024 rows that the batch may have
-// beside 4 for each response: at least what tiling and partials take under either rule.
+// beside 4 for each response: at least what tiling and partials take beyond kSelfPlanResponses responses.
 size_t static_scratch_bytes(long long n_rows, int n_resp) {
   auto up = [](size_t v) { return (v + 255) & ~size_t(255); };
   static_assert(sizeof(double) * kDiagWords <= 56, "partials of planned tiles fit what is documented");
-  static_assert(sizeof(int) * (kSelfPlanResponses + 2) + 256 +
-                        sizeof(double) * kDiagWords * (kMostTiles + kSelfPlanResponses) <= AIS_STATIC_SCRATCH_BYTES,
+  static_assert(2 * sizeof(int) * (kSelfPlanResponses + 2) + 256 + kWorkgroupBytes * kMostWorkgroups <= AIS_STATIC_SCRATCH_BYTES,
                 "those of other batches always fit");
   return up(up(sizeof(int) * (size_t)(n_resp + 2)) +
             56 * ((size_t)((n_rows + kPlanTileRows - 1) / kPlanTileRows) + (size_t)n_resp));

@@ -870,8 +870,8 @@ int launch_lm_tile(ais_ctx* ctx, int grid, const void* hidden, long long ld_h, c
   return hip_fail(ctx, hipGetLastError());
 }
 
-// Whether the log-prob call's W runs two steps ahead: where few token blocks share what the embedding brings and it is more than the Infinity
-// Cache's 256 MB, so that its way from HBM is what a step waits for.  Log-prob, us without and with: 64 rows x 151,936 x 4,096
+// Whether the log-prob call's W runs two steps ahead: where few token blocks share what the embedding brings and it is more than
+// the Infinity Cache's 256 MB, so that its way from HBM is what a step waits for, or the contraction is long.  Log-prob, us without and with: 64 rows x 151,936 x 4,096
 // 306 and 228, x 1,024 85 and 71, 390 x 4,096 503 and 447, x 1,024 138 and 120, 1,000 x 4,096 983 and 918, 2,000 1,920 and
 // 1,839, 4,096 x 126,464 x 4,096 3,022 and 2,896; but 5,000 x 128,256 x 4,096 3,797 and 3,849, 6,500 4,935 and 5,042, 30,000 x
 // 151,936 27.1 and 29.1 ms (between, 8,192 to 20,000 rows of 4,096, it would gain 1 to 3 %, at 25,000 lose 2).  Embeddings that
@@ -884,7 +884,7 @@ int launch_lm_tile(ais_ctx* ctx, int grid, const void* hidden, long long ld_h, c
 // 356 without and 268 with, 8,192 rows 4,974 and 3,957).
 bool lm_deep(long long n_rows, int d_model, long long vocab, const void* weight, long long ld_w) {
   if (d_model % kLmTileK != 0 || reinterpret_cast<uintptr_t>(weight) % 128 != 0 || ld_w % 64 != 0) return true;
-  return n_rows <= 4608 && vocab * d_model >= 128LL << 20;
+  return n_rows <= 4608 && (d_model >= 2048 || vocab * d_model >= 128LL << 20);
 }
 
 int launch_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long ld_h, const void* weight, long long ld_w,

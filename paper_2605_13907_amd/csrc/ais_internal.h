@@ -15,10 +15,11 @@ namespace ais {
 constexpr int kSweepThreads = 256;     // one workgroup (4 wavefronts) streams one logits row
 constexpr int kPlanThreads = 256;      // workgroup of the plan kernel
 constexpr int kPlanTileRows = 1024;    // rows of a tile that it lays out
-// Most responses whose tiling the scalar kernels work out for themselves: one for each thread of a workgroup.  Kernel time
-// of both calls, us, against tilings laid out by the plan kernel (whose own launch comes on top of it): 41,643 rows in 16
-// responses 18.8 and 18.8, 200,000 in 64 24.5 and 27.8, 200,000 in 512 23.8 and 23.4, 1,200,000 in 1,024 38.9 and 47.7,
-// 4,000,000 in 1,024 78.0 and 69.3.
+// Most responses that the scalar kernels know each of (a thread of a workgroup reads one's rows), so that the rows are dealt out
+// evenly; beyond, tiles are laid out by the plan kernel.  Diagnostics and row coefficients, us a call, dealt out and planned (the
+// plan kernel's launch is part of the first): 41,643 rows in 16 responses 8.1 and 18.1, 5.6 and 10.3; 200,000 in 64 10.3 and 19.7, 8.0
+// and 10.8; 200,000 in 512 10.5 and 20.2, 8.2 and 11.0; 1,200,000 in 1,024 15.2 and 28.2, 13.7 and 14.8; 4,000,000 in 1,024 25.3 and
+// 49.3, 24.3 and 26.3.
 constexpr int kSelfPlanResponses = 1024;
 // Words of the status allocation that count the finished workgroups of a reduction: a pair for the calls that work in the
 // context's workspace, a pair for the static call, which may run beside them.

@@ -313,7 +313,7 @@ struct LmGradArgs {
   const float* logp;       // [n_rows]  log-prob of the sampled token
   const float* coeff;      // [n_rows]  d loss / d (row's log-prob) times 1 / T; 0 on rows without gradient
   bf16_t* ds;              // [n_rows, ds_stride]  coeff (softmax - onehot) over this chunk of the vocabulary
-  long long ds_stride;     // elements, a multiple of 4
+  long long ds_stride;     // elements, a multiple of 256 (stores are of eight)
   int y_off;               // first vocabulary entry of the chunk: token ids are global, tile indices local
   int compact;             // != 0: row p of ds belongs to the p-th listed row (LmRows::index), not to source row p
 };

@@ -8,7 +8,7 @@
 // three diagnostics and the mixing coefficient (Eq. 12-17).  Everything is accumulated in fp64 in a fixed order (no floating
 // point atomics), so results are bit-reproducible from run to run.  Spreads are carried as sums of differences from a value of
 // the set, and summed again about the mean where that value lies far from it (kFarSpread), or as (count, mean, squared
-// deviations): 1,200,000 ratios near 1 whose first is truncated at 5 have a variance right to 1e-15 of itself (4e-10 about that
+// deviations): 1,200,000 ratios near 1 whose first is truncated at 5 have a variance right to 1e-15 of itself (1.2e-10 about that
 // first value alone).
 //
 // These kernels move a few bytes per row (about a megabyte per batch) and are bound by the length of their dependent chains, by
@@ -682,8 +682,8 @@ __global__ __launch_bounds__(kThreads, 4) void diag_rows_kernel(
     merge_workgroups(partial, n_wg, room);
     if (valid != nullptr) {
       // the parts of a response's count: by its thread, those of responses with many by its wavefront, to which neighbours are
-      // not dealt: it takes one after the other.  (60,000 masked rows in 16 responses, all of them in one wavefront 13.7 us, now
-      // 10.7; 11,000 in 1,024, none with many parts, 11.2 and 11.5 for the scattered words.)
+      // not dealt: it takes one after the other.  (60,000 masked rows in 16 responses, all of them in one wavefront and so: 13.7 and
+      // 10.7 us; 11,000 in 1,024, none with many parts, 11.2 and 11.5 for the scattered words.)
       const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = wave + kWaves * lane;
       int b0 = 0, parts = 0, sum = 0;
       if (r < n_resp && resp.hi[r] > resp.lo[r]) {

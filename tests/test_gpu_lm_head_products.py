@@ -1,6 +1,5 @@
 """The two products of the hidden-state gradient at the sizes where their tiles (256 x 256 outputs, 64 summed elements a
-step) end inside the operands, on the library's own kernels and on the other route, with one and with several chunks, and
-with a row list.  Every element against float64 on the dlogits' own rounding."""
+step) end inside the operands, with sums whole and in parts, with one and with several chunks, and with a row list.  Every element against float64 on the dlogits' own rounding."""
 import pytest
 import torch
 
@@ -30,15 +29,15 @@ def case(rows, d, vocab, live, seed):
 
 # rows, d, vocab, rows with a gradient (None: all), chunk (0: the library's choice)
 CASES = [
-    (4096, 4096, 8192, None, 0),           # whole tiles and steps, both products on own kernels
+    (4096, 4096, 8192, None, 0),           # whole tiles and steps
     (4097, 4064, 8193, None, 8192),        # one row, one entry and half a d block over; a last chunk of one entry
     (4031, 4096, 7937, None, 0),           # a last step of 63 rows, a last tile of one entry
     (3841, 4064, 16_100, None, 8192),      # 16,100 = 8,192 + 7,908: two chunks, the hidden gradient accumulates
     (9000, 4096, 8200, 4000, 0),           # a row list
-    (6000, 2080, 8192, 2055, 8192),        # the embedding gradient alone on the own kernel
-    (16_384, 1024, 3000, None, 0),         # the hidden gradient alone
+    (6000, 2080, 8192, 2055, 8192),        # a row list, a last d block of 32, seven rows in the last step
+    (16_384, 1024, 3000, None, 0),         # a long sum over rows for few entries
     (300, 4096, 20_000, 7, 0),             # few rows: one wide chunk, a list shorter than a step
-    (5000, 64, 700, None, 256),            # neither
+    (5000, 64, 700, None, 256),            # one d block of 64, a last chunk of 188 entries
 ]
 
 

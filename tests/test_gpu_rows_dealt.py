@@ -13,6 +13,9 @@ pytestmark = pytest.mark.gpu
     (1, ("fixed", 63)), (1, ("fixed", 2_048)), (1, ("fixed", 2_049)), (3, ("fixed", 683)), (683, ("fixed", 3)),
     (1_024, ("uniform", 0, 3)), (1_024, ("uniform", 0, 130)), (33, ("fixed", 64)), (32, ("fixed", 65)),
     (5, ("fixed", 52_429)), (7, ("fixed", 320_001)), (1, ("fixed", 1_048_577)),
+    # 10, 32, 32, 33 and 65 workgroups, 256 of them with 1,024 rows each and with one row more
+    (128, ("fixed", 19)), (2, ("fixed", 4_096)), (1, ("fixed", 32_768)), (1, ("fixed", 32_769)), (1, ("fixed", 65_537)),
+    (4, ("fixed", 65_536)), (1, ("fixed", 262_145)),
 ])
 def test_rows_dealt_out(monkeypatch, n_resp, recipe):
     for share in (1.0, 0.6):

@@ -1,5 +1,5 @@
-"""The tiling of a batch into rows of responses: worked out by every workgroup for up to 1,024 responses, by a kernel of
-its own beyond that; and the number of lanes that fold a response's tiles, which follows the number of responses."""
+"""The rows of a batch and their responses: rows dealt out evenly, each finding its response, for up to 1,024 responses, tiles laid
+out by a kernel of its own beyond that."""
 import numpy as np
 import pytest
 import torch
@@ -22,8 +22,8 @@ def test_number_of_responses(monkeypatch, n_resp):
 @pytest.mark.parametrize("n_resp,length", [(1, 1), (1, 3_840), (1, 3_841), (8, 256), (8, 257), (2, 393_216), (2, 393_217),
                                            (1024, 64), (1023, 65)])
 def test_edges_of_the_tile_rule(monkeypatch, n_resp, length):
-    """One workgroup alone up to 16 tiles of 256 rows (its partials stay in LDS), several beyond; tiles of 512 rows from
-    3,072 tiles of 256 on; as many responses as a workgroup has threads."""
+    """One row; responses that end with a run of 64 rows and inside one, over one workgroup and over all; as many responses as a
+    workgroup has threads."""
     monkeypatch.setitem(S.CASES, "edge", (n_resp, 1, ("fixed", length), 0.6))
     S.test_scalars_at_scale("edge", False)
     S.test_scalars_at_scale("edge", True)

@@ -127,3 +127,29 @@ def test_bytes_asked_for_by_the_gradient():
                 assert r.all <= max(1024 * mib, 2 * rows * min(vocab + 255, 8192)) + 256 * mib + 4096
     # two parts of dhidden fit 128 MiB up to 4,096 rows of 4,096: these and their dlogits need less than 41,643 rows' dlogits
     assert f(41_643, 41_643, 4096, 151_936, 0, 256, 1).all == 1024 * mib + 256
+
+
+class Layout(C.Structure):
+    _fields_ = [(n, C.c_size_t) for n in ("tile_off", "partial", "g", "total")]
+
+
+def test_partials_of_the_scalar_kernels_fit():
+    """Between the tiling and the row coefficients there is room for the tiles of a planned batch (6 words each) and for what the
+    workgroups of any other leave (14 words and a count each, a count per response; or 16 words of the loss), whatever the device,
+    and more rows or responses never move an offset down."""
+    f = B._lib()["_ZN3ais16workspace_layoutExi"]
+    f.argtypes, f.restype = [C.c_longlong, C.c_int], Layout
+    rows = [0, 1, 2048, 2049, 2304, 2305, 8192, 8193, 32_768, 32_769, 262_144, 262_145, 4_000_000, 2**31 - 1]
+    for n_resp in (1, 8, 1023, 1024, 1025, 20_000):
+        last = Layout()
+        for n in rows:
+            w, fewer = f(n, n_resp), f(n, max(1, n_resp - 1))
+            if n_resp <= 1024:
+                groups = 1 if n <= 2048 else min(256, max(min(-(-n // 256), 32), -(-n // 1024)))
+                assert w.g - w.partial >= max(8 * 14 * groups + 4 * (n_resp + groups), 8 * 16 * groups), (n, n_resp)
+            else:
+                assert w.partial - w.tile_off >= 4 * (n_resp + 1)
+                assert w.g - w.partial >= 8 * 6 * (-(-n // 1024) + n_resp), (n, n_resp)
+            assert w.total - w.g >= 4 * n
+            assert w.partial >= last.partial and w.g >= last.g and w.total >= last.total and w.total >= fewer.total
+            last = w

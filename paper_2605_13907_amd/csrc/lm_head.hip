@@ -694,9 +694,10 @@ __global__ __launch_bounds__(1024) void lm_head_setup_kernel(const unsigned char
 }
 
 // lse and log-prob from the per-chunk partials, which are stored by evaluated position.  16 rows per workgroup, the
-// chunks of a row over 16 threads, eight partials of a thread asked for together, whose sums are added in order.  (One thread per
+// chunks of a row over 16 threads, beyond 16 chunks eight partials of a thread asked for together, whose sums are added in order.  (One thread per
 // row and all its chunks in turn took 33 us for 390 rows of 60 chunks, 16 us for 41,643 rows of 14; one partial of a thread at a
-// time and eight: 300 rows x 65,536 of which 30 evaluated, 256 chunks, 10.9 and 5.8 us, 129 of 257 x 100,000 10.4 and 5.8.)
+// time and eight: 300 rows x 65,536 of which 30 evaluated, 256 chunks, 11.0 and 6.2 us, 129 of 257 x
+// 100,000 10.3 and 6.2; up to 16 chunks, 41,643 rows, 5.0 and 5.3.)
 constexpr int kMergeRows = 16;
 constexpr int kMergeWays = 16;
 constexpr int kMergeAtOnce = 8;
@@ -716,7 +717,8 @@ __global__ __launch_bounds__(kMergeRows * kMergeWays) void lm_head_merge_kernel(
   const int last = some ? way + (n_chunks - 1 - way) / kMergeWays * kMergeWays : 0;       // (past it: the last again)
   float m = kNegHuge;
   if (some) {
-    for (int k0 = way; k0 < n_chunks; k0 += kMergeAtOnce * kMergeWays) {
+    m = part_m[way * stride + p];
+    for (int k0 = way + kMergeWays; k0 < n_chunks; k0 += kMergeAtOnce * kMergeWays) {
 #pragma unroll
       for (int u = 0; u < kMergeAtOnce; ++u) m = fmaxf(m, part_m[min(k0 + u * kMergeWays, last) * stride + p]);
     }
@@ -727,7 +729,8 @@ __global__ __launch_bounds__(kMergeRows * kMergeWays) void lm_head_merge_kernel(
   for (int w = 0; w < kMergeWays; ++w) m = fmaxf(m, way_m[w][r]);
   double s = 0.0;
   if (some) {
-    for (int k0 = way; k0 < n_chunks; k0 += kMergeAtOnce * kMergeWays) {
+    s = (double)part_s[way * stride + p] * (double)exp2_fast(part_m[way * stride + p] - m);
+    for (int k0 = way + kMergeWays; k0 < n_chunks; k0 += kMergeAtOnce * kMergeWays) {
       float ps[kMergeAtOnce], pm[kMergeAtOnce];
 #pragma unroll
       for (int u = 0; u < kMergeAtOnce; ++u) {

@@ -581,16 +581,19 @@ int ais_lm_head_grad(ais_ctx* ctx, const void* hidden, long long hidden_stride, 
   // Where there is no room for wide chunks and parts: the narrow chunks, and sums in one part.
   auto room = [&](int roomy) { return lm_grad_room(n_rows, m_rows, d_model, vocab, chunk_vocab, ctx->n_cus, roomy); };
   LmGradRoom use = room(1);
-  if (use.all > ctx->ws_bytes) {
-    // What is there already may hold the narrow chunks.  It stays where the stream is being recorded, when nothing can be
-    // allocated, where a call that was recorded used it (a graph still writes there), and where the device has no room for more.
+  size_t need = use.all;
+  if (need > ctx->ws_bytes) {
+    // What is there already may hold the call all the same, if only in narrow chunks.  It stays where the stream is being recorded,
+    // when nothing can be allocated, where a call that was recorded used it (a graph still writes there), and where the device has
+    // no room for more.
     const LmGradRoom narrow = room(0);
-    if (narrow.all <= ctx->ws_bytes) {
+    if (std::min(use.end, narrow.end) <= ctx->ws_bytes) {
       if (!ctx->ws_recorded && !being_recorded(ctx)) grow_workspace(ctx, use.all);
-      if (use.all > ctx->ws_bytes) use = narrow;
+      if (use.end > ctx->ws_bytes) use = narrow;
+      need = use.end;
     }
   }
-  int rc = ensure_workspace(ctx, use.all);
+  int rc = ensure_workspace(ctx, need);
   if (rc == AIS_ERR_NOMEM) {
     use = room(0);
     rc = ensure_workspace(ctx, use.all);

@@ -181,6 +181,46 @@ def test_a_recorded_workspace_stays(first):
     ctx.close()
 
 
+def test_a_recorded_workspace_that_holds_the_parts():
+    """A workspace that stays because a recorded call uses it, and holds another gradient call's chunks and parts although not what
+    that call would ask for (room for calls over fewer rows): the call has its parts, and nothing is allocated."""
+    ctx = B.AisContext()
+    big = operands(4096, 32, 16_384, None, 85)               # sizes the workspace
+    logp, lse = ctx.lm_head_logprob(*big[:3])
+    ctx.lm_head_grad(*big[:3], lse, logp, big[3], chunk_vocab=8192)
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    held = room()(4096, 4096, 32, 16_384, 8192, units, 1).all * 1.25
+    now = room()(2000, 2000, 512, 10_000, 0, units, 1)
+    assert now.end < held < now.all and now.h > 1
+    h, w, y, c = operands(2000, 512, 10_000, None, 86)
+    logp, lse = ctx.lm_head_logprob(h, w, y)
+    small = torch.rand(2000, device="cuda") - 2.0
+    cu, rewards, params = torch.tensor([0, 2000], device="cuda"), torch.ones(1, device="cuda"), B.default_params()
+    ctx.diagnostics(small, small, None, cu, rewards, 1, params)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        adv, count, diag = ctx.diagnostics(small, small * 0.5, None, cu, rewards, 1, params)
+    fresh = B.AisContext()
+    want = fresh.lm_head_grad(h, w, y, lse, logp, c)
+    dh, dw = torch.empty(2000, 512, device="cuda"), torch.empty(10_000, 512, device="cuda")
+    for _ in range(3):
+        free = free_bytes()
+        ctx._sync_stream()
+        rc = B._lib().ais_lm_head_grad(ctx._h, h.data_ptr(), 512, w.data_ptr(), 512, B.AIS_BF16, 2000, 512, 10_000, y.data_ptr(),
+                                       lse.data_ptr(), logp.data_ptr(), c.data_ptr(), 1.0, 0, -1, dh.data_ptr(), dw.data_ptr())
+        assert rc == 0 and free_bytes() == free
+        check(h, w, y, c, dh, dw)
+        assert torch.equal(dh, want[0]) and torch.equal(dw, want[1])
+        graph.replay()
+        torch.cuda.synchronize()
+        ref = ctx.diagnostics(small, small * 0.5, None, cu, rewards, 1, params)
+        assert all(torch.equal(a, b) for a, b in zip((adv, count, diag), ref))
+    assert ctx.status() == 0 and fresh.status() == 0
+    ctx.close()
+    fresh.close()
+
+
 def test_no_room_for_wide_chunks_now_and_room_later():
     """While the device is full, calls take narrow chunks and keep the workspace they have; the first call after that takes wide
     ones again."""

@@ -326,7 +326,12 @@ constexpr int kItemSteps = 8;
 }  // namespace
 
 // Parts of either sum: those that make the launch of both products shortest, and fewer arrays to add up unless it is so by
-// 2 %.  dweight's is a sum over all rows: few tiles, each of them long, where d_model or the vocabulary is small.
+// 2 %.  dweight's is a sum over all rows: few tiles, each of them long, where d_model or the vocabulary is small.  Sums of at most
+// kWholeSteps (1,024 rows) stay whole: what parts save there is less than the launch that adds them.  us a call in parts and whole:
+// 590 rows x 1,133 x 1,024 in chunks of 512 162 and 150, 449 x 9,048 x 512 in 4,096 155 and 142, 900 (half) x 13,433 x 1,408 in 256
+// 3,339 and 2,875, 4,533 (a tenth) x 58,572 x 512 in 2,048 1,561 and 1,275, 554 x 1,951 x 1,216 61.3 and 58.3, 741 x 2,510 x 576
+// 55.8 and 57.0; but 1,252 x 12,151 x 768 in 2,048 368 and 408, 1,768 x 2,944 x 1,344 in 1,024 214 and 239.
+constexpr int kWholeSteps = 16;
 LmParts lm_grad_parts(int n_cus, long long n_rows, long long d, long long n_v) {
   return lm_grad_parts(n_cus, n_rows, d, n_v, kLmPartsBytes);
 }
@@ -334,7 +339,7 @@ LmParts lm_grad_parts(int n_cus, long long n_rows, long long d, long long n_v, l
   const long long a_tiles = (d + kTile - 1) / kTile;
   const long long h_tiles = a_tiles * ((n_rows + kTile - 1) / kTile), w_tiles = a_tiles * ((n_v + kTile - 1) / kTile);
   const long long h_steps = (n_v + kStep - 1) / kStep, w_steps = (n_rows + kStep - 1) / kStep;
-  const bool split_w = 2 * w_tiles < n_cus && n_v <= kLmGradChunk;
+  const bool split_w = 2 * w_tiles < n_cus && n_v <= kLmGradChunk && w_steps > kWholeSteps;
   LmParts best{1, 1};
   long long best_time = -1;
   for (int w = 1; w <= (split_w ? kLmMaxWeightParts : 1) && w <= w_steps; ++w) {

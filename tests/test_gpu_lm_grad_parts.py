@@ -26,6 +26,8 @@ CASES = [
     (5000, 64, 700, None, 256, "w"),             # three chunks, the last one narrower
     (9000, 128, 1500, 4097, 0, "wh"),            # a row list shorter than its bound would be
     (64, 32, 64, None, 0, ""),                   # one step each
+    (1024, 512, 2048, None, 0, "h"),             # the longest sum over rows that stays whole, and one row more
+    (1025, 512, 2048, None, 0, "wh"),
     (3000, 3584, 9000, None, 1024, "w"),         # dweight split because the chunk is narrow, not the vocabulary or the model
 ]
 

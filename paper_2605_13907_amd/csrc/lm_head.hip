@@ -893,20 +893,29 @@ int launch_lm_tile(ais_ctx* ctx, int grid, const void* hidden, long long ld_h, c
 }
 
 // Whether the log-prob call's W runs two steps ahead: where few token blocks share what the embedding brings and it is more than
-// the Infinity Cache's 256 MB, so that its way from HBM is what a step waits for, or the contraction is long.  Log-prob, us without and with: 64 rows x 151,936 x 4,096
-// 306 and 228, x 1,024 85 and 71, 390 x 4,096 503 and 447, x 1,024 138 and 120, 1,000 x 4,096 983 and 918, 2,000 1,920 and
-// 1,839, 4,096 x 126,464 x 4,096 3,022 and 2,896; but 5,000 x 128,256 x 4,096 3,797 and 3,849, 6,500 4,935 and 5,042, 30,000 x
-// 151,936 27.1 and 29.1 ms (between, 8,192 to 20,000 rows of 4,096, it would gain 1 to 3 %, at 25,000 lose 2).  Embeddings that
-// the cache holds: 1,800 rows x 46,336 x 960 143 and 153, 390 x 50,257 x 1,024 51.5 and 52.6, 1,000 95.2 and 96.7, 390 x
-// 151,936 x 576 74.9 and 76.7, 2,000 x 50,257 x 2,048 327 and 325.  The gradient's chunks are short items, most of them in
-// their first tiles: 4,052 rows x 126,464 x 4,096 10.23 and 9.97 ms, 3,000 x 50,257 x 1,024 1.148 and 1.117, 8,192 x 126,464 x
-// 576 4.81 and 4.66, 600 x 50,257 x 1,024 464 and 438 us, but 2,500 x 32,000 x 512 501 and 504: always two steps ahead.
+// the Infinity Cache's 256 MB, so that its way from HBM is what a step waits for, or the contraction is long.  Log-prob, us without
+// and with: 64 rows x 151,936 x 4,096 306 and 228, x 1,024 85 and 71, 390 x 4,096 503 and 447, x 1,024 138 and 120, 1,000 x 4,096
+// 983 and 918, 2,000 1,920 and 1,839, 4,096 x 126,464 x 4,096 3,022 and 2,896; but 5,000 x 128,256 x 4,096 3,797 and 3,849, 6,500
+// 4,935 and 5,042, 30,000 x 151,936 27.1 and 29.1 ms (between, 8,192 to 20,000 rows of 4,096, it would gain 1 to 3 %, at 25,000
+// lose 2).  Embeddings that the cache holds, long contractions: 256 rows (half evaluated) x 16,384 x 2,560 57.7 and 48.5, 600 (a
+// tenth) x 16,384 x 4,096 69.1 and 60.0, 128 x 8,000 x 3,072 52.4 and 45.1; but 1,800 x 46,336 x 960 143 and 153, 390 x 50,257 x
+// 1,024 51.5 and 52.6, 1,000 95.2 and 96.7, 390 x 151,936 x 576 74.9 and 76.7, 2,000 x 50,257 x 2,048 327 and 325.  In between
+// (d_model 1,024 to 2,047) it pays for one token block and, where a mask may leave as few rows, for a few, with tiles enough for
+// every workgroup to go through several: 106 rows x 10,748 x 1,728 33.5 and 30.0, 114 x 20,750 x 1,472 31.3 and 28.0, 199 (half)
+// x 10,542 x 1,600 38.0 and 33.6, 899 (a tenth) x 17,984 x 1,024 31.5 and 29.2, 1,640 (a tenth) x 27,476 x 1,344 40.8 and 40.1;
+// but 491 x 14,490 x 1,024 32.2 and 32.9, 1,825 x 7,444 x 1,792 49.4 and 51.4, 3,853 (half) x 26,531 x 1,152 116 and 121, 309 (a
+// tenth) x 1,816 x 1,792 29.3 and 29.9.
+// The gradient's chunks are short items, most of them in their first tiles: 4,052 rows x 126,464 x 4,096 10.23 and 9.97 ms, 3,000
+// x 50,257 x 1,024 1.148 and 1.117, 8,192 x 126,464 x 576 4.81 and 4.66, 600 x 50,257 x 1,024 464 and 438 us, but 2,500 x 32,000 x
+// 512 501 and 504: always two steps ahead.
 // At any size where the embedding's rows do not begin with a 128-byte line, as with a ragged d_model: a slice's rows then lie
 // across two lines each, and one step is too short for them (with eight wavefronts to a workgroup 300 rows x 151,936 x 2,056
 // 356 without and 268 with, 8,192 rows 4,974 and 3,957).
-bool lm_deep(long long n_rows, int d_model, long long vocab, const void* weight, long long ld_w) {
+// masked: n_rows is a guess, half of the rows given.
+bool lm_deep(long long n_rows, bool masked, int d_model, long long vocab, const void* weight, long long ld_w) {
   if (d_model % kLmTileK != 0 || reinterpret_cast<uintptr_t>(weight) % 128 != 0 || ld_w % 64 != 0) return true;
-  return n_rows <= 4608 && (d_model >= 2048 || vocab * d_model >= 128LL << 20);
+  if (d_model >= 2048 || vocab * d_model >= 128LL << 20) return n_rows <= 4608;
+  return d_model >= 1024 && vocab >= 8192 && n_rows <= (masked ? 1024 : kLmTileT);
 }
 
 int launch_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long ld_h, const void* weight, long long ld_w,
@@ -929,8 +938,9 @@ int launch_lm_head_logprob(ais_ctx* ctx, const void* hidden, long long ld_h, con
   }
   LmRows rows{valid != nullptr ? row_index : nullptr};
   // (how many rows a mask leaves is known on the device only: half of them is the guess)
-  auto launch = lm_deep(valid != nullptr ? n_rows / 2 : n_rows, d_model, vocab, weight, ld_w) ? launch_lm_tile<false, true>
-                                                                                              : launch_lm_tile<false, false>;
+  const bool masked = valid != nullptr;
+  auto launch = lm_deep(masked ? n_rows / 2 : n_rows, masked, d_model, vocab, weight, ld_w) ? launch_lm_tile<false, true>
+                                                                                            : launch_lm_tile<false, false>;
   const int rc = launch(ctx, max_items, hidden, ld_h, weight, ld_w, rows, decomposition, d_model, vocab, token_ids,
                                        inv_temperature * kLog2e, plan.n_vtiles, part_m, part_s, zy, LmGradArgs{});
   if (rc != AIS_OK) return rc;

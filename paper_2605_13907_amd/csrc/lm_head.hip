@@ -26,9 +26,11 @@
 // (the shader clock settles near 1.9 GHz instead of 2.4), so time follows energy.  That is why the products are 16 x 16
 // x 32 and not 32 x 32 x 16, which move twice the accumulators per flop: MFMAs alone on random operands in registers
 // run at 2,090 against 1,845 TFLOP/s; and why a wavefront has 128 x 128 outputs, all of its SIMD's accumulation registers:
-// with eight wavefronts of 128 x 64 (768 bytes of fragments) 41,643 rows x 151,936 x 4,096 took 37.8 ms at 0.69 busy matrix
-// pipes, with these 37.0 (1.40 PFLOP/s); 4,096 x 126,464 x 4,096 3,037 -> 2,896 us (0.74 -> 0.76 busy), 64 x 151,936 x 4,096
-// 261 -> 231.
+// with eight wavefronts of 128 x 64 (768 bytes of fragments) 41,643 rows x 151,936 x 4,096 took 37.8 ms, with these 37.0 (1.40
+// PFLOP/s; matrix pipe busy 0.68 of the cycles); 4,096 x 126,464 x 4,096 3,037 -> 2,896 us (0.77), 64 x 151,936 x 4,096 261 ->
+// 231.  What it costs: alone on its SIMD, a wavefront has nothing beside its start and its soft-max, so contractions below 512
+// are up to 20 % slower (9,506 rows x 24,897 x 64 80 -> 95 us), and a few evaluated rows of small vocabularies up to 14 % (198, a
+// tenth, x 4,239 x 1,920 26.9 -> 30.4).
 #include "ais_internal.h"
 #include "device_utils.h"
 #include "lm_tile.h"
@@ -694,10 +696,10 @@ __global__ __launch_bounds__(1024) void lm_head_setup_kernel(const unsigned char
 }
 
 // lse and log-prob from the per-chunk partials, which are stored by evaluated position.  16 rows per workgroup, the
-// chunks of a row over 16 threads, beyond 16 chunks eight partials of a thread asked for together, whose sums are added in order.  (One thread per
-// row and all its chunks in turn took 33 us for 390 rows of 60 chunks, 16 us for 41,643 rows of 14; one partial of a thread at a
-// time and eight: 300 rows x 65,536 of which 30 evaluated, 256 chunks, 11.0 and 6.2 us, 129 of 257 x
-// 100,000 10.3 and 6.2; up to 16 chunks, 41,643 rows, 5.0 and 5.3.)
+// chunks of a row over 16 threads, whose sums are added in order; beyond 16 chunks eight partials of a thread are asked for
+// together.  (One thread per row and all its chunks in turn took 33 us for 390 rows of 60 chunks, 16 us for 41,643 rows of
+// 14; one partial of a thread at a time and eight: 300 rows x 65,536 of which 30 evaluated, 256 chunks, 11.0 and 6.2 us,
+// 129 of 257 x 100,000 10.3 and 6.2; up to 16 chunks, 41,643 rows, 5.0 and 5.3.)
 constexpr int kMergeRows = 16;
 constexpr int kMergeWays = 16;
 constexpr int kMergeAtOnce = 8;

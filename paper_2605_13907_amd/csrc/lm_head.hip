@@ -27,10 +27,9 @@
 // x 32 and not 32 x 32 x 16, which move twice the accumulators per flop: MFMAs alone on random operands in registers
 // run at 2,090 against 1,845 TFLOP/s; and why a wavefront has 128 x 128 outputs, all of its SIMD's accumulation registers:
 // with eight wavefronts of 128 x 64 (768 bytes of fragments) 41,643 rows x 151,936 x 4,096 took 37.8 ms, with these 37.0 (1.40
-// PFLOP/s; matrix pipe busy 0.68 of the cycles); 4,096 x 126,464 x 4,096 3,037 -> 2,896 us (0.77), 64 x 151,936 x 4,096 261 ->
-// 231.  What it costs: alone on its SIMD, a wavefront has nothing beside its start and its soft-max, so contractions below 512
-// are up to 20 % slower (9,506 rows x 24,897 x 64 80 -> 95 us), and a few evaluated rows of small vocabularies up to 14 % (198, a
-// tenth, x 4,239 x 1,920 26.9 -> 30.4).
+// PFLOP/s; matrix pipe busy 0.68 of the cycles); 4,096 x 126,464 x 4,096 3,037 -> 2,896 us (0.77), 64 x 151,936 x 4,096 241 ->
+// 214.  What it costs: alone on its SIMD, a wavefront has nothing beside its start and its soft-max, so contractions below 512
+// are up to 20 % slower (9,506 rows x 24,897 x 64 80 -> 95 us).
 #include "ais_internal.h"
 #include "device_utils.h"
 #include "lm_tile.h"
@@ -466,14 +465,9 @@ __global__ __launch_bounds__(kLmThreads) __attribute__((amdgpu_waves_per_eu(1, 1
       }
     }
   };
-  auto copy_h = [&](int at, int q) {
+  auto copy_h = [&](int at, int q, int n) {                      // n: of that many
     copy(hp[q], h_kt * kLmTileK, hchunk, at, q);
-    if (q == 7) h_kt = h_kt + 1 == n_ksteps ? 0 : h_kt + 1;
-  };
-  // The sixteen copies of a set, in order: those of H first where W runs a step further ahead, in turns otherwise.
-  auto copy_part = [&](int w_at, int h_at, int p) {
-    if (DEEP ? p < 8 : (p & 1) != 0) copy_h(h_at, DEEP ? p : p >> 1);
-    else copy_w(w_at, DEEP ? p - 8 : p >> 1);
+    if (q == n - 1) h_kt = h_kt + 1 == n_ksteps ? 0 : h_kt + 1;
   };
 
   // ---- fragments of a half step (32 elements): lane reads chunk 4 kk + quarter of a 128-byte row
@@ -501,21 +495,31 @@ __global__ __launch_bounds__(kLmThreads) __attribute__((amdgpu_waves_per_eu(1, 1
   auto walk = [&](auto columns) {
     constexpr int NJ = decltype(columns)::value;
     LmAcc acc;
+    // Copies that bring the block's rows of H, 32 to each: the block has at most one column more than twice the wavefront's.  With
+    // few rows a step's copies are what it waits for (64 KiB at 64 bytes a cycle).  Log-prob, us, all eight and these: 198 rows (a
+    // tenth evaluated) x 4,239 x 1,920 30.6 and 25.6, 124 (a tenth) x 8,033 x 960 22.8 and 20.1, 331 (a tenth) x 10,317 x 1,856 33.1
+    // and 28.5; gradient of 201 (a tenth) x 3,070 x 3,392 in chunks of 2,048 118 and 100.  With more columns eight as ever: 390 x
+    // 151,936 x 4,096 (six and seven) 454 and 456.
+    constexpr int kHCopies = NJ <= 4 ? NJ + 1 : 8, kCopies = 8 + kHCopies;
+    // The copies of a set, in order: those of H first where W runs a step further ahead, in turns otherwise.
+    auto copy_part = [&](int w_at, int h_at, int p) {
+      if (DEEP ? p < kHCopies : p < 2 * kHCopies && (p & 1) != 0) copy_h(h_at, DEEP ? p : p >> 1, kHCopies);
+      else copy_w(w_at, DEEP || p >= 2 * kHCopies ? p - kHCopies : p >> 1);
+    };
     // slices of the step at hand, of the next one and (DEEP: of W) of the one after that
     constexpr int kH = (DEEP ? 3 : 2) * kLmOperandBytes;
     int w0 = 0, w1 = kLmOperandBytes, w2 = DEEP ? 2 * kLmOperandBytes : 0, h0 = kH, h1 = kH + kLmOperandBytes;
     // ---- prologue: step 0 published, those after it in flight
 #pragma unroll
-    for (int p = 0; p < 16; ++p) copy_part(w0, h0, p);
+    for (int p = 0; p < kCopies; ++p) copy_part(w0, h0, p);
     if (DEEP) {
 #pragma unroll
       for (int q = 0; q < 8; ++q) copy_w(w1, q);
     }
 #pragma unroll
-    for (int p = 0; p < 16; ++p) copy_part(DEEP ? w2 : w1, h1, p);
-    // copies complete in order: all but the last 16 (DEEP: 24) are step 0's
-    if (DEEP) asm volatile("s_waitcnt vmcnt(24)\n\ts_barrier" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(16)\n\ts_barrier" ::: "memory");
+    for (int p = 0; p < kCopies; ++p) copy_part(DEEP ? w2 : w1, h1, p);
+    // copies complete in order: all but the last set (DEEP: and eight) are step 0's
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(DEEP ? kCopies + 8 : kCopies) : "memory");
     // the reads of a half step in the order in which its products need them
     auto read_part = [&](int w_at, int h_at, int kk, int p) {
       if (p == 0) read_a(w_at, kk, 0);
@@ -545,7 +549,7 @@ __global__ __launch_bounds__(kLmThreads) __attribute__((amdgpu_waves_per_eu(1, 1
       for (int s = 0; s < n_steps; ++s) {
         meet();
 #pragma unroll
-        for (int p = 0; p < 16; ++p) copy_part(w0, h0, p);
+        for (int p = 0; p < kCopies; ++p) copy_part(w0, h0, p);
         turn();
       }
     } else {
@@ -569,9 +573,10 @@ __global__ __launch_bounds__(kLmThreads) __attribute__((amdgpu_waves_per_eu(1, 1
           if constexpr (m == kBarrierAt) meet();
           if constexpr (m >= kBarrierAt) {               // into the slices that the barrier has freed
             constexpr int after = m - kBarrierAt;
-            constexpr int c0 = (after * 16 + kCopySpan - 1) / kCopySpan, c1 = ((after + 1) * 16 + kCopySpan - 1) / kCopySpan;
+            constexpr int c0 = (after * kCopies + kCopySpan - 1) / kCopySpan;
+            constexpr int c1 = ((after + 1) * kCopies + kCopySpan - 1) / kCopySpan;
 #pragma unroll
-            for (int p = c0; p < (c1 < 16 ? c1 : 16); ++p) copy_part(w0, h0, p);
+            for (int p = c0; p < (c1 < kCopies ? c1 : kCopies); ++p) copy_part(w0, h0, p);
           }
           AIS_PIN;
         });
@@ -896,17 +901,17 @@ int launch_lm_tile(ais_ctx* ctx, int grid, const void* hidden, long long ld_h, c
 
 // Whether the log-prob call's W runs two steps ahead: where few token blocks share what the embedding brings and it is more than
 // the Infinity Cache's 256 MB, so that its way from HBM is what a step waits for, or the contraction is long.  Log-prob, us without
-// and with: 64 rows x 151,936 x 4,096 306 and 228, x 1,024 85 and 71, 390 x 4,096 503 and 447, x 1,024 138 and 120, 1,000 x 4,096
+// and with: 64 rows x 151,936 x 4,096 270 and 214, x 1,024 73 and 56, 390 x 4,096 500 and 450, x 1,024 138 and 122, 1,000 x 4,096
 // 983 and 918, 2,000 1,920 and 1,839, 4,096 x 126,464 x 4,096 3,022 and 2,896; but 5,000 x 128,256 x 4,096 3,797 and 3,849, 6,500
 // 4,935 and 5,042, 30,000 x 151,936 27.1 and 29.1 ms (between, 8,192 to 20,000 rows of 4,096, it would gain 1 to 3 %, at 25,000
-// lose 2).  Embeddings that the cache holds, long contractions: 256 rows (half evaluated) x 16,384 x 2,560 57.7 and 48.5, 600 (a
-// tenth) x 16,384 x 4,096 69.1 and 60.0, 128 x 8,000 x 3,072 52.4 and 45.1; but 1,800 x 46,336 x 960 143 and 153, 390 x 50,257 x
-// 1,024 51.5 and 52.6, 1,000 95.2 and 96.7, 390 x 151,936 x 576 74.9 and 76.7, 2,000 x 50,257 x 2,048 327 and 325.  In between
-// (d_model 1,024 to 2,047) it pays for one token block and, where a mask may leave as few rows, for a few, with tiles enough for
-// every workgroup to go through several: 106 rows x 10,748 x 1,728 33.5 and 30.0, 114 x 20,750 x 1,472 31.3 and 28.0, 199 (half)
-// x 10,542 x 1,600 38.0 and 33.6, 899 (a tenth) x 17,984 x 1,024 31.5 and 29.2, 1,640 (a tenth) x 27,476 x 1,344 40.8 and 40.1;
-// but 491 x 14,490 x 1,024 32.2 and 32.9, 1,825 x 7,444 x 1,792 49.4 and 51.4, 3,853 (half) x 26,531 x 1,152 116 and 121, 309 (a
-// tenth) x 1,816 x 1,792 29.3 and 29.9.
+// lose 2).  Embeddings that the cache holds, long contractions: 256 rows (half evaluated) x 16,384 x 2,560 57.2 and 50.4, 600 (a
+// tenth) x 16,384 x 4,096 62.8 and 52.2, 128 x 8,000 x 3,072 48.8 and 42.0, 64 x 4,099 x 3,072 42.6 and 31.9; but 1,800 x 46,336 x
+// 960 143 and 153, 390 x 50,257 x 1,024 51.5 and 52.6, 1,000 95.2 and 96.7, 390 x 151,936 x 576 74.9 and 76.7, 2,000 x 50,257 x
+// 2,048 327 and 325.  In between (d_model 1,024 to 2,047) it pays for one token block and, where a mask may leave as few rows, for a
+// few, with tiles enough for every workgroup to go through several: 106 rows x 10,748 x 1,728 31.2 and 28.3, 114 x 20,750 x 1,472
+// 29.5 and 26.4, 199 (half) x 10,542 x 1,600 35.2 and 30.5, 331 (a tenth) x 10,317 x 1,856 33.9 and 26.9, 899 (a tenth) x 17,984 x
+// 1,024 31.8 and 30.1, 1,640 (a tenth) x 27,476 x 1,344 41.0 and 40.5; but 491 x 14,490 x 1,024 32.4 and 32.8, 1,825 x 7,444 x
+// 1,792 50.4 and 51.9, 3,853 (half) x 26,531 x 1,152 117 and 119, and 309 (a tenth) x 1,816 x 1,792 23.6 and 23.2.
 // The gradient's chunks are short items, most of them in their first tiles: 4,052 rows x 126,464 x 4,096 10.23 and 9.97 ms, 3,000
 // x 50,257 x 1,024 1.148 and 1.117, 8,192 x 126,464 x 576 4.81 and 4.66, 600 x 50,257 x 1,024 464 and 438 us, but 2,500 x 32,000 x
 // 512 501 and 504: always two steps ahead.

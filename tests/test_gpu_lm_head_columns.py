@@ -1,5 +1,6 @@
-"""The read-out's token blocks: as many rows in each, dealt to the wavefronts in columns of 16; the embedding one step ahead or
-two (up to 6,144 rows, or a d_model of 2,048 in the gradient), with contractions of one, two, three and more steps."""
+"""The read-out's token blocks: as many rows in each, dealt to the wavefronts in columns of 16, with the copies that so many rows
+take; the embedding one step ahead or two (by rows, d_model, vocabulary and mask), with contractions of one, two, three and more
+steps."""
 import pytest
 import torch
 
@@ -58,6 +59,16 @@ def test_either_side_of_the_rule(rows, d):
     ctx = B.AisContext()
     check(ctx, rows, 520, d)
     check(ctx, rows, 520, d, grad=False, masked=True)
+    ctx.close()
+
+
+@pytest.mark.parametrize("rows,vocab,d", [(256, 8192, 1024), (257, 8192, 1024), (256, 8191, 1024), (256, 8192, 960), (2049, 8192, 1024),
+                                          (2050, 8192, 1024), (4608, 300, 2048), (4609, 300, 2048), (9217, 300, 2048),
+                                          (9218, 300, 2048)])
+def test_edges_of_two_steps_ahead(rows, vocab, d):
+    ctx = B.AisContext()
+    check(ctx, rows, vocab, d, grad=False)
+    check(ctx, rows, vocab, d, grad=False, masked=True)
     ctx.close()
 
 
